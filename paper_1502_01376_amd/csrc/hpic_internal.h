@@ -317,46 +317,47 @@ template <class R> __device__ __forceinline__ void half3(R d, R w[3], bool ec) {
 // s[0..2] of the nodes m-1, m, m+1 with exact sum 2^P; returns m.  The same
 // definition as the FP32-precision reference deposit:
 //   s[0] = floor(((2^(P-1) - D)^2 + 2^P) / 2^(P+1)), s[2] likewise with +D,
-// D = rint(d 2^P).  SMALL (P <= 22): the square is a full-rate 24-bit
-// multiply pair and floor((x^2 + 2^P) / 2^(P+1)) is evaluated as
-// (floor(x^2 / 2^P) + 1) >> 1, which is the same integer.
+// D = rint(d 2^P).  The squares differ by 4 2^(P-1) D = 2^(P+1) D, so
+// s[2] = s[0] + D and s[1] = 2^P - 2 s[0] - D: one square per coordinate.
+// SMALL (P <= 22): the square is a full-rate 24-bit multiply pair and
+// floor((x^2 + 2^P) / 2^(P+1)) is evaluated as (floor(x^2 / 2^P) + 1) >> 1,
+// which is the same integer.
 template <bool SMALL>
 __device__ __forceinline__ int fixed_shape(int cell, float f, int P, int s[3]) {
   const int up = (f >= 0.5f) ? 1 : 0;
-  const float d = up ? (f - 1.0f) : f;             // exact
-  const float scaled = d * (float)(1 << P);         // exact
-  const int D = (int)rintf(scaled);                 // |D| <= 2^(P-1)
-  const int h = 1 << (P - 1);
-  const int lo = h - D, hi = h + D;                 // in [0, 2^P]
+  const float d = f - (float)up;                    // exact
+  int D;                                            // |D| <= 2^(P-1)
+  if (SMALL)  // |d 2^P| <= 2^21: 1.5 2^23 rounds it to an integer in the low bits
+    D = __float_as_int(__builtin_fmaf(d, (float)(1 << P), 12582912.0f)) - 0x4b400000;
+  else
+    D = (int)rintf(d * (float)(1 << P));            // exact product
+  const int lo = (1 << (P - 1)) - D;                // in [0, 2^P]
   if (SMALL) {
     const unsigned long long l2 = (unsigned long long)(unsigned)(lo & 0xffffff) * (unsigned)(lo & 0xffffff);
-    const unsigned long long h2 = (unsigned long long)(unsigned)(hi & 0xffffff) * (unsigned)(hi & 0xffffff);
     const unsigned ql = __builtin_amdgcn_alignbit((unsigned)(l2 >> 32), (unsigned)l2, (unsigned)P);
-    const unsigned qh = __builtin_amdgcn_alignbit((unsigned)(h2 >> 32), (unsigned)h2, (unsigned)P);
     s[0] = (int)((ql + 1u) >> 1);
-    s[2] = (int)((qh + 1u) >> 1);
   } else {
-    const long long bias = 1ll << P;
-    s[0] = (int)(((long long)lo * lo + bias) >> (P + 1));
-    s[2] = (int)(((long long)hi * hi + bias) >> (P + 1));
+    s[0] = (int)(((long long)lo * lo + (1ll << P)) >> (P + 1));
   }
+  s[2] = s[0] + D;
   s[1] = (1 << P) - s[0] - s[2];
   return cell + up;
 }
 
-// Exact product of two integers in [-2^23, 2^23) as a 64-bit value.  The
-// explicit sign extension from 24 bits lets the compiler select the full-rate
-// v_mul_i32_i24 / v_mul_hi_i32_i24 pair.
-__device__ __forceinline__ long long mul24_wide(int a, int b) {
-  return (long long)((a << 8) >> 8) * (long long)((b << 8) >> 8);
-}
-// Product of two integers in [-2^23, 2^23) whose value fits 32 bits: one
-// v_mul_i32_i24 (written out, as the compiler otherwise folds the sign
-// extensions into a quarter-rate 32-bit multiply).
+// Products of two integers in [-2^23, 2^23): the low half (the whole product
+// where it fits 32 bits) and the 64-bit value.  The full-rate 24-bit multiplies
+// are written out: from the C expression the compiler takes a quarter-rate
+// 32-bit multiply, or adds sign extensions that these operands do not need.
 __device__ __forceinline__ int mul24_lo(int a, int b) {
   int r;
   asm("v_mul_i32_i24 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
+}
+__device__ __forceinline__ long long mul24_wide(int a, int b) {
+  int lo, hi;
+  asm("v_mul_i32_i24 %0, %1, %2" : "=v"(lo) : "v"(a), "v"(b));
+  asm("v_mul_hi_i32_i24 %0, %1, %2" : "=v"(hi) : "v"(a), "v"(b));
+  return ((long long)hi << 32) | (unsigned)lo;
 }
 
 // Nearest integer (ties to even) of |v| < 2^51 as a 64-bit integer: adding
@@ -405,9 +406,16 @@ __device__ __forceinline__ int wave_atomic_inc(int *cnt, int key, bool active) {
 // Error bits of the device error word.
 enum : unsigned { ERR_RANGE = 1u, ERR_NUMERIC = 2u };
 
-// Statistics words of the push kernel: [0] tiles that fell back to global
-// memory (bounding box too large for LDS), [1] tiles processed.
-enum { STAT_FALLBACK = 0, STAT_TILES = 1, NSTAT = 2 };
+// Statistics of the push kernel: tiles that fell back to global memory
+// (bounding box too large for LDS) and tiles processed, counted in STAT_SLOTS
+// pairs of counters on cache lines of their own and added up by the host.
+// (Device-scope atomics on one address are served every 12 ns: a single
+// counter held a launch of 16384 tiles for 197 us, of 65536 for 790 us.)
+enum { STAT_FALLBACK = 0, STAT_TILES = 1 };
+constexpr int STAT_SLOTS = 256, STAT_STRIDE = 32, NSTAT = STAT_SLOTS * STAT_STRIDE;
+__device__ __forceinline__ void count_stat(unsigned *stats, int which) {
+  atomicAdd(stats + (blockIdx.x & (STAT_SLOTS - 1)) * STAT_STRIDE + which, 1u);
+}
 
 // LDS of one push+deposit workgroup: staged fields (24 B per node in FP32,
 // 48 B in FP64) and current accumulators (3 x 8 B per node).  The budget is
@@ -415,7 +423,18 @@ enum { STAT_FALLBACK = 0, STAT_TILES = 1, NSTAT = 2 };
 // and maximum here.
 constexpr int KSTRIP = 8;  // rows per thread of the 2D k-space update
 constexpr int PUSH_THREADS = 256;
-constexpr int PUSH_BATCH = 4;  // particles loaded per thread before pushing
+// Columns of the 2D push's current box for tiles t wide: the tile, two cells of
+// drift on each side, the stencil's six and one more, which makes the row
+// stride odd for even widths (rows a multiple of 16 of the 8-byte bank slots
+// apart put the rows a wave touches on the same banks: 191 instead of 153 us on
+// 2048 x 512 cells).
+__host__ __device__ constexpr int push_cols(int t) { return t + 11; }
+// LDS bytes of its boxes for a current box of w columns and h rows: 64-bit
+// accumulators of three components, then the six fields one node less on
+// every side.
+__host__ __device__ constexpr long long push_box_bytes(int w, int h, size_t real) {
+  return ((3ll * w * h * 8 + 15) & ~15ll) + (long long)(w - 2) * (h - 2) * 6 * (long long)real;
+}
 constexpr int PUSH_LDS_MIN = 16384;
 constexpr int PUSH_LDS_MAX = 64512;  // with the static LDS, under 64 KiB
 // The 3D push of the FP32 form runs 3 waves per SIMD (register budget 168,
@@ -433,8 +452,8 @@ struct Launch {
   // unit: every run's charges satisfy the 24-bit product bound (FP32 form);
   // ec: energy-conserving gather (all runs of a handle share it)
   static void push_deposit(const Run<R> *runs, const Item *items, int nitems, int parity,
-                           int pp, int lds_bytes, bool unit, bool ec, unsigned *err,
-                           unsigned *stats, hipStream_t s);
+                           int pp, int lds_bytes, int tile1, bool unit, bool ec,
+                           unsigned *err, unsigned *stats, hipStream_t s);
   // tile sort of the particles of all runs: items are (run, first particle,
   // count) chunks; per_run lists (run, 0, 0) once per run.  scramble = true
   // spreads the particles of one cell over a tile's slots (for input in cell

@@ -27,6 +27,7 @@ template <> struct V2<double> { using T = double2; };
 // e3 on (i1, i2), b3 on (i1+1/2, i2+1/2).
 template <class R>
 struct GlobalFields {
+  static constexpr bool local = false;
   gptr<const R> F;
   int n1, n2, cells;
   __device__ int col(int i) const { return wrap_pow2(i, n1); }
@@ -47,38 +48,75 @@ struct GlobalFields {
   __device__ R b3(int r, int c) const { return F[5 * cells + r + c]; }
 };
 
-template <class R>
+// Field box in LDS with row stride FS, or W where FS is 0.  A literal stride
+// makes the nine nodes of a component immediate offsets from one address.
+template <class T> using lptr = T __attribute__((address_space(3))) *;
+template <class R, int FS>
 struct LdsFields {
-  const typename V2<R>::T *P0, *P1;
-  const R *E3, *B3;
+  static constexpr bool local = true;
+  typedef R T2 __attribute__((ext_vector_type(2)));
+  lptr<const T2> P0, P1;
+  lptr<const R> E3, B3;
   int W;
-  __device__ int col(int i) const { return i; }
-  __device__ int row(int j) const { return __mul24(j, W); }
-  __device__ typename V2<R>::T p0(int r, int c) const { return P0[r + c]; }
-  __device__ typename V2<R>::T p1(int r, int c) const { return P1[r + c]; }
+  __device__ int stride() const { return FS > 0 ? FS : W; }
+  __device__ int row(int j) const { return __mul24(j, stride()); }
+  __device__ T2 p0(int r, int c) const { return P0[r + c]; }
+  __device__ T2 p1(int r, int c) const { return P1[r + c]; }
   __device__ R e3(int r, int c) const { return E3[r + c]; }
   __device__ R b3(int r, int c) const { return B3[r + c]; }
 };
 
+// Twice the quadratic B-spline weights (an exact factor, which saves the two
+// halvings per stencil).
+template <class R> __device__ __forceinline__ void spline3x2(R d, R w[3]) {
+  const R a = R(0.5) - d, b = R(0.5) + d;
+  w[0] = a * a;
+  w[1] = R(1.5) - R(2) * d * d;
+  w[2] = b * b;
+}
+// Factor of gather2's result: weights along both axes are doubled in the
+// momentum-conserving gather.
+template <class R, bool EC> constexpr R GATHER_SCALE = EC ? R(1) : R(0.25);
+
 // Quadratic gather (Appendix A): momentum-conserving (every component uses the
-// quadratic B-spline around its own staggered node) or, with ec, energy-
+// quadratic B-spline around its own staggered node) or, with EC, energy-
 // conserving (linear weights along the component's staggered directions).
-template <class R, class Src>
+// Returns the fields over GATHER_SCALE.
+template <class R, bool EC, class Src>
 __device__ __forceinline__ void gather2(const Src &S, int i1, int i2, R f1, R f2, R Ef[3],
-                                        R Bf[3], bool ec) {
+                                        R Bf[3]) {
   const int up1 = f1 >= R(0.5), up2 = f2 >= R(0.5);
   R wi1[3], wh1[3], wi2[3], wh2[3];
-  spline3<R>(f1 - R(up1), wi1);   // integer nodes along x1
-  half3<R>(f1 - R(0.5), wh1, ec);  // half nodes along x1
-  spline3<R>(f2 - R(up2), wi2);
-  half3<R>(f2 - R(0.5), wh2, ec);
+  if constexpr (EC) {
+    spline3<R>(f1 - R(up1), wi1);  // integer nodes along x1
+    line3<R>(f1 - R(0.5), wh1);    // half nodes along x1
+    spline3<R>(f2 - R(up2), wi2);
+    line3<R>(f2 - R(0.5), wh2);
+  } else {
+    spline3x2<R>(f1 - R(up1), wi1);
+    spline3x2<R>(f1 - R(0.5), wh1);
+    spline3x2<R>(f2 - R(up2), wi2);
+    spline3x2<R>(f2 - R(0.5), wh2);
+  }
   int ci[3], ch[3], ri[3], rh[3];
+  if constexpr (Src::local) {
+    // one origin per axis and stencil, the other nodes at fixed distances
+    const int c0 = i1 + up1 - 1, r0 = S.row(i2 + up2 - 1), s0 = S.row(i2 - 1), w = S.stride();
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    ci[a] = S.col(i1 + up1 - 1 + a);
-    ch[a] = S.col(i1 - 1 + a);
-    ri[a] = S.row(i2 + up2 - 1 + a);
-    rh[a] = S.row(i2 - 1 + a);
+    for (int a = 0; a < 3; ++a) {
+      ci[a] = c0 + a;
+      ch[a] = i1 - 1 + a;
+      ri[a] = r0 + a * w;
+      rh[a] = s0 + a * w;
+    }
+  } else {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      ci[a] = S.col(i1 + up1 - 1 + a);
+      ch[a] = S.col(i1 - 1 + a);
+      ri[a] = S.row(i2 + up2 - 1 + a);
+      rh[a] = S.row(i2 - 1 + a);
+    }
   }
   R e1 = 0, e2 = 0, e3 = 0, b1 = 0, b2 = 0, b3 = 0;
 #pragma unroll
@@ -133,36 +171,51 @@ __device__ __forceinline__ void boris(R qmhdt, const R E[3], const R B[3], R u[3
 // out-of-plane velocity enters the fixed-point deposit, which tests reproduce
 // bit for bit on the host): g = sqrt(((1 + u1 u1) + u2 u2) + u3 u3) and
 // v = u * (1/g), square root and reciprocal correctly rounded.
+__device__ __forceinline__ double inv_gamma(double s) {
+  const double g = sqrt(s);
+  return 1.0 / g;
+}
+// 1/g with g = sqrt(s), both correctly rounded, for s >= 1: no scaling against
+// underflow is needed there, which leaves half the instructions of the general
+// square root and division.  g: the hardware root is within one unit, the
+// residuals of its neighbours decide.  1/g: two residual corrections of the
+// hardware reciprocal.  (Equal to the general operations for every float s >=
+// 1, checked exhaustively; infinity gives 0.)
+__device__ __forceinline__ float inv_gamma(float s) {
+#pragma clang fp contract(off)
+  float g = __builtin_amdgcn_sqrtf(s);
+  const float gm = __int_as_float(__float_as_int(g) - 1), gp = __int_as_float(__float_as_int(g) + 1);
+  const float rm = __builtin_fmaf(-gm, g, s), rp = __builtin_fmaf(-gp, g, s);
+  g = rm <= 0.0f ? gm : g;
+  g = rp > 0.0f ? gp : g;
+  float q = __builtin_amdgcn_rcpf(g);
+  q = __builtin_fmaf(__builtin_fmaf(-g, q, 1.0f), q, q);
+  q = __builtin_fmaf(__builtin_fmaf(-g, q, 1.0f), q, q);
+  return s <= 3.402823466e38f ? q : (s > 0.0f ? 0.0f : s);
+}
+
 template <class R>
 __device__ __forceinline__ void velocity(const R u[3], R v[3]) {
 #pragma clang fp contract(off)
   R s = R(1) + u[0] * u[0];
   s = s + u[1] * u[1];
   s = s + u[2] * u[2];
-  const R g = sqrt(s);
-  const R ig = R(1) / g;
+  const R ig = inv_gamma(s);
   v[0] = u[0] * ig;
   v[1] = u[1] * ig;
   v[2] = u[2] * ig;
 }
 
 // New offset in [0,1) and cell shift in {-1, 0, 1} after a move d (|d| < 1).
+// The subtraction is exact above 1; below 0 it may round up to 1, and the
+// position is then the next cell edge.
 template <class R>
 __device__ __forceinline__ int advance(R f, R d, R &g) {
-  g = f + d;
-  int s = 0;
-  if (g >= R(1)) {
-    g = g - R(1);  // exact for g in [1, 2)
-    s = 1;
-  } else if (g < R(0)) {
-    g = g + R(1);
-    s = -1;
-    if (g >= R(1)) {  // rounded up to 1: the position is the next cell edge
-      g = R(0);
-      s = 0;
-    }
-  }
-  return s;
+  const R t = f + d, c = floor(t);
+  g = t - c;
+  const bool edge = g >= R(1);
+  g = edge ? R(0) : g;
+  return (int)c + (edge ? 1 : 0);
 }
 
 // Place the three stencil values s[] of nearest node m in a 4-node window
@@ -190,15 +243,13 @@ struct GlobalFixed {
                                 __MEMORY_SCOPE_DEVICE);
   }
 };
+// Current box in LDS: rows of three component rows, [row][component][column],
+// CS columns (a literal), or W where CS is 0.
+template <int CS>
 struct LdsFixed {
-  unsigned long long *J;
-  int W, plane;
-  __device__ int row(int j) const { return __mul24(j, W); }
-  __device__ int col(int i) const { return i; }
-  __device__ void add(int c, int off, long long v) const {
-    // nodes a particle does not reach hold zero: skipping them saves LDS traffic
-    if (v != 0) atomicAdd(J + c * plane + off, (unsigned long long)v);
-  }
+  lptr<unsigned long long> J;
+  int W;
+  __device__ int width() const { return CS > 0 ? CS : W; }
 };
 struct GlobalFp64 {
   double *J;
@@ -209,13 +260,15 @@ struct GlobalFp64 {
     if (v != 0.0) unsafeAtomicAdd(J + c * cells + off, v);
   }
 };
+template <int CS>
 struct LdsFp64 {
   double *J;
-  int W, plane;
-  __device__ int row(int j) const { return __mul24(j, W); }
+  int W;
+  __device__ int width() const { return CS > 0 ? CS : W; }
+  __device__ int row(int j) const { return __mul24(j, 3 * width()); }
   __device__ int col(int i) const { return i; }
   __device__ void add(int c, int off, double v) const {
-    if (v != 0.0) unsafeAtomicAdd(J + c * plane + off, v);
+    if (v != 0.0) unsafeAtomicAdd(J + c * width() + off, v);
   }
 };
 
@@ -367,7 +420,23 @@ __device__ __forceinline__ void deposit2_fp64(const Sink &K, double jfx1, double
   }
 }
 
-template <class T> using lptr = T __attribute__((address_space(3))) *;
+// What the fixed-point deposit needs of its run, read once per block.
+struct Fix {
+  int P;
+  float inv_wunit, c3;
+  float hz;  // |h| below which every j3 value rounds to zero
+};
+__device__ __forceinline__ float uniform(float x) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+// every j3 value rounds to zero when |h| (S0x t0 + S1x t1) stays below 1/2: the
+// bracket is at most 2 (3/4)(9/4) 2^(2P) = 3.375 2^(2P), and 0.45 leaves room
+// for the FP32 rounding of the products
+__device__ __forceinline__ Fix fix_of(const Run<float> &r) {
+  return Fix{r.P, r.inv_wunit, r.c3, uniform((0.45f / 3.375f) / ((float)(1 << r.P) * (float)(1 << r.P)))};
+}
+struct NoFix {};
+__device__ __forceinline__ NoFix fix_of(const Run<double> &) { return NoFix{}; }
 
 // The same deposit into a workgroup's LDS box, giving the same integers bit for
 // bit; only the addressing and which zero contributions are left out differ.
@@ -378,19 +447,20 @@ template <class T> using lptr = T __attribute__((address_space(3))) *;
 // of j1 (zero unless the lane switches nodes along x1); along x2, row 3 of j1
 // and j3 and C2[2] of j2; all of j1 (j2) for a particle that does not move
 // along x1 (x2) by a quantisation step; all of j3 when |h| is too small for
-// any value to round away from zero.  The x1 column is skipped per lane; the
-// x2 row for the whole wave when no lane switches along x2 (the common case
-// for plasmas drifting along x1); a component for the lanes that do not move
-// along its axis, and for the whole wave when none does (a cold drift along x1
-// has no j2 and j3 outside the laser).  Every other node is added without a
-// test (adding an exact zero changes nothing).  Each window row is one LDS
-// pointer, so the nodes of a row are immediate offsets of the atomics.
-template <bool UNIT>
-__device__ __forceinline__ void deposit2_fixed_lds(const LdsFixed &K, int P, float inv_wunit,
-                                                   float c3, int i1, int i2, float fa1, float fa2,
-                                                   int d1, int d2, float fb1, float fb2, float v3,
-                                                   float qw) {
+// any value to round away from zero.  The x1 column is left to the lanes that
+// switch, in one block at the end; the x2 row is skipped for the whole wave
+// when no lane switches along x2 (the common case for plasmas drifting along
+// x1); a component for the lanes that do not move along its axis (a cold drift
+// along x1 has no j2 and j3 outside the laser).  Every other node is added
+// without a test (adding an exact zero changes nothing).  With a literal column
+// stride every node of the three components is an immediate offset of one
+// address.
+template <bool UNIT, int CS>
+__device__ __forceinline__ void deposit2_fixed_lds(const LdsFixed<CS> &K, const Fix &fx, int i1,
+                                                   int i2, float fa1, float fa2, int d1, int d2,
+                                                   float fb1, float fb2, float v3, float qw) {
 #pragma clang fp contract(off)
+  const int P = fx.P;
   int sa1[3], sb1[3], sa2[3], sb2[3];
   const int na1 = fixed_shape<UNIT>(i1, fa1, P, sa1);
   const int nb1 = fixed_shape<UNIT>(i1 + d1, fb1, P, sb1);
@@ -402,28 +472,30 @@ __device__ __forceinline__ void deposit2_fixed_lds(const LdsFixed &K, int P, flo
   place4(sb1, nb1 - 1 - base1, S1x);
   place4(sa2, na2 - 1 - base2, S0y);
   place4(sb2, nb2 - 1 - base2, S1y);
-  const float qs = qw * inv_wunit;
+  const float qs = qw * fx.inv_wunit;
   const int Q = (int)rintf(qs);
-  int C1[4], C2[4], A1[4], A2[4];
+  int C1[3], C2[3], A1[4], A2[4];
   int acc1 = 0, acc2 = 0;
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     acc1 += S1x[a] - S0x[a];
     acc2 += S1y[a] - S0y[a];
-    C1[a] = acc1;
-    C2[a] = acc2;
+    if (a < 3) {
+      C1[a] = acc1;
+      C2[a] = acc2;
+    }
     A1[a] = S0x[a] + S1x[a];
     A2[a] = S0y[a] + S1y[a];
   }
-  const bool sw1 = na1 != nb1;                      // per lane
-  const bool row3 = __ballot(na2 != nb2) != 0;     // wave-uniform
+  const bool sw1 = na1 != nb1;                   // per lane
+  const bool row3 = __ballot(na2 != nb2) != 0;  // wave-uniform
   // j1 (j2) vanishes when the quantised x1 (x2) shapes are the same before
   // and after the move (three integers summing to 2^P: two of them decide)
   const bool mv1 = (na1 != nb1) | (sa1[0] != sb1[0]) | (sa1[2] != sb1[2]);
   const bool mv2 = (na2 != nb2) | (sa2[0] != sb2[0]) | (sa2[2] != sb2[2]);
-  const int W = K.W;
-  const lptr<unsigned long long> J1 = (lptr<unsigned long long>)K.J + (__mul24(base2, W) + base1);
-  const lptr<unsigned long long> J2 = J1 + K.plane, J3 = J2 + K.plane;
+  const int W = K.width(), W3 = 3 * W;
+  const lptr<unsigned long long> J1 = K.J + (__mul24(base2, W3) + base1);
+  const lptr<unsigned long long> J2 = J1 + W, J3 = J2 + W;
   auto add = [](lptr<unsigned long long> q, long long v) {
     __hip_atomic_fetch_add(q, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   };
@@ -431,88 +503,101 @@ __device__ __forceinline__ void deposit2_fixed_lds(const LdsFixed &K, int P, flo
     if (UNIT) return mul24_wide(qc, f);
     return ((long long)Q * (long long)c) * (long long)f;
   };
-  // j1 = Q C1[a] A2[b], a = 0..2 (C1[3] = 0)
-  if (__ballot(mv1) != 0 && mv1) {
-    int qc1[3];
+  int qc1[3], qc2[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) qc1[a] = UNIT ? mul24_lo(Q, C1[a]) : 0;
+  for (int a = 0; a < 3; ++a) {
+    qc1[a] = UNIT ? mul24_lo(Q, C1[a]) : 0;
+    qc2[a] = UNIT ? mul24_lo(Q, C2[a]) : 0;
+  }
+  // j1 = Q C1[a] A2[b], a = 0..2 (C1[3] = 0)
+  if (mv1) {
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
       if (b == 3 && !row3) break;
-      const lptr<unsigned long long> row = J1 + __mul24(b, W);
+      const lptr<unsigned long long> row = J1 + b * W3;
       add(row, prod(qc1[0], C1[0], A2[b]));
       add(row + 1, prod(qc1[1], C1[1], A2[b]));
-      if (sw1) add(row + 2, prod(qc1[2], C1[2], A2[b]));
     }
   }
   // j2 = Q C2[b] A1[a], b = 0..2 (C2[3] = 0)
-  if (__ballot(mv2) != 0 && mv2) {
+  if (mv2) {
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
       if (b == 2 && !row3) break;
-      const lptr<unsigned long long> row = J2 + __mul24(b, W);
-      const int qc = UNIT ? mul24_lo(Q, C2[b]) : 0;
-      add(row, prod(qc, C2[b], A1[0]));
-      add(row + 1, prod(qc, C2[b], A1[1]));
-      add(row + 2, prod(qc, C2[b], A1[2]));
-      if (sw1) add(row + 3, prod(qc, C2[b], A1[3]));
+      const lptr<unsigned long long> row = J2 + b * W3;
+      add(row, prod(qc2[b], C2[b], A1[0]));
+      add(row + 1, prod(qc2[b], C2[b], A1[1]));
+      add(row + 2, prod(qc2[b], C2[b], A1[2]));
     }
   }
   // j3 = rint(x0[a] t0[b] + x1[a] t1[b]) with the operation order of deposit2_fixed
   const float hv = qs * v3;
-  const float h = hv * c3;
-  // every j3 value rounds to zero when |h| (S0x t0 + S1x t1) stays below 1/2:
-  // the bracket is at most 2 (3/4)(9/4) 2^(2P) = 3.375 2^(2P), and 0.45 leaves
-  // room for the FP32 rounding of the products
-  const bool z3 = fabsf(h) * (3.375f * (float)(1 << P) * (float)(1 << P)) < 0.45f;
-  if (__ballot(!z3) == 0 || z3) return;
-  float x0[4], x1[4];
+  const float h = hv * fx.c3;
+  const bool on3 = !(fabsf(h) < fx.hz);
+  auto j3 = [&](int a0, int a1) {
+    float x0[4], x1[4];
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    x0[a] = (float)S0x[a] * h;
-    x1[a] = (float)S1x[a] * h;
-  }
-  auto j3v = [&](int a, float t0, float t1) -> long long {
-    const float p1 = x1[a] * t1;
-    const float v = __builtin_fmaf(x0[a], t0, p1);
-    return (long long)(int)rintf(v);
+    for (int a = a0; a < a1; ++a) {
+      x0[a] = (float)S0x[a] * h;
+      x1[a] = (float)S1x[a] * h;
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      if (b == 3 && !row3) break;
+      const float B0 = (float)S0y[b], B1 = (float)S1y[b];
+      const float t0 = 2.0f * B0 + B1;
+      const float t1 = B0 + 2.0f * B1;
+      const lptr<unsigned long long> row = J3 + b * W3;
+#pragma unroll
+      for (int a = a0; a < a1; ++a) {
+        const float p1 = x1[a] * t1;
+        const float v = __builtin_fmaf(x0[a], t0, p1);
+        add(row + a, (long long)(int)rintf(v));
+      }
+    }
   };
+  if (on3) j3(0, 3);
+  // the fourth column, of the lanes that switch nodes along x1 (they all move)
+  if (sw1) {
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    if (b == 3 && !row3) break;
-    const float B0 = (float)S0y[b], B1 = (float)S1y[b];
-    const float t0 = 2.0f * B0 + B1;
-    const float t1 = B0 + 2.0f * B1;
-    const lptr<unsigned long long> row = J3 + __mul24(b, W);
-    add(row, j3v(0, t0, t1));
-    add(row + 1, j3v(1, t0, t1));
-    add(row + 2, j3v(2, t0, t1));
-    if (sw1) add(row + 3, j3v(3, t0, t1));
+    for (int b = 0; b < 4; ++b) {
+      if (b == 3 && !row3) break;
+      add(J1 + b * W3 + 2, prod(qc1[2], C1[2], A2[b]));
+    }
+    if (mv2) {
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        if (b == 2 && !row3) break;
+        add(J2 + b * W3 + 3, prod(qc2[b], C2[b], A1[3]));
+      }
+    }
+    if (on3) j3(3, 4);
   }
 }
 
 template <bool UNIT, class Sink>
-__device__ __forceinline__ void deposit_one(const Run<float> &r, const Sink &K, int i1, int i2,
-                                            float fa1, float fa2, int d1, int d2, float fb1,
-                                            float fb2, float v3, float qw) {
-  deposit2_fixed<UNIT>(K, r.P, r.inv_wunit, r.c3, i1, i2, fa1, fa2, d1, d2, fb1, fb2, v3, qw);
+__device__ __forceinline__ void deposit_one(const Run<float> &r, const Fix &fx, const Sink &K,
+                                            int i1, int i2, float fa1, float fa2, int d1, int d2,
+                                            float fb1, float fb2, float v3, float qw) {
+  deposit2_fixed<UNIT>(K, fx.P, fx.inv_wunit, fx.c3, i1, i2, fa1, fa2, d1, d2, fb1, fb2, v3, qw);
 }
-template <bool UNIT>
-__device__ __forceinline__ void deposit_one(const Run<float> &r, const LdsFixed &K, int i1, int i2,
-                                            float fa1, float fa2, int d1, int d2, float fb1,
-                                            float fb2, float v3, float qw) {
-  deposit2_fixed_lds<UNIT>(K, r.P, r.inv_wunit, r.c3, i1, i2, fa1, fa2, d1, d2, fb1, fb2, v3, qw);
+template <bool UNIT, int CS>
+__device__ __forceinline__ void deposit_one(const Run<float> &r, const Fix &fx,
+                                            const LdsFixed<CS> &K, int i1, int i2, float fa1,
+                                            float fa2, int d1, int d2, float fb1, float fb2,
+                                            float v3, float qw) {
+  deposit2_fixed_lds<UNIT, CS>(K, fx, i1, i2, fa1, fa2, d1, d2, fb1, fb2, v3, qw);
 }
 template <bool UNIT, class Sink>
-__device__ __forceinline__ void deposit_one(const Run<double> &r, const Sink &K, int i1, int i2,
-                                            double fa1, double fa2, int d1, int d2, double fb1,
-                                            double fb2, double v3, double qw) {
+__device__ __forceinline__ void deposit_one(const Run<double> &r, const NoFix &, const Sink &K,
+                                            int i1, int i2, double fa1, double fa2, int d1, int d2,
+                                            double fb1, double fb2, double v3, double qw) {
   deposit2_fp64(K, r.jfx1, r.jfx2, i1, i2, fa1, fa2, d1, d2, fb1, fb2, v3, qw);
 }
 
-template <class R> struct Sinks;
-template <> struct Sinks<float> { using G = GlobalFixed; using L = LdsFixed; using T = unsigned long long; };
-template <> struct Sinks<double> { using G = GlobalFp64; using L = LdsFp64; using T = double; };
+template <class R, int CS> struct Sinks;
+template <int CS> struct Sinks<float, CS> { using G = GlobalFixed; using L = LdsFixed<CS>; using T = unsigned long long; };
+template <int CS> struct Sinks<double, CS> { using G = GlobalFp64; using L = LdsFp64<CS>; using T = double; };
 
 // State of one particle as loaded from the buffers.
 template <class R>
@@ -521,56 +606,83 @@ struct PState {
   R f1, f2, u1, u2, u3, qw;
 };
 
+// Element p of an array whose base is uniform: a 32-bit byte offset from a
+// scalar base where every offset fits (at most 10^9 particles: 4-byte
+// elements), which saves the 64-bit address of each access.
+template <class T>
+__device__ __forceinline__ gptr<T> elem(T *a, int p) {
+  if constexpr (sizeof(T) == 4)
+    return (gptr<T>)((gptr<char>)G((char *)a) + (unsigned)p * 4u);
+  else
+    return G(a) + p;
+}
+
 template <class R>
 __device__ __forceinline__ PState<R> load_state(const Parts<R> &P, int p) {
   PState<R> s;
-  s.cell = G(P.cell)[p];
-  s.f1 = G(P.f1)[p];
-  s.f2 = G(P.f2)[p];
-  s.u1 = G(P.u1)[p];
-  s.u2 = G(P.u2)[p];
-  s.u3 = G(P.u3)[p];
-  s.qw = G(P.qw)[p];
+  s.cell = *elem(P.cell, p);
+  s.f1 = *elem(P.f1, p);
+  s.f2 = *elem(P.f2, p);
+  s.u1 = *elem(P.u1, p);
+  s.u2 = *elem(P.u2, p);
+  s.u3 = *elem(P.u3, p);
+  s.qw = *elem(P.qw, p);
   return s;
 }
 
-// Push one particle (state s, index p of buffer P): gather from S at the
-// particle's cell (li1, li2) in S's frame, Boris, move, deposit into K in the
-// same frame, store.  (gi1, gi2) is the global cell.  Returns the global cell
-// after the step (unchanged if the particle was rejected: a non-finite or a
-// too-long move leaves it as it was and sets the error word).
-template <class R, bool UNIT, bool EC, class Src, class Sink>
-__device__ __forceinline__ int push_one(const Run<R> &r, const Parts<R> &P, int p,
-                                        const PState<R> &s, int gi1, int gi2, int li1, int li2,
-                                        const Src &S, const Sink &K, unsigned *err) {
+// Push one particle (state s): gather from S at the particle's cell (li1, li2)
+// in S's frame, Boris, move, deposit into K in the same frame; s becomes the new
+// state, (gi1, gi2) being the global cell.  Sets the cell moves (d1, d2), zero
+// if the particle was rejected: a non-finite or a too-long move leaves it as it
+// was, sets the error word and returns false.  One test of the velocities
+// catches both: a non-finite momentum makes its velocity component NaN (inf *
+// 0, or NaN throughout), and every comparison with NaN is false.
+template <class R, bool UNIT, bool EC, class FX, class Src, class Sink>
+__device__ __forceinline__ bool push_one(const Run<R> &r, const FX &fx, PState<R> &s, int gi1,
+                                         int gi2, int li1, int li2, const Src &S, const Sink &K,
+                                         unsigned *err, int &d1, int &d2) {
   R u[3] = {s.u1, s.u2, s.u3};
   R Ef[3], Bf[3];
-  gather2<R>(S, li1, li2, s.f1, s.f2, Ef, Bf, EC);
-  boris<R>(r.qmhdt, Ef, Bf, u);
+  gather2<R, EC>(S, li1, li2, s.f1, s.f2, Ef, Bf);
+  boris<R>(r.qmhdt * GATHER_SCALE<R, EC>, Ef, Bf, u);
   R v[3];
   velocity<R>(u, v);
   const R m1 = r.dtdx1 * v[0], m2 = r.dtdx2 * v[1];
-  if (!(isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]) && isfinite(m1) && isfinite(m2))) {
-    atomicOr(err, ERR_NUMERIC);
-    return s.cell;
-  }
-  if (!(fabs(m1) < R(1)) || !(fabs(m2) < R(1))) {
-    atomicOr(err, ERR_RANGE);
-    return s.cell;
+  d1 = d2 = 0;
+  if (!(fabs(m1) < R(1) && fabs(m2) < R(1) && fabs(v[2]) < R(2))) {
+    const bool fin = isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]) && isfinite(m1) && isfinite(m2);
+    atomicOr(err, fin ? ERR_RANGE : ERR_NUMERIC);
+    return false;
   }
   R g1, g2;
-  const int d1 = advance<R>(s.f1, m1, g1);
-  const int d2 = advance<R>(s.f2, m2, g2);
-  deposit_one<UNIT>(r, K, li1, li2, s.f1, s.f2, d1, d2, g1, g2, v[2], s.qw);
-  const int j1 = wrap_pow2(gi1 + d1, r.n1), j2 = wrap_small(gi2 + d2, r.n2);
-  const int cell = (j2 << r.log2n1) | j1;
-  G(P.cell)[p] = cell;
-  G(P.f1)[p] = g1;
-  G(P.f2)[p] = g2;
-  G(P.u1)[p] = u[0];
-  G(P.u2)[p] = u[1];
-  G(P.u3)[p] = u[2];
-  return cell;
+  d1 = advance<R>(s.f1, m1, g1);
+  d2 = advance<R>(s.f2, m2, g2);
+  deposit_one<UNIT>(r, fx, K, li1, li2, s.f1, s.f2, d1, d2, g1, g2, v[2], s.qw);
+  s.cell = (wrap_small(gi2 + d2, r.n2) << r.log2n1) | wrap_pow2(gi1 + d1, r.n1);
+  s.f1 = g1;
+  s.f2 = g2;
+  s.u1 = u[0];
+  s.u2 = u[1];
+  s.u3 = u[2];
+  return true;
+}
+
+template <class R>
+__device__ __forceinline__ void store_state(const Parts<R> &P, int p, const PState<R> &s) {
+  *elem(P.cell, p) = s.cell;
+  *elem(P.f1, p) = s.f1;
+  *elem(P.f2, p) = s.f2;
+  *elem(P.u1, p) = s.u1;
+  *elem(P.u2, p) = s.u2;
+  *elem(P.u3, p) = s.u3;
+}
+// Has the loads of s returned here.  Loads and stores are counted in one queue:
+// a state still awaited when the next particle starts would wait out the stores
+// issued after its loads as well (277 -> 265 us on 8192 x 512 cells, two
+// particles a cell).
+template <class R>
+__device__ __forceinline__ void arrived(PState<R> &s) {
+  asm volatile("" : "+v"(s.cell), "+v"(s.f1), "+v"(s.f2), "+v"(s.u1), "+v"(s.u2), "+v"(s.u3), "+v"(s.qw));
 }
 
 __device__ __forceinline__ int wrap_delta_pow2(int d, int n) { return ((d + (n >> 1)) & (n - 1)) - (n >> 1); }
@@ -589,15 +701,140 @@ __device__ __forceinline__ int wave_max(int v) {
   return v;
 }
 
+// Cell i (0 <= i < n) relative to a tile origin, in the tile's frame: the
+// period [-o, n - o) with o = (n - T) / 2, i.e. centred on the tile, so that
+// particles may drift half the rest of the box from their tile before the
+// frame's edge splits them.
+__device__ __forceinline__ int frame_pow2(int d, int o, int n) { return ((d + o) & (n - 1)) - o; }
+__device__ __forceinline__ int frame_any(int d, int o, int n) {
+  d += (d < -o) ? n : 0;
+  d -= (d >= n - o) ? n : 0;
+  return d;
+}
+// i mod n for any i within a few periods
+__device__ __forceinline__ int wrap_any(int i, int n) {
+  while (i >= n) i -= n;
+  while (i < 0) i += n;
+  return i;
+}
+
+// Walks the nodes of a W x H box with the workgroup's threads: f(row, column).
+// Rows of up to 32 (64) nodes take half a wave (a wave) each, so that no
+// thread divides; wider rows are walked in pieces of 64.
+template <class F>
+__device__ __forceinline__ void for_box(int W, int H, F f) {
+  const int sh = W <= 32 ? 5 : 6, lanes = 1 << sh;
+  for (int b = (int)threadIdx.x >> sh; b < H; b += PUSH_THREADS >> sh)
+    for (int a = (int)threadIdx.x & (lanes - 1); a < W; a += lanes) f(b, a);
+}
+
+// Bounding box of the cells a thread's particles move to, then of the
+// workgroup's (nbox, initialised before a barrier).
+struct CellBox {
+  int lo1 = 1 << 30, hi1 = -(1 << 30), lo2 = 1 << 30, hi2 = -(1 << 30);
+  __device__ __forceinline__ void add(int d1, int d2) {
+    lo1 = min(lo1, d1); hi1 = max(hi1, d1);
+    lo2 = min(lo2, d2); hi2 = max(hi2, d2);
+  }
+  __device__ __forceinline__ void reduce(int *nbox) const {
+    const int a = wave_min(lo1), b = wave_max(hi1), c = wave_min(lo2), d = wave_max(hi2);
+    if ((threadIdx.x & 63) == 0) {
+      atomicMin(&nbox[0], a); atomicMax(&nbox[1], b);
+      atomicMin(&nbox[2], c); atomicMax(&nbox[3], d);
+    }
+  }
+};
+
+// The workgroup's tile through LDS boxes with column strides CS (current) and
+// CS - 2 (fields), or the box's own where CS is 0; the thread's first particle
+// s0 (loaded before, so that its loads wait out the latency with the
+// staging's).  box collects the particles' new cells in the frame.
+template <class R, bool UNIT, bool EC, int CS>
+__device__ __forceinline__ void push_tile(const Run<R> &r, const Parts<R> &P, int parity, int start,
+                                          int end, PState<R> s0, int ref1, int ref2, int lo1,
+                                          int lo2, int W, int H, unsigned char *smem,
+                                          unsigned *err, int *nbox) {
+  using SK = Sinks<R, CS>;
+  using T = typename SK::T;
+  constexpr int FS = CS > 0 ? CS - 2 : 0;
+  const int n1 = r.n1, n2 = r.n2, cells = n1 * n2;
+  const int FW = W - 2, FH = H - 2;
+  const int cs = CS > 0 ? CS : W, fs = CS > 0 ? FS : FW;
+  const int jrow = 3 * cs, fnodes = fs * FH;
+  const int jbytes = (jrow * H * (int)sizeof(T) + 15) & ~15;
+  // LDS layout: current accumulators first, then the fields (16-byte aligned)
+  using LF = LdsFields<R, FS>;
+  using T2 = typename LF::T2;
+  const lptr<T> lj = (lptr<T>)smem;
+  const lptr<T2> lp0 = (lptr<T2>)(smem + jbytes);
+  const lptr<T2> lp1 = lp0 + fnodes;
+  const lptr<R> le3 = (lptr<R>)(lp1 + fnodes);
+  const lptr<R> lb3 = le3 + fnodes;
+  const gptr<const R> F = G((const R *)r.F);
+  const int o1 = ref1 + lo1 - 1, o2 = ref2 + lo2 - 1;  // global cell of the field-box origin
+  for_box(FW, FH, [&](int b, int a) {
+    const int g = wrap_any(o2 + b, n2) * n1 + wrap_pow2(o1 + a, n1), q = b * fs + a;
+    const R e1 = F[g], e2 = F[cells + g], e3 = F[2 * cells + g];
+    const R b1 = F[3 * cells + g], b2 = F[4 * cells + g], b3 = F[5 * cells + g];
+    lp0[q] = T2{e1, b2};
+    lp1[q] = T2{e2, b1};
+    le3[q] = e3;
+    lb3[q] = b3;
+  });
+  for (int q = threadIdx.x; q < jrow * H; q += PUSH_THREADS) lj[q] = 0;
+  __syncthreads();
+  // Particles use field-box coordinates (origin: cell lo-1).  The current box
+  // starts one cell earlier, so its sink is shifted by one row and one column.
+  const LF S{lp0, lp1, le3, lb3, fs};
+  typename SK::L K;
+  K.J = (decltype(K.J))(lj + jrow + 1);
+  K.W = W;
+  const int f1 = (n1 - r.T1) >> 1, f2 = (n2 - r.T2) >> 1;
+  const auto fx = fix_of(r);
+  CellBox box;
+  PState<R> st = s0;
+  for (int p = start + (int)threadIdx.x; p < end;) {
+    // the next particle's loads are in flight while this one is pushed
+    const int pn = p + PUSH_THREADS;
+    PState<R> sn = st;
+    if (pn < end) sn = load_state(P, pn);
+    const int i1 = st.cell & (n1 - 1), i2 = st.cell >> r.log2n1;
+    const int l1 = frame_pow2(i1 - ref1, f1, n1), l2 = frame_any(i2 - ref2, f2, n2);
+    int d1, d2;
+    const bool ok = push_one<R, UNIT, EC>(r, fx, st, i1, i2, l1 - lo1 + 1, l2 - lo2 + 1, S, K, err,
+                                          d1, d2);
+    box.add(l1 + d1, l2 + d2);
+    arrived(sn);
+    if (ok) store_state(P, p, st);
+    st = sn;
+    p = pn;
+  }
+  box.reduce(nbox);
+  __syncthreads();
+  // add the box to the global accumulators
+  const auto J = G((T *)r.J[parity]);
+  for_box(W, H, [&](int b, int a) {
+    const int g = wrap_any(o2 - 1 + b, n2) * n1 + wrap_pow2(o1 - 1 + a, n1);
+#pragma unroll
+    for (int comp = 0; comp < 3; ++comp) {
+      const T v = lj[b * jrow + comp * cs + a];
+      if (v != 0)
+        __scoped_atomic_fetch_add(J + comp * cells + g, v, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+    }
+  });
+}
+
 // One workgroup per (run, tile).  The tile's bounding box (from the previous
 // push, or the tile itself right after a sort) sizes the LDS staging; the new
-// box of the pushed particles is written back for the next step.
-template <class R, bool UNIT, bool EC>
-__global__ void __launch_bounds__(PUSH_THREADS)
+// box of the pushed particles is written back for the next step.  CS: the
+// literal column stride of the boxes (the tile's width and its drift margin),
+// used by every tile whose box is no wider; a wider one takes the box's own
+// stride.
+template <class R, bool UNIT, bool EC, int CS>
+__global__ void __launch_bounds__(PUSH_THREADS, sizeof(R) == 4 ? 5 : 3)
 k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, int parity, int pp,
                int lds_bytes, unsigned *err, unsigned *stats) {
-  using T2 = typename V2<R>::T;
-  using SK = Sinks<R>;
+  using SK = Sinks<R, 0>;
   extern __shared__ unsigned char smem_raw[];
   __shared__ int nbox[4];
   const Item it = items[blockIdx.x];
@@ -606,6 +843,8 @@ k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, 
   const int t = it.a;
   const int start = r.tile_start[t], end = r.tile_start[t + 1];
   if (start >= end) return;
+  PState<R> s0{};
+  if (start + (int)threadIdx.x < end) s0 = load_state(P, start + (int)threadIdx.x);
   const int n1 = r.n1, n2 = r.n2, cells = n1 * n2;
   const int t2 = t / r.nt1, t1 = t - t2 * r.nt1;
   const int ref1 = t1 * r.T1, ref2 = t2 * r.T2;  // tile origin
@@ -613,108 +852,53 @@ k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, 
   const int lo1 = box[0], hi1 = box[1], lo2 = box[2], hi2 = box[3];
   if (threadIdx.x == 0) {
     nbox[0] = 1 << 30; nbox[1] = -(1 << 30); nbox[2] = 1 << 30; nbox[3] = -(1 << 30);
-    atomicAdd(&stats[STAT_TILES], 1u);
   }
-  // field box: cells lo-1 .. hi+2; current box: lo-2 .. hi+3
-  const int FW = hi1 - lo1 + 4, FH = hi2 - lo2 + 4;
+  // current box: lo-2 .. hi+3; field box: cells lo-1 .. hi+2
   const int W = hi1 - lo1 + 6, H = hi2 - lo2 + 6;
-  const int fnodes = FW * FH, jnodes = W * H;
-  const size_t jbytes = ((size_t)3 * jnodes * sizeof(typename SK::T) + 15) & ~(size_t)15;
-  const size_t need = jbytes + (size_t)fnodes * (2 * sizeof(T2) + 2 * sizeof(R));
-  int blo1 = 1 << 30, bhi1 = -(1 << 30), blo2 = 1 << 30, bhi2 = -(1 << 30);
-  auto track = [&](int cell) {
-    const int d1 = wrap_delta_pow2((cell & (n1 - 1)) - ref1, n1);
-    const int d2 = wrap_delta((cell >> r.log2n1) - ref2, n2);
-    blo1 = min(blo1, d1); bhi1 = max(bhi1, d1);
-    blo2 = min(blo2, d2); bhi2 = max(bhi2, d2);
-  };
-  if (need > (size_t)lds_bytes) {
+  auto need = [&](int w) { return push_box_bytes(w, H, sizeof(R)); };
+  const int f1 = (n1 - r.T1) >> 1, f2 = (n2 - r.T2) >> 1;
+  const bool local = need(W) <= lds_bytes;
+  if (CS > 0 && W <= CS && need(CS) <= lds_bytes) {
+    push_tile<R, UNIT, EC, CS>(r, P, parity, start, end, s0, ref1, ref2, lo1, lo2, W, H, smem_raw,
+                               err, nbox);
+  } else if (local) {
+    push_tile<R, UNIT, EC, 0>(r, P, parity, start, end, s0, ref1, ref2, lo1, lo2, W, H, smem_raw,
+                              err, nbox);
+  } else {
     // fallback: gather and deposit in global memory.  The barrier orders the
     // box initialisation above before every wave's min/max at the end (the
-    // LDS branch has its own barrier after the staging).
+    // LDS paths have their own barriers).
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(&stats[STAT_FALLBACK], 1u);
+    CellBox nb;
     const GlobalFields<R> S{G((const R *)r.F), n1, n2, cells};
     const typename SK::G K{(decltype(SK::G::J))G((typename SK::T *)r.J[parity]), n1, n2, cells};
     for (int p = start + threadIdx.x; p < end; p += PUSH_THREADS) {
-      const PState<R> s = load_state(P, p);
+      PState<R> s = load_state(P, p);
       const int i1 = s.cell & (n1 - 1), i2 = s.cell >> r.log2n1;
-      track(push_one<R, UNIT, EC>(r, P, p, s, i1, i2, i1, i2, S, K, err));
+      int d1, d2;
+      if (push_one<R, UNIT, EC>(r, fix_of(r), s, i1, i2, i1, i2, S, K, err, d1, d2)) store_state(P, p, s);
+      nb.add(frame_pow2(i1 - ref1, f1, n1) + d1, frame_any(i2 - ref2, f2, n2) + d2);
     }
-  } else {
-    // LDS layout: current accumulators first, then the fields (16-byte aligned)
-    typename SK::T *lj = (typename SK::T *)smem_raw;
-    T2 *lp0 = (T2 *)(smem_raw + jbytes);
-    T2 *lp1 = lp0 + fnodes;
-    R *le3 = (R *)(lp1 + fnodes);
-    R *lb3 = le3 + fnodes;
-    const gptr<const R> F = G((const R *)r.F);
-    const int o1 = ref1 + lo1 - 1, o2 = ref2 + lo2 - 1;  // global cell of the field-box origin
-    for (int q = threadIdx.x; q < fnodes; q += PUSH_THREADS) {
-      const int b = q / FW, a = q - b * FW;
-      int g2 = (o2 + b) % n2;
-      g2 += g2 < 0 ? n2 : 0;
-      const int g = g2 * n1 + wrap_pow2(o1 + a, n1);
-      T2 v0, v1;
-      v0.x = F[g];             // E1
-      v0.y = F[4 * cells + g]; // B2
-      v1.x = F[cells + g];     // E2
-      v1.y = F[3 * cells + g]; // B1
-      lp0[q] = v0;
-      lp1[q] = v1;
-      le3[q] = F[2 * cells + g];
-      lb3[q] = F[5 * cells + g];
-    }
-    for (int q = threadIdx.x; q < 3 * jnodes; q += PUSH_THREADS) lj[q] = 0;
+    nb.reduce(nbox);
     __syncthreads();
-    // Particles use field-box coordinates (origin: cell lo-1).  The current box
-    // starts one cell earlier, so its sink is shifted by one row and one column.
-    const LdsFields<R> S{lp0, lp1, le3, lb3, FW};
-    const typename SK::L K{lj + W + 1, W, jnodes};
-    // each thread loads a batch of PUSH_BATCH particles (strided by the block,
-    // so every load stays coalesced) before pushing them: more bytes in flight
-    for (int p0 = start + threadIdx.x; p0 < end; p0 += PUSH_BATCH * PUSH_THREADS) {
-      PState<R> st[PUSH_BATCH];
-#pragma unroll
-      for (int k = 0; k < PUSH_BATCH; ++k) {
-        const int p = p0 + k * PUSH_THREADS;
-        if (p < end) st[k] = load_state(P, p);
-      }
-#pragma unroll
-      for (int k = 0; k < PUSH_BATCH; ++k) {
-        const int p = p0 + k * PUSH_THREADS;
-        if (p < end) {
-          const int i1 = st[k].cell & (n1 - 1), i2 = st[k].cell >> r.log2n1;
-          const int d1 = wrap_delta_pow2(i1 - ref1, n1), d2 = wrap_delta(i2 - ref2, n2);
-          track(push_one<R, UNIT, EC>(r, P, p, st[k], i1, i2, d1 - lo1 + 1, d2 - lo2 + 1, S, K, err));
-        }
-      }
+  }
+  // new bounding box of the tile's particles; one that reaches past the
+  // frame's edge wraps, so it becomes the whole frame
+  if (threadIdx.x < 2) {
+    const int k = threadIdx.x, f = k ? f2 : f1, n = k ? n2 : n1;
+    int lo = nbox[2 * k], hi = nbox[2 * k + 1];
+    if (lo < -f || hi >= n - f) {
+      lo = -f;
+      hi = n - f - 1;
     }
-    __syncthreads();
-    // add the box to the global accumulators
-    const auto J = G((typename SK::T *)r.J[parity]);
-    const int c1 = ref1 + lo1 - 2, c2 = ref2 + lo2 - 2;
-    for (int q = threadIdx.x; q < jnodes; q += PUSH_THREADS) {
-      const int b = q / W, a = q - b * W;
-      int g2 = (c2 + b) % n2;
-      g2 += g2 < 0 ? n2 : 0;
-      const int g = g2 * n1 + wrap_pow2(c1 + a, n1);
-#pragma unroll
-      for (int comp = 0; comp < 3; ++comp) {
-        const typename SK::T v = lj[comp * jnodes + q];
-        if (v != 0)
-          __scoped_atomic_fetch_add(J + comp * cells + g, v, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
-      }
+    r.tile_box[6 * t + 2 * k] = lo;
+    r.tile_box[6 * t + 2 * k + 1] = hi;
+    // (counted last: nothing waits for these atomics)
+    if (k == 0) {
+      count_stat(stats, STAT_TILES);
+      if (!local) count_stat(stats, STAT_FALLBACK);
     }
   }
-  // new bounding box of the tile's particles
-  blo1 = wave_min(blo1); bhi1 = wave_max(bhi1); blo2 = wave_min(blo2); bhi2 = wave_max(bhi2);
-  if ((threadIdx.x & 63) == 0) {
-    atomicMin(&nbox[0], blo1); atomicMax(&nbox[1], bhi1);
-    atomicMin(&nbox[2], blo2); atomicMax(&nbox[3], bhi2);
-  }
-  __syncthreads();
-  if (threadIdx.x < 4) r.tile_box[6 * t + threadIdx.x] = nbox[threadIdx.x];
 }
 
 // ---------------------------------------------------------------- tile sort
@@ -773,20 +957,16 @@ __global__ void __launch_bounds__(1024) k_sort_scan(const Run<R> *runs, const It
     r.tile_start[t] = run;
     r.tile_cnt[t] = run;
     run += c;
-    // right after the sort every particle of tile t lies in the tile; the box
-    // is expressed in the frame the push uses (cell minus tile origin, wrapped
-    // into [-n/2, n - n/2)), so a tile wider than half the grid covers the
-    // whole wrapped range
+    // right after the sort every particle of tile t lies in the tile, which the
+    // frame of the push (centred on the tile) always holds whole
     const int t3 = t / (r.nt1 * r.nt2), t12 = t - t3 * r.nt1 * r.nt2;
     const int t2 = t12 / r.nt1, t1 = t12 - t2 * r.nt1;
     const int w[3] = {min(r.T1, r.n1 - t1 * r.T1), min(r.T2, r.n2 - t2 * r.T2),
                       min(r.T3, r.n3 - t3 * r.T3)};
-    const int nn[3] = {r.n1, r.n2, r.n3};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      const bool full = w[d] > nn[d] - (nn[d] >> 1);
-      r.tile_box[6 * t + 2 * d] = full ? -(nn[d] >> 1) : 0;
-      r.tile_box[6 * t + 2 * d + 1] = full ? nn[d] - (nn[d] >> 1) - 1 : w[d] - 1;
+      r.tile_box[6 * t + 2 * d] = 0;
+      r.tile_box[6 * t + 2 * d + 1] = w[d] - 1;
     }
   }
   if (threadIdx.x == 1023) r.tile_start[nt] = part[1023];
@@ -923,28 +1103,33 @@ __global__ void k_kinetic(const Run<R> *run, int pp, double *partial) {
 }
 
 // ---------------------------------------------------------------- launches
+// Literal strides for the tile widths in use; other widths, and the
+// energy-conserving gather, take the box's own stride.
 template <class R>
 void Launch<R>::push_deposit(const Run<R> *runs, const Item *items, int nitems, int parity, int pp,
-                             int lds_bytes, bool unit, bool ec, unsigned *err, unsigned *stats,
-                             hipStream_t s) {
+                             int lds_bytes, int tile1, bool unit, bool ec, unsigned *err,
+                             unsigned *stats, hipStream_t s) {
   if (nitems <= 0) return;
-  if constexpr (std::is_same<R, float>::value) {
-    if (unit) {
-      if (ec)
-        hipLaunchKernelGGL((k_push_deposit<R, true, true>), dim3(nitems), dim3(PUSH_THREADS),
-                           lds_bytes, s, runs, items, parity, pp, lds_bytes, err, stats);
-      else
-        hipLaunchKernelGGL((k_push_deposit<R, true, false>), dim3(nitems), dim3(PUSH_THREADS),
-                           lds_bytes, s, runs, items, parity, pp, lds_bytes, err, stats);
-      return;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nitems), dim3(PUSH_THREADS), lds_bytes, s, runs, items, parity,
+                       pp, lds_bytes, err, stats);
+  };
+  constexpr bool F = std::is_same<R, float>::value;
+  auto by_width = [&](auto u) {
+    constexpr bool U = decltype(u)::value;
+    if (ec) return go(k_push_deposit<R, U, true, 0>);
+    switch (tile1) {
+      case 8: return go(k_push_deposit<R, U, false, push_cols(8)>);
+      case 16: return go(k_push_deposit<R, U, false, push_cols(16)>);
+      case 32: return go(k_push_deposit<R, U, false, push_cols(32)>);
+      case 64: return go(k_push_deposit<R, U, false, push_cols(64)>);
+      default: return go(k_push_deposit<R, U, false, 0>);
     }
-  }
-  if (ec)
-    hipLaunchKernelGGL((k_push_deposit<R, false, true>), dim3(nitems), dim3(PUSH_THREADS),
-                       lds_bytes, s, runs, items, parity, pp, lds_bytes, err, stats);
+  };
+  if (F && unit)
+    by_width(std::integral_constant<bool, F>{});
   else
-    hipLaunchKernelGGL((k_push_deposit<R, false, false>), dim3(nitems), dim3(PUSH_THREADS),
-                       lds_bytes, s, runs, items, parity, pp, lds_bytes, err, stats);
+    by_width(std::false_type{});
 }
 
 template <class R>

@@ -19,10 +19,12 @@
 
 namespace hp {
 
-__device__ __forceinline__ int wrap_delta_pow2_3(int d, int n) { return ((d + (n >> 1)) & (n - 1)) - (n >> 1); }
-__device__ __forceinline__ int wrap_delta_3(int d, int n) {
-  d += (d < -(n >> 1)) ? n : 0;
-  d -= (d >= n - (n >> 1)) ? n : 0;
+// Cell minus tile origin in the tile's frame: the period [-o, n - o), o = (n -
+// T) / 2, centred on the tile.
+__device__ __forceinline__ int frame_pow2_3(int d, int o, int n) { return ((d + o) & (n - 1)) - o; }
+__device__ __forceinline__ int frame_any_3(int d, int o, int n) {
+  d += (d < -o) ? n : 0;
+  d -= (d >= n - o) ? n : 0;
   return d;
 }
 // i mod n for any i (a loop of corrections: boxes that fit the LDS reach at
@@ -487,6 +489,7 @@ k_push_deposit3(const Run<R> *__restrict__ runs, const Item *__restrict__ items,
   const int t3 = t / (r.nt1 * r.nt2), t12 = t - t3 * r.nt1 * r.nt2;
   const int t2 = t12 / r.nt1, t1 = t12 - t2 * r.nt1;
   const int ref[3] = {t1 * r.T1, t2 * r.T2, t3 * r.T3};
+  const int fo[3] = {(n1 - r.T1) >> 1, (n2 - r.T2) >> 1, (n3 - r.T3) >> 1};
   const int *box = r.tile_box + 6 * t;
   int lo[3], hi[3];
 #pragma unroll
@@ -500,7 +503,7 @@ k_push_deposit3(const Run<R> *__restrict__ runs, const Item *__restrict__ items,
       nbox[2 * d] = 1 << 30;
       nbox[2 * d + 1] = -(1 << 30);
     }
-    atomicAdd(&stats[STAT_TILES], 1u);
+    count_stat(stats, STAT_TILES);
   }
   // current box: cells lo-2 .. hi+3 per axis
   const int W = hi[0] - lo[0] + 6, H = hi[1] - lo[1] + 6, D = hi[2] - lo[2] + 6;
@@ -510,8 +513,8 @@ k_push_deposit3(const Run<R> *__restrict__ runs, const Item *__restrict__ items,
   auto track = [&](int cell) {
     int i1, i2, i3;
     unpack3(cell, r.log2n1, r.sh3, n1, i1, i2, i3);
-    const int dl[3] = {wrap_delta_pow2_3(i1 - ref[0], n1), wrap_delta_3(i2 - ref[1], n2),
-                       wrap_delta_3(i3 - ref[2], n3)};
+    const int dl[3] = {frame_pow2_3(i1 - ref[0], fo[0], n1), frame_any_3(i2 - ref[1], fo[1], n2),
+                       frame_any_3(i3 - ref[2], fo[2], n3)};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       bl[d] = min(bl[d], dl[d]);
@@ -522,7 +525,7 @@ k_push_deposit3(const Run<R> *__restrict__ runs, const Item *__restrict__ items,
     // the barrier orders the box initialisation above before every wave's
     // min/max at the end (the LDS branch has its own after the staging)
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(&stats[STAT_FALLBACK], 1u);
+    if (threadIdx.x == 0) count_stat(stats, STAT_FALLBACK);
     const typename SK::G K{(decltype(SK::G::J))G((typename SK::T *)r.J[parity]), n1, n2, n3,
                            n1 * n2, r.cells};
     for (int p = start + threadIdx.x; p < end; p += 256) {
@@ -587,9 +590,9 @@ k_push_deposit3(const Run<R> *__restrict__ runs, const Item *__restrict__ items,
       }
       int i1, i2, i3;
       unpack3(cell, r.log2n1, r.sh3, n1, i1, i2, i3);
-      const int l[3] = {wrap_delta_pow2_3(i1 - ref[0], n1) - lo[0] + 2,
-                        wrap_delta_3(i2 - ref[1], n2) - lo[1] + 2,
-                        wrap_delta_3(i3 - ref[2], n3) - lo[2] + 2};
+      const int l[3] = {frame_pow2_3(i1 - ref[0], fo[0], n1) - lo[0] + 2,
+                        frame_any_3(i2 - ref[1], fo[1], n2) - lo[1] + 2,
+                        frame_any_3(i3 - ref[2], fo[2], n3) - lo[2] + 2};
       if (use_fl)
         track(push_one3<R>(r, P, p, cell, st, i1, i2, i3, l, SL, K, err));
       else

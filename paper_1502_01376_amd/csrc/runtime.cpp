@@ -685,7 +685,7 @@ class Sim : public SimBase {
       launch_push_cubic<R>(d_runs_, d_tiles_, n_tiles_, p, pp_, push_lds_, all_unit(),
                            runs_[0].cfg.interp == 1, d_err_, stream_);
     else
-      Launch<R>::push_deposit(d_runs_, d_tiles_, n_tiles_, p, pp_, push_lds_, all_unit(),
+      Launch<R>::push_deposit(d_runs_, d_tiles_, n_tiles_, p, pp_, push_lds_, tile1_, all_unit(),
                               runs_[0].cfg.interp == 1, d_err_,
                               d_stats_, stream_);
     mark(HP_K_PUSH_DEPOSIT, false);
@@ -1506,10 +1506,13 @@ class Sim : public SimBase {
   int push_stats(int64_t *out) override {
     int rc;
     if ((rc = sync())) return rc;
-    unsigned h[NSTAT];
-    if ((rc = d2h(h, d_stats_, NSTAT))) return rc;
-    out[0] = h[STAT_FALLBACK];
-    out[1] = h[STAT_TILES];
+    std::vector<unsigned> h(NSTAT);
+    if ((rc = d2h(h.data(), d_stats_, NSTAT))) return rc;
+    out[0] = out[1] = 0;
+    for (int s = 0; s < NSTAT; s += STAT_STRIDE) {
+      out[0] += h[s + STAT_FALLBACK];
+      out[1] += h[s + STAT_TILES];
+    }
     return HP_OK;
   }
 
@@ -1646,7 +1649,14 @@ class Sim : public SimBase {
     // always does, it was measured faster so)
     const int node_bytes = FIXED ? 48 : (dim_ == 3 ? 24 : 72);
     const int lds_max = (FIXED && dim_ == 3) ? PUSH3_LDS_MAX_FP32 : PUSH_LDS_MAX;
-    push_lds_ = std::min(lds_max, std::max(PUSH_LDS_MIN, ((maxbox * node_bytes + 1023) / 1024) * 1024));
+    long long need = (long long)maxbox * node_bytes;
+    if (dim_ == 2 && runs_[0].d.shape == 2) {
+      need = 0;
+      for (const RunHost &h : runs_)
+        need = std::max(need, push_box_bytes(push_cols(std::min(t1, h.d.n1)),
+                                             std::min(h.d.T2 + 2 * SLACK2, h.d.n2) + 6, sizeof(R)));
+    }
+    push_lds_ = (int)std::min<long long>(lds_max, std::max<long long>(PUSH_LDS_MIN, (need + 511) / 512 * 512));
     if (d_tiles_) release(d_tiles_);
     d_tiles_ = nullptr;
     n_tiles_ = 0;
