@@ -421,7 +421,6 @@ __device__ __forceinline__ void count_stat(unsigned *stats, int which) {
 // 48 B in FP64) and current accumulators (3 x 8 B per node).  The budget is
 // set per handle from the tile shape (push_lds_bytes), between the minimum
 // and maximum here.
-constexpr int KSTRIP = 8;  // rows per thread of the 2D k-space update
 constexpr int PUSH_THREADS = 256;
 // Columns of the 2D push's current box for tiles t wide: the tile, two cells of
 // drift on each side, the stencil's six and one more, which makes the row
@@ -464,7 +463,7 @@ struct Launch {
   // or 1 (item = run, row, component) for long rows
   static void fft_j(const Run<R> *runs, const Item *items, int nitems, int parity, int maxM,
                     int ncomp, hipStream_t s);
-  static void kupdate(const Run<R> *runs, const Item *items, int nitems, int parity,
+  static void kupdate(const Run<R> *runs, const Item *items, int nitems, int parity, int strip,
                       hipStream_t s);
   // 3D: the same update as two passes (E and the half-step B, then B)
   static void kupdate3(const Run<R> *runs, const Item *items, int nitems, int parity,

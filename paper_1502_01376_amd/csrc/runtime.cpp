@@ -18,7 +18,6 @@
 
 #include "hpic.h"
 #include "hpic_q3d.h"
-#include "hpic_update3.h"
 
 using namespace hp;
 
@@ -373,13 +372,12 @@ class Sim : public SimBase {
       h.grp0 = (int)grps.size();
       for (int r = 0; r < d.rows; ++r)
         for (int g = 0; g < 6; g += ncomp_) grps.push_back(Item{i, r, ncomp_ == 3 ? g / 3 : g});
-      // 2D: one update thread per (strip of KSTRIP rows, kappa1); 3D: per
-      // (strip of KSTRIP3 planes, i2, kappa1)
-      const int nel =
-          (d.dim == 3 ? ((d.n3 + KSTRIP3 - 1) / KSTRIP3) * d.n2 : (d.n2 + KSTRIP - 1) / KSTRIP) * d.nk;
-      for (int e = 0; e < nel; e += UPD_BLOCK) upd.push_back(Item{i, e, 0});
       perrun.push_back(Item{i, 0, 0});
     }
+    // one update thread per strip of rows i2 (2D) or row (3D) and mode
+    strip_ = update_strip();
+    for (int i = 0; i < nruns; ++i)
+      for (int e = 0; e < update_threads(runs_[i].d, strip_); e += UPD_BLOCK) upd.push_back(Item{i, e, 0});
     for (int i = 0; i < nruns; ++i)
       if (cfgs[i].sort_interval > 0) sort_interval_ = cfgs[i].sort_interval;
     int rc;
@@ -388,6 +386,17 @@ class Sim : public SimBase {
     if (dim_ == 3) {
       tile1_ = TILE1_3D;
       tile2_ = TILE2_3D;
+    } else {
+      // smaller tiles where the default ones would leave compute units without
+      // a workgroup (64 x 32: push 18.0 us with 8 tiles of 32 x 8, 13.0 with 16
+      // of 16 x 8, 11.6 with 32 of 8 x 8, 9.2 with 64 of 8 x 4)
+      auto tiles = [&] {
+        long long n = 0;
+        for (const RunHost &h : runs_)
+          n += (long long)((h.d.n1 + tile1_ - 1) / tile1_) * ((h.d.n2 + tile2_ - 1) / tile2_);
+        return n;
+      };
+      while (tiles() < 256 && tile1_ * tile2_ > 32) (tile1_ > tile2_ ? tile1_ : tile2_) /= 2;
     }
     if ((rc = make_tiles(tile1_, tile2_))) return rc;
     if ((rc = upload_items(perrun, &d_perrun_, &n_perrun_))) return rc;
@@ -396,6 +405,24 @@ class Sim : public SimBase {
     if ((rc = upload_items(grps, &d_grps_, &n_grps_))) return rc;
     if ((rc = upload_items(upd, &d_upd_, &n_upd_))) return rc;
     return upload_runs();
+  }
+
+  // Threads of a run's k-space update with strips of that many rows (2D; 3D:
+  // one thread per plane).
+  static int update_threads(const Run<R> &d, int strip) {
+    return d.dim == 3 ? d.rows * d.nk : ((d.n2 + strip - 1) / strip) * d.nk;
+  }
+  // Rows per thread of the 2D update.  A long strip reads each row once (2048 x
+  // 512: 27.6 us with strips of 8, 32.9 with 2), but leaves too few threads on
+  // small grids: 1024 x 300 18.0 -> 12.0 us with strips of 2, four 256 x 256
+  // 13.3 -> 10.7, and 64 x 32 10.3 -> 7.0, 6.5 with single rows.
+  int update_strip() const {
+    long long rows8 = 0, rows2 = 0;
+    for (const RunHost &h : runs_) {
+      rows8 += update_threads(h.d, 8);
+      rows2 += update_threads(h.d, 2);
+    }
+    return rows8 >= 49152 ? 8 : rows2 >= 8192 ? 2 : 1;
   }
 
   int set_stream(hipStream_t s) override {
@@ -698,7 +725,7 @@ class Sim : public SimBase {
     if (dim_ == 3)
       Launch<R>::kupdate3(d_runs_, d_upd_, n_upd_, p, stream_);
     else
-      Launch<R>::kupdate(d_runs_, d_upd_, n_upd_, p, stream_);
+      Launch<R>::kupdate(d_runs_, d_upd_, n_upd_, p, strip_, stream_);
     mark(HP_K_KUPDATE, false);
     mark(HP_K_IFFT_EB, true);
     Launch<R>::ifft_eb(d_runs_, d_grps_, n_grps_, p ^ 1, maxM_, ncomp_, stream_);
@@ -1834,6 +1861,7 @@ class Sim : public SimBase {
   int n_perrun_ = 0;
   int sort_interval_ = DEFAULT_SORT_INTERVAL, since_sort_ = 0;
   unsigned *d_stats_ = nullptr;
+  int strip_ = 8;  // rows per thread of the 2D k-space update
   int tile1_ = TILE1, tile2_ = TILE2, push_lds_ = PUSH_LDS_MIN;
   R *cur_tmp_ = nullptr;  // staging of hp_get_current_device (corrected current)
   size_t cur_tmp_n_ = 0;

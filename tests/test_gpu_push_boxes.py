@@ -2,7 +2,9 @@
 boxes that outgrow them, tiles wider than half the grid (the tile's frame is
 centred on it), and rejected particles.  The FP32 form's integer deposit makes
 every setting bit-identical, so each is compared with single-row tiles sorted
-every step; the FP64 form agrees to the rounding of its atomics."""
+every step; the FP64 form agrees to the rounding of its atomics.  The k-space
+update's strips, whose length the handle's size decides, give the same bits
+too."""
 import numpy as np
 import pytest
 
@@ -74,3 +76,19 @@ def test_a_non_finite_push_is_reported(hpic, precision, big, comp):
     for k in ("x", "u"):
         assert np.array_equal(before[k][:, o], after[k][:, q])
     sim.close()
+
+
+def test_update_strips_give_the_same_bits(hpic):
+    """Strips of 1 and 2 rows (small handles) against 8 (a handle with a large
+    run), at row counts that leave partial strips."""
+    ds = [W.drift2d(n1, n2, 0.2, 0.2, 0.05, sub=(1, 1), gamma=5.0, sigma_u=0.3, jitter=True,
+                    seed=W.SEED0 + 302 + n2, name="strips") for n1, n2 in ((64, 33), (256, 161), (2048, 397))]
+    batch = hpic.from_workloads(ds, "fp32")
+    batch.step(3)
+    for r in (0, 1):
+        one = hpic.from_workload(ds[r], "fp32")
+        one.step(3)
+        for a, b in zip(one.fields(0), batch.fields(r)):
+            assert np.array_equal(a, b)
+        one.close()
+    batch.close()
