@@ -240,11 +240,11 @@ typedef struct hp_tune {
  * are bit-identical for every setting.  HP_EINVAL out of range.
  * Quasi-3D handles: the bins of the periodic particle sort, tile1 z columns x
  * tile2 radial rows (default 4 x 2), and its interval (default 64 steps; a
- * load sorts before the first step); the push works on waves of 64
- * consecutive particles, so the bins set how compact a wave is.  The sort
- * only permutes storage: FP32_FIXED results are bit-identical for every
- * setting (FP64: equal to rounding, the deposit's atomics add in another
- * order).  lds_bytes reads 0 for these handles. */
+ * load sorts before the first step); the push works on tiles of 4 x 2 bins,
+ * at most 16 x 4 cells and smaller for more than three modes, in whose cells
+ * the sort leaves the particles.  The sort only permutes storage: FP32_FIXED
+ * results are bit-identical for every setting (FP64: equal to rounding, the
+ * deposit's atomics add in another order).  lds_bytes reads 0 for these handles. */
 int hp_set_tiling(hp_sim *sim, int32_t tile1, int32_t tile2, int32_t sort_interval);
 int hp_get_tiling(hp_sim *sim, hp_tune *out);
 

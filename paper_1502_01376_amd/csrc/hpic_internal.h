@@ -370,10 +370,44 @@ __device__ __forceinline__ long long rint_i64(double v) {
   return __double_as_longlong(t) - 0x4338000000000000LL;
 }
 
+__device__ __forceinline__ double inv_gamma(double s) {
+  const double g = sqrt(s);
+  return 1.0 / g;
+}
+// 1/g with g = sqrt(s), both correctly rounded, for s >= 1: no scaling against
+// underflow is needed there, which leaves half the instructions of the general
+// square root and division.  g: the hardware root is within one unit, the
+// residuals of its neighbours decide.  1/g: two residual corrections of the
+// hardware reciprocal.  (Equal to the general operations for every float s >=
+// 1, checked exhaustively; infinity gives 0.)
+__device__ __forceinline__ float inv_gamma(float s) {
+#pragma clang fp contract(off)
+  float g = __builtin_amdgcn_sqrtf(s);
+  const float gm = __int_as_float(__float_as_int(g) - 1), gp = __int_as_float(__float_as_int(g) + 1);
+  const float rm = __builtin_fmaf(-gm, g, s), rp = __builtin_fmaf(-gp, g, s);
+  g = rm <= 0.0f ? gm : g;
+  g = rp > 0.0f ? gp : g;
+  float q = __builtin_amdgcn_rcpf(g);
+  q = __builtin_fmaf(__builtin_fmaf(-g, q, 1.0f), q, q);
+  q = __builtin_fmaf(__builtin_fmaf(-g, q, 1.0f), q, q);
+  return s <= 3.402823466e38f ? q : (s > 0.0f ? 0.0f : s);
+}
+
 // Global-memory view of a pointer held in a descriptor: lets the compiler use
 // global (not flat) loads, stores and atomics.
 template <class T> using gptr = T __attribute__((address_space(1))) *;
 template <class T> __device__ __forceinline__ gptr<T> G(T *p) { return (gptr<T>)p; }
+
+// Element p of an array whose base is uniform: a 32-bit byte offset from a
+// scalar base where every offset fits (at most 10^9 particles: 4-byte
+// elements), which saves the 64-bit address of each access.
+template <class T>
+__device__ __forceinline__ gptr<T> elem(T *a, int p) {
+  if constexpr (sizeof(T) == 4)
+    return (gptr<T>)((gptr<char>)G((char *)a) + (unsigned)p * 4u);
+  else
+    return G(a) + p;
+}
 
 __device__ __forceinline__ int wrap_pow2(int i, int n) { return i & (n - 1); }
 __device__ __forceinline__ int wrap_small(int i, int n) {

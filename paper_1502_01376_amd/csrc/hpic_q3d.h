@@ -28,6 +28,28 @@ template <class R> struct AccQ;
 template <> struct AccQ<float> { using T = long long; };
 template <> struct AccQ<double> { using T = double; };
 
+// The cells of a tile (at most 64) that hold more than k particles, and how many
+// particles of the tile have a lower rank than k in their cell.
+struct QLevel {
+  unsigned long long mask;
+  int base, pad;
+};
+constexpr int Q_LEVELS = 64;
+
+// Part of a tile's particles that one workgroup pushes, in storage order, and the
+// box of their cells: z columns relative to the tile, radial nodes.  Segment t is
+// tile t's first; a tile of more than Q_SEG particles goes on in those from
+// nbins + q_seg_more(its first particle), of which it has as many as it can need,
+// so a tile of any density is shared out.  (The spare ones stand last: empty
+// workgroups between the others left compute units idle, 54 us against 46 for the
+// FP64 push on 256 x 61 and 465 against 427 for the FP32 push on 2048 x 256.)
+struct QSeg {
+  int tile, start, end, pad;
+  int zlo, zhi, rlo, rhi;
+};
+constexpr int Q_SEG = 2048;
+__host__ __device__ constexpr int q_seg_more(int start) { return start / Q_SEG; }
+
 template <class R>
 struct RunQ {
   using C = typename Cplx<R>::T;
@@ -43,10 +65,14 @@ struct RunQ {
   // particle side (np = 0: field solve only)
   PartsQ<R> pt;
   PartsQ<R> pt2;     // the other particle buffer: target of the periodic sort
-  int *skey, *srank; // [np]: sort bin of each particle and its rank in the bin
-  int *sbin;         // [nbins + 1]: bin counts, then their exclusive prefix sums
+  int *skey, *srank; // [np]: cell of each particle (tile by tile) and its rank in it
+  int *ccnt;         // [nbins sbz sbr]: particles per cell
+  QLevel *level;     // [nbins][Q_LEVELS]: order of a tile's particles by rank
+  int *sbin;         // [nbins + 1]: particles per tile, then their exclusive prefix
+                     // sums (the first particle of each tile after a sort)
+  QSeg *seg;         // [nbins + np / Q_SEG]: the push's work
   int *ssum;         // [ceil(nbins / 1024) + 1]: per-block sums of the scan
-  int sbz, sbr, nbr, nbins;  // bins of sbz z columns x sbr radial rows, nbr bins along r
+  int sbz, sbr, nbr, nbins;  // tiles of sbz z columns x sbr radial rows, nbr tiles along r
   int np;
   R qmhdt, dtdz, dtdr, rmax;  // q/m dt/2, dt/dz, dt/dr, limit of r/dr
   R wscale;                       // contribution scale: inv_wunit cj (FP32), 1 (FP64)
@@ -58,6 +84,27 @@ struct RunQ {
   const double2 *tw64;  // [n1] FP64 twiddles (diagnostics)
   const double *filt64; // [n1] filter mask (diagnostics)
 };
+// LDS of a push workgroup of 256 threads.  FP32 form: three workgroups per compute
+// unit (3 waves per SIMD, 168 registers); FP64 form: two.  (Workgroups of 384
+// threads with twice the tile ran one per compute unit: six waves do not go
+// twice into four SIMDs that hold three each.)
+template <class R> struct QPush;
+template <> struct QPush<float> {
+  static constexpr int LDS = 53248, WAVES_PER_SIMD = 3;
+};
+template <> struct QPush<double> {
+  static constexpr int LDS = 64512, WAVES_PER_SIMD = 2;
+};
+// Columns of the push's current box for tiles tz wide (literal in the kernels): the
+// tile, the stencils' five and three of drift.
+__host__ __device__ constexpr int q_push_cols(int tz) { return tz > 8 ? 24 : tz > 4 ? 16 : 12; }
+// LDS bytes of its boxes for current boxes of w columns and h rows of M modes:
+// 64-bit accumulators, and in the FP32 form the fields next to them (the real
+// part of mode 0, both parts of the others).
+__host__ __device__ constexpr long long q_push_bytes(int w, int h, int M, size_t real) {
+  return 3ll * (2 * M - 1) * w * h * 8 + (real == 4 ? (12ll * M - 6) * (w - 2) * (h - 1) * 4 : 0);
+}
+
 template <class R>
 struct LaunchQ {
   // forward transform of the real-space fields into the master of a parity
@@ -74,15 +121,14 @@ struct LaunchQ {
   // by its transform along z; NULL for the vacuum law)
   static void gauss(const RunQ<R> *runs, const Item *items, int nitems, int parity,
                     const double2 *rho, double *rows_out, int maxn1, hipStream_t s);
-  // counting sort of a run's particles by (z column, radial row) bin into
-  // pt2, then pt and pt2 swap places (in the device copy of the run; the
-  // caller swaps its host copy)
+  // counting sort of a run's particles by tile into pt2, then pt and pt2 swap
+  // places (in the device copy of the run; the caller swaps its host copy)
   static void sort(RunQ<R> *run_dev, int np, int nbins, hipStream_t s);
-  // gather, Boris, move and per-mode deposit into J[parity]; items (run,
-  // first particle) of 256 particles; modes: the mode count of every run in
-  // the launch, or 0 when they differ
+  // gather, Boris, move and per-mode deposit into J[parity]; items (run, tile);
+  // modes: the mode count of every run in the launch, or 0 when they differ;
+  // tz: the widest tile's z columns
   static void push_deposit(const RunQ<R> *runs, const Item *items, int nitems, int parity,
-                           int modes, unsigned *err, hipStream_t s);
+                           int modes, int tz, unsigned *err, hipStream_t s);
   // per (run, 3 m + c, row): accumulator J[parity] -> complex current, forward
   // transform, correction and filter, background; clears J[parity ^ 1]
   static void fft_j(const RunQ<R> *runs, const Item *items, int nitems, int parity, int maxn1,

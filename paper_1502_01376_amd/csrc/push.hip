@@ -171,29 +171,6 @@ __device__ __forceinline__ void boris(R qmhdt, const R E[3], const R B[3], R u[3
 // out-of-plane velocity enters the fixed-point deposit, which tests reproduce
 // bit for bit on the host): g = sqrt(((1 + u1 u1) + u2 u2) + u3 u3) and
 // v = u * (1/g), square root and reciprocal correctly rounded.
-__device__ __forceinline__ double inv_gamma(double s) {
-  const double g = sqrt(s);
-  return 1.0 / g;
-}
-// 1/g with g = sqrt(s), both correctly rounded, for s >= 1: no scaling against
-// underflow is needed there, which leaves half the instructions of the general
-// square root and division.  g: the hardware root is within one unit, the
-// residuals of its neighbours decide.  1/g: two residual corrections of the
-// hardware reciprocal.  (Equal to the general operations for every float s >=
-// 1, checked exhaustively; infinity gives 0.)
-__device__ __forceinline__ float inv_gamma(float s) {
-#pragma clang fp contract(off)
-  float g = __builtin_amdgcn_sqrtf(s);
-  const float gm = __int_as_float(__float_as_int(g) - 1), gp = __int_as_float(__float_as_int(g) + 1);
-  const float rm = __builtin_fmaf(-gm, g, s), rp = __builtin_fmaf(-gp, g, s);
-  g = rm <= 0.0f ? gm : g;
-  g = rp > 0.0f ? gp : g;
-  float q = __builtin_amdgcn_rcpf(g);
-  q = __builtin_fmaf(__builtin_fmaf(-g, q, 1.0f), q, q);
-  q = __builtin_fmaf(__builtin_fmaf(-g, q, 1.0f), q, q);
-  return s <= 3.402823466e38f ? q : (s > 0.0f ? 0.0f : s);
-}
-
 template <class R>
 __device__ __forceinline__ void velocity(const R u[3], R v[3]) {
 #pragma clang fp contract(off)
@@ -605,17 +582,6 @@ struct PState {
   int cell;
   R f1, f2, u1, u2, u3, qw;
 };
-
-// Element p of an array whose base is uniform: a 32-bit byte offset from a
-// scalar base where every offset fits (at most 10^9 particles: 4-byte
-// elements), which saves the 64-bit address of each access.
-template <class T>
-__device__ __forceinline__ gptr<T> elem(T *a, int p) {
-  if constexpr (sizeof(T) == 4)
-    return (gptr<T>)((gptr<char>)G((char *)a) + (unsigned)p * 4u);
-  else
-    return G(a) + p;
-}
 
 template <class R>
 __device__ __forceinline__ PState<R> load_state(const Parts<R> &P, int p) {

@@ -25,9 +25,12 @@
 // wscale; the row-transform kernel converts them to current densities with
 // the face areas and node volumes.
 //
-// One thread per particle; each wave accumulates into an LDS box (global
-// atomics if its particles spread too far), then adds the box to the global
-// accumulators.  The deposit's arithmetic (shapes, phases and fluxes of the
+// One workgroup per particle tile (particles are counting-sorted by tiles of
+// z columns x radial rows every few steps): the FP32 form stages the fields its
+// particles gather in LDS, and both forms accumulate the current of the tile's
+// box in LDS, which is then added to the global accumulators with one atomic per
+// node (a tile whose particles spread too far gathers and deposits in global
+// memory).  The deposit's arithmetic (shapes, phases and fluxes of the
 // stored positions, their radius and direction in R) is FP64 in both forms;
 // the FP32 form rounds each contribution once to a 64-bit integer on a fine
 // scale (2^40 per unit charge), so the sums do not depend on the order and
@@ -78,20 +81,13 @@ __device__ __forceinline__ void radial(int ix, R fx, int iy, R fy, int &m, R &d,
 // New offset in [0,1) and cell shift in {-1, 0, 1} after a move d (|d| < 1).
 template <class R>
 __device__ __forceinline__ int advq(R f, R d, R &g) {
-  g = f + d;
-  int s = 0;
-  if (g >= R(1)) {
-    g = g - R(1);
-    s = 1;
-  } else if (g < R(0)) {
-    g = g + R(1);
-    s = -1;
-    if (g >= R(1)) {
-      g = R(0);
-      s = 0;
-    }
-  }
-  return s;
+  const R a = f + d;
+  const bool up = a >= R(1), down = a < R(0);
+  const R b = a + (up ? R(-1) : down ? R(1) : R(0));
+  // a negative rest too small to keep its distance to the upper node
+  const bool back = down && b >= R(1);
+  g = back ? R(0) : b;
+  return up ? 1 : (down && !back) ? -1 : 0;
 }
 
 template <class R>
@@ -133,6 +129,20 @@ __device__ __forceinline__ void place4(const R s[3], int off, R out[4]) {
   out[3] = off ? s[2] : R(0);
 }
 
+// The gather's sums with their contractions spelled out: a tile whose box leaves
+// the LDS takes them from global memory, and gives the same bits.
+__device__ __forceinline__ float fmaq(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmaq(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <class R> __device__ __forceinline__ R dot3q(const R w[3], R a, R b, R c) {
+  return fmaq(w[2], c, fmaq(w[1], b, w[0] * a));
+}
+// P_m to P_{m+1} = P_m (c - i s).
+template <class R> __device__ __forceinline__ void next_phase(R c, R s, R &Pr, R &Pi) {
+  const R t = fmaq(Pr, c, Pi * s);
+  Pi = fmaq(Pi, c, -(Pr * s));
+  Pr = t;
+}
+
 // One mode of one staggered component at the particle: the complex
 // interpolated value (vx, vy) from weights wz/wr, node columns oz[3] and rows
 // rr[3] (a ghost row already mirrored; ghost0: row 0 of the stencil is the
@@ -150,33 +160,13 @@ __device__ __forceinline__ void gather_q(PC F, const R wz[3], const int oz[3], c
 #pragma unroll
   for (int b = 0; b < 3; ++b) {
     const PC row = F + rr[b] * rowstride;
-    R sx = 0, sy = 0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const auto v = row[oz[a]];
-      sx += wz[a] * v.x;
-      sy += wz[a] * v.y;
-    }
+    const auto v0 = row[oz[0]], v1 = row[oz[1]], v2 = row[oz[2]];
     R w = wr[b];
     if (b == 0 && ghost0 && odd != vec) w = -w;  // (-1)^m for z components, -(-1)^m for r, th
-    vx += w * sx;
-    vy += w * sy;
+    vx = fmaq(w, dot3q(wz, v0.x, v1.x, v2.x), vx);
+    vy = fmaq(w, dot3q(wz, v0.y, v1.y, v2.y), vy);
   }
 }
-
-// LDS of one push workgroup: a private region per wave of WAVE_CAP 64-bit
-// accumulators (the wave's particles are consecutive, hence close together).
-// FP32 form: three workgroups per compute unit (3 waves per SIMD, the register
-// budget 168); FP64 form: two.
-template <class R> struct QPush;
-template <> struct QPush<float> {
-  static constexpr int LDS = 53248;
-  static constexpr int WAVES_PER_SIMD = 3;
-};
-template <> struct QPush<double> {
-  static constexpr int LDS = 64512;
-  static constexpr int WAVES_PER_SIMD = 2;
-};
 
 __device__ __forceinline__ int wmin(int v) {
   for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
@@ -192,51 +182,48 @@ template <class R> struct LdsC;
 template <> struct LdsC<float> { typedef float T __attribute__((ext_vector_type(2))); };
 template <> struct LdsC<double> { typedef double T __attribute__((ext_vector_type(2))); };
 
-// One FP64 contribution in the accumulator's type: FP32 form the nearest 64-bit
-// integer (|v| < 2^44: charges are scaled to at most 2^40 and every weight
-// factor is at most 4 in magnitude), FP64 form the value.
-template <class A> __device__ __forceinline__ A to_acc(double v);
-template <> __device__ __forceinline__ long long to_acc<long long>(double v) {
-  return rint_i64(v);
+// One contribution x y in the accumulator's type: FP32 form the nearest 64-bit
+// integer (|x y| < 2^44: charges are scaled to at most 2^40 and every weight
+// factor is at most 4 in magnitude), rounded once by the fused multiply-add that
+// brings it next to 1.5 2^52; FP64 form the product.
+template <class A> __device__ __forceinline__ A acc_mul(double x, double y);
+template <> __device__ __forceinline__ long long acc_mul<long long>(double x, double y) {
+  return __double_as_longlong(__builtin_fma(x, y, 6755399441055744.0)) - 0x4338000000000000LL;
 }
-template <> __device__ __forceinline__ double to_acc<double>(double v) { return v; }
+template <> __device__ __forceinline__ double acc_mul<double>(double x, double y) { return x * y; }
 
-// Deposit targets: the wave's LDS box, or the global accumulators.
-template <class A>
+// Deposit targets: the tile's LDS box, or the global accumulators.  A node row is
+// found once per move (row()) and serves every component, mode and part, whose
+// slot() is a distance from it.
+//
+// LDS box: [row][slot][column], CW columns (a literal), slots in the order
+// component, then m = 0, then the real and imaginary parts of m = 1, 2, ..
+template <class A, int MC, int CW>
 struct SinkLdsQ {
-  lptr<A> box;
-  int H, W, rlo, z0, per;  // z0: box column of global column 0 of the window frame
-  int bzrel;               // box column of the window's first column
-  __device__ __forceinline__ void window(int bz) { bzrel = bz + z0; }
-  // the window's first node in row `row` of accumulator (c, m, part); the
-  // nodes of the row are then immediate offsets
+  lptr<A> box;  // the window's first column in row 0 (may lie below the LDS box)
+  int M;
   using Row = lptr<A>;
-  __device__ __forceinline__ Row row(int c, int m, int part, int row) const {
-    const int slot = c * per + (m == 0 ? 0 : 2 * m - 1 + part);
-    return box + (__mul24(__mul24(slot, H) + (row - rlo), W) + bzrel);
-  }
-  __device__ __forceinline__ void put(Row r, int a, double v) const {
-    const A q = to_acc<A>(v);
-    if (q != A(0)) __hip_atomic_fetch_add(r + a, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __device__ __forceinline__ int per() const { return MC > 0 ? 2 * MC - 1 : 2 * M - 1; }
+  __device__ __forceinline__ Row row(int j) const { return box + __mul24(j, 3 * per() * CW); }
+  __device__ __forceinline__ int slot(int c, int m) const { return (c * per() + (m == 0 ? 0 : 2 * m - 1)) * CW; }
+  __device__ __forceinline__ void put(Row r, int slot, int part, int a, double x, double y) const {
+    __hip_atomic_fetch_add(r + slot + part * CW + a, acc_mul<A>(x, y), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 };
 template <class A>
 struct SinkGlobQ {
   A *J;
   long long plane;
-  int n1, col[4];
-  __device__ __forceinline__ void window(int bz) {
-#pragma unroll
-    for (int a = 0; a < 4; ++a) col[a] = wrap_pow2(bz + a, n1);
-  }
-  using Row = gptr<A>;
-  __device__ __forceinline__ Row row(int c, int m, int part, int row) const {
-    return G(J) + ((long long)(m * 3 + c) * plane + (long long)row * n1) * 2 + part;
-  }
-  __device__ __forceinline__ void put(Row r, int a, double v) const {
-    const A q = to_acc<A>(v);
+  int n1, bz;
+  using Row = long long;
+  __device__ __forceinline__ Row row(int j) const { return (long long)j * n1; }
+  __device__ __forceinline__ long long slot(int c, int m) const { return (m * 3 + c) * plane; }
+  __device__ __forceinline__ void put(Row r, long long slot, int part, int a, double x, double y) const {
+    const A q = acc_mul<A>(x, y);
     if (q != A(0))
-      __hip_atomic_fetch_add(r + 2 * col[a], q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_add(G(J) + 2 * (slot + r + wrap_pow2(bz + a, n1)) + part, q,
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 };
 __device__ __forceinline__ void glob_add(gptr<long long> p, long long v) {
@@ -246,146 +233,181 @@ __device__ __forceinline__ void glob_add(gptr<double> p, double v) {
   __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Per-mode deposit of one move (see the file header): window shapes S0/S1
-// along z and r, their running sums C and means T, window row base br, the
-// old and new directions (cta, sta), (ctb, stb) (phases P_m = (c - i s)^m by
-// the same recurrence for both, so the new phase of one step is bit for bit
-// the old phase of the next), scaled charge g and v_th dt.
-template <int MC, class R, class Sink>
-__device__ __forceinline__ void deposit_q(const Sink &put, int M, const R S0z[4], const R S1z[4],
-                                          const R S0r[4], const R S1r[4], const R Cz[4],
-                                          const R Tz[4], const R Cr[4], const R Tr[4], int br,
-                                          R cta, R sta, R ctb, R stb, R g, R vthdt) {
-#pragma clang fp contract(off)
-  R P0r = 1, P0i = 0;  // phase at the old position
-  R P1r = 1, P1i = 0;  // phase at the new position
+// Per-mode deposit of one move (see the file header) through K, whose columns
+// start at the window's: window shapes S0/S1 along z and r (first row br >= -1),
+// the old and new directions (cta, sta), (ctb, stb) (phases P_m = (c - i s)^m by
+// the same recurrence for both, so the new phase of one step is bit for bit the
+// old phase of the next), scaled charge g and v_th dt.
+//
+// A particle that keeps its nearest node along an axis has three-node stencils
+// there: the window's fourth node and the third running sum along the axis are
+// zero (the sum up to the rounding of 1 - 1, which the FP32 form rounds away).
+// The fourth column is left to the lanes that change their node along z (zswitch),
+// the fourth row to the waves with a lane that changes it along r (rswitch, wave-
+// uniform); everything else is added without a test.
+template <int MC, class Sink>
+__device__ __forceinline__ void deposit_q(const Sink &K, int M, const double S0z[4],
+                                          const double S1z[4], const double S0r[4],
+                                          const double S1r[4], int br, bool zswitch, bool rswitch,
+                                          double cta, double sta, double ctb, double stb, double g,
+                                          double vthdt) {
+  using D = double;
+  D Cz[3], Cr[3];
+  {
+    D az = 0, ar = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      az = az + (S1z[k] - S0z[k]);
+      ar = ar + (S1r[k] - S0r[k]);
+      Cz[k] = az;
+      Cr[k] = ar;
+    }
+  }
+  // rows: node rows |br + b|; the face below the axis lands on face 0
+  const bool ghost = br < 0;
+  typename Sink::Row row[4];
+  row[0] = K.row(ghost ? 1 : br);
+#pragma unroll
+  for (int b = 1; b < 4; ++b) row[b] = K.row(br + b);
+  const typename Sink::Row face0 = K.row(ghost ? 0 : br);
+  const bool axis = __ballot(br <= 0) != 0;  // some lane's window holds the axis row
+  D P0r = 1, P0i = 0;  // phase at the old position
+  D P1r = 1, P1i = 0;  // phase at the new position
   if (MC > 0) M = MC;
   for (int m = 0; m < M; ++m) {
     if (m > 0) {
-      const R t0 = P0r * cta + P0i * sta;
+      const D t0 = P0r * cta + P0i * sta;
       P0i = P0i * cta - P0r * sta;
       P0r = t0;
-      const R t = P1r * ctb + P1i * stb;
+      const D t1 = P1r * ctb + P1i * stb;
       P1i = P1i * ctb - P1r * stb;
-      P1r = t;
+      P1r = t1;
     }
-    const R cm = m == 0 ? R(1) : R(2);
-    const bool odd = m & 1;
-    const R Pmr = R(0.5) * (P0r + P1r), Pmi = R(0.5) * (P0i + P1i);
-    const R qr = -cm * g * Pmr, qi = -cm * g * Pmi;
-    // z faces
+    const D cm = m == 0 ? 1.0 : 2.0;
+    const D even = (m & 1) ? -1.0 : 1.0;  // (-1)^m
+    const D Pmr = 0.5 * (P0r + P1r), Pmi = 0.5 * (P0i + P1i);
+    const D qr = -0.5 * cm * g * Pmr, qi = -0.5 * cm * g * Pmi;
+    const D fold = ghost ? even : 1.0;    // of the first row's node fluxes
+    // z faces: running sum along z times the mean radial shape
+    {
+      const auto s = K.slot(0, m);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      int row = br + b;
-      R f = Tr[b];
-      if (row < 0) {
-        row = -row;
-        if (odd) f = -f;
-      }
-      if (f == R(0)) continue;
-      const auto r0 = put.row(0, m, 0, row), r1 = put.row(0, m, 1, row);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const R w = Cz[a] * f;
-        put.put(r0, a, qr * w);
-        if (m > 0) put.put(r1, a, qi * w);
-      }
-    }
-    // r faces (face j at (j + 1/2) dr; face -1 lands on face 0)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      int face = br + b;
-      R f = Cr[b];
-      if (face < 0) {
-        face = 0;
-        if (!odd) f = -f;
-      }
-      if (f == R(0)) continue;
-      const auto r0 = put.row(1, m, 0, face), r1 = put.row(1, m, 1, face);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const R w = Tz[a] * f;
-        if (w == R(0)) continue;
-        put.put(r0, a, qr * w);
-        if (m > 0) put.put(r1, a, qi * w);
+      for (int b = 0; b < 4; ++b) {
+        if (b == 3 && !rswitch) break;
+        const D T = (S0r[b] + S1r[b]) * (b == 0 ? fold : 1.0);
+        const D xr = qr * T, xi = qi * T;
+        K.put(row[b], s, 0, 0, xr, Cz[0]);
+        K.put(row[b], s, 0, 1, xr, Cz[1]);
+        if (m > 0) {
+          K.put(row[b], s, 1, 0, xi, Cz[0]);
+          K.put(row[b], s, 1, 1, xi, Cz[1]);
+        }
+        if (zswitch) {
+          K.put(row[b], s, 0, 2, xr, Cz[2]);
+          if (m > 0) K.put(row[b], s, 1, 2, xi, Cz[2]);
+        }
       }
     }
-    // azimuthal current
-    const R dPr = P1r - P0r, dPi = P1i - P0i;
-    const R inv_m = m > 0 ? R(1) / R(m) : R(0);
+    // r faces (face j at (j + 1/2) dr): running sum along r times the mean z shape
+    {
+      const auto s = K.slot(1, m);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      int row = br + b;
-      const bool ghost = row < 0;
-      if (ghost) row = -row;
-      const bool direct = m == 0 || (m == 1 && row == 0);
-      if (!direct && row == 0) continue;
-      const auto r0 = put.row(2, m, 0, row), r1 = put.row(2, m, 1, row);
+      for (int b = 0; b < 3; ++b) {
+        if (b == 2 && !rswitch) break;
+        const D T = b == 0 ? Cr[0] * (ghost ? -even : 1.0) : Cr[b];
+        const D xr = qr * T, xi = qi * T;
+        const auto f = b == 0 ? face0 : row[b];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        if (direct) {
-          const R W3 = S0z[a] * S0r[b] * R(1.0 / 3.0) + S1z[a] * S0r[b] * R(1.0 / 6.0) +
-                       S0z[a] * S1r[b] * R(1.0 / 6.0) + S1z[a] * S1r[b] * R(1.0 / 3.0);
-          if (W3 == R(0)) continue;
-          R sv = cm * g * W3 * vthdt;
-          if (ghost && !odd) sv = -sv;  // -(-1)^m
-          put.put(r0, a, sv * Pmr);
-          if (m > 0) put.put(r1, a, sv * Pmi);
+        for (int a = 0; a < 3; ++a) {
+          const D t = S0z[a] + S1z[a];
+          K.put(f, s, 0, a, xr, t);
+          if (m > 0) K.put(f, s, 1, a, xi, t);
+        }
+        if (zswitch) {
+          const D t = S0z[3] + S1z[3];
+          K.put(f, s, 0, 3, xr, t);
+          if (m > 0) K.put(f, s, 1, 3, xi, t);
+        }
+      }
+    }
+    // azimuthal current: m = 0 from the azimuthal velocity with the weight W3,
+    // m > 0 the flux i c_m q w Wbar (P1 - P0) / m (none on the axis row)
+    {
+      const auto s = K.slot(2, m);
+      const D h = m == 0 ? g * vthdt * (1.0 / 6.0) : 0.5 * cm * g / (D)m;
+      const D xr = m == 0 ? 1.0 : -(P1i - P0i), xi = P1r - P0r;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        if (b == 3 && !rswitch) break;
+        D k0, k1;
+        if (m == 0) {
+          const D hb = b == 0 && ghost ? -h : h;
+          k0 = hb * (2.0 * S0r[b] + S1r[b]);
+          k1 = hb * (S0r[b] + 2.0 * S1r[b]);
         } else {
-          const R Wb = R(0.5) * (S0z[a] * S0r[b] + S1z[a] * S1r[b]);
-          if (Wb == R(0)) continue;
-          R sv = cm * g * Wb * inv_m;
-          if (ghost && odd) sv = -sv;  // (-1)^m
-          // i sv dP
-          put.put(r0, a, -sv * dPi);
-          put.put(r1, a, sv * dPr);
+          D hb = b == 0 ? h * fold : h;
+          if (b < 2) hb = (b == 0 ? br == 0 : br == -1) ? 0.0 : hb;
+          k0 = hb * S0r[b];
+          k1 = hb * S1r[b];
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const D w = S0z[a] * k0 + S1z[a] * k1;
+          K.put(row[b], s, 0, a, w, xr);
+          if (m > 0) K.put(row[b], s, 1, a, w, xi);
+        }
+        if (zswitch) {
+          const D w = S0z[3] * k0 + S1z[3] * k1;
+          K.put(row[b], s, 0, 3, w, xr);
+          if (m > 0) K.put(row[b], s, 1, 3, w, xi);
+        }
+      }
+      // m = 1 on the axis row: the direct current
+      if (m == 1 && axis) {
+        const D h1 = cm * g * vthdt * (1.0 / 6.0);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          if (b == 0 ? br != 0 : br != -1) continue;
+          const D k0 = h1 * (2.0 * S0r[b] + S1r[b]), k1 = h1 * (S0r[b] + 2.0 * S1r[b]);
+#pragma unroll
+          for (int a = 0; a < 4; ++a) {
+            if (a == 3 && !zswitch) break;
+            const D w = S0z[a] * k0 + S1z[a] * k1;
+            K.put(row[b], s, 0, a, w, Pmr);
+            K.put(row[b], s, 1, a, w, Pmi);
+          }
         }
       }
     }
   }
 }
 
-// Deposit of one move from the particle's old and new positions: cell cz
-// with z offset fz, moved by dz cells to offset gz; radial nodes mri, mrb with
-// offsets dri, drb; old and new directions; scaled charge g; v_th dt.  Builds
-// the 4-node windows along z and r holding both stencils, their running sums
-// and means, and deposits through K (whose column origin follows the window).
-template <int MC, class Sink>
-__device__ __forceinline__ void deposit_move(Sink K, int M, int cz, double fz, int dz, double gz,
-                                             int mri, double dri, int mrb, double drb, double ct,
-                                             double st, double ctb, double stb, double g,
-                                             double vthdt) {
+// One move of a particle: from cell cz with z offset fz, by dz cells to offset
+// gz; radial nodes mri, mrb with offsets dri, drb; old and new directions; scaled
+// charge g; v_th dt.
+struct MoveQ {
+  int cz, dz, mri, mrb;
+  double fz, gz, dri, drb, ct, st, ctb, stb, g, vthdt;
+};
+// Builds the 4-node windows along z and r holding both stencils and deposits
+// through the sink that sink(bz) gives for the window's first column bz.
+template <int MC, class F>
+__device__ __forceinline__ void deposit_move(const MoveQ &v, int M, const F &sink) {
   using D = double;
   D S0z[4], S1z[4], S0r[4], S1r[4];
-  int bz, br;
-  {
-    D sa[3], sb[3];
-    const int na = zshape<D>(cz, fz, sa);
-    const int nb = zshape<D>(cz + dz, gz, sb);
-    bz = min(na, nb) - 1;
-    place4<D>(sa, na - 1 - bz, S0z);
-    place4<D>(sb, nb - 1 - bz, S1z);
-    splineq<D>(dri, sa);
-    splineq<D>(drb, sb);
-    br = min(mri, mrb) - 1;
-    place4<D>(sa, mri - 1 - br, S0r);
-    place4<D>(sb, mrb - 1 - br, S1r);
-  }
-  D Cz[4], Tz[4], Cr[4], Tr[4];
-  {
-    D az = 0, ar = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      az = az + (S1z[k] - S0z[k]);
-      ar = ar + (S1r[k] - S0r[k]);
-      Cz[k] = az;
-      Cr[k] = ar;
-      Tz[k] = 0.5 * (S0z[k] + S1z[k]);
-      Tr[k] = 0.5 * (S0r[k] + S1r[k]);
-    }
-  }
-  K.window(bz);
-  deposit_q<MC, D>(K, M, S0z, S1z, S0r, S1r, Cz, Tz, Cr, Tr, br, ct, st, ctb, stb, g, vthdt);
+  D sa[3], sb[3];
+  const int na = zshape<D>(v.cz, v.fz, sa);
+  const int nb = zshape<D>(v.cz + v.dz, v.gz, sb);
+  const int bz = min(na, nb) - 1;
+  place4<D>(sa, na - 1 - bz, S0z);
+  place4<D>(sb, nb - 1 - bz, S1z);
+  splineq<D>(v.dri, sa);
+  splineq<D>(v.drb, sb);
+  const int br = min(v.mri, v.mrb) - 1;
+  place4<D>(sa, v.mri - 1 - br, S0r);
+  place4<D>(sb, v.mrb - 1 - br, S1r);
+  deposit_q<MC>(sink(bz), M, S0z, S1z, S0r, S1r, br, na != nb, __ballot(v.mri != v.mrb) != 0, v.ct,
+                v.st, v.ctb, v.stb, v.g, v.vthdt);
 }
 
 // The rare global-atomic path out of line, with plain arguments (no array
@@ -396,281 +418,375 @@ __device__ __noinline__ void deposit_move_global(A *J, long long plane, int n1, 
                                                  double fz, int dz, double gz, int mri, double dri,
                                                  int mrb, double drb, double ct, double st,
                                                  double ctb, double stb, double g, double vthdt) {
-  SinkGlobQ<A> K;
-  K.J = J;
-  K.plane = plane;
-  K.n1 = n1;
-  deposit_move<0>(K, M, cz, fz, dz, gz, mri, dri, mrb, drb, ct, st, ctb, stb, g, vthdt);
+  deposit_move<0>(MoveQ{cz, dz, mri, mrb, fz, gz, dri, drb, ct, st, ctb, stb, g, vthdt}, M,
+                  [&](int bz) { return SinkGlobQ<A>{J, plane, n1, bz}; });
+}
+
+// State of one particle as loaded.
+template <class R>
+struct PStateQ {
+  int cell, ix, iy;
+  R fz, fx, fy, u[3], qw;
+};
+template <class R>
+__device__ __forceinline__ PStateQ<R> load_q(const PartsQ<R> &P, int p) {
+  PStateQ<R> s;
+  s.cell = *elem(P.cell, p);
+  s.ix = *elem(P.ix, p);
+  s.iy = *elem(P.iy, p);
+  s.fz = *elem(P.fz, p);
+  s.fx = *elem(P.fx, p);
+  s.fy = *elem(P.fy, p);
+  s.u[0] = *elem(P.uz, p);
+  s.u[1] = *elem(P.ux, p);
+  s.u[2] = *elem(P.uy, p);
+  s.qw = *elem(P.qw, p);
+  return s;
+}
+
+// Twice the quadratic weights (the gather scales its sums by 1/4), or the
+// energy-conserving gather's (unscaled) along a staggered direction.
+template <class R> __device__ __forceinline__ void spline2q(R d, R w[3]) {
+  const R a = R(0.5) - d, b = R(0.5) + d;
+  w[0] = a * a;
+  w[1] = R(1.5) - R(2) * d * d;
+  w[2] = b * b;
+}
+template <class R> __device__ __forceinline__ void half2q(R d, R w[3], bool ec) {
+  if (ec) {
+    line3<R>(d, w);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k] = R(2) * w[k];
+  } else {
+    spline2q<R>(d, w);
+  }
 }
 
 }  // namespace
 
-// One thread per particle (items: run, first particle of 256).  Each wave
-// bounds the deposit footprint of its 64 particles before the push (a move is
-// less than a cell: columns cz-2 .. cz+3, rows m-2 .. m+2 around the nearest
-// integer-r node m, ghost rows folded onto rows 0 and 1).  In the FP32 form
-// its LDS region first holds a copy of the fields its particles gather; then,
-// if the box fits, the region is its current box, added to the global
-// accumulators at the end; otherwise the wave deposits with global atomics.
-// MC: the mode count when every run of the launch has it (the gather's mode
-// loop is then unrolled and the deposit's has a constant trip count), or 0.
-template <class R, int MC>
+// One workgroup per (run, segment of a tile).  A segment's box (from the previous push, or the
+// whole tile right after a sort) bounds the cells of its particles: z columns
+// relative to the tile and nearest integer-r nodes; a move is less than a cell,
+// so the current box is columns lo - 2 .. hi + 3 and rows lo - 2 .. hi + 2 (ghost
+// rows folded onto rows 0 and 1).  In the FP32 form the fields over columns
+// lo - 1 .. hi + 2 and rows lo - 2 .. hi + 1 are staged next to it.  Every row of
+// either box holds all components and modes, with CW columns each (CW - 2 of the
+// fields), so that an address found for one row serves them all.  MC: the mode
+// count when every run of the launch has it (the gather's mode loop is then
+// unrolled and the deposit's has a constant trip count), or 0.
+//
+// What bounds it: the instructions and the LDS atomics of about 145 contributions
+// a particle, with three modes.  On 2048 x 256 cells (8 particles each over 250
+// rows, three modes, FP32) a push takes 424 us, 1098 with a box per wave of 64
+// particles, which carried a halo of 8 x 8 nodes for 8 cells and tested every
+// contribution; FP64 on 256 x 61 with two modes 44 us, 56 before.  Of that:
+// tiles in place of waves (a third of the nodes flushed and staged per particle)
+// and contributions without tests, 744; particles in the order of their cells, so
+// that the lanes of an atomic meet different nodes (LDS cycles 374 to 290 us) and
+// 16 x 4 tiles, 672; workgroups of 256 threads, three per compute unit, 424.
+template <class R, int MC, int CW>
 __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
     k_q_push_deposit(const RunQ<R> *__restrict__ runs, const Item *__restrict__ items, int parity,
                      unsigned *err) {
-  using C = typename Cplx<R>::T;
+  constexpr int NT = 256;
   using A = typename AccQ<R>::T;
+  using V2 = typename LdsC<R>::T;
+  constexpr bool STAGE = sizeof(R) == 4;
+  constexpr int FWD = CW - 2;
   extern __shared__ unsigned char smem_raw[];
-  constexpr int WAVE_CAP = QPush<R>::LDS / 4 / 8;
+  __shared__ int nbox[4];
   const Item it = items[blockIdx.x];
   const RunQ<R> &r = runs[it.run];
-  const int p0 = it.a + threadIdx.x;
-  const bool active = p0 < r.np;
-  // inactive lanes shadow the run's last particle, which lies in their wave's
-  // box whenever the wave has an active lane
-  const int p = active ? p0 : r.np - 1;
+  const gptr<QSeg> seg = G(r.seg) + it.a;
+  const int t = seg->tile, start = seg->start, end = seg->end;
+  if (start >= end) return;
   const PartsQ<R> P = r.pt;
+  PStateQ<R> st{};
+  if (start + (int)threadIdx.x < end) st = load_q(P, start + (int)threadIdx.x);
   const int n1 = r.n1, M = MC > 0 ? MC : r.M;
   const long long plane = r.plane;
-  const int cz = G(P.cell)[p], ix = G(P.ix)[p], iy = G(P.iy)[p];
-  const R fz = G(P.fz)[p], fx = G(P.fx)[p], fy = G(P.fy)[p];
-  R u[3] = {G(P.uz)[p], G(P.ux)[p], G(P.uy)[p]};
-  const R qw = G(P.qw)[p];
-  // nearest integer-r node mri with offset dri, nearest half-r node (j + 1/2)
-  // mrh with offset drh, direction (ct, st)
-  int mri;
-  R dri, ct, st;
-  radial<R>(ix, fx, iy, fy, mri, dri, ct, st);
-  const int mrh = dri >= R(0) ? mri : mri - 1;
-  const R drh = dri >= R(0) ? dri - R(0.5) : dri + R(0.5);
-  // ---- the wave's deposit box (relative z columns, absolute rows)
-  const int NS = 3 * (2 * M - 1);  // accumulator slots per node
-  const int cz0 = __shfl(cz, 0);
-  const int relz = ((cz - cz0 + (n1 >> 1)) & (n1 - 1)) - (n1 >> 1);
-  const int zlo = wmin(active ? relz : (1 << 29)) - 2;
-  const int zhi = wmax(active ? relz : -(1 << 29)) + 3;
-  const int rlo = max(0, wmin(active ? mri : (1 << 29)) - 2);
-  const int rhi = wmax(active ? mri : -(1 << 29)) + 2;
-  const int W = zhi - zlo + 1, H = rhi - rlo + 1;
-  const bool any = zhi >= zlo;
-  const bool use_lds = any && W <= n1 && (long long)W * H * NS <= WAVE_CAP;
-  const lptr<A> box = (lptr<A>)smem_raw + (threadIdx.x >> 6) * WAVE_CAP;
-  const int lane = threadIdx.x & 63;
-  const C *F = r.F;
-  // FP32 form: before the push the wave's LDS region holds a copy of the
-  // fields its particles gather (all modes and components over columns
-  // relz - 1 .. relz + 2 and rows rlo .. rhi - 1), laid out
-  // [mode][component][row][column]
-  constexpr bool STAGE = sizeof(R) == 4;
-  const int fzlo = zlo + 1, Wf = W - 2, Hf = H - 1;
-  const bool use_fl = STAGE && any && Wf <= 64 &&
-                      (long long)6 * M * Wf * Hf * (long long)sizeof(C) <=
-                          (long long)WAVE_CAP * (long long)sizeof(A);
-  using V2 = typename LdsC<R>::T;
-  const lptr<V2> fbox =
-      (lptr<V2>)smem_raw + (threadIdx.x >> 6) * (int)(WAVE_CAP * sizeof(A) / sizeof(V2));
-  if constexpr (STAGE) {
-    if (use_fl) {
-      // lane -> (row in a group of rpi rows, column)
-      const int rpi = 64 / Wf, sub = lane / Wf, cc = lane - sub * Wf;
-      const int col = wrap_pow2(cz0 + fzlo + cc, n1);
-      // a mode's six components per pass, all six loads in flight before
-      // their LDS stores
-      if (sub < rpi)
-        for (int r0 = sub; r0 < Hf; r0 += rpi) {
-          const long long ro = (long long)(rlo + r0) * n1 + col;
-          for (int m = 0; m < M; ++m) {
-            C v[6];
+  const int z0 = (t / r.nbr) * r.sbz;   // first column of the tile
+  const int fo = (n1 - r.sbz) >> 1;     // the tile's frame along z: [-fo, n1 - fo), centred on it
+  const int zlo = seg->zlo - 2, W = seg->zhi - seg->zlo + 6;
+  const int rlo = max(0, seg->rlo - 2), H = min(seg->rhi + 2, r.n2) - rlo + 1;
+  if (threadIdx.x == 0) {
+    nbox[0] = nbox[2] = 1 << 30;
+    nbox[1] = nbox[3] = -(1 << 30);
+  }
+  const int per = 2 * M - 1, NS = 3 * per;
+  const int RS = NS * CW;                       // one row of the current box
+  // one row of the field box: six components of mode 0 (the real part, all that
+  // the gather takes of it), then of each further mode, complex; its used size
+  const int FS = (12 * M - 6) * FWD, Wf = W - 2, Hf = H - 1;
+  const bool local = W <= CW && q_push_bytes(CW, H, M, sizeof(R)) <= (long long)QPush<R>::LDS;
+  const lptr<A> box = (lptr<A>)smem_raw;
+  const lptr<R> fbox = (lptr<R>)(smem_raw + (size_t)RS * H * sizeof(A));
+  const gptr<const V2> F = G((const V2 *)r.F);
+  if (local) {
+    for (int q = threadIdx.x; q < RS * H; q += NT) box[q] = 0;
+    if constexpr (STAGE) {
+      // half a wave per (row, mode): its six components' loads all in flight
+      // before their LDS stores
+      const int cc = threadIdx.x & 31;
+      if (cc < Wf)
+        for (int e = (int)threadIdx.x >> 5; e < Hf * M; e += NT / 32) {
+          const int j = e / M, m = e - j * M;
+          const gptr<const V2> src = F + (long long)(6 * m) * plane + (long long)(rlo + j) * n1 +
+                         wrap_pow2(z0 + zlo + 1 + cc, n1);
+          V2 v[6];
 #pragma unroll
-            for (int c = 0; c < 6; ++c) v[c] = F[(long long)(6 * m + c) * plane + ro];
+          for (int c = 0; c < 6; ++c) v[c] = src[c * plane];
+          const lptr<R> row = fbox + j * FS;
+          if (m == 0) {
 #pragma unroll
-            for (int c = 0; c < 6; ++c) fbox[((6 * m + c) * Hf + r0) * Wf + cc] = V2{v[c].x, v[c].y};
+            for (int c = 0; c < 6; ++c) row[c * FWD + cc] = v[c].x;
+          } else {
+            const lptr<V2> crow = (lptr<V2>)(row + (12 * m - 6) * FWD);
+#pragma unroll
+            for (int c = 0; c < 6; ++c) crow[c * FWD + cc] = v[c];
           }
         }
     }
-  } else {
-    if (use_lds)
-      for (int e = lane; e < W * H * NS; e += 64) box[e] = 0;
   }
   __syncthreads();
-  // ---- gather: integer (i) and half (h) stencils along z and r
-  R wzi[3], wzh[3], wri[3], wrh[3];
-  int ozi[3], ozh[3], rri[3], rrh[3];
-  const int upz = fz >= R(0.5);
-  splineq<R>(fz - R(upz), wzi);
-  half3<R>(fz - R(0.5), wzh, r.interp != 0);
+  int blo = 1 << 30, bhi = -(1 << 30), rlo2 = 1 << 30, rhi2 = -(1 << 30);
+  for (int p = start + (int)threadIdx.x; p < end; p += NT) {
+    if (p != start + (int)threadIdx.x) st = load_q(P, p);
+    const int cz = st.cell, ix = st.ix, iy = st.iy;
+    const R fz = st.fz, fx = st.fx, fy = st.fy;
+    R u[3] = {st.u[0], st.u[1], st.u[2]};
+    const int relz = ((cz - z0 + fo) & (n1 - 1)) - fo;
+    // nearest integer-r node mri with offset dri, nearest half-r node (j + 1/2)
+    // mrh with offset drh, direction (ct, sn)
+    int mri;
+    R dri, ct, sn;
+    radial<R>(ix, fx, iy, fy, mri, dri, ct, sn);
+    const int mrh = dri >= R(0) ? mri : mri - 1;
+    const R drh = dri >= R(0) ? dri - R(0.5) : dri + R(0.5);
+    // ---- gather: integer (i) and half (h) stencils along z and r, weights
+    // doubled along both
+    R wzi[3], wzh[3], wri[3], wrh[3];
+    const int upz = fz >= R(0.5);
+    spline2q<R>(fz - R(upz), wzi);
+    half2q<R>(fz - R(0.5), wzh, r.interp != 0);
+    spline2q<R>(dri, wri);
+    half2q<R>(drh, wrh, r.interp != 0);
+    const bool gi = mri == 0, gh = mrh == 0;  // ghost row in the stencil
+    // sum over the modes of Re(F_m e^{i m th}), with P_m = (ct - i sn)^m by
+    // recurrence (m = 0: the real part alone)
+    R Ec[3] = {0, 0, 0}, Bc[3] = {0, 0, 0};
+    R Pr = 1, Pi = 0;
+    constexpr int MU = MC > 0 ? MC : 1;
+    int rri[3], rrh[3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    ozi[a] = wrap_pow2(cz + upz - 1 + a, n1);
-    ozh[a] = wrap_pow2(cz - 1 + a, n1);
-  }
-  splineq<R>(dri, wri);
-  half3<R>(drh, wrh, r.interp != 0);
-#pragma unroll
-  for (int b = 0; b < 3; ++b) {
-    const int ji = mri - 1 + b, jh = mrh - 1 + b;
-    rri[b] = ji < 0 ? -ji : ji;
-    rrh[b] = jh < 0 ? -jh - 1 : jh;
-  }
-  const bool gi = mri == 0, gh = mrh == 0;  // ghost row in the stencil
-  // sum over the modes of Re(F_m e^{i m th}), with P_m = (ct - i st)^m by
-  // recurrence
-  R Ec[3] = {0, 0, 0}, Bc[3] = {0, 0, 0};
-  R Pr = 1, Pi = 0;
-  constexpr int MU = MC > 0 ? MC : 1;
-#pragma unroll MU
-  for (int m = 0; m < M; ++m) {
-    if (m > 0) {
-      const R t = Pr * ct + Pi * st;
-      Pi = Pi * ct - Pr * st;
-      Pr = t;
+    for (int b = 0; b < 3; ++b) {
+      const int ji = mri - 1 + b, jh = mrh - 1 + b;
+      rri[b] = ji < 0 ? -ji : ji;
+      rrh[b] = jh < 0 ? -jh - 1 : jh;
     }
-    const bool odd = m & 1;
-    R vx[6], vy[6];
-    if (use_fl) {
-      // the same stencils in box coordinates
-      int lzi[3], lzh[3], lri[3], lrh[3];
+    if (STAGE && local) {
+      // first node of each stencil row, integer (i) or half (h) along z and r
+      int oi[3], oh[3];
+      const int c0 = relz - zlo - 2;
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        oi[b] = __mul24(rri[b] - rlo, FS);
+        oh[b] = __mul24(rrh[b] - rlo, FS);
+      }
+      {
+        auto sum = [&](int z, const int o[3], int c, const R wz[3], const R wr[3], R sign) {
+          R v = 0;
+#pragma unroll
+          for (int b = 0; b < 3; ++b) {
+            const lptr<const R> row = fbox + (o[b] + z) + c * FWD;
+            v = fmaq(b == 0 ? wr[0] * sign : wr[b], dot3q(wz, row[0], row[1], row[2]), v);
+          }
+          return v;
+        };
+        // ghost rows of mode 0: as they are for z components, negative for r, th
+        const R si = gi ? R(-1) : R(1), sh = gh ? R(-1) : R(1);
+        const int zi = c0 + upz, zh = c0;
+        Ec[0] = sum(zh, oi, 0, wzh, wri, R(1));
+        Ec[1] = sum(zi, oh, 1, wzi, wrh, sh);
+        Ec[2] = sum(zi, oi, 2, wzi, wri, si);
+        Bc[0] = sum(zi, oh, 3, wzi, wrh, R(1));
+        Bc[1] = sum(zh, oi, 4, wzh, wri, si);
+        Bc[2] = sum(zh, oh, 5, wzh, wrh, sh);
+      }
+#pragma unroll MU
+      for (int m = 1; m < M; ++m) {
+        next_phase(ct, sn, Pr, Pi);
+        // ghost rows: (-1)^m for z components, -(-1)^m for r, th
+        const R odd = (m & 1) ? R(-1) : R(1);
+        const R szi = gi ? odd : R(1), svi = gi ? -odd : R(1);
+        const R szh = gh ? odd : R(1), svh = gh ? -odd : R(1);
+        const int zi = 2 * (c0 + upz), zh = 2 * c0;
+        // Re(v e^{i m th}) with P = e^{-i m th}
+        auto sum = [&](int z, const int o[3], int c, const R wz[3], const R wr[3], R sign) {
+          R vx = 0, vy = 0;
+#pragma unroll
+          for (int b = 0; b < 3; ++b) {
+            const lptr<const V2> row =
+                (lptr<const V2>)(fbox + (o[b] + z)) + ((6 * m - 3) + c) * FWD;
+            const V2 f0 = row[0], f1 = row[1], f2 = row[2];
+            const R w = b == 0 ? wr[0] * sign : wr[b];
+            vx = fmaq(w, dot3q<R>(wz, f0.x, f1.x, f2.x), vx);
+            vy = fmaq(w, dot3q<R>(wz, f0.y, f1.y, f2.y), vy);
+          }
+          return fmaq(vx, Pr, vy * Pi);
+        };
+        Ec[0] += sum(zh, oi, 0, wzh, wri, szi);
+        Ec[1] += sum(zi, oh, 1, wzi, wrh, svh);
+        Ec[2] += sum(zi, oi, 2, wzi, wri, svi);
+        Bc[0] += sum(zi, oh, 3, wzi, wrh, szh);
+        Bc[1] += sum(zh, oi, 4, wzh, wri, svi);
+        Bc[2] += sum(zh, oh, 5, wzh, wrh, svh);
+      }
+    } else {
+      int ozi[3], ozh[3];
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        lzi[a] = relz - fzlo + upz - 1 + a;
-        lzh[a] = relz - fzlo - 1 + a;
-        lri[a] = rri[a] - rlo;
-        lrh[a] = rrh[a] - rlo;
+        ozi[a] = wrap_pow2(cz + upz - 1 + a, n1);
+        ozh[a] = wrap_pow2(cz - 1 + a, n1);
       }
-      const int fp = Wf * Hf;
-      const lptr<V2> fb = fbox + 6 * m * fp;
-      gather_q<R>(fb, wzh, lzh, wri, lri, gi, odd, false, Wf, vx[0], vy[0]);
-      gather_q<R>(fb + fp, wzi, lzi, wrh, lrh, gh, odd, true, Wf, vx[1], vy[1]);
-      gather_q<R>(fb + 2 * fp, wzi, lzi, wri, lri, gi, odd, true, Wf, vx[2], vy[2]);
-      gather_q<R>(fb + 3 * fp, wzi, lzi, wrh, lrh, gh, odd, false, Wf, vx[3], vy[3]);
-      gather_q<R>(fb + 4 * fp, wzh, lzh, wri, lri, gi, odd, true, Wf, vx[4], vy[4]);
-      gather_q<R>(fb + 5 * fp, wzh, lzh, wrh, lrh, gh, odd, true, Wf, vx[5], vy[5]);
-    } else {
-      const long long rs = n1;
-      const C *Fm = F + 6 * m * plane;
-      gather_q<R>(Fm, wzh, ozh, wri, rri, gi, odd, false, rs, vx[0], vy[0]);
-      gather_q<R>(Fm + plane, wzi, ozi, wrh, rrh, gh, odd, true, rs, vx[1], vy[1]);
-      gather_q<R>(Fm + 2 * plane, wzi, ozi, wri, rri, gi, odd, true, rs, vx[2], vy[2]);
-      gather_q<R>(Fm + 3 * plane, wzi, ozi, wrh, rrh, gh, odd, false, rs, vx[3], vy[3]);
-      gather_q<R>(Fm + 4 * plane, wzh, ozh, wri, rri, gi, odd, true, rs, vx[4], vy[4]);
-      gather_q<R>(Fm + 5 * plane, wzh, ozh, wrh, rrh, gh, odd, true, rs, vx[5], vy[5]);
-    }
+#pragma unroll MU
+      for (int m = 0; m < M; ++m) {
+        if (m > 0) next_phase(ct, sn, Pr, Pi);
+        const bool odd = m & 1;
+        R vx[6], vy[6];
+        const long long rs = n1;
+        const gptr<const V2> Fm = F + 6 * m * plane;
+        gather_q<R>(Fm, wzh, ozh, wri, rri, gi, odd, false, rs, vx[0], vy[0]);
+        gather_q<R>(Fm + plane, wzi, ozi, wrh, rrh, gh, odd, true, rs, vx[1], vy[1]);
+        gather_q<R>(Fm + 2 * plane, wzi, ozi, wri, rri, gi, odd, true, rs, vx[2], vy[2]);
+        gather_q<R>(Fm + 3 * plane, wzi, ozi, wrh, rrh, gh, odd, false, rs, vx[3], vy[3]);
+        gather_q<R>(Fm + 4 * plane, wzh, ozh, wri, rri, gi, odd, true, rs, vx[4], vy[4]);
+        gather_q<R>(Fm + 5 * plane, wzh, ozh, wrh, rrh, gh, odd, true, rs, vx[5], vy[5]);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      Ec[c] += vx[c] * Pr + vy[c] * Pi;  // Re(v e^{i m th}) with P = e^{-i m th}
-      Bc[c] += vx[c + 3] * Pr + vy[c + 3] * Pi;
-    }
-  }
-  if constexpr (STAGE) {
-    // the region becomes the wave's current box
-    __syncthreads();
-    if (use_lds)
-      for (int e = lane; e < W * H * NS; e += 64) box[e] = 0;
-    __syncthreads();
-  }
-  const R E[3] = {Ec[0], Ec[1] * ct - Ec[2] * st, Ec[1] * st + Ec[2] * ct};
-  const R B[3] = {Bc[0], Bc[1] * ct - Bc[2] * st, Bc[1] * st + Bc[2] * ct};
-  borisq<R>(r.qmhdt, E, B, u);
-  R v[3];
-  {
-#pragma clang fp contract(off)
-    R s = R(1) + u[0] * u[0];
-    s = s + u[1] * u[1];
-    s = s + u[2] * u[2];
-    const R ig = R(1) / sqrt(s);
-    v[0] = u[0] * ig;
-    v[1] = u[1] * ig;
-    v[2] = u[2] * ig;
-  }
-  // moves in cells
-  const R mz = r.dtdz * v[0], mx = r.dtdr * v[1], my = r.dtdr * v[2];
-  bool ok = active;
-  if (ok && !(isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]) && isfinite(mz) && isfinite(mx) &&
-              isfinite(my))) {
-    atomicOr(err, ERR_NUMERIC);
-    ok = false;
-  }
-  R gz = fz, gx = fx, gy = fy;
-  int dz = 0, dx = 0, dy = 0, mrb = mri;
-  R drb = dri, ctb = ct, stb = st;
-  if (ok) {
-    if (!(fabs(mz) < R(1)) || !(fabs(mx) < R(1)) || !(fabs(my) < R(1))) {
-      atomicOr(err, ERR_RANGE);
-      ok = false;
-    } else {
-      dz = advq<R>(fz, mz, gz);
-      dx = advq<R>(fx, mx, gx);
-      dy = advq<R>(fy, my, gy);
-      radial<R>(ix + dx, gx, iy + dy, gy, mrb, drb, ctb, stb);
-      // within the wall margin, and less than a cell in r (the deposit window
-      // and the wave's box assume it)
-      const R dmove = R(mrb - mri) + (drb - dri);
-      if (!(R(mrb) + drb < r.rmax) || !(fabs(dmove) < R(1)) || abs(mrb - mri) > 1) {
-        atomicOr(err, ERR_RANGE);
-        ok = false;
-      }
-    }
-  }
-  if (ok) {
-    // the new state first (fewer values live across the deposit)
-    G(P.cell)[p] = wrap_pow2(cz + dz, n1);
-    G(P.fz)[p] = gz;
-    G(P.ix)[p] = ix + dx;
-    G(P.fx)[p] = gx;
-    G(P.iy)[p] = iy + dy;
-    G(P.fy)[p] = gy;
-    G(P.uz)[p] = u[0];
-    G(P.ux)[p] = u[1];
-    G(P.uy)[p] = u[2];
-    // ---- deposit (FP64)
-    using D = double;
-    // azimuthal velocity at the mid point times dt: the move (mx, my) dr
-    // projected on the azimuthal direction of the mid point
-    const D xmid = D(ix) + (D)fx + 0.5 * (D)mx, ymid = D(iy) + (D)fy + 0.5 * (D)my;
-    const D rmid = sqrt(xmid * xmid + ymid * ymid);
-    const D vthdt = rmid > 0.0 ? (xmid * (D)my - ymid * (D)mx) / rmid * (D)r.dr : 0.0;
-    const D g = (D)qw * (D)r.wscale;
-    if (use_lds) {
-      SinkLdsQ<A> K{box, H, W, rlo, relz - cz - zlo, 2 * M - 1, 0};
-      deposit_move<MC>(K, M, cz, (D)fz, dz, (D)gz, mri, (D)dri, mrb, (D)drb, (D)ct, (D)st, (D)ctb,
-                   (D)stb, g, vthdt);
-    } else {
-      deposit_move_global<A>(r.J[parity], plane, n1, M, cz, (D)fz, dz, (D)gz, mri, (D)dri, mrb,
-                             (D)drb, (D)ct, (D)st, (D)ctb, (D)stb, g, vthdt);
-    }
-  }
-  __syncthreads();
-  if (use_lds) {
-    A *J = r.J[parity];
-    const int per = 2 * M - 1;
-    if (W <= 64) {
-      // each lane keeps one column of the box and walks its rows, slot by
-      // slot (box layout [slot][row][column])
-      const int rpi = 64 / W, sub = lane / W, cc = lane - sub * W;
-      if (sub < rpi) {
-        const int col = wrap_pow2(cz0 + zlo + cc, n1);
-        for (int slot = 0; slot < NS; ++slot) {
-          const int c = slot / per, s2 = slot - c * per;
-          const int m = (s2 + 1) >> 1, part = s2 == 0 ? 0 : (s2 - 1) & 1;
-          const auto Jb = G(J) + (long long)(m * 3 + c) * plane * 2 + part;
-          for (int r0 = sub; r0 < H; r0 += rpi) {
-            const A v = box[(slot * H + r0) * W + cc];
-            if (v != A(0)) glob_add(Jb + ((long long)(rlo + r0) * n1 + col) * 2, v);
-          }
+        for (int c = 0; c < 3; ++c) {
+          Ec[c] += m > 0 ? fmaq(vx[c], Pr, vy[c] * Pi) : vx[c];
+          Bc[c] += m > 0 ? fmaq(vx[c + 3], Pr, vy[c + 3] * Pi) : vx[c + 3];
         }
       }
-    } else {
-      for (int e = lane; e < W * H * NS; e += 64) {
-        const A v = box[e];
-        if (v == A(0)) continue;
-        const int cc = e % W, rest = e / W;
-        const int row = rlo + rest % H, slot = rest / H;
-        const int c = slot / per, s2 = slot - c * per;
-        const int m = (s2 + 1) >> 1, part = s2 == 0 ? 0 : (s2 - 1) & 1;
-        const int col = wrap_pow2(cz0 + zlo + cc, n1);
-        glob_add(G(J) + ((long long)(m * 3 + c) * plane + (long long)row * n1 + col) * 2 + part, v);
+    }
+    const R E[3] = {Ec[0], Ec[1] * ct - Ec[2] * sn, Ec[1] * sn + Ec[2] * ct};
+    const R B[3] = {Bc[0], Bc[1] * ct - Bc[2] * sn, Bc[1] * sn + Bc[2] * ct};
+    borisq<R>(R(0.25) * r.qmhdt, E, B, u);
+    R v[3];
+    {
+#pragma clang fp contract(off)
+      R s = R(1) + u[0] * u[0];
+      s = s + u[1] * u[1];
+      s = s + u[2] * u[2];
+      const R ig = inv_gamma(s);
+      v[0] = u[0] * ig;
+      v[1] = u[1] * ig;
+      v[2] = u[2] * ig;
+    }
+    // moves in cells
+    const R mz = r.dtdz * v[0], mx = r.dtdr * v[1], my = r.dtdr * v[2];
+    bool ok = true;
+    if (!(isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]) && isfinite(mz) && isfinite(mx) &&
+          isfinite(my))) {
+      atomicOr(err, ERR_NUMERIC);
+      ok = false;
+    }
+    R gz = fz, gx = fx, gy = fy;
+    int dz = 0, dx = 0, dy = 0, mrb = mri;
+    R drb = dri, ctb = ct, stb = sn;
+    if (ok) {
+      if (!(fabs(mz) < R(1)) || !(fabs(mx) < R(1)) || !(fabs(my) < R(1))) {
+        atomicOr(err, ERR_RANGE);
+        ok = false;
+      } else {
+        dz = advq<R>(fz, mz, gz);
+        dx = advq<R>(fx, mx, gx);
+        dy = advq<R>(fy, my, gy);
+        radial<R>(ix + dx, gx, iy + dy, gy, mrb, drb, ctb, stb);
+        // within the wall margin, and less than a cell in r (the deposit window
+        // and the tile's box assume it)
+        const R dmove = R(mrb - mri) + (drb - dri);
+        if (!(R(mrb) + drb < r.rmax) || !(fabs(dmove) < R(1)) || abs(mrb - mri) > 1) {
+          atomicOr(err, ERR_RANGE);
+          ok = false;
+        }
       }
     }
+    const int nz = ok ? relz + dz : relz, nm = ok ? mrb : mri;
+    blo = min(blo, nz);
+    bhi = max(bhi, nz);
+    rlo2 = min(rlo2, nm);
+    rhi2 = max(rhi2, nm);
+    if (ok) {
+      // the new state first (fewer values live across the deposit)
+      *elem(P.cell, p) = wrap_pow2(cz + dz, n1);
+      *elem(P.fz, p) = gz;
+      *elem(P.ix, p) = ix + dx;
+      *elem(P.fx, p) = gx;
+      *elem(P.iy, p) = iy + dy;
+      *elem(P.fy, p) = gy;
+      *elem(P.uz, p) = u[0];
+      *elem(P.ux, p) = u[1];
+      *elem(P.uy, p) = u[2];
+      // ---- deposit (FP64)
+      using D = double;
+      // azimuthal velocity at the mid point times dt: the move (mx, my) dr
+      // projected on the azimuthal direction of the mid point
+      const D xmid = D(ix) + (D)fx + 0.5 * (D)mx, ymid = D(iy) + (D)fy + 0.5 * (D)my;
+      const D rmid = sqrt(xmid * xmid + ymid * ymid);
+      const D vthdt = rmid > 0.0 ? (xmid * (D)my - ymid * (D)mx) / rmid * (D)r.dr : 0.0;
+      const D g = (D)st.qw * (D)r.wscale;
+      if (local) {
+        deposit_move<MC>(MoveQ{cz, dz, mri, mrb, (D)fz, (D)gz, (D)dri, (D)drb, (D)ct, (D)sn, (D)ctb,
+                               (D)stb, g, vthdt},
+                         M, [&](int bz) {
+                           return SinkLdsQ<A, MC, CW>{box + ((bz - cz + relz - zlo) - rlo * RS), M};
+                         });
+      } else {
+        deposit_move_global<A>(r.J[parity], plane, n1, M, cz, (D)fz, dz, (D)gz, mri, (D)dri, mrb,
+                               (D)drb, (D)ct, (D)sn, (D)ctb, (D)stb, g, vthdt);
+      }
+    }
+  }
+  blo = wmin(blo);
+  bhi = wmax(bhi);
+  rlo2 = wmin(rlo2);
+  rhi2 = wmax(rhi2);
+  if ((threadIdx.x & 63) == 0) {
+    atomicMin(&nbox[0], blo);
+    atomicMax(&nbox[1], bhi);
+    atomicMin(&nbox[2], rlo2);
+    atomicMax(&nbox[3], rhi2);
+  }
+  __syncthreads();
+  if (local) {
+    // add the box to the global accumulators: half a wave per (row, slot)
+    A *J = r.J[parity];
+    const int cc = threadIdx.x & 31;
+    if (cc < W) {
+      const int col = wrap_pow2(z0 + zlo + cc, n1);
+      for (int e = (int)threadIdx.x >> 5; e < H * NS; e += NT / 32) {
+        const A v = box[e * CW + cc];
+        if (v == A(0)) continue;
+        const int j = e / NS, slot = e - j * NS;
+        const int c = slot / per, s2 = slot - c * per;
+        const int m = (s2 + 1) >> 1, part = s2 == 0 ? 0 : (s2 - 1) & 1;
+        glob_add(G(J) + ((long long)(m * 3 + c) * plane + (long long)(rlo + j) * n1 + col) * 2 + part, v);
+      }
+    }
+  }
+  // the box of the pushed particles; one that reaches past the frame's edge
+  // wraps, so it becomes the whole frame
+  if (threadIdx.x == 0) {
+    int lo = nbox[0], hi = nbox[1];
+    if (lo < -fo || hi >= n1 - fo) {
+      lo = -fo;
+      hi = n1 - fo - 1;
+    }
+    seg->zlo = lo;
+    seg->zhi = hi;
+    seg->rlo = nbox[2];
+    seg->rhi = nbox[3];
   }
 }
 
@@ -745,37 +861,76 @@ __global__ void __launch_bounds__(256) k_q_jbg(const RunQ<R> *__restrict__ run, 
 }
 
 // ---------------------------------------------------------------- sort
-// The particles of a wave come from consecutive storage slots; the loader
-// stores them by (z column, radial row), and a periodic counting sort by bins
-// of sbz columns x sbr rows keeps a wave's particles, and so its field copy
-// and its current box, compact as they move.  Order within a bin is the
-// order of the atomics: the FP32 form's integer deposit does not depend on it.
+// A periodic counting sort by the push's tiles, of sbz z columns x sbr radial
+// rows, that also orders the particles within a tile: by their rank among the
+// particles of their cell, then by cell in q_place_of's order.  Consecutive
+// particles, which the lanes of a wave take, then lie in cells two apart along z
+// or r, so that they neither queue on the same LDS accumulators nor, where their
+// stencils start half a cell apart, on their neighbours'.
+__device__ __forceinline__ int half_up(int n) { return (n + 1) >> 1; }
+// Place of the tile's cell (column z, row j): even rows before odd, then even
+// columns before odd, then by row and column.
+__device__ __forceinline__ int q_place_of(int z, int j, int tz, int tr) {
+  const int ez = half_up(tz), er = half_up(tr);
+  const int pr = j & 1, pz = z & 1, nr = pr ? tr - er : er;
+  return (pr ? er * tz : 0) + (pz ? nr * ez : 0) + (j >> 1) * (pz ? tz - ez : ez) + (z >> 1);
+}
+// Tile and place of a particle's cell.
 template <class R>
-__device__ __forceinline__ int q_sort_bin(const RunQ<R> &r, const PartsQ<R> &P, int p) {
-  const float x = (float)G(P.ix)[p] + (float)G(P.fx)[p];
-  const float y = (float)G(P.iy)[p] + (float)G(P.fy)[p];
-  const int j = min(max((int)sqrtf(x * x + y * y), 0), r.n2 - 1);
-  return (G(P.cell)[p] / r.sbz) * r.nbr + j / r.sbr;
+__device__ __forceinline__ int q_sort_cell(const RunQ<R> &r, const PartsQ<R> &P, int p) {
+  const float x = (float)*elem(P.ix, p) + (float)*elem(P.fx, p);
+  const float y = (float)*elem(P.iy, p) + (float)*elem(P.fy, p);
+  const int j = min(max((int)sqrtf(x * x + y * y), 0), r.n2 - 1), z = *elem(P.cell, p);
+  const int tz = z / r.sbz, tr = j / r.sbr;
+  return (tz * r.nbr + tr) * (r.sbz * r.sbr) + q_place_of(z - tz * r.sbz, j - tr * r.sbr, r.sbz, r.sbr);
 }
 
 template <class R>
 __global__ void k_q_sort_clear(const RunQ<R> *__restrict__ run) {
   const RunQ<R> &r = *run;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i <= r.nbins; i += gridDim.x * blockDim.x)
-    r.sbin[i] = 0;
+  const int n = r.nbins * r.sbz * r.sbr;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) r.ccnt[i] = 0;
 }
 
 template <class R>
 __global__ void __launch_bounds__(256) k_q_sort_count(const RunQ<R> *__restrict__ run) {
   const RunQ<R> &r = *run;
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  const bool active = p < r.np;
-  // neighbours in storage share bins: one atomic per distinct bin of a wave
-  const int b = active ? q_sort_bin<R>(r, r.pt, p) : 0;
-  const int rank = wave_atomic_inc(r.sbin, b, active);
-  if (!active) return;
-  r.skey[p] = b;
-  r.srank[p] = rank;
+  if (p >= r.np) return;
+  const int c = q_sort_cell<R>(r, r.pt, p);
+  r.skey[p] = c;
+  // a wave within one cell (a dense beam) adds once
+  const int c0 = __builtin_amdgcn_readfirstlane(c);
+  const unsigned long long act = __ballot(1);
+  int k;
+  if (__ballot(c == c0) == act) {
+    const int lane = threadIdx.x & 63, head = __builtin_ctzll(act);
+    k = lane == head ? atomicAdd(r.ccnt + c, __popcll(act)) : 0;
+    k = __builtin_amdgcn_readfirstlane(k) + __popcll(act & ((1ull << lane) - 1));
+  } else {
+    k = atomicAdd(r.ccnt + c, 1);
+  }
+  r.srank[p] = k;
+}
+
+// Particles per tile and the tile's levels, one wave a tile, a lane a cell.
+template <class R>
+__global__ void __launch_bounds__(256) k_q_sort_tiles(const RunQ<R> *__restrict__ run) {
+  const RunQ<R> &r = *run;
+  const int t = blockIdx.x * 4 + ((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (t >= r.nbins) return;
+  const int area = r.sbz * r.sbr;
+  const int cnt = lane < area ? G(r.ccnt)[t * area + lane] : 0;
+  int base = 0;
+  for (int k = 0; k < Q_LEVELS; ++k) {
+    const unsigned long long mask = __ballot(cnt > k);
+    if (!mask) break;
+    if (lane == 0) r.level[(long long)t * Q_LEVELS + k] = QLevel{mask, base, 0};
+    base += __popcll(mask);
+  }
+  int n = cnt;
+  for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+  if (lane == 0) r.sbin[t] = n;
 }
 
 // Exclusive prefix sum of the bin counts in three launches: each block of
@@ -827,15 +982,50 @@ template <class R>
 __global__ void __launch_bounds__(1024) k_q_scan_add(const RunQ<R> *__restrict__ run) {
   const RunQ<R> &r = *run;
   const int i = blockIdx.x * 1024 + threadIdx.x;
-  if (i < r.nbins) r.sbin[i] += r.ssum[blockIdx.x];
+  if (i >= r.nbins) return;
+  r.sbin[i] += r.ssum[blockIdx.x];
 }
 
+// The push's segments, one thread a tile; right after the sort a tile's particles
+// lie in it.
+template <class R>
+__global__ void __launch_bounds__(256) k_q_sort_segments(const RunQ<R> *__restrict__ run) {
+  const RunQ<R> &r = *run;
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= r.nbins) return;
+  const int s0 = r.sbin[t], s1 = r.sbin[t + 1];
+  const int tz = t / r.nbr, r0 = (t - tz * r.nbr) * r.sbr;
+  QSeg g;
+  g.tile = t;
+  g.pad = 0;
+  g.zlo = 0;
+  g.zhi = min(r.sbz, r.n1 - tz * r.sbz) - 1;
+  g.rlo = r0;
+  g.rhi = max(r0, min(r0 + r.sbr, r.n2 - 3));  // no particle reaches r = n2 - 3
+  const int parts = max(1, (s1 - s0 + Q_SEG - 1) / Q_SEG), len = (s1 - s0 + parts - 1) / parts;
+  const int m0 = q_seg_more(s0), m1 = q_seg_more(s1);
+  for (int k = 0; k <= m1 - m0; ++k) {
+    g.start = min(s0 + k * len, s1);
+    g.end = min(g.start + len, s1);
+    r.seg[k == 0 ? t : r.nbins + m0 + k - 1] = g;
+  }
+}
+
+// Scatter.  A particle of rank k in its cell comes after those of lower rank in
+// any of the tile's cells and those of rank k in the cells before its own.
 template <class R>
 __global__ void __launch_bounds__(256) k_q_sort_scatter(const RunQ<R> *__restrict__ run) {
   const RunQ<R> &r = *run;
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= r.np) return;
-  const int d = r.sbin[r.skey[p]] + r.srank[p];
+  const int area = r.sbz * r.sbr, c = r.skey[p], t = c / area, place = c - t * area, k = r.srank[p];
+  int d = r.sbin[t];
+  if (k < Q_LEVELS) {
+    const QLevel l = r.level[(long long)t * Q_LEVELS + k];
+    d += l.base + __popcll(l.mask & ((1ull << place) - 1));
+  } else {
+    for (int i = 0; i < area; ++i) d += min(r.ccnt[t * area + i], i < place ? k + 1 : k);
+  }
   const PartsQ<R> &A = r.pt, &B = r.pt2;
   G(B.cell)[d] = G(A.cell)[p];
   G(B.ix)[d] = G(A.ix)[p];
@@ -861,24 +1051,36 @@ template <class R>
 void LaunchQ<R>::sort(RunQ<R> *run_dev, int np, int nbins, hipStream_t s) {
   if (np <= 0 || nbins <= 0) return;
   const int pb = (np + 255) / 256;
-  hipLaunchKernelGGL(k_q_sort_clear<R>, dim3(std::min((nbins + 256) / 256, 1024)), dim3(256), 0, s,
-                     run_dev);
+  hipLaunchKernelGGL(k_q_sort_clear<R>, dim3(std::min(nbins, 1024)), dim3(256), 0, s, run_dev);
   hipLaunchKernelGGL(k_q_sort_count<R>, dim3(pb), dim3(256), 0, s, run_dev);
+  hipLaunchKernelGGL(k_q_sort_tiles<R>, dim3((nbins + 3) / 4), dim3(256), 0, s, run_dev);
   const int sb = (nbins + 1023) / 1024;
   hipLaunchKernelGGL(k_q_scan_local<R>, dim3(sb), dim3(1024), 0, s, run_dev);
   hipLaunchKernelGGL(k_q_scan_sums<R>, dim3(1), dim3(1024), 0, s, run_dev);
   hipLaunchKernelGGL(k_q_scan_add<R>, dim3(sb), dim3(1024), 0, s, run_dev);
+  hipLaunchKernelGGL(k_q_sort_segments<R>, dim3((nbins + 255) / 256), dim3(256), 0, s, run_dev);
   hipLaunchKernelGGL(k_q_sort_scatter<R>, dim3(pb), dim3(256), 0, s, run_dev);
   hipLaunchKernelGGL(k_q_sort_swap<R>, dim3(1), dim3(1), 0, s, run_dev);
 }
 
 template <class R>
 void LaunchQ<R>::push_deposit(const RunQ<R> *runs, const Item *items, int nitems, int parity,
-                              int modes, unsigned *err, hipStream_t s) {
+                              int modes, int tz, unsigned *err, hipStream_t s) {
   if (nitems <= 0) return;
-  // kernels with the mode loops unrolled for the common mode counts
-  auto k = modes == 2 ? k_q_push_deposit<R, 2> : modes == 3 ? k_q_push_deposit<R, 3>
-                                                            : k_q_push_deposit<R, 0>;
+  // kernels with the mode loops unrolled for the common mode counts, and literal
+  // column strides for the tile widths the runtime uses
+  constexpr int C16 = q_push_cols(16), C8 = q_push_cols(8), C4 = q_push_cols(4);
+  auto k = k_q_push_deposit<R, 0, C4>;
+  if (tz > 8)
+    k = modes == 1   ? k_q_push_deposit<R, 1, C16>
+        : modes == 2 ? k_q_push_deposit<R, 2, C16>
+        : modes == 3 ? k_q_push_deposit<R, 3, C16>
+                     : k_q_push_deposit<R, 0, C16>;
+  else if (tz > 4)
+    k = modes == 2   ? k_q_push_deposit<R, 2, C8>
+        : modes == 3 ? k_q_push_deposit<R, 3, C8>
+        : modes == 4 ? k_q_push_deposit<R, 4, C8>
+                     : k_q_push_deposit<R, 0, C8>;
   hipLaunchKernelGGL(k, dim3(nitems), dim3(256), (size_t)QPush<R>::LDS, s, runs, items, parity, err);
 }
 template <class R>
@@ -892,9 +1094,9 @@ void LaunchQ<R>::jbg(const RunQ<R> *run_dev, int np, double *jbg, hipStream_t s)
   hipLaunchKernelGGL(k_q_jbg<R>, dim3((np + 255) / 256), dim3(256), 0, s, run_dev, jbg);
 }
 
-template void LaunchQ<float>::push_deposit(const RunQ<float> *, const Item *, int, int, int,
+template void LaunchQ<float>::push_deposit(const RunQ<float> *, const Item *, int, int, int, int,
                                            unsigned *, hipStream_t);
-template void LaunchQ<double>::push_deposit(const RunQ<double> *, const Item *, int, int, int,
+template void LaunchQ<double>::push_deposit(const RunQ<double> *, const Item *, int, int, int, int,
                                             unsigned *, hipStream_t);
 template void LaunchQ<float>::sort(RunQ<float> *, int, int, hipStream_t);
 template void LaunchQ<double>::sort(RunQ<double> *, int, int, hipStream_t);

@@ -2079,8 +2079,8 @@ class SimQ : public SimBase {
       if (n_push_ > 0) {
         ++since_sort_;
         mark(HP_K_PUSH_DEPOSIT, true);
-        LaunchQ<R>::push_deposit(d_runs_, d_push_, n_push_, parity_, common_modes(), d_err_,
-                                 stream_);
+        LaunchQ<R>::push_deposit(d_runs_, d_push_, n_push_, parity_, common_modes(), push_tz_,
+                                 d_err_, stream_);
         mark(HP_K_PUSH_DEPOSIT, false);
         mark(HP_K_FFT_J, true);
         LaunchQ<R>::fft_j(d_runs_, d_jitems_, n_jitems_, parity_, maxn1_, stream_);
@@ -2617,6 +2617,7 @@ class SimQ : public SimBase {
     int rc;
     if ((rc = sync()) || (rc = set_bins(t1, t2))) return rc;
     sort_interval_ = k;
+    since_sort_ = k;  // the new tiles hold no particles until a sort
     return upload_runs();
   }
   int get_tiling(hp_tune *out) override {
@@ -2669,25 +2670,39 @@ class SimQ : public SimBase {
     since_sort_ = sort_interval_;  // sort before the first step
     return HP_OK;
   }
-  // Sort bins of sbz z columns x sbr radial rows for every run.
+  // Push tiles: 4 x 2 bins of sbz z columns x sbr radial rows, at most 16 x 4
+  // cells, halved until the boxes of every run's modes fit the LDS (three modes:
+  // 16 x 4, four: 8 x 4).  The particles are sorted by tile, so a change needs a
+  // sort before the next push.
   int set_bins(int sbz, int sbr) {
+    int tz = 4 * std::min(sbz, 4), tr = 2 * std::min(sbr, 2), modes = 1;
+    for (const RunHostQ &h : runs_) modes = std::max(modes, h.d.M);
+    // rows: the tile's, its far edge, the stencil's four and one of drift
+    while (tz * tr > 1 && q_push_bytes(q_push_cols(tz), tr + 6, modes, sizeof(R)) > QPush<R>::LDS)
+      (tz > tr ? tz : tr) /= 2;
+    push_tz_ = tz;
     for (RunHostQ &h : runs_) {
       RunQ<R> &d = h.d;
-      d.sbz = std::min(sbz, d.n1);
-      d.sbr = std::min(sbr, d.n2);
+      d.sbz = std::min(tz, d.n1);
+      d.sbr = std::min(tr, d.n2);
       d.nbr = (d.n2 + d.sbr - 1) / d.sbr;
       d.nbins = ((d.n1 + d.sbz - 1) / d.sbz) * d.nbr;
-      if (d.sbin) release(d.sbin);
-      if (d.ssum) release(d.ssum);
-      d.sbin = d.ssum = nullptr;
+      for (int **a : {&d.sbin, &d.ssum, &d.ccnt}) {
+        if (*a) release(*a);
+        *a = nullptr;
+      }
+      if (d.level) release(d.level);
+      d.level = nullptr;
       int rc;
       if ((rc = alloc(&d.sbin, (size_t)d.nbins + 1)) ||
-          (rc = alloc(&d.ssum, (size_t)(d.nbins + 1023) / 1024 + 1)))
+          (rc = alloc(&d.ssum, (size_t)(d.nbins + 1023) / 1024 + 1)) ||
+          (rc = alloc(&d.ccnt, (size_t)d.nbins * d.sbz * d.sbr)) ||
+          (rc = alloc(&d.level, (size_t)d.nbins * Q_LEVELS)))
         return rc;
     }
     sbz_ = sbz;
     sbr_ = sbr;
-    return HP_OK;
+    return rebuild_push_items();
   }
   void release(void *p) {
     for (auto it = allocs_.begin(); it != allocs_.end(); ++it)
@@ -2745,10 +2760,26 @@ class SimQ : public SimBase {
       }
     (void)hipMemcpy((void *)d.jconv, cv.data(), sizeof(double) * cv.size(), hipMemcpyHostToDevice);
   }
+  // One push item per segment of a tile in every run that has particles.
   int rebuild_push_items() {
     std::vector<Item> v;
-    for (int i = 0; i < (int)runs_.size(); ++i)
-      for (int p = 0; p < runs_[i].d.np; p += 256) v.push_back(Item{i, p, 0});
+    for (int i = 0; i < (int)runs_.size(); ++i) {
+      RunQ<R> &d = runs_[i].d;
+      if (d.seg) release(d.seg);
+      d.seg = nullptr;
+      if (d.np <= 0) continue;
+      const int ns = d.nbins + q_seg_more(d.np);
+      if (int rc = alloc(&d.seg, (size_t)ns)) return rc;
+      // Workgroups go to the eight dies in turn: of eight columns of tiles each die
+      // takes one, so that radial neighbours, which share halo nodes, share an L2
+      // (FP64 push on 256 x 61: 43.9 us against 45.9 in storage order; FP32 on
+      // 2048 x 256: 424 against 428).
+      const int nc = d.nbins / d.nbr, full = nc / 8 * 8 * d.nbr;
+      for (int t = 0; t < ns; ++t) {
+        const int g = t / (8 * d.nbr) * 8 * d.nbr, o = t - g;
+        v.push_back(Item{i, t < full ? g + o % 8 * d.nbr + o / 8 : t, 0});
+      }
+    }
     if (d_push_) release(d_push_);
     d_push_ = nullptr;
     n_push_ = 0;
@@ -2772,11 +2803,9 @@ class SimQ : public SimBase {
   std::vector<Event2> events_;
   double kms_[HP_NK] = {0};
   int64_t kn_[HP_NK] = {0};
-  // particle sort: bins of sbz_ z columns x sbr_ radial rows, every
-  // sort_interval_ steps, and before the first step after a load (4 x 2
-  // cells: a wave's 64 particles of an 8-per-cell column then span few rows;
-  // on the 4096 x 256 drift 1.27 ms per push against 1.47 ms for 2 x 4 and
-  // 1.93 ms unsorted)
+  // particle sort: push tiles of 4 x 2 bins of sbz_ z columns x sbr_ radial rows,
+  // every sort_interval_ steps, and before the first step after a load
+  int push_tz_ = 1;  // z columns of the tiles
   int sbz_ = 4, sbr_ = 2, sort_interval_ = 64, since_sort_ = 0;
 };
 
