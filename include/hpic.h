@@ -235,7 +235,8 @@ typedef struct hp_tune {
 } hp_tune;
 
 /* Sets the tile shape (1..4096 cells per direction; 3D tiles are
- * tile1 x tile2 x tile2) and sort interval
+ * tile1 x tile2 x tile2, of which the push takes neighbours together where
+ * many are left) and sort interval
  * (1..1024 steps) and re-sorts the particles.  Results of the FP32_FIXED form
  * are bit-identical for every setting.  HP_EINVAL out of range.
  * Quasi-3D handles: the bins of the periodic particle sort, tile1 z columns x

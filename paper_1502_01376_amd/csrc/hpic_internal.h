@@ -313,6 +313,43 @@ template <class R> __device__ __forceinline__ void half3(R d, R w[3], bool ec) {
     spline3<R>(d, w);
 }
 
+// Twice the quadratic weights (the gather scales its sums by 1/2 per
+// axis), or twice the energy-conserving gather's along a staggered direction.
+template <class R> __device__ __forceinline__ void spline3x2(R d, R w[3]) {
+  const R a = R(0.5) - d, b = R(0.5) + d;
+  w[0] = a * a;
+  w[1] = R(1.5) - R(2) * d * d;
+  w[2] = b * b;
+}
+template <class R> __device__ __forceinline__ void half3x2(R d, R w[3], bool ec) {
+  if (ec) {
+    line3<R>(d, w);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k] = R(2) * w[k];
+  } else {
+    spline3x2<R>(d, w);
+  }
+}
+
+// A gather's sums with their contractions spelled out: a tile whose box leaves the
+// LDS takes them from global memory, and gives the same bits.
+__device__ __forceinline__ float fmaq(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmaq(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <class R> __device__ __forceinline__ R dot3q(const R w[3], R a, R b, R c) {
+  return fmaq(w[2], c, fmaq(w[1], b, w[0] * a));
+}
+// New offset in [0,1) and cell shift in {-1, 0, 1} after a move d (|d| < 1).
+// The subtraction is exact above 1; below 0 it may round up to 1, and the
+// position is then the next cell edge.
+template <class R>
+__device__ __forceinline__ int advance(R f, R d, R &g) {
+  const R t = f + d, c = floor(t);
+  g = t - c;
+  const bool edge = g >= R(1);
+  g = edge ? R(0) : g;
+  return (int)c + (edge ? 1 : 0);
+}
+
 // Quantised quadratic shape of one coordinate (cell + FP32 offset): integers
 // s[0..2] of the nodes m-1, m, m+1 with exact sum 2^P; returns m.  The same
 // definition as the FP32-precision reference deposit:
@@ -470,13 +507,16 @@ __host__ __device__ constexpr long long push_box_bytes(int w, int h, size_t real
 }
 constexpr int PUSH_LDS_MIN = 16384;
 constexpr int PUSH_LDS_MAX = 64512;  // with the static LDS, under 64 KiB
-// The 3D push of the FP32 form runs 3 waves per SIMD (register budget 168,
-// three workgroups per compute unit), so its LDS budget is a third of the
-// compute unit's 160 KiB less the static LDS; the FP64 form runs 2 (budget
-// 256 registers: left alone the compiler takes 259 and gets 1 wave).
-constexpr int PUSH3_LDS_MAX_FP32 = 53248;
-template <class R> struct Push3Occupancy { static constexpr int WAVES_PER_SIMD = 2; };
-template <> struct Push3Occupancy<float> { static constexpr int WAVES_PER_SIMD = 3; };
+// The 3D push.  FP32 form: 4 waves per SIMD (128 registers), four workgroups of 256
+// threads per compute unit with LDS_256 bytes each, or two of NT_MAX = 512 with
+// LDS_MAX for tiles that need more.  FP64 form: 2 waves per SIMD (256 registers),
+// two workgroups of 256.
+template <class R> struct Push3Occupancy {
+  static constexpr int WAVES_PER_SIMD = 2, NT_MAX = 256, LDS_256 = 80896, LDS_MAX = 80896;
+};
+template <> struct Push3Occupancy<float> {
+  static constexpr int WAVES_PER_SIMD = 4, NT_MAX = 512, LDS_256 = 40448, LDS_MAX = 80896;
+};
 
 // ---------------------------------------------------------------- launches
 // Host-side launch wrappers (kernels.hip), one instantiation per precision.

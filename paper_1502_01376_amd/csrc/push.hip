@@ -66,14 +66,6 @@ struct LdsFields {
   __device__ R b3(int r, int c) const { return B3[r + c]; }
 };
 
-// Twice the quadratic B-spline weights (an exact factor, which saves the two
-// halvings per stencil).
-template <class R> __device__ __forceinline__ void spline3x2(R d, R w[3]) {
-  const R a = R(0.5) - d, b = R(0.5) + d;
-  w[0] = a * a;
-  w[1] = R(1.5) - R(2) * d * d;
-  w[2] = b * b;
-}
 // Factor of gather2's result: weights along both axes are doubled in the
 // momentum-conserving gather.
 template <class R, bool EC> constexpr R GATHER_SCALE = EC ? R(1) : R(0.25);
@@ -181,18 +173,6 @@ __device__ __forceinline__ void velocity(const R u[3], R v[3]) {
   v[0] = u[0] * ig;
   v[1] = u[1] * ig;
   v[2] = u[2] * ig;
-}
-
-// New offset in [0,1) and cell shift in {-1, 0, 1} after a move d (|d| < 1).
-// The subtraction is exact above 1; below 0 it may round up to 1, and the
-// position is then the next cell edge.
-template <class R>
-__device__ __forceinline__ int advance(R f, R d, R &g) {
-  const R t = f + d, c = floor(t);
-  g = t - c;
-  const bool edge = g >= R(1);
-  g = edge ? R(0) : g;
-  return (int)c + (edge ? 1 : 0);
 }
 
 // Place the three stencil values s[] of nearest node m in a 4-node window

@@ -2,13 +2,12 @@
 // field gather + relativistic Boris push + Esirkepov current deposit in 3D,
 // and the 3D charge density of the diagnostics.
 //
-// One workgroup per particle tile (T1 x T2 x T3 cells).  The tile's particles
-// gather the 27-node quadratic stencil of each field component, in the FP32
-// form from a copy of the tile's field box staged in LDS when it fits next to
-// the current box (else, and in the FP64 form, through the cache), and deposit
-// into an LDS copy of the current box that is added to the global accumulators
-// with one atomic per touched node.  Too large a box falls back to depositing
-// with global atomics.
+// One workgroup per particle tile (T1 x T2 x T3 cells), in two passes that share
+// one piece of LDS: the tile's particles gather the 27-node quadratic stencil of
+// each field component from a copy of the tile's field box and get their new
+// momenta; then they move and deposit into an LDS copy of the current box, which
+// is added to the global accumulators with one atomic per touched node.  A tile
+// whose boxes do not fit is pushed in slabs, or through global memory.
 //
 // FP32 form: the Esirkepov weights of the FP32 offsets are computed in FP64
 // and each node's contribution is rounded once to an integer, accumulated in
@@ -49,27 +48,6 @@ __device__ __forceinline__ double rsqrt3(double x) { return 1.0 / sqrt(x); }
 __device__ __forceinline__ float rcp3(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double rcp3(double x) { return 1.0 / x; }
 
-// Momentum-conserving quadratic gather of one staggered component: the
-// weights along each axis are those of the integer (h = 0) or half (h = 1)
-// node stencil; o_d[3] are the node offsets (already wrapped and scaled).
-template <class R, class PT>
-__device__ __forceinline__ R gather_comp(PT F, const R w1[3], const int o1[3], const R w2[3],
-                                         const int o2[3], const R w3[3], const int o3[3]) {
-  R acc = 0;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    R s2 = 0;
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      const PT row = F + o3[c] + o2[b];
-      const R s1 = w1[0] * row[o1[0]] + w1[1] * row[o1[1]] + w1[2] * row[o1[2]];
-      s2 += w2[b] * s1;
-    }
-    acc += w3[c] * s2;
-  }
-  return acc;
-}
-
 template <class R>
 __device__ __forceinline__ void boris3(R qmhdt, const R E[3], const R B[3], R u[3]) {
   const R e0 = qmhdt * E[0], e1 = qmhdt * E[1], e2 = qmhdt * E[2];
@@ -84,38 +62,6 @@ __device__ __forceinline__ void boris3(R qmhdt, const R E[3], const R B[3], R u[
   u[0] = m0 + (p1 * s2 - p2 * s1) + e0;
   u[1] = m1 + (p2 * s0 - p0 * s2) + e1;
   u[2] = m2 + (p0 * s1 - p1 * s0) + e2;
-}
-
-// v = u / sqrt(((1 + u1 u1) + u2 u2) + u3 u3), one correctly rounded square
-// root and reciprocal.
-template <class R>
-__device__ __forceinline__ void velocity3(const R u[3], R v[3]) {
-#pragma clang fp contract(off)
-  R s = R(1) + u[0] * u[0];
-  s = s + u[1] * u[1];
-  s = s + u[2] * u[2];
-  const R ig = R(1) / sqrt(s);
-  v[0] = u[0] * ig;
-  v[1] = u[1] * ig;
-  v[2] = u[2] * ig;
-}
-
-template <class R>
-__device__ __forceinline__ int advance3(R f, R d, R &g) {
-  g = f + d;
-  int s = 0;
-  if (g >= R(1)) {
-    g = g - R(1);
-    s = 1;
-  } else if (g < R(0)) {
-    g = g + R(1);
-    s = -1;
-    if (g >= R(1)) {
-      g = R(0);
-      s = 0;
-    }
-  }
-  return s;
 }
 
 // FP64 shape factors of one coordinate at the nodes m-1, m, m+1 around the
@@ -141,57 +87,84 @@ __device__ __forceinline__ void place4_3(const T s[3], int off, T out[4]) {
   out[3] = off ? s[2] : T(0);
 }
 
-// Current sinks: node offset = o1[a] + o2[b] + o3[c] (from offs()), add().
-// (FP32 form: node offsets in bytes, so that an address is one add; the LDS
-// atomic is issued for zero contributions too: adding an exact zero changes
-// nothing, and it costs less than the test)
-struct Sink3Lds {
-  unsigned char __attribute__((address_space(3))) *J;
-  int W8, WH8, vol8;
-  static __device__ Sink3Lds make(void *lj, int W, int WH, int vol) {
-    return Sink3Lds{(unsigned char __attribute__((address_space(3))) *)lj, 8 * W, 8 * WH, 8 * vol};
+// One node's contribution x y, and sums of two products, in the form's
+// arithmetic.  FP32 form: every operation rounded once as written, the node's
+// value rounded to an integer.
+template <class A> struct Acc3;
+template <> struct Acc3<unsigned long long> {
+  static __device__ __forceinline__ double sum2(double a, double b, double c, double d) {
+#pragma clang fp contract(off)
+    const double x = a * b, y = c * d;
+    return x + y;
   }
-  __device__ int offs(int axis, int i) const { return axis == 0 ? 8 * i : (axis == 1 ? i * W8 : i * WH8); }
-  using Base = unsigned char __attribute__((address_space(3))) *;
-  __device__ Base base(int c, int off) const { return J + c * vol8 + off; }
-  __device__ void put(Base b, int off, long long v) const {
-    __hip_atomic_fetch_add((unsigned long long __attribute__((address_space(3))) *)(b + off),
-                           (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  static __device__ __forceinline__ unsigned long long node(double x, double y) {
+#pragma clang fp contract(off)
+    const double v = x * y;
+    return (unsigned long long)rint_i64(v);
   }
 };
-struct Sink3Global {
-  gptr<unsigned long long> J;
-  int n1, n2, n3, n12, cells;
-  __device__ int offs(int axis, int i) const {
-    return axis == 0 ? wrap_pow2(i, n1) : (axis == 1 ? wrap_small(i, n2) * n1 : wrap_small(i, n3) * n12);
+template <> struct Acc3<double> {
+  static __device__ __forceinline__ double sum2(double a, double b, double c, double d) {
+    return __builtin_fma(a, b, c * d);
   }
-  using Base = gptr<unsigned long long>;
-  __device__ Base base(int c, int off) const { return J + c * cells + off; }
-  __device__ void put(Base b, int off, long long v) const {
-    if (v != 0)
-      __scoped_atomic_fetch_add(b + off, (unsigned long long)v, __ATOMIC_RELAXED,
-                                __MEMORY_SCOPE_DEVICE);
+  static __device__ __forceinline__ double node(double x, double y) { return x * y; }
+};
+template <class R> struct AccOf3;
+template <> struct AccOf3<float> { using T = unsigned long long; };
+template <> struct AccOf3<double> { using T = double; };
+
+template <class T> using lptr3 = T __attribute__((address_space(3))) *;
+typedef int int4v __attribute__((ext_vector_type(4)));
+
+// Current sinks.  window(): the 4 x 4 x 4 nodes from (b1, b2, b3); put(): adds to
+// component comp of the window's node (i, j, k).  The LDS box holds the three
+// components of a row next to each other, [k][j][comp][i], so that a node's
+// address is the window's plus a uniform offset and a literal one.  (Components
+// next to each other at every node would save an addition per row, but put the
+// nodes of a row on every third bank: 1866 against 1644 us, 512 x 128 x 128.)  Its atomic is
+// issued for zero contributions too: adding an exact zero changes nothing, and
+// costs less than the test.
+template <class A>
+struct Lds3 {
+  lptr3<unsigned char> J;
+  int CS, RS, PS;  // bytes from component to component, row to row, plane to plane
+  struct Window {
+    lptr3<unsigned char> w;
+    int CS, RS, PS;
+    __device__ __forceinline__ void put(int comp, int i, int j, int k, A v) const {
+      __hip_atomic_fetch_add((lptr3<A>)(w + (comp * CS + j * RS + k * PS) + 8 * i), v,
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  };
+  __device__ __forceinline__ Window window(int b1, int b2, int b3) const {
+    return Window{J + b1 * 8 + __mul24(b2, RS) + __mul24(b3, PS), CS, RS, PS};
   }
 };
-struct Sink3LdsF64 {
-  double *J;
-  int W, WH, vol;
-  static __device__ Sink3LdsF64 make(void *lj, int W, int WH, int vol) {
-    return Sink3LdsF64{(double *)lj, W, WH, vol};
-  }
-  __device__ int offs(int axis, int i) const { return axis == 0 ? i : (axis == 1 ? i * W : i * WH); }
-  __device__ void add(int c, int off, double v) const {
-    if (v != 0.0) unsafeAtomicAdd(J + c * vol + off, v);
-  }
-};
-struct Sink3GlobalF64 {
-  double *J;
-  int n1, n2, n3, n12, cells;
-  __device__ int offs(int axis, int i) const {
-    return axis == 0 ? wrap_pow2(i, n1) : (axis == 1 ? wrap_small(i, n2) * n1 : wrap_small(i, n3) * n12);
-  }
-  __device__ void add(int c, int off, double v) const {
-    if (v != 0.0) unsafeAtomicAdd(J + c * cells + off, v);
+template <class A>
+struct Global3 {
+  gptr<A> J;
+  int n1, n2, n3;
+  long long cells;
+  struct Window {
+    gptr<A> J;
+    long long cells;
+    int row[4][4], col[4];
+    __device__ __forceinline__ void put(int comp, int i, int j, int k, A v) const {
+      if (v != A(0))
+        __hip_atomic_fetch_add(J + (comp * cells + row[k][j] + col[i]), v, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
+  };
+  __device__ __forceinline__ Window window(int b1, int b2, int b3) const {
+    Window w{J, cells};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      w.col[k] = wrap_pow2(b1 + k, n1);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        w.row[k][j] = (wrap_small(b3 + k, n3) * n2 + wrap_small(b2 + j, n2)) * n1;
+    }
+    return w;
   }
 };
 
@@ -200,7 +173,7 @@ struct Sink3GlobalF64 {
 // offsets.  For component d, with (e, f) the other axes in cyclic order:
 //   T[i][j] = S0e[i] (2 S0f[j] + S1f[j]) + S1e[i] (S0f[j] + 2 S1f[j])
 //           (6 times the Esirkepov bracket), C[k] = running sum of S1d - S0d,
-//   J_d[k][i][j] += C[k] g T[i][j],  k = 0..2.
+//   J_d[k][i][j] += C[k] g[d] T[i][j],  k = 0..2.
 // FP32 form: the weights of the FP32 offsets in FP64, g = (qw inv_wunit) cj
 // with cj = 2^40, every FP64 operation rounded once in the order written, the
 // node value rounded to a 64-bit integer (j_d = -(dx_d/dt) J / (6 inv_wunit
@@ -214,135 +187,62 @@ struct Sink3GlobalF64 {
 // blocks of terms are skipped for the whole wave.  In the FP32 form the skip
 // is exact: the skipped rows add exact zeros, and |C[2]| is a few units of
 // 2^-53, so |C[2] g T| < 2^-53 x 8 x 2^40 x 3.4 stays far below the half
-// unit that would round away from zero.  The FP32 form walks the nodes (i, j)
-// of the two other axes outside the three running sums, so only one bracket
-// T is live at a time (the whole 4 x 4 block of brackets spilled registers).
-template <class Sink>
-__device__ __forceinline__ void deposit3_fixed(const Sink &K, float inv_wunit, float cj,
-                                               const int l[3], const float fa[3], const int dd[3],
-                                               const float fb[3], float qw) {
+// unit that would round away from zero.  The nodes (i, j) of the two other
+// axes are walked outside the three running sums, so only one bracket T is
+// live at a time (the whole 4 x 4 block of brackets spilled registers).
+template <class A, class Sink>
+__device__ __forceinline__ void deposit3(const Sink &K, const double g[3], const int l[3],
+                                         const double fa[3], const int dd[3], const double fb[3]) {
 #pragma clang fp contract(off)
-  double S0[3][4], S1[3][4], C[3][4];
-  int o[3][4];
-  bool w4[3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    double sa[3], sb[3];
-    const int na = dshape3(l[d], (double)fa[d], sa);
-    const int nb = dshape3(l[d] + dd[d], (double)fb[d], sb);
-    const int base = min(na, nb) - 1;
-    w4[d] = __ballot(na != nb) != 0;
-    place4_3(sa, na - 1 - base, S0[d]);
-    place4_3(sb, nb - 1 - base, S1[d]);
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      acc = acc + (S1[d][k] - S0[d][k]);
-      C[d][k] = acc;
-      o[d][k] = K.offs(d, base + k);
-    }
-  }
-  const double gq = ((double)qw * (double)inv_wunit) * (double)cj;
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const int e = (d + 1) % 3, f = (d + 2) % 3;
-    double u0[4], u1[4], cg[3];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      u0[j] = 2.0 * S0[f][j] + S1[f][j];
-      u1[j] = S0[f][j] + 2.0 * S1[f][j];
-    }
-    typename Sink::Base bk[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      cg[k] = C[d][k] * gq;
-      bk[k] = K.base(d, o[d][k]);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (i == 3 && !w4[e]) continue;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (j == 3 && !w4[f]) continue;
-        const double T = S0[e][i] * u0[j] + S1[e][i] * u1[j];
-        const int oij = o[e][i] + o[f][j];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          if (k == 2 && !w4[d]) continue;
-          K.put(bk[k], oij, rint_i64(cg[k] * T));
-        }
-      }
-    }
-  }
-}
-
-template <class Sink>
-__device__ __forceinline__ void deposit3_fp64(const Sink &K, const double jf[3], const int l[3],
-                                              const double fa[3], const int dd[3],
-                                              const double fb[3], double qw) {
-  double S0[3][4], S1[3][4], C[3][4];
-  int o[3][4];
+  using Op = Acc3<A>;
+  double S0[3][4], S1[3][4], C[3][3];
+  int base[3];
   bool w4[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     double sa[3], sb[3];
     const int na = dshape3(l[d], fa[d], sa);
     const int nb = dshape3(l[d] + dd[d], fb[d], sb);
-    const int base = min(na, nb) - 1;
+    base[d] = min(na, nb) - 1;
     w4[d] = __ballot(na != nb) != 0;
-    place4_3(sa, na - 1 - base, S0[d]);
-    place4_3(sb, nb - 1 - base, S1[d]);
+    place4_3(sa, na - 1 - base[d], S0[d]);
+    place4_3(sb, nb - 1 - base[d], S1[d]);
     double acc = 0.0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      acc += S1[d][k] - S0[d][k];
+    for (int k = 0; k < 3; ++k) {
+      acc = acc + (S1[d][k] - S0[d][k]);
       C[d][k] = acc;
-      o[d][k] = K.offs(d, base + k);
     }
   }
+  const auto W = K.window(base[0], base[1], base[2]);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const int e = (d + 1) % 3, f = (d + 2) % 3;
-    const double g = qw * jf[d] * (1.0 / 6.0);
-    double u0[4], u1[4];
+    double u0[4], u1[4], cg[3];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      u0[j] = 2.0 * S0[f][j] + S1[f][j];
-      u1[j] = S0[f][j] + 2.0 * S1[f][j];
+    for (int j = 0; j < 4; ++j) {  // 2 S is exact
+      u0[j] = __builtin_fma(2.0, S0[f][j], S1[f][j]);
+      u1[j] = __builtin_fma(2.0, S1[f][j], S0[f][j]);
     }
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      if (k == 2 && !w4[d]) continue;  // three-node stencil along d
-      const double cg = C[d][k] * g;
+    for (int k = 0; k < 3; ++k) cg[k] = C[d][k] * g[d];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (i == 3 && !w4[e]) continue;
+    for (int i = 0; i < 4; ++i) {
+      if (i == 3 && !w4[e]) continue;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (j == 3 && !w4[f]) continue;
-          K.add(d, o[d][k] + o[e][i] + o[f][j], cg * (S0[e][i] * u0[j] + S1[e][i] * u1[j]));
+      for (int j = 0; j < 4; ++j) {
+        if (j == 3 && !w4[f]) continue;
+        const double T = Op::sum2(S0[e][i], u0[j], S1[e][i], u1[j]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          if (k == 2 && !w4[d]) continue;
+          const int x[3] = {d == 0 ? k : (e == 0 ? i : j), d == 1 ? k : (e == 1 ? i : j),
+                            d == 2 ? k : (e == 2 ? i : j)};
+          W.put(d, x[0], x[1], x[2], Op::node(cg[k], T));
         }
       }
     }
   }
-}
-
-template <class R> struct Sinks3;
-template <> struct Sinks3<float> { using G = Sink3Global; using L = Sink3Lds; using T = unsigned long long; };
-template <> struct Sinks3<double> { using G = Sink3GlobalF64; using L = Sink3LdsF64; using T = double; };
-
-template <class Sink>
-__device__ __forceinline__ void deposit3_one(const Run<float> &r, const Sink &K, const int l[3],
-                                             const float fa[3], const int dd[3], const float fb[3],
-                                             float qw) {
-  deposit3_fixed(K, r.inv_wunit, r.cj, l, fa, dd, fb, qw);
-}
-template <class Sink>
-__device__ __forceinline__ void deposit3_one(const Run<double> &r, const Sink &K, const int l[3],
-                                             const double fa[3], const int dd[3],
-                                             const double fb[3], double qw) {
-  const double jf[3] = {r.jfx1, r.jfx2, r.jfx3};
-  deposit3_fp64(K, jf, l, fa, dd, fb, qw);
 }
 
 __device__ __forceinline__ void unpack3(int cell, int log2n1, int sh3, int n1, int &i1, int &i2,
@@ -352,151 +252,444 @@ __device__ __forceinline__ void unpack3(int cell, int log2n1, int sh3, int n1, i
   i3 = cell >> sh3;
 }
 
-template <class T> using lptr3 = T __attribute__((address_space(3))) *;
-
-// Field sources of the gather: the whole grid in global memory, or the tile's
-// field box in LDS ([6][FD][FH][FW], origin one cell below the tile's particle
-// box, i.e. sink-frame cell - 1 along each axis; FP32 form only).
-template <class R> struct GlobalF3 {
-  static constexpr bool local = false;
-};
-template <class R> struct LdsF3 {
-  static constexpr bool local = true;
-  lptr3<R> F;
-  int FW, FWH, plane;
-};
-
-// State of one particle as loaded: offsets, momenta, charge.
+// State of one particle as loaded: cell, offsets, momenta, charge.
 template <class R> struct PState3 {
+  int cell;
   R f[3], u[3], qw;
 };
 template <class R>
 __device__ __forceinline__ PState3<R> load_state3(const Parts<R> &P, int p) {
   PState3<R> s;
-  s.f[0] = G(P.f1)[p];
-  s.f[1] = G(P.f2)[p];
-  s.f[2] = G(P.f3)[p];
-  s.u[0] = G(P.u1)[p];
-  s.u[1] = G(P.u2)[p];
-  s.u[2] = G(P.u3)[p];
-  s.qw = G(P.qw)[p];
+  s.cell = *elem(P.cell, p);
+  s.f[0] = *elem(P.f1, p);
+  s.f[1] = *elem(P.f2, p);
+  s.f[2] = *elem(P.f3, p);
+  s.u[0] = *elem(P.u1, p);
+  s.u[1] = *elem(P.u2, p);
+  s.u[2] = *elem(P.u3, p);
+  s.qw = *elem(P.qw, p);
   return s;
 }
+// Move of a particle of momentum u over a step, in cells.
+template <class R>
+__device__ __forceinline__ void move3(const Run<R> &r, const R u[3], R m[3]) {
+#pragma clang fp contract(off)
+  R s = R(1) + u[0] * u[0];
+  s = s + u[1] * u[1];
+  s = s + u[2] * u[2];
+  const R ig = inv_gamma(s);
+  m[0] = r.dtdx1 * (u[0] * ig);
+  m[1] = r.dtdx2 * (u[1] * ig);
+  m[2] = r.dtdx3 * (u[2] * ig);
+}
 
-// Push particle p (loaded state st, packed cell `cell`): gather at global
-// cell (g1, g2, g3) (from the field box when S is local), Boris, move, deposit
-// into K in the sink's frame (cell l[]), store.  Returns the new packed cell
-// (the old one if the particle was rejected).
-template <class R, class Src, class Sink>
-__device__ __forceinline__ int push_one3(const Run<R> &r, const Parts<R> &P, int p, int cell,
-                                         const PState3<R> &st, int g1, int g2, int g3,
-                                         const int l[3], const Src &S, const Sink &K,
-                                         unsigned *err) {
-  const R f[3] = {st.f[0], st.f[1], st.f[2]};
-  R u[3] = {st.u[0], st.u[1], st.u[2]};
-  const R qw = st.qw;
-  const int n1 = r.n1, n2 = r.n2, n3 = r.n3, n12 = n1 * n2, cells = r.cells;
-  // stencil weights and offsets, integer (i) and half (h) nodes per axis
+// Sum of one staggered component over its 27 nodes: weights w along the axes,
+// row(b, c) the first of three nodes along x1.
+template <class R, class F>
+__device__ __forceinline__ R gather3(const R w1[3], const R w2[3], const R w3[3], const F &row) {
+  R acc = 0;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    R s2 = 0;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const auto r = row(b, c);
+      s2 = fmaq(w2[b], dot3q(w1, R(r[0]), R(r[1]), R(r[2])), s2);
+    }
+    acc = fmaq(w3[c], s2, acc);
+  }
+  return acc;
+}
+// The same through wrapped node indices.
+template <class R>
+__device__ __forceinline__ R gather3_at(gptr<const R> F, const R w1[3], const int o1[3],
+                                        const R w2[3], const int o2[3], const R w3[3],
+                                        const int o3[3]) {
+  R acc = 0;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    R s2 = 0;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const int r = o3[c] + o2[b];
+      s2 = fmaq(w2[b], dot3q(w1, F[r + o1[0]], F[r + o1[1]], F[r + o1[2]]), s2);
+    }
+    acc = fmaq(w3[c], s2, acc);
+  }
+  return acc;
+}
+
+// a / b for 0 <= a < 1024, 0 < b: the quotient's distance from an integer is at least
+// 1 / 2b before it is cut off, the product's error below 2^-12.
+__device__ __forceinline__ int small_div(int a, int b) {
+  return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
+}
+// Walks the nodes of a box of w x h x d at the grid's (c1, c2, c3) with the workgroup's
+// NT threads.  A thread keeps its column (i, j) and walks the planes, N at a time:
+// get(u, node in the grid) for each of them, then put(u, i, j, k).
+template <int N, int NT, class Get, class Put>
+__device__ __forceinline__ void for_box3(int w, int h, int d, int c1, int c2, int c3, int n1, int n2,
+                                         int n3, Get get, Put put) {
+  const int wh = w * h, step = max(1, NT / wh);  // planes at once
+  const int k0 = step > 1 ? small_div((int)threadIdx.x, wh) : 0;
+  const int n12 = n1 * n2;
+  c2 = wrap_any3(c2, n2);
+  c3 = wrap_any3(c3, n3);
+  for (int q = (int)threadIdx.x - k0 * wh; q < wh && k0 < step; q += NT) {
+    const int j = wh <= 1024 ? small_div(q, w) : q / w, i = q - j * w;
+    const int col = wrap_any3(c2 + j, n2) * n1 + wrap_pow2(c1 + i, n1);
+    int g3 = wrap_any3(c3 + k0, n3);
+    for (int k = k0; k < d; k += N * step) {
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        if (k + u * step < d) get(u, (long long)g3 * n12 + col);
+        g3 += step;
+        while (g3 >= n3) g3 -= n3;
+      }
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        if (k + u * step < d) put(u, i, j, k + u * step);
+    }
+  }
+}
+
+// A tile's place in its run.
+struct Tile3 {
+  int ref[3], fo[3];  // first cell; the frame along each axis is [-fo, n - fo), centred on the tile
+  template <class R>
+  __device__ __forceinline__ Tile3(const Run<R> &r, int t) {
+    const int t3 = t / (r.nt1 * r.nt2), t12 = t - t3 * r.nt1 * r.nt2;
+    const int t2 = t12 / r.nt1, t1 = t12 - t2 * r.nt1;
+    ref[0] = t1 * r.T1;
+    ref[1] = t2 * r.T2;
+    ref[2] = t3 * r.T3;
+    fo[0] = (r.n1 - r.T1) >> 1;
+    fo[1] = (r.n2 - r.T2) >> 1;
+    fo[2] = (r.n3 - r.T3) >> 1;
+  }
+  // cell of a particle in the grid and in the tile's frame
+  template <class R>
+  __device__ __forceinline__ void cell(const Run<R> &r, int cell, int gc[3], int l[3]) const {
+    unpack3(cell, r.log2n1, r.sh3, r.n1, gc[0], gc[1], gc[2]);
+    l[0] = frame_pow2_3(gc[0] - ref[0], fo[0], r.n1);
+    l[1] = frame_any_3(gc[1] - ref[1], fo[1], r.n2);
+    l[2] = frame_any_3(gc[2] - ref[2], fo[2], r.n3);
+  }
+};
+// Stencil weights (doubled) of a particle, integer (i) and half (h) nodes per axis.
+template <class R>
+struct Weights3 {
   R wi[3][3], wh[3][3];
-  int oi[3][3], oh[3][3];
-  const int gc[3] = {g1, g2, g3};
+  int up[3];
+  __device__ __forceinline__ Weights3(const R f[3], bool ec) {
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const int up = f[d] >= R(0.5);
-    spline3<R>(f[d] - R(up), wi[d]);
-    half3<R>(f[d] - R(0.5), wh[d], r.interp != 0);
+    for (int d = 0; d < 3; ++d) {
+      up[d] = f[d] >= R(0.5);
+      spline3x2<R>(f[d] - R(up[d]), wi[d]);
+      half3x2<R>(f[d] - R(0.5), wh[d], ec);
+    }
+  }
+};
+// New momentum, and whether the particle moves: a non-finite or a too long move
+// leaves it as it was.  (A non-finite momentum makes its move NaN, inf x 0, which
+// fails every comparison.)
+template <class R>
+__device__ __forceinline__ bool kick3(const Run<R> &r, const R E[3], const R B[3], R u[3], unsigned *err) {
+  boris3<R>(R(0.125) * r.qmhdt, E, B, u);
+  R m[3];
+  move3<R>(r, u, m);
+  if (fabs(m[0]) < R(1) && fabs(m[1]) < R(1) && fabs(m[2]) < R(1)) return true;
+  const bool fin = isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]) && isfinite(m[0]) &&
+                   isfinite(m[1]) && isfinite(m[2]);
+  atomicOr(err, fin ? ERR_RANGE : ERR_NUMERIC);
+  return false;
+}
+// Scale of the deposit along each axis.
+template <class R>
+__device__ __forceinline__ void scale3(const Run<R> &r, R qw, double g[3]) {
+  if constexpr (sizeof(R) == 4) {
+#pragma clang fp contract(off)
+    g[0] = g[1] = g[2] = ((double)qw * (double)r.inv_wunit) * (double)r.cj;
+  } else {
+    g[0] = qw * r.jfx1 * (1.0 / 6.0);
+    g[1] = qw * r.jfx2 * (1.0 / 6.0);
+    g[2] = qw * r.jfx3 * (1.0 / 6.0);
+  }
+}
+template <class R>
+__device__ __forceinline__ void store_place3(const Run<R> &r, const Parts<R> &P, int p, const int gc[3],
+                                             const int dd[3], const R g[3]) {
+  *elem(P.cell, p) = (wrap_small(gc[2] + dd[2], r.n3) << r.sh3) |
+                     (wrap_small(gc[1] + dd[1], r.n2) << r.log2n1) | wrap_pow2(gc[0] + dd[0], r.n1);
+  *elem(P.f1, p) = g[0];
+  *elem(P.f2, p) = g[1];
+  *elem(P.f3, p) = g[2];
+}
+// Bounding box of the cells a thread's particles move to, then of the
+// workgroup's (nbox, initialised before a barrier).
+struct CellBox3 {
+  int lo[3] = {1 << 30, 1 << 30, 1 << 30}, hi[3] = {-(1 << 30), -(1 << 30), -(1 << 30)};
+  __device__ __forceinline__ void add(const int l[3], const int dd[3]) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      if constexpr (Src::local) {
-        // box-local nodes: sink-frame cell - 1, then the stencil
-        const int ni = l[d] - 1 + up - 1 + a, nh = l[d] - 1 - 1 + a;
-        const int sc = d == 0 ? 1 : (d == 1 ? S.FW : S.FWH);
-        oi[d][a] = ni * sc;
-        oh[d][a] = nh * sc;
-      } else {
-        const int ni = gc[d] + up - 1 + a, nh = gc[d] - 1 + a;
-        if (d == 0) {
-          oi[0][a] = wrap_pow2(ni, n1);
-          oh[0][a] = wrap_pow2(nh, n1);
-        } else if (d == 1) {
-          oi[1][a] = wrap_small(ni, n2) * n1;
-          oh[1][a] = wrap_small(nh, n2) * n1;
-        } else {
-          oi[2][a] = wrap_small(ni, n3) * n12;
-          oh[2][a] = wrap_small(nh, n3) * n12;
-        }
+    for (int d = 0; d < 3; ++d) {
+      lo[d] = min(lo[d], l[d] + dd[d]);
+      hi[d] = max(hi[d], l[d] + dd[d]);
+    }
+  }
+  __device__ __forceinline__ void reduce(lptr3<int> nbox) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      lo[d] = wave_min3(lo[d]);
+      hi[d] = wave_max3(hi[d]);
+      if ((threadIdx.x & 63) == 0) {
+        __hip_atomic_fetch_min(nbox + 2 * d, lo[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_max(nbox + 2 * d + 1, hi[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
   }
-  R E[3], B[3];
-  auto gather6 = [&](auto F, int stride) {
-    E[0] = gather_comp<R>(F, wh[0], oh[0], wi[1], oi[1], wi[2], oi[2]);
-    E[1] = gather_comp<R>(F + stride, wi[0], oi[0], wh[1], oh[1], wi[2], oi[2]);
-    E[2] = gather_comp<R>(F + 2 * stride, wi[0], oi[0], wi[1], oi[1], wh[2], oh[2]);
-    B[0] = gather_comp<R>(F + 3 * stride, wi[0], oi[0], wh[1], oh[1], wh[2], oh[2]);
-    B[1] = gather_comp<R>(F + 4 * stride, wh[0], oh[0], wi[1], oi[1], wh[2], oh[2]);
-    B[2] = gather_comp<R>(F + 5 * stride, wh[0], oh[0], wh[1], oh[1], wi[2], oi[2]);
-  };
-  if constexpr (Src::local)
-    gather6(S.F, S.plane);
-  else
-    gather6((const R *)r.F, cells);
-  boris3<R>(r.qmhdt, E, B, u);
-  R v[3];
-  velocity3<R>(u, v);
-  const R m[3] = {r.dtdx1 * v[0], r.dtdx2 * v[1], r.dtdx3 * v[2]};
-  if (!(isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]) && isfinite(m[0]) && isfinite(m[1]) &&
-        isfinite(m[2]))) {
-    atomicOr(err, ERR_NUMERIC);
-    return cell;
-  }
-  if (!(fabs(m[0]) < R(1)) || !(fabs(m[1]) < R(1)) || !(fabs(m[2]) < R(1))) {
-    atomicOr(err, ERR_RANGE);
-    return cell;
-  }
-  R g[3];
-  int dd[3];
+};
+
+// A tile whose boxes do not fit the LDS: fields through the cache, current to global
+// atomics.  Out of line, so that it takes no registers from the LDS path.
+template <class R, int NT>
+__device__ __noinline__ void push_tile3_global(const Run<R> *run, int t, int parity, int pp,
+                                               lptr3<int> nbox, unsigned *err) {
+  using A = typename AccOf3<R>::T;
+  const Run<R> &r = *run;
+  const Parts<R> P = r.pt[pp];
+  const Tile3 T(r, t);
+  const int n1 = r.n1, n2 = r.n2, n3 = r.n3, end = G(r.tile_start)[t + 1];
+  const long long cells = r.cells;
+  const gptr<const R> F = G((const R *)r.F);
+  CellBox3 box;
+  for (int p = G(r.tile_start)[t] + (int)threadIdx.x; p < end; p += NT) {
+    PState3<R> st = load_state3(P, p);
+    int gc[3], l[3], dd[3] = {0, 0, 0};
+    T.cell(r, st.cell, gc, l);
+    const Weights3<R> w(st.f, r.interp != 0);
+    int oi[3][3], oh[3][3];
 #pragma unroll
-  for (int d = 0; d < 3; ++d) dd[d] = advance3<R>(f[d], m[d], g[d]);
-  deposit3_one(r, K, l, f, dd, g, qw);
-  const int j1 = wrap_pow2(g1 + dd[0], n1), j2 = wrap_small(g2 + dd[1], n2),
-            j3 = wrap_small(g3 + dd[2], n3);
-  const int nc = (j3 << r.sh3) | (j2 << r.log2n1) | j1;
-  G(P.cell)[p] = nc;
-  G(P.f1)[p] = g[0];
-  G(P.f2)[p] = g[1];
-  G(P.f3)[p] = g[2];
-  G(P.u1)[p] = u[0];
-  G(P.u2)[p] = u[1];
-  G(P.u3)[p] = u[2];
-  return nc;
+    for (int a = 0; a < 3; ++a) {
+      oi[0][a] = wrap_pow2(gc[0] + w.up[0] - 1 + a, n1);
+      oh[0][a] = wrap_pow2(gc[0] - 1 + a, n1);
+      oi[1][a] = wrap_small(gc[1] + w.up[1] - 1 + a, n2) * n1;
+      oh[1][a] = wrap_small(gc[1] - 1 + a, n2) * n1;
+      oi[2][a] = wrap_small(gc[2] + w.up[2] - 1 + a, n3) * (n1 * n2);
+      oh[2][a] = wrap_small(gc[2] - 1 + a, n3) * (n1 * n2);
+    }
+    const R E[3] = {gather3_at<R>(F, w.wh[0], oh[0], w.wi[1], oi[1], w.wi[2], oi[2]),
+                    gather3_at<R>(F + cells, w.wi[0], oi[0], w.wh[1], oh[1], w.wi[2], oi[2]),
+                    gather3_at<R>(F + 2 * cells, w.wi[0], oi[0], w.wi[1], oi[1], w.wh[2], oh[2])};
+    const R B[3] = {gather3_at<R>(F + 3 * cells, w.wi[0], oi[0], w.wh[1], oh[1], w.wh[2], oh[2]),
+                    gather3_at<R>(F + 4 * cells, w.wh[0], oh[0], w.wi[1], oi[1], w.wh[2], oh[2]),
+                    gather3_at<R>(F + 5 * cells, w.wh[0], oh[0], w.wh[1], oh[1], w.wi[2], oi[2])};
+    if (kick3<R>(r, E, B, st.u, err)) {
+      *elem(P.u1, p) = st.u[0];
+      *elem(P.u2, p) = st.u[1];
+      *elem(P.u3, p) = st.u[2];
+      R m[3], g[3];
+      move3<R>(r, st.u, m);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) dd[d] = advance<R>(st.f[d], m[d], g[d]);
+      store_place3<R>(r, P, p, gc, dd, g);
+      double gq[3];
+      scale3<R>(r, st.qw, gq);
+      const double fa[3] = {(double)st.f[0], (double)st.f[1], (double)st.f[2]};
+      const double fb[3] = {(double)g[0], (double)g[1], (double)g[2]};
+      deposit3<A>(Global3<A>{G((A *)r.J[parity]), n1, n2, n3, cells}, gq, gc, fa, dd, fb);
+    }
+    box.add(l, dd);
+  }
+  box.reduce(nbox);
 }
 
-template <class R>
-__global__ void __launch_bounds__(256, Push3Occupancy<R>::WAVES_PER_SIMD)
+// The tile's particles from tile_first to tile_end through the LDS boxes; lo, hi the
+// box of their cells, Z the planes of a slab (ONE: all of them, and at most 32
+// particles a thread); st the thread's first particle, loaded.
+//
+// Two passes through one piece of LDS:
+// first it holds the fields around the tile [6][k][j][i] (cells lo - 1 .. hi + 2 per
+// axis, lo .. hi the tile's particles') and every particle gathers and gets its new
+// momentum, then the current box [k][j][3][i] (cells lo - 2 .. hi + 3) and every
+// particle moves and deposits.  Where the particles have spread so far that a box does
+// not fit, the tile is pushed in slabs of planes that do, each particle in the slab of
+// its old cell.
+//
+// What bounds it: the waits between a workgroup's phases, with the instructions
+// (about 1100 a particle) and the LDS (240 accesses) each half busy.  Both boxes
+// at once left the LDS to 12 waves of 168 registers on tiles of 8 x 4 x 4 cells;
+// taking turns they leave it to 16 waves of 128 on tiles of 8 x 8 x 8, which also halves
+// the halo nodes a particle stages and flushes.  512 x 128 x 128 cells, two particles
+// a cell, mean of the first 128 steps: 1530 us before, 1200 now; 128 x 37 x 45, three
+// a cell: 85 and 67, 220 and 155 once it is so hot that the boxes outgrow 53 KB; FP64
+// form, 128 x 64 x 64: 234 us when it gathered through the cache, 159 now.  (The
+// slabs' loops in the same body spilled 26 registers: 1460 us.)
+template <class R, int NT, bool ONE>
+__device__ __forceinline__ void push_tile3(const Run<R> &r, const Tile3 &T, int tile_first, int tile_end,
+                                           int parity, int pp, const int lo[3], const int hi[3], int Z,
+                                           PState3<R> st, lptr3<unsigned char> box, lptr3<int> nbox,
+                                           unsigned *err) {
+  using A = typename AccOf3<R>::T;
+  const Parts<R> P = r.pt[pp];
+  const int W = hi[0] - lo[0] + 6, H = hi[1] - lo[1] + 6, FW = W - 2, FH = H - 2;
+  const int RS = 24 * W, PS = RS * H;
+  const int FRS = (int)sizeof(R) * FW, FPS = FRS * FH, FCS = FPS * (Z + 3);
+  CellBox3 cbox;
+  // up to 32 particles a thread at a time, with a bit each
+  for (int start = tile_first; start < tile_end; start += 32 * NT) {
+    const int end = ONE ? tile_end : min(tile_end, start + 32 * NT);
+    unsigned done = 0;  // pushed, in an earlier slab
+    for (int z0 = lo[2]; z0 <= hi[2]; z0 += Z) {
+      const int zn = ONE ? Z : min(Z, hi[2] + 1 - z0);
+      if (!ONE && (start != tile_first || z0 != lo[2])) __syncthreads();
+      {
+        // four nodes' loads in flight before their LDS stores: most boxes of the
+        // default tiles take one round of memory latency
+        R v[4][6];
+        const gptr<const R> F = G((const R *)r.F);
+        const long long cells = r.cells;
+        for_box3<4, NT>(
+            FW, FH, zn + 3, T.ref[0] + lo[0] - 1, T.ref[1] + lo[1] - 1, T.ref[2] + z0 - 1, r.n1, r.n2,
+            r.n3,
+            [&](int u, long long g) {
+#pragma unroll
+              for (int c = 0; c < 6; ++c) v[u][c] = (F + c * cells)[g];
+            },
+            [&](int u, int i, int j, int k) {
+              const lptr3<unsigned char> node = box + (i * (int)sizeof(R) + j * FRS + k * FPS);
+#pragma unroll
+              for (int c = 0; c < 6; ++c) *(lptr3<R>)(node + c * FCS) = v[u][c];
+            });
+      }
+      __syncthreads();
+      // ---- pass 1: new momenta
+      unsigned here = 0, moves = 0;  // of this slab, and not rejected
+      for (int p = start + (int)threadIdx.x, k = 0; p < end; p += NT, ++k) {
+        if (p != tile_first + (int)threadIdx.x || (!ONE && z0 != lo[2])) st = load_state3(P, p);
+        int gc[3], l[3];
+        T.cell(r, st.cell, gc, l);
+        if (!ONE) {
+          if (done >> k & 1 || l[2] < z0 || l[2] >= z0 + Z) continue;
+          here |= 1u << k;
+        }
+        const Weights3<R> w(st.f, r.interp != 0);
+        const int u1 = w.up[0] ? (int)sizeof(R) : 0, u2 = w.up[1] ? FRS : 0, u3 = w.up[2] ? FPS : 0;
+        const lptr3<unsigned char> hhh = box + (l[0] - lo[0]) * (int)sizeof(R) +
+                                         __mul24(l[1] - lo[1], FRS) + __mul24(l[2] - z0, FPS);
+        auto comp = [&](int c, int off, const R w1[3], const R w2[3], const R w3[3]) {
+          const lptr3<unsigned char> f = hhh + off + c * FCS;
+          return gather3(w1, w2, w3, [&](int b, int q) { return (lptr3<const R>)(f + (b * FRS + q * FPS)); });
+        };
+        R E[3], B[3];
+        E[0] = comp(0, u2 + u3, w.wh[0], w.wi[1], w.wi[2]);
+        E[1] = comp(1, u1 + u3, w.wi[0], w.wh[1], w.wi[2]);
+        E[2] = comp(2, u1 + u2, w.wi[0], w.wi[1], w.wh[2]);
+        B[0] = comp(3, u1, w.wi[0], w.wh[1], w.wh[2]);
+        B[1] = comp(4, u2, w.wh[0], w.wi[1], w.wh[2]);
+        B[2] = comp(5, u3, w.wh[0], w.wh[1], w.wi[2]);
+        if (kick3<R>(r, E, B, st.u, err)) {
+          *elem(P.u1, p) = st.u[0];
+          *elem(P.u2, p) = st.u[1];
+          *elem(P.u3, p) = st.u[2];
+          moves |= 1u << k;
+        }
+      }
+      __syncthreads();
+      for (int q = 16 * (int)threadIdx.x; q < PS * (zn + 5); q += 16 * NT)
+        *(lptr3<int4v>)(box + q) = int4v{0, 0, 0, 0};
+      __syncthreads();
+      // ---- pass 2: move and deposit, last particle first (the thread still holds it)
+      const int last = end - 1 - start - (int)threadIdx.x;
+      for (int k = last < 0 ? -1 : last / NT, held = 1; k >= 0; --k, held = 0) {
+        const int p = start + (int)threadIdx.x + k * NT;
+        if (!held) st = load_state3(P, p);
+        if (!ONE && !(here >> k & 1)) continue;
+        int gc[3], l[3], dd[3] = {0, 0, 0};
+        T.cell(r, st.cell, gc, l);
+        if (moves >> k & 1) {
+          R m[3], g[3];
+          move3<R>(r, st.u, m);
+#pragma unroll
+          for (int d = 0; d < 3; ++d) dd[d] = advance<R>(st.f[d], m[d], g[d]);
+          store_place3<R>(r, P, p, gc, dd, g);
+          double gq[3];
+          scale3<R>(r, st.qw, gq);
+          const int lb[3] = {l[0] - lo[0] + 2, l[1] - lo[1] + 2, l[2] - z0 + 2};
+          const double fa[3] = {(double)st.f[0], (double)st.f[1], (double)st.f[2]};
+          const double fb[3] = {(double)g[0], (double)g[1], (double)g[2]};
+          deposit3<A>(Lds3<A>{box, 8 * W, RS, PS}, gq, lb, fa, dd, fb);
+        }
+        cbox.add(l, dd);
+      }
+      done |= here;
+      __syncthreads();
+      const gptr<A> J = G((A *)r.J[parity]);
+      const long long cells = r.cells;
+      long long g;
+      for_box3<1, NT>(
+          W, H, zn + 5, T.ref[0] + lo[0] - 2, T.ref[1] + lo[1] - 2, T.ref[2] + z0 - 2, r.n1, r.n2, r.n3,
+          [&](int, long long node) { g = node; },
+          [&](int, int i, int j, int k) {
+            const lptr3<A> node = (lptr3<A>)(box + (i * 8 + j * RS + k * PS));
+            const A v[3] = {node[0], node[W], node[2 * W]};
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+              if (v[c] != A(0))
+                __hip_atomic_fetch_add((J + c * cells) + g, v[c], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+          });
+      if (ONE) break;
+    }
+    if (ONE) break;
+  }
+  cbox.reduce(nbox);
+}
+
+// Slabs, or more particles, out of line as well.
+template <class R, int NT>
+__device__ __noinline__ void push_tile3_slabs(const Run<R> *run, int t, int parity, int pp, int Z,
+                                              lptr3<unsigned char> box, lptr3<int> nbox,
+                                              unsigned *err) {
+  const Run<R> &r = *run;
+  const int first = G(r.tile_start)[t], end = G(r.tile_start)[t + 1];
+  const auto b = G(r.tile_box) + 6 * t;
+  const int lo[3] = {b[0], b[2], b[4]}, hi[3] = {b[1], b[3], b[5]};
+  PState3<R> st{};
+  if (first + (int)threadIdx.x < end) st = load_state3(r.pt[pp], first + (int)threadIdx.x);
+  push_tile3<R, NT, false>(r, Tile3(r, t), first, end, parity, pp, lo, hi, Z, st, box, nbox, err);
+}
+
+// One workgroup of NT threads per tile.
+template <class R, int NT>
+__global__ void __launch_bounds__(NT, Push3Occupancy<R>::WAVES_PER_SIMD)
 k_push_deposit3(const Run<R> *__restrict__ runs, const Item *__restrict__ items, int parity, int pp,
                 int lds_bytes, unsigned *err, unsigned *stats) {
-  using SK = Sinks3<R>;
   extern __shared__ unsigned char smem_raw[];
   __shared__ int nbox[6];
   const Item it = items[blockIdx.x];
   const Run<R> &r = runs[it.run];
   const Parts<R> P = r.pt[pp];
   const int t = it.a;
-  const int start = r.tile_start[t], end = r.tile_start[t + 1];
-  if (start >= end) return;
-  const int n1 = r.n1, n2 = r.n2, n3 = r.n3;
-  const int t3 = t / (r.nt1 * r.nt2), t12 = t - t3 * r.nt1 * r.nt2;
-  const int t2 = t12 / r.nt1, t1 = t12 - t2 * r.nt1;
-  const int ref[3] = {t1 * r.T1, t2 * r.T2, t3 * r.T3};
-  const int fo[3] = {(n1 - r.T1) >> 1, (n2 - r.T2) >> 1, (n3 - r.T3) >> 1};
-  const int *box = r.tile_box + 6 * t;
+  const int tile_first = G(r.tile_start)[t], tile_end = G(r.tile_start)[t + 1];
+  if (tile_first >= tile_end) return;
+  // the thread's first particle is loaded before the staging, so that its loads
+  // wait out the memory latency together with the staging's
+  PState3<R> st{};
+  if (tile_first + (int)threadIdx.x < tile_end) st = load_state3(P, tile_first + (int)threadIdx.x);
+  const Tile3 T(r, t);
+  const auto tbox = G(r.tile_box) + 6 * t;
   int lo[3], hi[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    lo[d] = box[2 * d];
-    hi[d] = box[2 * d + 1];
+    lo[d] = tbox[2 * d];
+    hi[d] = tbox[2 * d + 1];
   }
+  const int W = hi[0] - lo[0] + 6, H = hi[1] - lo[1] + 6, FW = W - 2, FH = H - 2;
+  // Slabs of Z planes of cells whose two boxes both fit; none: through global memory.
+  const int all = hi[2] - lo[2] + 1;
+  const int jplane = 24 * (int)min((long long)W * H, 1ll << 20);
+  const int fplane = 6 * (int)sizeof(R) * (int)min((long long)FW * FH, 1ll << 20);
+  const int Z = min(all, min(lds_bytes / jplane - 5, lds_bytes / fplane - 3));
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -504,152 +697,33 @@ k_push_deposit3(const Run<R> *__restrict__ runs, const Item *__restrict__ items,
       nbox[2 * d + 1] = -(1 << 30);
     }
     count_stat(stats, STAT_TILES);
+    if (Z < 1) count_stat(stats, STAT_FALLBACK);
   }
-  // current box: cells lo-2 .. hi+3 per axis
-  const int W = hi[0] - lo[0] + 6, H = hi[1] - lo[1] + 6, D = hi[2] - lo[2] + 6;
-  const long long jn = (long long)W * H * D;
-  const size_t need = (size_t)3 * jn * sizeof(typename SK::T);
-  int bl[3] = {1 << 30, 1 << 30, 1 << 30}, bh[3] = {-(1 << 30), -(1 << 30), -(1 << 30)};
-  auto track = [&](int cell) {
-    int i1, i2, i3;
-    unpack3(cell, r.log2n1, r.sh3, n1, i1, i2, i3);
-    const int dl[3] = {frame_pow2_3(i1 - ref[0], fo[0], n1), frame_any_3(i2 - ref[1], fo[1], n2),
-                       frame_any_3(i3 - ref[2], fo[2], n3)};
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      bl[d] = min(bl[d], dl[d]);
-      bh[d] = max(bh[d], dl[d]);
-    }
-  };
-  if (need > (size_t)lds_bytes) {
-    // the barrier orders the box initialisation above before every wave's
-    // min/max at the end (the LDS branch has its own after the staging)
-    __syncthreads();
-    if (threadIdx.x == 0) count_stat(stats, STAT_FALLBACK);
-    const typename SK::G K{(decltype(SK::G::J))G((typename SK::T *)r.J[parity]), n1, n2, n3,
-                           n1 * n2, r.cells};
-    for (int p = start + threadIdx.x; p < end; p += 256) {
-      const int cell = G(P.cell)[p];
-      int i1, i2, i3;
-      unpack3(cell, r.log2n1, r.sh3, n1, i1, i2, i3);
-      const int l[3] = {i1, i2, i3};
-      track(push_one3<R>(r, P, p, cell, load_state3(P, p), i1, i2, i3, l, GlobalF3<R>{}, K, err));
-    }
+  const lptr3<unsigned char> box = (lptr3<unsigned char>)smem_raw;
+  if (Z == all && tile_end - tile_first <= 32 * NT) {
+    push_tile3<R, NT, true>(r, T, tile_first, tile_end, parity, pp, lo, hi, Z, st, box, (lptr3<int>)nbox,
+                            err);
   } else {
-    typename SK::T *lj = (typename SK::T *)smem_raw;
-    const int vol = (int)jn;
-    // field box: cells lo-1 .. hi+2 per axis, after the current box when both fit
-    const int FW = hi[0] - lo[0] + 4, FH = hi[1] - lo[1] + 4, FD = hi[2] - lo[2] + 4;
-    const int fplane = FW * FH * FD;
-    const size_t jbytes = (need + 15) & ~(size_t)15;
-    const bool use_fl =
-        sizeof(R) == 4 && jbytes + (size_t)6 * fplane * sizeof(R) <= (size_t)lds_bytes;
-    const lptr3<R> fl = (lptr3<R>)(smem_raw + jbytes);
-    // FP32 form: the thread's first particle is loaded before the staging, so
-    // that its loads wait out the memory latency together with the staging's
-    const int p0 = start + (int)threadIdx.x;
-    constexpr bool pre = sizeof(R) == 4;
-    int cell0 = 0;
-    PState3<R> st0{};
-    if (pre && p0 < end) {
-      cell0 = G(P.cell)[p0];
-      st0 = load_state3(P, p0);
-    }
-    for (int q = threadIdx.x; q < 3 * vol; q += 256) lj[q] = 0;
-    if (use_fl) {
-      const gptr<const R> F = G((const R *)r.F);
-      const long long cells = r.cells;
-      const int o1 = ref[0] + lo[0] - 1, o2 = ref[1] + lo[1] - 1, o3 = ref[2] + lo[2] - 1;
-      // one node's six components per pass, all six loads in flight before
-      // their LDS stores (a tile stages about 13 values per thread, which one
-      // at a time would wait out the memory latency in turn)
-      for (int e = threadIdx.x; e < fplane; e += 256) {
-        const int k = e / (FW * FH), rem = e - k * FW * FH;
-        const int b = rem / FW, a = rem - b * FW;
-        const int g3 = wrap_any3(o3 + k, n3), g2 = wrap_any3(o2 + b, n2);
-        const long long g = ((long long)g3 * n2 + g2) * n1 + wrap_pow2(o1 + a, n1);
-        R v[6];
-#pragma unroll
-        for (int c = 0; c < 6; ++c) v[c] = F[c * cells + g];
-#pragma unroll
-        for (int c = 0; c < 6; ++c) fl[c * fplane + e] = v[c];
-      }
-    }
     __syncthreads();
-    const typename SK::L K = SK::L::make(lj, W, W * H, vol);
-    const LdsF3<R> SL{fl, FW, FW * FH, fplane};
-    for (int p = p0; p < end; p += 256) {
-      int cell;
-      PState3<R> st;
-      if (pre && p == p0) {
-        cell = cell0;
-        st = st0;
-      } else {
-        cell = G(P.cell)[p];
-        st = load_state3(P, p);
-      }
-      int i1, i2, i3;
-      unpack3(cell, r.log2n1, r.sh3, n1, i1, i2, i3);
-      const int l[3] = {frame_pow2_3(i1 - ref[0], fo[0], n1) - lo[0] + 2,
-                        frame_any_3(i2 - ref[1], fo[1], n2) - lo[1] + 2,
-                        frame_any_3(i3 - ref[2], fo[2], n3) - lo[2] + 2};
-      if (use_fl)
-        track(push_one3<R>(r, P, p, cell, st, i1, i2, i3, l, SL, K, err));
-      else
-        track(push_one3<R>(r, P, p, cell, st, i1, i2, i3, l, GlobalF3<R>{}, K, err));
-    }
-    __syncthreads();
-    const auto J = G((typename SK::T *)r.J[parity]);
-    const int c1 = ref[0] + lo[0] - 2, c2 = ref[1] + lo[1] - 2, c3 = ref[2] + lo[2] - 2;
-    auto flush = [&](int q, long long g) {
-#pragma unroll
-      for (int comp = 0; comp < 3; ++comp) {
-        const typename SK::T v = lj[comp * vol + q];
-        if (v != 0)
-          __scoped_atomic_fetch_add(J + comp * (long long)r.cells + g, v, __ATOMIC_RELAXED,
-                                    __MEMORY_SCOPE_DEVICE);
-      }
-    };
-    if (W <= 256) {
-      // each thread keeps one column a of the box and walks the rows
-      // (k, b) = rr, rr + rpp, ... with rpp = 256 / W rows per pass
-      const int rpp = 256 / W, rr = (int)threadIdx.x / W, a = (int)threadIdx.x - rr * W;
-      if (rr < rpp) {
-        const int col = wrap_pow2(c1 + a, n1);
-        int k = rr / H, b = rr - k * H;
-        for (int row = rr; row < H * D; row += rpp) {
-          const int g3 = wrap_any3(c3 + k, n3), g2 = wrap_any3(c2 + b, n2);
-          flush(row * W + a, ((long long)g3 * n2 + g2) * n1 + col);
-          b += rpp;
-          while (b >= H) {
-            b -= H;
-            ++k;
-          }
-        }
-      }
-    } else {
-      for (int q = threadIdx.x; q < vol; q += 256) {
-        const int k = q / (W * H), rem = q - k * W * H;
-        const int b = rem / W, a = rem - b * W;
-        const int g3 = wrap_any3(c3 + k, n3), g2 = wrap_any3(c2 + b, n2);
-        flush(q, ((long long)g3 * n2 + g2) * n1 + wrap_pow2(c1 + a, n1));
-      }
-    }
-  }
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    bl[d] = wave_min3(bl[d]);
-    bh[d] = wave_max3(bh[d]);
-  }
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      atomicMin(&nbox[2 * d], bl[d]);
-      atomicMax(&nbox[2 * d + 1], bh[d]);
-    }
+    if (Z < 1)
+      push_tile3_global<R, NT>(&r, t, parity, pp, (lptr3<int>)nbox, err);
+    else
+      push_tile3_slabs<R, NT>(&r, t, parity, pp, Z, box, (lptr3<int>)nbox, err);
   }
   __syncthreads();
-  if (threadIdx.x < 6) r.tile_box[6 * t + threadIdx.x] = nbox[threadIdx.x];
+  // the box of the pushed particles; one that reaches past the frame's edge
+  // wraps, so it becomes the whole frame
+  if (threadIdx.x < 3) {
+    const int d = threadIdx.x, o = d == 0 ? T.fo[0] : d == 1 ? T.fo[1] : T.fo[2];
+    const int n = d == 0 ? r.n1 : d == 1 ? r.n2 : r.n3;
+    int a = nbox[2 * d], b = nbox[2 * d + 1];
+    if (a < -o || b >= n - o) {
+      a = -o;
+      b = n - o - 1;
+    }
+    tbox[2 * d] = a;
+    tbox[2 * d + 1] = b;
+  }
 }
 
 template <class R>
@@ -657,8 +731,11 @@ void Launch<R>::push_deposit3(const Run<R> *runs, const Item *items, int nitems,
                               int pp, int lds_bytes, unsigned *err, unsigned *stats,
                               hipStream_t s) {
   if (nitems <= 0) return;
-  hipLaunchKernelGGL(k_push_deposit3<R>, dim3(nitems), dim3(256), lds_bytes, s, runs, items,
-                     parity, pp, lds_bytes, err, stats);
+  const bool wide = lds_bytes > Push3Occupancy<R>::LDS_256;
+  constexpr int NT = Push3Occupancy<R>::NT_MAX;
+  hipLaunchKernelGGL((wide ? k_push_deposit3<R, NT> : k_push_deposit3<R, 256>), dim3(nitems),
+                     dim3(wide ? NT : 256), lds_bytes, s, runs, items, parity, pp, lds_bytes, err,
+                     stats);
 }
 template void Launch<float>::push_deposit3(const Run<float> *, const Item *, int, int, int, int,
                                            unsigned *, unsigned *, hipStream_t);

@@ -78,18 +78,6 @@ __device__ __forceinline__ void radial(int ix, R fx, int iy, R fy, int &m, R &d,
   s = rho > R(0) ? Y / rho : R(0);
 }
 
-// New offset in [0,1) and cell shift in {-1, 0, 1} after a move d (|d| < 1).
-template <class R>
-__device__ __forceinline__ int advq(R f, R d, R &g) {
-  const R a = f + d;
-  const bool up = a >= R(1), down = a < R(0);
-  const R b = a + (up ? R(-1) : down ? R(1) : R(0));
-  // a negative rest too small to keep its distance to the upper node
-  const bool back = down && b >= R(1);
-  g = back ? R(0) : b;
-  return up ? 1 : (down && !back) ? -1 : 0;
-}
-
 template <class R>
 __device__ __forceinline__ void borisq(R qmhdt, const R E[3], const R B[3], R u[3]) {
   const R e0 = qmhdt * E[0], e1 = qmhdt * E[1], e2 = qmhdt * E[2];
@@ -129,13 +117,6 @@ __device__ __forceinline__ void place4(const R s[3], int off, R out[4]) {
   out[3] = off ? s[2] : R(0);
 }
 
-// The gather's sums with their contractions spelled out: a tile whose box leaves
-// the LDS takes them from global memory, and gives the same bits.
-__device__ __forceinline__ float fmaq(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fmaq(double a, double b, double c) { return __builtin_fma(a, b, c); }
-template <class R> __device__ __forceinline__ R dot3q(const R w[3], R a, R b, R c) {
-  return fmaq(w[2], c, fmaq(w[1], b, w[0] * a));
-}
 // P_m to P_{m+1} = P_m (c - i s).
 template <class R> __device__ __forceinline__ void next_phase(R c, R s, R &Pr, R &Pi) {
   const R t = fmaq(Pr, c, Pi * s);
@@ -444,24 +425,6 @@ __device__ __forceinline__ PStateQ<R> load_q(const PartsQ<R> &P, int p) {
   return s;
 }
 
-// Twice the quadratic weights (the gather scales its sums by 1/4), or the
-// energy-conserving gather's (unscaled) along a staggered direction.
-template <class R> __device__ __forceinline__ void spline2q(R d, R w[3]) {
-  const R a = R(0.5) - d, b = R(0.5) + d;
-  w[0] = a * a;
-  w[1] = R(1.5) - R(2) * d * d;
-  w[2] = b * b;
-}
-template <class R> __device__ __forceinline__ void half2q(R d, R w[3], bool ec) {
-  if (ec) {
-    line3<R>(d, w);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) w[k] = R(2) * w[k];
-  } else {
-    spline2q<R>(d, w);
-  }
-}
-
 }  // namespace
 
 // One workgroup per (run, segment of a tile).  A segment's box (from the previous push, or the
@@ -567,10 +530,10 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
     // doubled along both
     R wzi[3], wzh[3], wri[3], wrh[3];
     const int upz = fz >= R(0.5);
-    spline2q<R>(fz - R(upz), wzi);
-    half2q<R>(fz - R(0.5), wzh, r.interp != 0);
-    spline2q<R>(dri, wri);
-    half2q<R>(drh, wrh, r.interp != 0);
+    spline3x2<R>(fz - R(upz), wzi);
+    half3x2<R>(fz - R(0.5), wzh, r.interp != 0);
+    spline3x2<R>(dri, wri);
+    half3x2<R>(drh, wrh, r.interp != 0);
     const bool gi = mri == 0, gh = mrh == 0;  // ghost row in the stencil
     // sum over the modes of Re(F_m e^{i m th}), with P_m = (ct - i sn)^m by
     // recurrence (m = 0: the real part alone)
@@ -699,9 +662,9 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
         atomicOr(err, ERR_RANGE);
         ok = false;
       } else {
-        dz = advq<R>(fz, mz, gz);
-        dx = advq<R>(fx, mx, gx);
-        dy = advq<R>(fy, my, gy);
+        dz = advance<R>(fz, mz, gz);
+        dx = advance<R>(fx, mx, gx);
+        dy = advance<R>(fy, my, gy);
         radial<R>(ix + dx, gx, iy + dy, gy, mrb, drb, ctb, stb);
         // within the wall margin, and less than a cell in r (the deposit window
         // and the tile's box assume it)

@@ -386,6 +386,9 @@ class Sim : public SimBase {
     if (dim_ == 3) {
       tile1_ = TILE1_3D;
       tile2_ = TILE2_3D;
+      // 32 x 16 x 16, five particles a cell: push 25.9 us with 64 tiles of 8 x 4 x 4,
+      // 14.8 with 256 of 8 x 2 x 2; 64 x 24 x 24: 26.4 with 288, 30.8 with 1152
+      while (tiles3(tile1_, tile2_) < 128 && tile2_ > 2) tile2_ /= 2;
     } else {
       // smaller tiles where the default ones would leave compute units without
       // a workgroup (64 x 32: push 18.0 us with 8 tiles of 32 x 8, 13.0 with 16
@@ -923,7 +926,7 @@ class Sim : public SimBase {
     // a shape whose current box, grown by one cell of particle spread per
     // axis, no longer fits the LDS budget would send its tiles to global
     // atomics later in a run (a short trial does not see that): skipped
-    const int lds_max = (FIXED && dim_ == 3) ? PUSH3_LDS_MAX_FP32 : PUSH_LDS_MAX;
+    const int lds_max = dim_ == 3 ? Push3Occupancy<R>::LDS_MAX : PUSH_LDS_MAX;
     auto fits = [&](int t1, int t2) {
       for (const RunHost &h : runs_) {
         const long long w = std::min(t1, h.d.n1) + 6, hh = std::min(t2, h.d.n2) + 6;
@@ -1639,10 +1642,30 @@ class Sim : public SimBase {
   // Particle tiles of every run (t1 x t2 cells, clipped to the grid), the
   // push work list and the push LDS budget; the caller uploads the runs and
   // re-sorts.
+  // Tiles of t1 x t2 x t2 cells in all 3D runs, and the LDS for the current box of
+  // particles that drift by part of a cell, but not apart.
+  long long tiles3(int t1, int t2) const {
+    long long n = 0;
+    for (const RunHost &h : runs_)
+      n += (long long)((h.d.n1 + t1 - 1) / t1) * ((h.d.n2 + t2 - 1) / t2) * ((h.d.n3 + t2 - 1) / t2);
+    return n;
+  }
+  static long long box3(int t1, int t2) { return 24ll * (t1 + 6) * (t2 + 6) * (t2 + 6); }
+
   int make_tiles(int t1, int t2) {
     drop_graphs();
     std::vector<Item> tiles;
     int maxbox = 0;
+    // 3D: the push takes 2 x 2 neighbours in x2 and x3 together, or 2 in x1, for as
+    // long as the box fits and at least 1024 workgroups remain: fewer halo nodes a
+    // particle, and two particles a thread to share them (512 x 128 x 128, two
+    // particles a cell: 8 x 4 x 4 cells 1620 us, 8 x 8 x 8 1200; 256 x 40 x 40, 800
+    // workgroups of 8 x 8 x 8: 90 us, 3200 of 8 x 4 x 4 83)
+    int p1 = t1, p2 = t2;
+    for (; dim_ == 3; (p1 <= p2 ? p1 : p2) *= 2) {
+      const int q1 = p1 <= p2 ? 2 * p1 : p1, q2 = p1 <= p2 ? p2 : 2 * p2;
+      if (box3(q1, q2) > Push3Occupancy<R>::LDS_MAX * 7 / 8 || tiles3(q1, q2) < 1024) break;
+    }
     for (int i = 0; i < (int)runs_.size(); ++i) {
       Run<R> &d = runs_[i].d;
       int **arrs[3] = {&d.tile_start, &d.tile_cnt, &d.tile_box};
@@ -1651,9 +1674,9 @@ class Sim : public SimBase {
           release(*a);
           *a = nullptr;
         }
-      d.T1 = std::min(t1, d.n1);
-      d.T2 = std::min(t2, d.n2);
-      d.T3 = d.dim == 3 ? std::min(t2, d.n3) : 1;
+      d.T1 = std::min(p1, d.n1);
+      d.T2 = std::min(p2, d.n2);
+      d.T3 = d.dim == 3 ? std::min(p2, d.n3) : 1;
       d.nt1 = (d.n1 + d.T1 - 1) / d.T1;
       d.nt2 = (d.n2 + d.T2 - 1) / d.T2;
       d.nt3 = (d.n3 + d.T3 - 1) / d.T3;
@@ -1666,16 +1689,11 @@ class Sim : public SimBase {
       // staged box of a tile whose particles spread SLACK cells beyond it
       const int b1 = std::min(d.T1 + 2 * SLACK1, d.n1) + 6;
       const int b2 = std::min(d.T2 + 2 * SLACK2, d.n2) + 6;
-      const int b3 = d.dim == 3 ? std::min(d.T3 + 2 * SLACK2, d.n3) + 6 : 1;
-      maxbox = std::max(maxbox, b1 * b2 * b3);
+      maxbox = std::max(maxbox, b1 * b2);
     }
     tile1_ = t1;
     tile2_ = t2;
-    // per node: 3 accumulators + 6 staged field values (a 3D tile whose two
-    // boxes do not fit gathers its fields through the cache; the 3D FP64 form
-    // always does, it was measured faster so)
-    const int node_bytes = FIXED ? 48 : (dim_ == 3 ? 24 : 72);
-    const int lds_max = (FIXED && dim_ == 3) ? PUSH3_LDS_MAX_FP32 : PUSH_LDS_MAX;
+    const int node_bytes = FIXED ? 48 : 72;  // 3 accumulators + 6 staged field values
     long long need = (long long)maxbox * node_bytes;
     if (dim_ == 2 && runs_[0].d.shape == 2) {
       need = 0;
@@ -1683,7 +1701,10 @@ class Sim : public SimBase {
         need = std::max(need, push_box_bytes(push_cols(std::min(t1, h.d.n1)),
                                              std::min(h.d.T2 + 2 * SLACK2, h.d.n2) + 6, sizeof(R)));
     }
-    push_lds_ = (int)std::min<long long>(lds_max, std::max<long long>(PUSH_LDS_MIN, (need + 511) / 512 * 512));
+    push_lds_ = (int)std::min<long long>(PUSH_LDS_MAX, std::max<long long>(PUSH_LDS_MIN, (need + 511) / 512 * 512));
+    // 3D: all the LDS that the occupancy leaves, for the particles' spread
+    using O3 = Push3Occupancy<R>;
+    if (dim_ == 3) push_lds_ = box3(p1, p2) <= O3::LDS_256 ? O3::LDS_256 : O3::LDS_MAX;
     if (d_tiles_) release(d_tiles_);
     d_tiles_ = nullptr;
     n_tiles_ = 0;
