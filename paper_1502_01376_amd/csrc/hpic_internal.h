@@ -29,6 +29,8 @@ struct Item {
 // i1 | i2 << log2n1 | i3 << sh3 (2D: i3 = 0, so the packed index is the
 // linear one), f1/f2/f3[np] offsets in [0,1) (f3 only in 3D), u1..u3[np]
 // momenta u = gamma v, qw[np] charge times weight, id[np] load index.
+constexpr int SORT_BLOCK = 2048;
+
 template <class R>
 struct Parts {
   int *cell, *id;
@@ -38,8 +40,10 @@ struct Parts {
 // Device-side description of one 2D run.  Arrays are owned by the host runtime.
 //   pt:  particle buffers, ping-pong for the tile sort (index = particle parity)
 //   tiles: T1 x T2 cells each, nt1 x nt2 of them; tile_start[ntiles + 1] is the
-//        first particle of each tile after the last sort, tile_cnt[ntiles] the
-//        histogram / scatter cursor of the sort; tile_box the bounding box of
+//        first particle of each tile after the last sort, cell_cnt[ntiles][area]
+//        the histogram / scatter cursor of the sort (one key per cell of a tile,
+//        or per tile), in blocks of SORT_BLOCK with their sums and first
+//        particles blk_sum, blk_base; tile_box the bounding box of
 //        the cells of each tile's particles (they drift out of the tile
 //        between sorts)
 //   F:   real-space fields [6][n2][n1] (E1 E2 E3 B1 B2 B3) for the gather
@@ -77,7 +81,8 @@ struct Run {
                      // row transform (so the transform sees the drift-free current)
   Parts<R> pt[2];
   int T1, T2, T3, nt1, nt2, nt3, ntiles;
-  int *tile_start, *tile_cnt;
+  int area;          // sort keys per tile
+  int *tile_start, *cell_cnt, *blk_sum, *blk_base;
   int *tile_box;     // [ntiles][6]: lo1, hi1, lo2, hi2, lo3, hi3 of the tile's particle cells
                      // relative to the tile origin (updated by every push)
   R *F;
@@ -453,25 +458,18 @@ __device__ __forceinline__ int wrap_small(int i, int n) {
   return i;
 }
 
-// Wave-aggregated atomic add of 1 per lane to cnt[key]: lanes with equal keys
-// share one atomic; returns the lane's rank among the previous value and its
-// peers (so the result equals a per-lane atomicAdd(cnt + key, 1) up to the
-// order among peers).
-__device__ __forceinline__ int wave_atomic_inc(int *cnt, int key, bool active) {
-  const int lane = threadIdx.x & 63;
-  unsigned long long todo = __ballot(active);
-  int result = 0;
-  while (todo) {
-    const int leader = __ffsll((long long)todo) - 1;
-    const int lk = __shfl(key, leader);
-    const unsigned long long same = __ballot(active && key == lk) & todo;
-    int base = 0;
-    if (lane == leader) base = atomicAdd(cnt + lk, __popcll(same));
-    base = __shfl(base, leader);
-    if (active && key == lk) result = base + __popcll(same & ((1ull << lane) - 1));
-    todo &= ~same;
-  }
-  return result;
+// Adds 1 per lane to cnt[key] and returns the lane's place in it; the active lanes
+// are the wave's first ones.  Neighbouring lanes with equal keys (particles as loaded
+// come cell by cell) share one atomic, which would serve them one after the other.
+__device__ __forceinline__ int cell_inc(int *cnt, int key) {
+  const int lane = threadIdx.x & 63, lanes = __popcll(__ballot(1));
+  const int before = __shfl_up(key, 1);
+  const unsigned long long heads = __ballot(lane == 0 || before != key);
+  const int head = 63 - __clzll(heads & (~0ull >> (63 - lane)));
+  const unsigned long long after = heads & (~1ull << lane);
+  int base = 0;
+  if (head == lane) base = atomicAdd(cnt + key, (after ? __ffsll((long long)after) - 1 : lanes) - lane);
+  return __shfl(base, head) + lane - head;
 }
 
 // Error bits of the device error word.
@@ -528,11 +526,9 @@ struct Launch {
                            int pp, int lds_bytes, int tile1, bool unit, bool ec,
                            unsigned *err, unsigned *stats, hipStream_t s);
   // tile sort of the particles of all runs: items are (run, first particle,
-  // count) chunks; per_run lists (run, 0, 0) once per run.  scramble = true
-  // spreads the particles of one cell over a tile's slots (for input in cell
-  // order); false keeps the arrival order, so the scatter writes are coalesced
-  static void sort(const Run<R> *runs, const Item *chunks, int nchunks, const Item *per_run,
-                   int nruns, int pp, bool scramble, hipStream_t s);
+  // count) chunks, and (run, b, 0) for every block b of SORT_BLOCK cell counts
+  static void sort(const Run<R> *runs, const Item *chunks, int nchunks, const Item *blocks,
+                   int nblocks, int pp, hipStream_t s);
   // row transforms: ncomp = 3 components per block (item = run, row[, group])
   // or 1 (item = run, row, component) for long rows
   static void fft_j(const Run<R> *runs, const Item *items, int nitems, int parity, int maxM,

@@ -848,61 +848,121 @@ k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, 
 }
 
 // ---------------------------------------------------------------- tile sort
-// Counting sort of the particles of every run by tile of their current cell:
-// count, exclusive scan (one workgroup per run), scatter into the other
-// particle buffer.  The order inside a tile is whatever the atomics give; the
-// step's results do not depend on it.
-template <class R>
-__device__ __forceinline__ int tile_of(const Run<R> &r, int cell) {
-  const int i1 = cell & (r.n1 - 1);
-  if (r.dim == 3) {
-    const int i2 = (cell >> r.log2n1) & ((1 << (r.sh3 - r.log2n1)) - 1), i3 = cell >> r.sh3;
-    return ((i3 / r.T3) * r.nt2 + i2 / r.T2) * r.nt1 + i1 / r.T1;
+// Counting sort of the particles of every run by tile and cell of the tile: count,
+// exclusive scan over the cells, scatter into the other particle buffer.  The
+// order inside a cell is whatever the atomics give; the step's results do not
+// depend on any of it.  Sorted by tile alone, particles kept their order of arrival,
+// and the lanes of one LDS atomic met on the same nodes (24 runs, 31M particles
+// loaded at random: push 667 us, 518 now) or came to (512 x 128 x 128 cells: 1380 us in
+// the first 64 steps, 1540 after four sorts, with the push as it was).  What bounds
+// it is the scatter's traffic, 80 bytes a particle, at 2.8 TB/s (893 us for the 24
+// runs, the whole sort 1160, 1600 when one workgroup a run scanned and
+// cleared the counts and a wave's lanes went to the tiles one by one).
+
+// a / b for 0 <= a < 2^23, 0 < b, and the remainder
+__device__ __forceinline__ int div_small(int a, int b, int &rem) {
+  int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+  int m = a - q * b;
+  if (m < 0) {
+    --q;
+    m += b;
+  } else if (m >= b) {
+    ++q;
+    m -= b;
   }
-  const int i2 = cell >> r.log2n1;
-  return (i2 / r.T2) * r.nt1 + i1 / r.T1;
+  rem = m;
+  return q;
+}
+// Tile of a cell, and the cell's place in the tile.  (Even columns and rows first, so
+// that lanes whose nearest node lies beside their cell still differ, moves more
+// memory in the scatter and gains the push nothing: 2D 518 and 526 us.)
+template <class R>
+__device__ __forceinline__ int tile_of(const Run<R> &r, int cell, int &place) {
+  int a1, a2, a3 = 0, t3 = 0, i2;
+  if (r.dim == 3) {
+    i2 = (cell >> r.log2n1) & ((1 << (r.sh3 - r.log2n1)) - 1);
+    t3 = div_small(cell >> r.sh3, r.T3, a3);
+  } else {
+    i2 = cell >> r.log2n1;
+  }
+  const int t1 = div_small(cell & (r.n1 - 1), r.T1, a1), t2 = div_small(i2, r.T2, a2);
+  place = r.area == 1 ? 0 : (a3 * r.T2 + a2) * r.T1 + a1;
+  return (t3 * r.nt2 + t2) * r.nt1 + t1;
 }
 
 template <class R>
-__global__ void k_sort_clear(const Run<R> *runs, const Item *per_run) {
-  const Run<R> &r = runs[per_run[blockIdx.x].run];
-  for (int t = threadIdx.x; t < r.ntiles; t += blockDim.x) r.tile_cnt[t] = 0;
+__global__ void __launch_bounds__(256) k_sort_clear(const Run<R> *runs, const Item *blocks) {
+  const Item it = blocks[blockIdx.x];
+  const Run<R> &r = runs[it.run];
+  const gptr<int> c = G(r.cell_cnt) + (long long)it.a * SORT_BLOCK;
+  const int n = min(SORT_BLOCK, r.ntiles * r.area - it.a * SORT_BLOCK);
+  for (int i = threadIdx.x; i < n; i += 256) c[i] = 0;
 }
 
 template <class R>
-__global__ void k_sort_count(const Run<R> *runs, const Item *chunks, int pp) {
+__global__ void __launch_bounds__(256) k_sort_count(const Run<R> *runs, const Item *chunks, int pp) {
   const Item it = chunks[blockIdx.x];
   const Run<R> &r = runs[it.run];
-  const bool active = threadIdx.x < (unsigned)it.b;
-  const int key = active ? tile_of(r, r.pt[pp].cell[it.a + threadIdx.x]) : 0;
-  wave_atomic_inc(r.tile_cnt, key, active);
+  if (threadIdx.x >= (unsigned)it.b) return;
+  int place;
+  const int t = tile_of(r, *elem(r.pt[pp].cell, it.a + (int)threadIdx.x), place);
+  (void)cell_inc(r.cell_cnt, t * r.area + place);
 }
 
-// exclusive scan of tile_cnt into tile_start (and back into tile_cnt as the
-// scatter cursor); one 1024-thread workgroup per run
+// Exclusive scan of the cell counts within blocks of SORT_BLOCK, and the blocks' sums.
 template <class R>
-__global__ void __launch_bounds__(1024) k_sort_scan(const Run<R> *runs, const Item *per_run) {
-  __shared__ int part[1024];
-  const Run<R> &r = runs[per_run[blockIdx.x].run];
-  const int nt = r.ntiles;
-  const int per = (nt + 1023) / 1024;
-  const int b0 = threadIdx.x * per;
-  int s = 0;
-  for (int t = b0; t < min(b0 + per, nt); ++t) s += r.tile_cnt[t];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int v = threadIdx.x >= (unsigned)off ? part[threadIdx.x - off] : 0;
-    __syncthreads();
-    part[threadIdx.x] += v;
-    __syncthreads();
+__global__ void __launch_bounds__(256) k_sort_scan(const Run<R> *runs, const Item *blocks) {
+  __shared__ int wsum[4];
+  const Item it = blocks[blockIdx.x];
+  const Run<R> &r = runs[it.run];
+  const gptr<int> c = G(r.cell_cnt) + (long long)it.a * SORT_BLOCK;
+  const int n = min(SORT_BLOCK, r.ntiles * r.area - it.a * SORT_BLOCK);
+  constexpr int PER = SORT_BLOCK / 256;
+  const int i0 = (int)threadIdx.x * PER, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int v[PER], s = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) v[k] = i0 + k < n ? c[i0 + k] : 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int x = v[k];
+    v[k] = s;
+    s += x;
   }
-  int run = part[threadIdx.x] - s;  // exclusive prefix of this thread's block
-  for (int t = b0; t < min(b0 + per, nt); ++t) {
-    const int c = r.tile_cnt[t];
-    r.tile_start[t] = run;
-    r.tile_cnt[t] = run;
-    run += c;
+  int inc = s;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(inc, o);
+    if (lane >= o) inc += x;
+  }
+  if (lane == 63) wsum[w] = inc;
+  __syncthreads();
+  int base = inc - s;
+  for (int k = 0; k < w; ++k) base += wsum[k];
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (i0 + k < n) c[i0 + k] = base + v[k];
+  if (threadIdx.x == 255) G(r.blk_sum)[it.a] = base + s;
+}
+
+// The blocks' first particles, and the tiles that start in them.
+template <class R>
+__global__ void __launch_bounds__(256) k_sort_tiles(const Run<R> *runs, const Item *blocks) {
+  __shared__ int wsum[4];
+  const Item it = blocks[blockIdx.x];
+  const Run<R> &r = runs[it.run];
+  int s = 0;
+  for (int b = threadIdx.x; b < it.a; b += 256) s += G(r.blk_sum)[b];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = s;
+  __syncthreads();
+  const int base = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  if (threadIdx.x == 0) {
+    G(r.blk_base)[it.a] = base;
+    if (it.a == 0) G(r.tile_start)[r.ntiles] = r.np;
+  }
+  const int c0 = it.a * SORT_BLOCK, c1 = min(c0 + SORT_BLOCK, r.ntiles * r.area);
+  const int first = (c0 + r.area - 1) / r.area;
+  for (int t = first + (int)threadIdx.x; t * r.area < c1 && t < r.ntiles; t += 256) {
+    G(r.tile_start)[t] = base + G(r.cell_cnt)[t * r.area];
     // right after the sort every particle of tile t lies in the tile, which the
     // frame of the push (centred on the tile) always holds whole
     const int t3 = t / (r.nt1 * r.nt2), t12 = t - t3 * r.nt1 * r.nt2;
@@ -911,44 +971,33 @@ __global__ void __launch_bounds__(1024) k_sort_scan(const Run<R> *runs, const It
                       min(r.T3, r.n3 - t3 * r.T3)};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      r.tile_box[6 * t + 2 * d] = 0;
-      r.tile_box[6 * t + 2 * d + 1] = w[d] - 1;
+      G(r.tile_box)[6 * t + 2 * d] = 0;
+      G(r.tile_box)[6 * t + 2 * d + 1] = w[d] - 1;
     }
   }
-  if (threadIdx.x == 1023) r.tile_start[nt] = part[1023];
 }
 
-// Scatter.  With `scramble`, a particle's rank within its tile (arrival order)
-// is transposed (a bijection, below) so that consecutive slots of a tile hold
-// particles of different cells: the lanes of a push wave then do not hit the
-// same LDS accumulator, and their addresses fall in different banks.  That is
-// needed once, for input in cell order; later sorts keep the arrival order
-// (already spread), so lanes of one wave with the same tile write consecutive
-// slots.
 template <class R>
-__global__ void k_sort_scatter(const Run<R> *runs, const Item *chunks, int pp, int scramble) {
+__global__ void __launch_bounds__(256) k_sort_scatter(const Run<R> *runs, const Item *chunks, int pp) {
   const Item it = chunks[blockIdx.x];
   const Run<R> &r = runs[it.run];
-  const bool active = threadIdx.x < (unsigned)it.b;
-  const int p = it.a + threadIdx.x;
+  if (threadIdx.x >= (unsigned)it.b) return;
+  const int p = it.a + (int)threadIdx.x;
   const Parts<R> &A = r.pt[pp];
   const Parts<R> &B = r.pt[pp ^ 1];
-  const int c = active ? A.cell[p] : 0;
-  const int t = tile_of(r, c);
-  const int q = wave_atomic_inc(r.tile_cnt, t, active);
-  if (!active) return;
-  const int t0 = r.tile_start[t], cnt = r.tile_start[t + 1] - t0;
-  const int rank = q - t0;
-  int slot = t0 + rank;
-  if (scramble) {
-    // ragged transpose by the tile's mean particles per cell m: arrival rank
-    // r = m j + k (loaded particles arrive in cell order) goes to column k,
-    // row j, so consecutive slots, the lanes of a wave, hold particles of
-    // different cells
-    const int area = (r.dim == 3) ? r.T1 * r.T2 * r.T3 : r.T1 * r.T2;
-    const int m = max(1, cnt / area);
-    const int rows = cnt / m, rem = cnt - rows * m;
-    const int k = rank % m, j = rank / m;
+  const int c = *elem(A.cell, p);
+  int place;
+  const int t = tile_of(r, c, place), key = t * r.area + place;
+  const int q = cell_inc(r.cell_cnt, key) + G(r.blk_base)[key / SORT_BLOCK];
+  const int t0 = G(r.tile_start)[t], cnt = G(r.tile_start)[t + 1] - t0, rank = q - t0;
+  // ragged transpose by the tile's particles per cell m: rank r = m j + k goes to
+  // column k, row j, so that consecutive slots, the lanes of a wave, hold
+  // particles of different cells
+  int slot = q;
+  if (cnt < 1 << 23) {
+    int rem, rest, k;
+    const int m = max(1, div_small(cnt + (r.area >> 1), r.area, rest));
+    const int rows = div_small(cnt, m, rem), j = div_small(rank, m, k);
     slot = t0 + k * rows + min(k, rem) + j;
   }
   B.cell[slot] = c;
@@ -1079,14 +1128,14 @@ void Launch<R>::push_deposit(const Run<R> *runs, const Item *items, int nitems, 
 }
 
 template <class R>
-void Launch<R>::sort(const Run<R> *runs, const Item *chunks, int nchunks, const Item *per_run,
-                     int nruns, int pp, bool scramble, hipStream_t s) {
+void Launch<R>::sort(const Run<R> *runs, const Item *chunks, int nchunks, const Item *blocks,
+                     int nblocks, int pp, hipStream_t s) {
   if (nchunks <= 0) return;
-  hipLaunchKernelGGL(k_sort_clear<R>, dim3(nruns), dim3(256), 0, s, runs, per_run);
+  hipLaunchKernelGGL(k_sort_clear<R>, dim3(nblocks), dim3(256), 0, s, runs, blocks);
   hipLaunchKernelGGL(k_sort_count<R>, dim3(nchunks), dim3(256), 0, s, runs, chunks, pp);
-  hipLaunchKernelGGL(k_sort_scan<R>, dim3(nruns), dim3(1024), 0, s, runs, per_run);
-  hipLaunchKernelGGL(k_sort_scatter<R>, dim3(nchunks), dim3(256), 0, s, runs, chunks, pp,
-                     scramble ? 1 : 0);
+  hipLaunchKernelGGL(k_sort_scan<R>, dim3(nblocks), dim3(256), 0, s, runs, blocks);
+  hipLaunchKernelGGL(k_sort_tiles<R>, dim3(nblocks), dim3(256), 0, s, runs, blocks);
+  hipLaunchKernelGGL(k_sort_scatter<R>, dim3(nchunks), dim3(256), 0, s, runs, chunks, pp);
 }
 
 template struct Launch<float>;

@@ -284,7 +284,7 @@ class Sim : public SimBase {
     HIPCHK(hipMalloc(&d_ant_, sizeof(AntennaDev) * std::max(nruns, 1)));
     allocs_.push_back(d_ant_);
     runs_.resize(nruns);
-    std::vector<Item> rows, grps, upd, perrun;
+    std::vector<Item> rows, grps, upd;
     for (int i = 0; i < nruns; ++i) {
       RunHost &h = runs_[i];
       h.cfg = cfgs[i];
@@ -372,7 +372,6 @@ class Sim : public SimBase {
       h.grp0 = (int)grps.size();
       for (int r = 0; r < d.rows; ++r)
         for (int g = 0; g < 6; g += ncomp_) grps.push_back(Item{i, r, ncomp_ == 3 ? g / 3 : g});
-      perrun.push_back(Item{i, 0, 0});
     }
     // one update thread per strip of rows i2 (2D) or row (3D) and mode
     strip_ = update_strip();
@@ -402,7 +401,6 @@ class Sim : public SimBase {
       while (tiles() < 256 && tile1_ * tile2_ > 32) (tile1_ > tile2_ ? tile1_ : tile2_) /= 2;
     }
     if ((rc = make_tiles(tile1_, tile2_))) return rc;
-    if ((rc = upload_items(perrun, &d_perrun_, &n_perrun_))) return rc;
     if ((rc = alloc(&d_runs_, nruns))) return rc;
     if ((rc = upload_items(rows, &d_rows_, &n_rows_))) return rc;
     if ((rc = upload_items(grps, &d_grps_, &n_grps_))) return rc;
@@ -492,7 +490,7 @@ class Sim : public SimBase {
     if ((rc = upload_jfac(run))) return rc;
     if ((rc = rebuild_sort_items())) return rc;
     if ((rc = upload_runs())) return rc;
-    return sort_now(true);
+    return sort_now();
   }
 
   // Particles from FP64 arrays in device memory: the conversion of
@@ -553,7 +551,7 @@ class Sim : public SimBase {
     if ((rc = upload_jfac(run))) return rc;
     if ((rc = rebuild_sort_items())) return rc;
     if ((rc = upload_runs())) return rc;
-    return sort_now(true);
+    return sort_now();
   }
 
   // The real-space field of one component (the copy the next gather reads) into
@@ -701,8 +699,7 @@ class Sim : public SimBase {
     const int p = parity_;
     if (sort_interval_ > 0 && since_sort_ >= sort_interval_) {
       mark(HP_K_SORT, true);
-      Launch<R>::sort(d_runs_, d_chunks_, n_chunks_, d_perrun_, (int)runs_.size(), pp_, false,
-                      stream_);
+      Launch<R>::sort(d_runs_, d_chunks_, n_chunks_, d_cblocks_, n_cblocks_, pp_, stream_);
       mark(HP_K_SORT, false);
       if (n_chunks_ > 0) pp_ ^= 1;
       since_sort_ = 0;
@@ -872,7 +869,7 @@ class Sim : public SimBase {
     if ((rc = sync())) return rc;
     if ((rc = make_tiles(t1, t2)) || (rc = upload_runs())) return rc;
     sort_interval_ = K;
-    return sort_now(false);
+    return sort_now();
   }
 
   int get_tiling(hp_tune *out) override {
@@ -1431,7 +1428,7 @@ class Sim : public SimBase {
     }
     if ((rc = rebuild_sort_items())) return rc;
     if ((rc = upload_runs())) return rc;
-    return sort_now(false);
+    return sort_now();
   }
 
   // Arguments of the deposit entry points: the 2D quadratic integer deposit of
@@ -1654,7 +1651,7 @@ class Sim : public SimBase {
 
   int make_tiles(int t1, int t2) {
     drop_graphs();
-    std::vector<Item> tiles;
+    std::vector<Item> tiles, cblocks;
     int maxbox = 0;
     // 3D: the push takes 2 x 2 neighbours in x2 and x3 together, or 2 in x1, for as
     // long as the box fits and at least 1024 workgroups remain: fewer halo nodes a
@@ -1668,7 +1665,7 @@ class Sim : public SimBase {
     }
     for (int i = 0; i < (int)runs_.size(); ++i) {
       Run<R> &d = runs_[i].d;
-      int **arrs[3] = {&d.tile_start, &d.tile_cnt, &d.tile_box};
+      int **arrs[] = {&d.tile_start, &d.cell_cnt, &d.tile_box, &d.blk_sum, &d.blk_base};
       for (int **a : arrs)
         if (*a) {
           release(*a);
@@ -1682,9 +1679,15 @@ class Sim : public SimBase {
       d.nt3 = (d.n3 + d.T3 - 1) / d.T3;
       d.ntiles = d.nt1 * d.nt2 * d.nt3;
       int rc;
-      if ((rc = alloc(&d.tile_start, d.ntiles + 1)) || (rc = alloc(&d.tile_cnt, d.ntiles)) ||
-          (rc = alloc(&d.tile_box, 6 * d.ntiles)))
+      // a key per cell of the tiles, where these fit 32-bit indices
+      const long long area = (long long)d.T1 * d.T2 * d.T3, keys = area * d.ntiles;
+      d.area = keys < (1ll << 30) ? (int)area : 1;
+      const int nb = (int)(((long long)d.area * d.ntiles + SORT_BLOCK - 1) / SORT_BLOCK);
+      if ((rc = alloc(&d.tile_start, d.ntiles + 1)) ||
+          (rc = alloc(&d.cell_cnt, (size_t)d.area * d.ntiles)) || (rc = alloc(&d.blk_sum, nb)) ||
+          (rc = alloc(&d.blk_base, nb)) || (rc = alloc(&d.tile_box, 6 * d.ntiles)))
         return rc;
+      for (int b = 0; b < nb; ++b) cblocks.push_back(Item{i, b, 0});
       for (int t = 0; t < d.ntiles; ++t) tiles.push_back(Item{i, t, 0});
       // staged box of a tile whose particles spread SLACK cells beyond it
       const int b1 = std::min(d.T1 + 2 * SLACK1, d.n1) + 6;
@@ -1706,8 +1709,10 @@ class Sim : public SimBase {
     using O3 = Push3Occupancy<R>;
     if (dim_ == 3) push_lds_ = box3(p1, p2) <= O3::LDS_256 ? O3::LDS_256 : O3::LDS_MAX;
     if (d_tiles_) release(d_tiles_);
-    d_tiles_ = nullptr;
-    n_tiles_ = 0;
+    if (d_cblocks_) release(d_cblocks_);
+    d_tiles_ = d_cblocks_ = nullptr;
+    n_tiles_ = n_cblocks_ = 0;
+    if (int rc = cblocks.empty() ? HP_OK : upload_items(cblocks, &d_cblocks_, &n_cblocks_)) return rc;
     return tiles.empty() ? HP_OK : upload_items(tiles, &d_tiles_, &n_tiles_);
   }
 
@@ -1750,12 +1755,8 @@ class Sim : public SimBase {
     return HP_OK;
   }
   // Sort the particles of every run by tile now (into the other buffer).
-  // scramble: the particles arrive in cell order (just loaded), so spread each
-  // tile's slots over its cells (see k_sort_scatter); otherwise keep the
-  // arrival order, already spread.
-  int sort_now(bool scramble) {
-    Launch<R>::sort(d_runs_, d_chunks_, n_chunks_, d_perrun_, (int)runs_.size(), pp_, scramble,
-                    stream_);
+  int sort_now() {
+    Launch<R>::sort(d_runs_, d_chunks_, n_chunks_, d_cblocks_, n_cblocks_, pp_, stream_);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(stream_));
     if (n_chunks_ > 0) pp_ ^= 1;
@@ -1874,12 +1875,12 @@ class Sim : public SimBase {
   std::vector<RunHost> runs_;
   std::vector<void *> allocs_;
   Run<R> *d_runs_ = nullptr;
-  Item *d_chunks_ = nullptr, *d_tiles_ = nullptr, *d_perrun_ = nullptr;
+  Item *d_chunks_ = nullptr, *d_tiles_ = nullptr, *d_cblocks_ = nullptr;
   Item *d_rows_ = nullptr, *d_grps_ = nullptr, *d_upd_ = nullptr;
   int n_chunks_ = 0, n_tiles_ = 0, n_rows_ = 0, n_grps_ = 0, n_upd_ = 0;
   void *scratch_ = nullptr;  // device address of the process's scratch region (this device)
   int pp_ = 0;             // particle buffer parity
-  int n_perrun_ = 0;
+  int n_cblocks_ = 0;
   int sort_interval_ = DEFAULT_SORT_INTERVAL, since_sort_ = 0;
   unsigned *d_stats_ = nullptr;
   int strip_ = 8;  // rows per thread of the 2D k-space update
