@@ -242,7 +242,7 @@ typedef struct hp_tune {
  * Quasi-3D handles: the bins of the periodic particle sort, tile1 z columns x
  * tile2 radial rows (default 4 x 2), and its interval (default 64 steps; a
  * load sorts before the first step); the push works on tiles of 4 x 2 bins,
- * at most 16 x 4 cells and smaller for more than three modes, in whose cells
+ * at most 16 x 4 cells and smaller for many modes or few tiles, in whose cells
  * the sort leaves the particles.  The sort only permutes storage: FP32_FIXED
  * results are bit-identical for every setting (FP64: equal to rounding, the
  * deposit's atomics add in another order).  lds_bytes reads 0 for these handles. */

@@ -1038,6 +1038,7 @@ void LaunchQ<R>::push_deposit(const RunQ<R> *runs, const Item *items, int nitems
     k = modes == 1   ? k_q_push_deposit<R, 1, C16>
         : modes == 2 ? k_q_push_deposit<R, 2, C16>
         : modes == 3 ? k_q_push_deposit<R, 3, C16>
+        : modes == 4 ? k_q_push_deposit<R, 4, C16>
                      : k_q_push_deposit<R, 0, C16>;
   else if (tz > 4)
     k = modes == 2   ? k_q_push_deposit<R, 2, C8>

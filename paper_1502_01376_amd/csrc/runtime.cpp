@@ -2692,16 +2692,22 @@ class SimQ : public SimBase {
     since_sort_ = sort_interval_;  // sort before the first step
     return HP_OK;
   }
-  // Push tiles: 4 x 2 bins of sbz z columns x sbr radial rows, at most 16 x 4
+  // Push tiles: 4 x 2 bins of sbz z columns x sbr radial rows, 8 to 16 x 2 to 4
   // cells, halved until the boxes of every run's modes fit the LDS (three modes:
   // 16 x 4, four: 8 x 4).  The particles are sorted by tile, so a change needs a
   // sort before the next push.
   int set_bins(int sbz, int sbr) {
-    int tz = 4 * std::min(sbz, 4), tr = 2 * std::min(sbr, 2), modes = 1;
+    int tz = 4 * std::min(std::max(sbz, 2), 4), tr = 2 * std::min(sbr, 2), modes = 1;
     for (const RunHostQ &h : runs_) modes = std::max(modes, h.d.M);
     // rows: the tile's, its far edge, the stencil's four and one of drift
     while (tz * tr > 1 && q_push_bytes(q_push_cols(tz), tr + 6, modes, sizeof(R)) > QPush<R>::LDS)
       (tz > tr ? tz : tr) /= 2;
+    // few workgroups: half as high (256 x 61, two modes, FP64: 35.6 us with 256 of 16 x 4
+    // cells, 27.8 with 512 of 16 x 2; 1024 x 150: 203 with 2432, 202 with 4800)
+    long long tiles = 0;
+    for (const RunHostQ &h : runs_)
+      tiles += (long long)((h.d.n1 + tz - 1) / tz) * ((h.d.n2 + tr - 1) / tr);
+    if (tiles < 1024 && tr > 2) tr = 2;
     push_tz_ = tz;
     for (RunHostQ &h : runs_) {
       RunQ<R> &d = h.d;
