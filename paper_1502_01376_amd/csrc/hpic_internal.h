@@ -95,6 +95,11 @@ struct Run {
   const R *jfac;     // [nk][3]: factor on the transformed accumulator per component
 };
 
+// Global-memory view of a pointer held in a descriptor: lets the compiler use
+// global (not flat) loads, stores and atomics.
+template <class T> using gptr = T __attribute__((address_space(1))) *;
+template <class T> __device__ __forceinline__ gptr<T> G(T *p) { return (gptr<T>)p; }
+
 // ---------------------------------------------------------------- complex
 __device__ __forceinline__ float2 cmk(float x, float y) { return make_float2(x, y); }
 __device__ __forceinline__ double2 cmk(double x, double y) { return make_double2(x, y); }
@@ -115,6 +120,40 @@ template <> __device__ __forceinline__ double2 from_d2<double2>(double2 a) { ret
 // multiply by +i (inv = true) or -i
 template <class C> __device__ __forceinline__ C cmuli(C a, bool plus) {
   return plus ? cmk(-a.y, a.x) : cmk(a.y, -a.x);
+}
+
+// Global loads and stores of pairs: element i of an array of complex values, and
+// elements i, i + 1 (i even) of one of accumulators or reals.  (Through a generic
+// pointer they would be flat accesses, which may alias the LDS and so cannot be
+// moved across its stores: every load of a row transform waited alone.)
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+typedef double double2v __attribute__((ext_vector_type(2)));
+typedef double double4v __attribute__((ext_vector_type(4)));
+typedef long long long2v __attribute__((ext_vector_type(2)));
+template <class T> struct Pair;
+template <> struct Pair<float2> { using V = float2v; };
+template <> struct Pair<double2> { using V = double2v; };
+template <> struct Pair<double> { using V = double2v; };
+template <> struct Pair<long long> { using V = long2v; };
+template <class R> struct Quad;
+template <> struct Quad<float> { using V = float4v; };
+template <> struct Quad<double> { using V = double4v; };
+template <class C> __device__ __forceinline__ C ldc(const C *p, long long i) {
+  const auto v = ((gptr<const typename Pair<C>::V>)G(p))[i];
+  return cmk(v.x, v.y);
+}
+template <class C> __device__ __forceinline__ void stc(C *p, long long i, C c) {
+  typename Pair<C>::V v;
+  v.x = c.x;
+  v.y = c.y;
+  ((gptr<typename Pair<C>::V>)G(p))[i] = v;
+}
+template <class A> __device__ __forceinline__ typename Pair<A>::V ldpair(const A *p, long long i) {
+  return *(gptr<const typename Pair<A>::V>)(G(p) + i);
+}
+template <class A> __device__ __forceinline__ void zeropair(A *p, long long i) {
+  *(gptr<typename Pair<A>::V>)(G(p) + i) = typename Pair<A>::V{0, 0};
 }
 
 // ---------------------------------------------------------------- LDS FFT
@@ -148,7 +187,7 @@ __device__ __forceinline__ void lds_fft(C *buf, int M, int log2M, int NF, const 
         if (s > 0) {
           // twiddle w^(r k), w = exp(-+2 pi i / (4 Ns)) -> table index r k M / (4 Ns)
           const int e = k << (log2Q - s);
-          C t1 = tw[(e)*tws], t2 = tw[(2 * e) * tws], t3 = tw[(3 * e) * tws];
+          C t1 = ldc(tw, e * tws), t2 = ldc(tw, 2 * e * tws), t3 = ldc(tw, 3 * e * tws);
           if (inverse) { t1 = cconj(t1); t2 = cconj(t2); t3 = cconj(t3); }
           a1 = cmul(a1, t1);
           a2 = cmul(a2, t2);
@@ -182,7 +221,7 @@ __device__ __forceinline__ void lds_fft(C *buf, int M, int log2M, int NF, const 
       const int f = g >> (log2M - 1);
       const int j = g & (H - 1);
       C *x = buf + f * M;
-      C t = tw[j * tws];
+      C t = ldc(tw, j * tws);
       if (inverse) t = cconj(t);
       const C a0 = x[j], a1 = cmul(x[j + H], t);
       x[j] = cadd(a0, a1);
@@ -258,7 +297,7 @@ __device__ __forceinline__ void lds_fft16(C *buf, int M, int log2M, int NF, cons
           const int e = k << (log2Q - s);
 #pragma unroll
           for (int r = 1; r < 16; ++r) {
-            C t = tw[(r * e) * tws];
+            C t = ldc(tw, r * e * tws);
             if (inverse) t = cconj(t);
             v[r] = cmul(v[r], t);
           }
@@ -434,11 +473,6 @@ __device__ __forceinline__ float inv_gamma(float s) {
   q = __builtin_fmaf(__builtin_fmaf(-g, q, 1.0f), q, q);
   return s <= 3.402823466e38f ? q : (s > 0.0f ? 0.0f : s);
 }
-
-// Global-memory view of a pointer held in a descriptor: lets the compiler use
-// global (not flat) loads, stores and atomics.
-template <class T> using gptr = T __attribute__((address_space(1))) *;
-template <class T> __device__ __forceinline__ gptr<T> G(T *p) { return (gptr<T>)p; }
 
 // Element p of an array whose base is uniform: a 32-bit byte offset from a
 // scalar base where every offset fits (at most 10^9 particles: 4-byte

@@ -113,7 +113,8 @@ struct LaunchQ {
   // the hybrid update of every mode, parity -> parity ^ 1 (two passes)
   static void kupdate(const RunQ<R> *runs, const Item *items, int nitems, int parity,
                       hipStream_t s);
-  // inverse transform of the master of a parity into the real-space fields
+  // second half step of B in the master of a parity and its inverse transform into
+  // the real-space fields
   static void ifft(const RunQ<R> *runs, const Item *items, int nitems, int parity, int maxn1,
                    hipStream_t s);
   // per (run, mode, row): sum |D.E - f rho|^2, max |D.E - f rho| and sum |f rho|^2

@@ -852,7 +852,7 @@ k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, 
 // exclusive scan over the cells, scatter into the other particle buffer.  The
 // order inside a cell is whatever the atomics give; the step's results do not
 // depend on any of it.  Sorted by tile alone, particles kept their order of arrival,
-// and the lanes of one LDS atomic met on the same nodes (24 runs, 31M particles
+// and the lanes of one LDS atomic met on the same nodes (24 runs, 34M particles
 // loaded at random: push 667 us, 518 now) or came to (512 x 128 x 128 cells: 1380 us in
 // the first 64 steps, 1540 after four sorts, with the push as it was).  What bounds
 // it is the scatter's traffic, 80 bytes a particle, at 2.8 TB/s (893 us for the 24

@@ -37,13 +37,17 @@ __device__ __forceinline__ C c2r_pre(C Xk, C Xmk, C Wk) {
 }
 
 // One workgroup per (run, row): the three current components of the row
-// (ncomp = 3), or per (run, row, component) for long rows (ncomp = 1, item.b
+// (NC = 3), or per (run, row, component) for long rows (NC = 1, item.b
 // the component), so that a block's LDS stays small enough for several
 // blocks per CU.
-template <class R, int MAXB>
+//
+// What bounds it: the traffic of the accumulators where the rows leave the last-
+// level cache (512 x 128 x 128 cells: 104 us, 106 at the rate of a large copy), else the
+// chain of load, transform and store, as all rows run at once (2048 x 512: 18.4 us, 21
+// with loads that waited one by one; 8192 x 512: 64, 80 before).
+template <class R, int MAXB, int NC>
 __global__ void __launch_bounds__(256) k_fft_j(const Run<R> *__restrict__ runs,
-                                               const Item *__restrict__ items, int parity,
-                                               int ncomp) {
+                                               const Item *__restrict__ items, int parity) {
   using C = typename Cplx<R>::T;
   extern __shared__ unsigned char smem_raw[];
   C *lds = (C *)smem_raw;
@@ -51,45 +55,54 @@ __global__ void __launch_bounds__(256) k_fft_j(const Run<R> *__restrict__ runs,
   const Run<R> &r = runs[it.run];
   const int row = it.a;
   const int n1 = r.n1, M = n1 >> 1, log2M = r.log2n1 - 1, cells = r.cells;
-  const auto *Jin = r.J[parity];
-  auto *Jz = r.J[parity ^ 1];
-  const int cb = ncomp == 3 ? 0 : it.b;
-  for (int cc = 0; cc < ncomp; ++cc) {
-    const long long base = (long long)(cb + cc) * cells + (long long)row * n1;
-    // the uniform background is added per node in FP64 before the conversion:
-    // for a drifting plasma it cancels the bulk current, so that the FP32
-    // transform (FP32 form) rounds relative to the current's fluctuation
-    const double bg = r.jbgu[cb + cc];
-    for (int n = threadIdx.x; n < M; n += blockDim.x) {
-      const R x0 = (R)((double)Jin[base + 2 * n] + bg);
-      const R x1 = (R)((double)Jin[base + 2 * n + 1] + bg);
-      lds[cc * M + n] = cmk(x0, x1);
-      Jz[base + 2 * n] = 0;
-      Jz[base + 2 * n + 1] = 0;
-    }
+  using Acc = typename Run<R>::Acc;
+  const Acc *Jin = r.J[parity];
+  Acc *Jz = r.J[parity ^ 1];
+  const int cb = NC == 3 ? 0 : it.b;
+  // a batch of loads in flight before their LDS stores
+  constexpr int U = NC == 3 ? 6 : 4;
+  auto place = [&](int q, int &c) {
+    const int cc = NC == 3 ? q >> log2M : 0;
+    c = cb + cc;
+    return (long long)c * cells + (long long)row * n1 + 2 * (q - (cc << log2M));
+  };
+  for (int q0 = threadIdx.x; q0 < NC * M; q0 += U * 256) {
+    typename Pair<Acc>::V v[U];
+    int c;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (q0 + u * 256 < NC * M) v[u] = ldpair(Jin, place(q0 + u * 256, c));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (q0 + u * 256 < NC * M) {
+        // the uniform background is added per node in FP64 before the conversion:
+        // for a drifting plasma it cancels the bulk current, so that the FP32
+        // transform (FP32 form) rounds relative to the current's fluctuation
+        place(q0 + u * 256, c);
+        const double bg = r.jbgu[c];
+        lds[q0 + u * 256] = cmk((R)((double)v[u].x + bg), (R)((double)v[u].y + bg));
+      }
   }
   __syncthreads();
-  lds_fft_rows<C, MAXB>(lds, M, log2M, ncomp, r.tw, 2, false);
+  lds_fft_rows<C, MAXB>(lds, M, log2M, NC, r.tw, 2, false);
   const int nk = r.nk;
-  for (int k = threadIdx.x; k <= (M >> 1); k += blockDim.x) {
-    const int mk = M - k;
-    const C Wk = r.tw[k], Wmk = r.tw[mk];
-    for (int cc = 0; cc < ncomp; ++cc) {
+  C *out = r.Jk + (long long)row * nk;
+  const long long plane = (long long)r.rows * nk;
+  auto post = [&](int k, int mk, bool both) {
+    const C Wk = ldc(r.tw, k), Wmk = ldc(r.tw, mk);
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) {
       const int c = cb + cc;
       const C Zk = lds[cc * M + k];
       const C Zmk = lds[cc * M + (mk & (M - 1))];
-      C Xk = r2c_post(Zk, Zmk, Wk);
-      const R fk = r.jfac[k * 3 + c];
-      Xk = cscale(Xk, fk);
-      C *out = r.Jk + (long long)c * r.rows * nk + (long long)row * nk;
-      out[k] = Xk;
-      if (mk != k) {
-        C Xm = r2c_post(Zmk, Zk, Wmk);
-        Xm = cscale(Xm, r.jfac[mk * 3 + c]);
-        out[mk] = Xm;
-      }
+      stc(out, c * plane + k, cscale(r2c_post(Zk, Zmk, Wk), G(r.jfac)[k * 3 + c]));
+      if (both) stc(out, c * plane + mk, cscale(r2c_post(Zmk, Zk, Wmk), G(r.jfac)[mk * 3 + c]));
     }
-  }
+  };
+  for (int k = threadIdx.x; k < (M >> 1); k += 256) post(k, M - k, true);
+  if (threadIdx.x == 255) post(M >> 1, M >> 1, false);
+  // the next step's accumulators, last: loads and stores wait in one queue
+  for (int q = threadIdx.x, c; q < NC * M; q += 256) zeropair(Jz, place(q, c));
 }
 
 // Forward transform of the six real-space fields of a row into the k-space
@@ -108,7 +121,7 @@ __global__ void __launch_bounds__(256) k_fields_to_k(const Run<R> *__restrict__ 
   const int n1 = r.n1, M = n1 >> 1, log2M = r.log2n1 - 1, cells = r.cells, nk = r.nk;
   for (int cc = 0; cc < ncomp; ++cc) {
     const R *src = r.F + (long long)(cb + cc) * cells + (long long)row * n1;
-    for (int n = threadIdx.x; n < M; n += blockDim.x) lds[cc * M + n] = cmk(src[2 * n], src[2 * n + 1]);
+    for (int n = threadIdx.x; n < M; n += blockDim.x) lds[cc * M + n] = ldc((const C *)src, n);
   }
   __syncthreads();
   lds_fft_rows<C, MAXB>(lds, M, log2M, ncomp, r.tw, 2, false);
@@ -118,8 +131,8 @@ __global__ void __launch_bounds__(256) k_fields_to_k(const Run<R> *__restrict__ 
       const C Zk = lds[cc * M + k];
       const C Zmk = lds[cc * M + (mk & (M - 1))];
       double2 *out = r.Fk[parity] + (long long)(cb + cc) * r.rows * nk + (long long)row * nk;
-      out[k] = to_d2(r2c_post(Zk, Zmk, r.tw[k]));
-      if (mk != k) out[mk] = to_d2(r2c_post(Zmk, Zk, r.tw[mk]));
+      stc(out, k, to_d2(r2c_post(Zk, Zmk, ldc(r.tw, k))));
+      if (mk != k) stc(out, mk, to_d2(r2c_post(Zmk, Zk, ldc(r.tw, mk))));
     }
   }
 }
@@ -160,12 +173,12 @@ __global__ void __launch_bounds__(256) k_kupdate(const Run<R> *__restrict__ runs
   const C *Fi = r.Fk[parity];
   C *Fo = r.Fk[parity ^ 1];
   auto at = [&](int comp, int row) {
-    return Fi[comp * plane + (long long)wrap_small(row, n2) * nk + k];
+    return ldc(Fi, comp * plane + (long long)wrap_small(row, n2) * nk + k);
   };
   const auto *Jk = r.Jk;
-  auto jat = [&](int comp, int row) { return to_d2(Jk[comp * plane + (long long)row * nk + k]); };
-  const C dp = cmk(r.sym[4 * k + 0], r.sym[4 * k + 1]);
-  const C dm = cmk(r.sym[4 * k + 2], r.sym[4 * k + 3]);
+  auto jat = [&](int comp, int row) { return to_d2(ldc(Jk, comp * plane + (long long)row * nk + k)); };
+  const C dp = ldc((const C *)r.sym, 2 * k);
+  const C dm = ldc((const C *)r.sym, 2 * k + 1);
   const double hdt = r.mhdt, dt = r.mdt, i2x = r.midx2;
   auto b1h = [&](C B, C Ea, C Eb) { return csub(B, cscale(csub(Eb, Ea), hdt * i2x)); };
   auto b2h = [&](C B, C E) { return cadd(B, cscale(cmul(dp, E), hdt)); };
@@ -199,12 +212,12 @@ __global__ void __launch_bounds__(256) k_kupdate(const Run<R> *__restrict__ runs
     if (j > q0) {
       // B^{n+1} on row j-1 and the stores of that row
       const long long o = (long long)(j - 1) * nk + k;
-      Fo[o] = pE1n;
-      Fo[plane + o] = pE2n;
-      Fo[2 * plane + o] = pE3n;
-      Fo[3 * plane + o] = b1h(pB1h, pE3n, E3n);
-      Fo[4 * plane + o] = b2h(pB2h, pE3n);
-      Fo[5 * plane + o] = b3h(pB3h, pE2n, pE1n, E1n);
+      stc(Fo, o, pE1n);
+      stc(Fo, plane + o, pE2n);
+      stc(Fo, 2 * plane + o, pE3n);
+      stc(Fo, 3 * plane + o, b1h(pB1h, pE3n, E3n));
+      stc(Fo, 4 * plane + o, b2h(pB2h, pE3n));
+      stc(Fo, 5 * plane + o, b3h(pB3h, pE2n, pE1n, E1n));
     }
     if (last) return;
     pE2n = cadd(E2, cscale(csub(cscale(cmul(dm, B3h), -1.0), jat(1, jw)), dt));
@@ -260,9 +273,9 @@ __global__ void __launch_bounds__(256) k_kupdate3a(const Run<R> *__restrict__ ru
   C *Fo = r.Fk[parity ^ 1];
   const int p2 = wrap_small(i2 + 1, n2), m2 = wrap_small(i2 - 1, n2);
   const int p3 = wrap_small(i3 + 1, n3), m3 = wrap_small(i3 - 1, n3);
-  auto at = [&](int comp, int j2, int j3) { return Fi[comp * vol + ((long long)j3 * n2 + j2) * nk + k]; };
-  const C dp = cmk(r.sym[4 * k + 0], r.sym[4 * k + 1]);
-  const C dm = cmk(r.sym[4 * k + 2], r.sym[4 * k + 3]);
+  auto at = [&](int comp, int j2, int j3) { return ldc(Fi, comp * vol + ((long long)j3 * n2 + j2) * nk + k); };
+  const C dp = ldc((const C *)r.sym, 2 * k);
+  const C dm = ldc((const C *)r.sym, 2 * k + 1);
   const double hdt = r.mhdt, dt = r.mdt, i2x = r.midx2, i3x = r.midx3;
   // curl E components, forward differences
   auto cE1 = [&](C e3, C e3n2, C e2, C e2n3) {
@@ -290,13 +303,13 @@ __global__ void __launch_bounds__(256) k_kupdate3a(const Run<R> *__restrict__ ru
   const C cB2 = csub(cscale(csub(B1h, B1h_3m), i3x), cmul(dm, B3h));
   const C cB3 = csub(cmul(dm, B2h), cscale(csub(B1h, B1h_2m), i2x));
   const auto *Jk = r.Jk;
-  const C j1 = to_d2(Jk[e]), j2 = to_d2(Jk[vol + e]), j3 = to_d2(Jk[2 * vol + e]);
-  Fo[e] = cadd(E1, cscale(csub(cB1, j1), dt));
-  Fo[vol + e] = cadd(E2, cscale(csub(cB2, j2), dt));
-  Fo[2 * vol + e] = cadd(E3, cscale(csub(cB3, j3), dt));
-  Fo[3 * vol + e] = B1h;
-  Fo[4 * vol + e] = B2h;
-  Fo[5 * vol + e] = B3h;
+  const C j1 = to_d2(ldc(Jk, e)), j2 = to_d2(ldc(Jk, vol + e)), j3 = to_d2(ldc(Jk, 2 * vol + e));
+  stc(Fo, e, cadd(E1, cscale(csub(cB1, j1), dt)));
+  stc(Fo, vol + e, cadd(E2, cscale(csub(cB2, j2), dt)));
+  stc(Fo, 2 * vol + e, cadd(E3, cscale(csub(cB3, j3), dt)));
+  stc(Fo, 3 * vol + e, B1h);
+  stc(Fo, 4 * vol + e, B2h);
+  stc(Fo, 5 * vol + e, B3h);
 }
 
 // Pass B over the same threads.
@@ -314,54 +327,75 @@ __global__ void __launch_bounds__(256) k_kupdate3b(const Run<R> *__restrict__ ru
   const long long vol = (long long)r.rows * nk;
   C *F = r.Fk[parity ^ 1];
   const int p2 = wrap_small(i2 + 1, n2), p3 = wrap_small(i3 + 1, n3);
-  auto at = [&](int comp, int j2, int j3) { return F[comp * vol + ((long long)j3 * n2 + j2) * nk + k]; };
-  const C dp = cmk(r.sym[4 * k + 0], r.sym[4 * k + 1]);
+  auto at = [&](int comp, int j2, int j3) { return ldc(F, comp * vol + ((long long)j3 * n2 + j2) * nk + k); };
+  const C dp = ldc((const C *)r.sym, 2 * k);
   const double hdt = r.mhdt, i2x = r.midx2, i3x = r.midx3;
   const C E1 = at(0, i2, i3), E2 = at(1, i2, i3), E3 = at(2, i2, i3);
   const C c1 = csub(cscale(csub(at(2, p2, i3), E3), i2x), cscale(csub(at(1, i2, p3), E2), i3x));
   const C c2 = csub(cscale(csub(at(0, i2, p3), E1), i3x), cmul(dp, E3));
   const C c3 = csub(cmul(dp, E2), cscale(csub(at(0, p2, i3), E1), i2x));
-  F[3 * vol + e] = csub(F[3 * vol + e], cscale(c1, hdt));
-  F[4 * vol + e] = csub(F[4 * vol + e], cscale(c2, hdt));
-  F[5 * vol + e] = csub(F[5 * vol + e], cscale(c3, hdt));
+  const C b1 = ldc(F, 3 * vol + e), b2 = ldc(F, 4 * vol + e), b3 = ldc(F, 5 * vol + e);
+  stc(F, 3 * vol + e, csub(b1, cscale(c1, hdt)));
+  stc(F, 4 * vol + e, csub(b2, cscale(c2, hdt)));
+  stc(F, 5 * vol + e, csub(b3, cscale(c3, hdt)));
 }
 
 // =====================================================================
 // inverse FFT of E and B
 // =====================================================================
 // Item = (run, row, group): components 3g..3g+2 of the master buffer of the
-// given parity, written to the real-space fields (ncomp = 3); or (run, row,
-// component) (ncomp = 1).
-template <class R, int MAXB>
+// given parity, written to the real-space fields (NC = 3); or (run, row,
+// component) (NC = 1).  (The 3D update's second pass done here as B is loaded spares
+// a pass over E and B, but the rows beside a workgroup's come from beyond its L2: 390
+// us for both on 512 x 128 x 128 cells, 295 apart.)
+//
+// Bound as k_fft_j is: 512 x 128 x 128 cells 142 us (204 with flat loads, which waited
+// one by one; 127 at the rate of a large copy), 2048 x 512 23.4 (27), 24 uneven runs
+// of 34M particles in all 73 (91).
+template <class R, int MAXB, int NC>
 __global__ void __launch_bounds__(256) k_ifft_eb(const Run<R> *__restrict__ runs,
-                                                 const Item *__restrict__ items, int parity,
-                                                 int ncomp) {
+                                                 const Item *__restrict__ items, int parity) {
   using C = typename Cplx<R>::T;
   extern __shared__ unsigned char smem_raw[];
   C *lds = (C *)smem_raw;
   const Item it = items[blockIdx.x];
   const Run<R> &r = runs[it.run];
-  const int row = it.a, cb = ncomp == 3 ? 3 * it.b : it.b;
-  const int n1 = r.n1, M = n1 >> 1, log2M = r.log2n1 - 1, cells = r.cells, nk = r.nk;
-  for (int k = threadIdx.x; k <= (M >> 1); k += blockDim.x) {
-    const int mk = M - k;
-    for (int cc = 0; cc < ncomp; ++cc) {
-      const double2 *X = r.Fk[parity] + (long long)(cb + cc) * r.rows * nk + (long long)row * nk;
-      const C Xk = from_d2<C>(X[k]), Xmk = from_d2<C>(X[mk]);
-      lds[cc * M + k] = c2r_pre(Xk, Xmk, r.tw[k]);
-      if (k != 0 && mk != k) lds[cc * M + mk] = c2r_pre(Xmk, Xk, r.tw[mk]);
+  const int row = it.a, cb = NC == 3 ? 3 * it.b : it.b;
+  const int n1 = r.n1, M = n1 >> 1, log2M = r.log2n1 - 1, nk = r.nk;
+  const long long plane = (long long)r.rows * nk;
+  const double2 *X = r.Fk[parity] + cb * plane + (long long)row * nk;
+#pragma unroll 2
+  for (int k = threadIdx.x; k < (M >> 1); k += 256) {
+    const C Wk = ldc(r.tw, k), Wmk = ldc(r.tw, M - k);
+    C Xk[NC], Xmk[NC];
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) Xk[cc] = from_d2<C>(ldc(X, cc * plane + k));
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) Xmk[cc] = from_d2<C>(ldc(X, cc * plane + M - k));
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) {
+      lds[cc * M + k] = c2r_pre(Xk[cc], Xmk[cc], Wk);
+      if (k != 0) lds[cc * M + M - k] = c2r_pre(Xmk[cc], Xk[cc], Wmk);
     }
   }
+  if (threadIdx.x == 255) {
+    const int half = M >> 1;
+    const C Wh = ldc(r.tw, half);
+    C Xh[NC];
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) Xh[cc] = from_d2<C>(ldc(X, cc * plane + half));
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) lds[cc * M + half] = c2r_pre(Xh[cc], Xh[cc], Wh);
+  }
   __syncthreads();
-  lds_fft_rows<C, MAXB>(lds, M, log2M, ncomp, r.tw, 2, true);
+  lds_fft_rows<C, MAXB>(lds, M, log2M, NC, r.tw, 2, true);
   const R s = r.inv_m;
-  for (int cc = 0; cc < ncomp; ++cc) {
-    R *dst = r.F + (long long)(cb + cc) * cells + (long long)row * n1;
-    for (int n = threadIdx.x; n < M; n += blockDim.x) {
-      const C z = lds[cc * M + n];
-      dst[2 * n] = z.x * s;
-      dst[2 * n + 1] = z.y * s;
-    }
+  for (int q = 2 * (int)threadIdx.x; q < NC * M; q += 512) {
+    const int cc = NC == 3 ? q >> log2M : 0, n = q - (cc << log2M);
+    const C a = lds[q], b = lds[q + 1];
+    using V4 = typename Quad<R>::V;
+    *(gptr<V4>)(G(r.F) + ((long long)(cb + cc) * r.cells + (long long)row * n1 + 2 * n)) =
+        V4{a.x * s, a.y * s, b.x * s, b.y * s};
   }
 }
 
@@ -542,10 +576,8 @@ void Launch<R>::fft_j(const Run<R> *runs, const Item *items, int nitems, int par
                       int ncomp, hipStream_t s) {
   if (nitems <= 0) return;
   const size_t lds = (size_t)ncomp * maxM * sizeof(typename Cplx<R>::T);
-  if (small_rows(maxM, ncomp))
-    hipLaunchKernelGGL((k_fft_j<R, 3>), dim3(nitems), dim3(256), lds, s, runs, items, parity, ncomp);
-  else
-    hipLaunchKernelGGL((k_fft_j<R, 6>), dim3(nitems), dim3(256), lds, s, runs, items, parity, ncomp);
+  auto k = ncomp == 1 ? k_fft_j<R, 3, 1> : maxM <= 1024 ? k_fft_j<R, 3, 3> : k_fft_j<R, 6, 3>;
+  hipLaunchKernelGGL(k, dim3(nitems), dim3(256), lds, s, runs, items, parity);
 }
 
 // 3D Gauss residual on the row (i2, i3): R = D1- E1 + D2- E2 + D3- E3 - f rho
@@ -657,10 +689,8 @@ void Launch<R>::ifft_eb(const Run<R> *runs, const Item *items, int nitems, int p
                         int ncomp, hipStream_t s) {
   if (nitems <= 0) return;
   const size_t lds = (size_t)ncomp * maxM * sizeof(typename Cplx<R>::T);
-  if (small_rows(maxM, ncomp))
-    hipLaunchKernelGGL((k_ifft_eb<R, 3>), dim3(nitems), dim3(256), lds, s, runs, items, parity, ncomp);
-  else
-    hipLaunchKernelGGL((k_ifft_eb<R, 6>), dim3(nitems), dim3(256), lds, s, runs, items, parity, ncomp);
+  auto k = ncomp == 1 ? k_ifft_eb<R, 3, 1> : maxM <= 1024 ? k_ifft_eb<R, 3, 3> : k_ifft_eb<R, 6, 3>;
+  hipLaunchKernelGGL(k, dim3(nitems), dim3(256), lds, s, runs, items, parity);
 }
 
 template <class R>

@@ -3,8 +3,8 @@
 // differences along r = x2).
 //
 // Each mode is a complex field.  The k-space master (FP64) is advanced in
-// (kappa1, r) space by two passes over (mode, r row, kappa1), every mode of
-// every run in one launch per pass; complex transforms along z per (mode,
+// (kappa1, r) space by a pass over (mode, r row, kappa1), every mode of every
+// run in one launch, and a half step of B as the inverse transform loads it; complex transforms along z per (mode,
 // component, row) move between the master and the real-space copy.  The per
 // mode curls with d/dth -> i m:
 //   (curl E)_z = (1/r) d_r(r Eth) - (i m/r) Er,  (curl E)_r = (i m/r) Ez - d_z Eth,
@@ -26,13 +26,17 @@ __global__ void __launch_bounds__(256) k_q_fields_to_k(const RunQ<R> *__restrict
   const Item it = items[blockIdx.x];
   const RunQ<R> &r = runs[it.run];
   const long long base = (long long)it.a * r.plane + (long long)it.b * r.n1;
-  for (int n = threadIdx.x; n < r.n1; n += blockDim.x) lds[n] = r.F[base + n];
+  for (int n = threadIdx.x; n < r.n1; n += blockDim.x) lds[n] = ldc(r.F, base + n);
   __syncthreads();
   lds_fft16<C, 6>(lds, r.n1, r.log2n1, 1, r.tw, 1, false);
   double2 *out = r.Fk[parity] + base;
-  for (int n = threadIdx.x; n < r.n1; n += blockDim.x) out[n] = to_d2(lds[n]);
+  for (int n = threadIdx.x; n < r.n1; n += blockDim.x) stc(out, n, to_d2(lds[n]));
 }
 
+// Inverse transforms, item = (run, 6 m + component, row).  B holds B^{n+1/2} on
+// entry and is advanced to B^{n+1} on the way:
+// B^{n+1} = B^{n+1/2} - (dt/2) curl E^{n+1}, which spares a pass that reads E and B
+// once more (2048 x 256, three modes: update and transform 180 us, now 172).
 template <class R>
 __global__ void __launch_bounds__(256) k_q_ifft(const RunQ<R> *__restrict__ runs,
                                                 const Item *__restrict__ items, int parity) {
@@ -41,13 +45,40 @@ __global__ void __launch_bounds__(256) k_q_ifft(const RunQ<R> *__restrict__ runs
   C *lds = (C *)smem_raw;
   const Item it = items[blockIdx.x];
   const RunQ<R> &r = runs[it.run];
-  const long long base = (long long)it.a * r.plane + (long long)it.b * r.n1;
-  const double2 *X = r.Fk[parity] + base;
-  for (int n = threadIdx.x; n < r.n1; n += blockDim.x) lds[n] = from_d2<C>(X[n]);
+  const int n1 = r.n1, j = it.b, m = it.a / 6, c = it.a - 6 * m;
+  const long long base = (long long)it.a * r.plane + (long long)j * n1;
+  double2 *const X = r.Fk[parity] + base;
+  const double2 *E = r.Fk[parity] + (long long)m * 6 * r.plane;
+  if (c >= 3 && j < r.n2 && (c != 4 || j > 0 || m == 1)) {
+    const double dr = r.dr, h = r.hdt, rh = (j + 0.5) * dr;
+    const double2 im = cmk(0.0, (double)m);
+    const double a0 = 1.0 / (rh * dr), a1 = 1.0 / rh, a2 = 1.0 / dr, a3 = j > 0 ? 1.0 / (j * dr) : 0.0;
+#pragma unroll 4
+    for (int k = threadIdx.x; k < n1; k += 256) {
+      auto at = [&](int comp, int row) { return ldc(E, comp * r.plane + (long long)row * n1 + k); };
+      const double2 dp = ldc((const double2 *)r.sym, 2 * k);
+      double2 curl;
+      if (c == 3)
+        curl = csub(cscale(csub(cscale(at(2, j + 1), (j + 1) * dr), cscale(at(2, j), j * dr)), a0),
+                    cscale(cmul(im, at(1, j)), a1));
+      else if (c == 5)
+        curl = csub(cmul(dp, at(1, j)), cscale(csub(at(0, j + 1), at(0, j)), a2));
+      else if (j > 0)
+        curl = csub(cscale(cmul(im, at(0, j)), a3), cmul(dp, at(2, j)));
+      else
+        curl = csub(cscale(cmk(-at(0, 1).y, at(0, 1).x), a2), cmul(dp, at(2, 0)));
+      const double2 b = csub(ldc(X, k), cscale(curl, h));
+      stc(X, k, b);
+      lds[k] = from_d2<C>(b);
+    }
+  } else {
+#pragma unroll 4
+    for (int n = threadIdx.x; n < n1; n += 256) lds[n] = from_d2<C>(ldc(X, n));
+  }
   __syncthreads();
-  lds_fft16<C, 6>(lds, r.n1, r.log2n1, 1, r.tw, 1, true);
-  const R s = R(1) / (R)r.n1;
-  for (int n = threadIdx.x; n < r.n1; n += blockDim.x) r.F[base + n] = cscale(lds[n], s);
+  lds_fft16<C, 6>(lds, n1, r.log2n1, 1, r.tw, 1, true);
+  const R s = R(1) / (R)n1;
+  for (int n = threadIdx.x; n < n1; n += 256) stc(r.F, base + n, cscale(lds[n], s));
 }
 
 // Current of the step per (run, 3 m + c, row): the deposit accumulators of a
@@ -73,24 +104,25 @@ __global__ void __launch_bounds__(256) k_q_fft_j(const RunQ<R> *__restrict__ run
   // so that the FP32 transform (FP32 form) rounds relative to its fluctuation
   const double conv = r.jconv[mc * r.nr + row];
   const double bg = (m == 0 && c == 0) ? r.jbgk[row] / (double)r.n1 : 0.0;
-  for (int n = threadIdx.x; n < r.n1; n += blockDim.x) {
-    lds[n] = cmk((R)((double)Jin[2 * n] * conv + bg), (R)((double)Jin[2 * n + 1] * conv));
-    Jclr[2 * n] = 0;
-    Jclr[2 * n + 1] = 0;
+#pragma unroll 4
+  for (int n = threadIdx.x; n < r.n1; n += 256) {
+    const auto v = ldpair(Jin, 2 * n);
+    lds[n] = cmk((R)((double)v.x * conv + bg), (R)((double)v.y * conv));
   }
   __syncthreads();
   lds_fft16<C, 6>(lds, r.n1, r.log2n1, 1, r.tw, 1, false);
   C *out = r.Jk + base;
   const int sel = c == 0 ? 0 : 1;
   for (int k = threadIdx.x; k < r.n1; k += blockDim.x) {
-    C v = cscale(lds[k], r.kfac[2 * k + sel]);
-    out[k] = v;
+    stc(out, k, cscale(lds[k], G(r.kfac)[2 * k + sel]));
   }
+  // the next step's accumulators, last: loads and stores wait in one queue
+  for (int n = threadIdx.x; n < r.n1; n += 256) zeropair(Jclr, 2 * n);
 }
 
 // Item = (run, first element, 0): elements e = (m nr + j) n1 + kappa.
 template <class R>
-__global__ void __launch_bounds__(256) k_q_update_a(const RunQ<R> *__restrict__ runs,
+__global__ void __launch_bounds__(256) k_q_update(const RunQ<R> *__restrict__ runs,
                                                     const Item *__restrict__ items, int parity) {
   using C = double2;
   const Item it = items[blockIdx.x];
@@ -98,14 +130,13 @@ __global__ void __launch_bounds__(256) k_q_update_a(const RunQ<R> *__restrict__ 
   const int n1 = r.n1, n2 = r.n2, nr = r.nr;
   const long long e = (long long)it.a + threadIdx.x;
   if (e >= (long long)r.M * nr * n1) return;
-  const int k = (int)(e % n1);
-  const long long mj = e / n1;
-  const int j = (int)(mj % nr), m = (int)(mj / nr);
+  const int k = (int)e & (n1 - 1), mj = (int)(e >> r.log2n1);
+  const int m = mj / nr, j = mj - m * nr;
   const C *Fi = r.Fk[parity] + (long long)m * 6 * r.plane;
   C *Fo = r.Fk[parity ^ 1] + (long long)m * 6 * r.plane;
-  auto at = [&](int comp, int row) { return Fi[comp * r.plane + (long long)row * n1 + k]; };
-  const C dp = cmk(r.sym[4 * k + 0], r.sym[4 * k + 1]);
-  const C dm = cmk(r.sym[4 * k + 2], r.sym[4 * k + 3]);
+  auto at = [&](int comp, int row) { return ldc(Fi, comp * r.plane + (long long)row * n1 + k); };
+  const C dp = ldc((const C *)r.sym, 2 * k);
+  const C dm = ldc((const C *)r.sym, 2 * k + 1);
   const double dr = r.dr, h = r.hdt, dt = r.dt, mm = (double)m;
   const C im = cmk(0.0, mm);
   // half-step B on a half row q (Bz, Bth) from E on rows q, q+1
@@ -140,7 +171,7 @@ __global__ void __launch_bounds__(256) k_q_update_a(const RunQ<R> *__restrict__ 
     const double rh = (j + 0.5) * dr;
     // current of the step (zero for a field-only run)
     const typename RunQ<R>::C *Jm = r.Jk + (long long)m * 3 * r.plane;
-    const C Jz = to_d2(Jm[o]), Jr = to_d2(Jm[r.plane + o]), Jt = to_d2(Jm[2 * r.plane + o]);
+    const C Jz = to_d2(ldc(Jm, o)), Jr = to_d2(ldc(Jm, r.plane + o)), Jt = to_d2(ldc(Jm, 2 * r.plane + o));
     Er = cadd(Er, cscale(csub(csub(cscale(cmul(im, Bz_j), 1.0 / rh), cmul(dm, Bt_j)), Jr), dt));
     if (j == 0) {
       if (m == 0) Ez = cadd(Ez, cscale(csub(cscale(Bt_j, 4.0 / dr), Jz), dt));
@@ -157,50 +188,12 @@ __global__ void __launch_bounds__(256) k_q_update_a(const RunQ<R> *__restrict__ 
       Et = cadd(Et, cscale(csub(ct, Jt), dt));
     }
   }
-  Fo[o] = Ez;
-  Fo[r.plane + o] = Er;
-  Fo[2 * r.plane + o] = Et;
-  Fo[3 * r.plane + o] = Bz_j;
-  Fo[4 * r.plane + o] = Br_j;
-  Fo[5 * r.plane + o] = Bt_j;
-}
-
-// B^{n+1} = B^{n+1/2} - (dt/2) curl E^{n+1}, in the output master.
-template <class R>
-__global__ void __launch_bounds__(256) k_q_update_b(const RunQ<R> *__restrict__ runs,
-                                                    const Item *__restrict__ items, int parity) {
-  using C = double2;
-  const Item it = items[blockIdx.x];
-  const RunQ<R> &r = runs[it.run];
-  const int n1 = r.n1, n2 = r.n2, nr = r.nr;
-  const long long e = (long long)it.a + threadIdx.x;
-  if (e >= (long long)r.M * nr * n1) return;
-  const int k = (int)(e % n1);
-  const long long mj = e / n1;
-  const int j = (int)(mj % nr), m = (int)(mj / nr);
-  C *F = r.Fk[parity ^ 1] + (long long)m * 6 * r.plane;
-  auto at = [&](int comp, int row) { return F[comp * r.plane + (long long)row * n1 + k]; };
-  const C dp = cmk(r.sym[4 * k + 0], r.sym[4 * k + 1]);
-  const double dr = r.dr, h = r.hdt, mm = (double)m;
-  const C im = cmk(0.0, mm);
-  const long long o = (long long)j * n1 + k;
-  if (j < n2) {
-    const double rh = (j + 0.5) * dr;
-    const C Et0 = at(2, j), Et1 = at(2, j + 1), Er0 = at(1, j), Ez0 = at(0, j), Ez1 = at(0, j + 1);
-    const C cz = csub(cscale(csub(cscale(Et1, (j + 1) * dr), cscale(Et0, j * dr)), 1.0 / (rh * dr)),
-                      cscale(cmul(im, Er0), 1.0 / rh));
-    const C ct = csub(cmul(dp, Er0), cscale(csub(Ez1, Ez0), 1.0 / dr));
-    F[3 * r.plane + o] = csub(at(3, j), cscale(cz, h));
-    F[5 * r.plane + o] = csub(at(5, j), cscale(ct, h));
-  }
-  if (j < n2 && (j > 0 || m == 1)) {
-    C cr;
-    if (j == 0)
-      cr = csub(cscale(cmk(-at(0, 1).y, at(0, 1).x), 1.0 / dr), cmul(dp, at(2, 0)));
-    else
-      cr = csub(cscale(cmul(im, at(0, j)), 1.0 / (j * dr)), cmul(dp, at(2, j)));
-    F[4 * r.plane + o] = csub(at(4, j), cscale(cr, h));
-  }
+  stc(Fo, o, Ez);
+  stc(Fo, r.plane + o, Er);
+  stc(Fo, 2 * r.plane + o, Et);
+  stc(Fo, 3 * r.plane + o, Bz_j);
+  stc(Fo, 4 * r.plane + o, Br_j);
+  stc(Fo, 5 * r.plane + o, Bt_j);
 }
 
 // Forward FP64 transform along z of one row (m, j) of a density, in place.
@@ -299,8 +292,7 @@ template <class R>
 void LaunchQ<R>::kupdate(const RunQ<R> *runs, const Item *items, int nitems, int parity,
                          hipStream_t s) {
   if (nitems <= 0) return;
-  hipLaunchKernelGGL(k_q_update_a<R>, dim3(nitems), dim3(256), 0, s, runs, items, parity);
-  hipLaunchKernelGGL(k_q_update_b<R>, dim3(nitems), dim3(256), 0, s, runs, items, parity);
+  hipLaunchKernelGGL(k_q_update<R>, dim3(nitems), dim3(256), 0, s, runs, items, parity);
 }
 template <class R>
 void LaunchQ<R>::gauss(const RunQ<R> *runs, const Item *items, int nitems, int parity,
