@@ -90,7 +90,7 @@ struct RunQ {
 // twice into four SIMDs that hold three each.)
 template <class R> struct QPush;
 template <> struct QPush<float> {
-  static constexpr int LDS = 53248, WAVES_PER_SIMD = 3;
+  static constexpr int LDS = 53728, WAVES_PER_SIMD = 3;
 };
 template <> struct QPush<double> {
   static constexpr int LDS = 64512, WAVES_PER_SIMD = 2;
@@ -98,11 +98,19 @@ template <> struct QPush<double> {
 // Columns of the push's current box for tiles tz wide (literal in the kernels): the
 // tile, the stencils' five and three of drift.
 __host__ __device__ constexpr int q_push_cols(int tz) { return tz > 8 ? 24 : tz > 4 ? 16 : 12; }
-// LDS bytes of its boxes for current boxes of w columns and h rows of M modes:
-// 64-bit accumulators, and in the FP32 form the fields next to them (the real
-// part of mode 0, both parts of the others).
+// Rows of its boxes for w columns of M modes: 64-bit accumulators, and in the FP32
+// form the fields next to them (the real part of mode 0, both parts of the
+// others), one row less and two columns less.  Neighbouring rows lie half of
+// the banks apart (see q_place_of).
+__host__ __device__ constexpr int q_row(int w, int M) {
+  return 3 * (2 * M - 1) * w + ((16 - 3 * (2 * M - 1) * w) & 31);
+}
+__host__ __device__ constexpr int q_field_row(int w, int M) {
+  return (12 * M - 6) * (w - 2) + ((32 - (12 * M - 6) * (w - 2)) & 63);
+}
+// LDS bytes of the boxes for h rows.
 __host__ __device__ constexpr long long q_push_bytes(int w, int h, int M, size_t real) {
-  return 3ll * (2 * M - 1) * w * h * 8 + (real == 4 ? (12ll * M - 6) * (w - 2) * (h - 1) * 4 : 0);
+  return 8ll * q_row(w, M) * h + (real == 4 ? 4ll * q_field_row(w, M) * (h - 1) : 0);
 }
 
 template <class R>

@@ -185,7 +185,7 @@ struct SinkLdsQ {
   int M;
   using Row = lptr<A>;
   __device__ __forceinline__ int per() const { return MC > 0 ? 2 * MC - 1 : 2 * M - 1; }
-  __device__ __forceinline__ Row row(int j) const { return box + __mul24(j, 3 * per() * CW); }
+  __device__ __forceinline__ Row row(int j) const { return box + __mul24(j, q_row(CW, MC > 0 ? MC : M)); }
   __device__ __forceinline__ int slot(int c, int m) const { return (c * per() + (m == 0 ? 0 : 2 * m - 1)) * CW; }
   __device__ __forceinline__ void put(Row r, int slot, int part, int a, double x, double y) const {
     __hip_atomic_fetch_add(r + slot + part * CW + a, acc_mul<A>(x, y), __ATOMIC_RELAXED,
@@ -440,13 +440,14 @@ __device__ __forceinline__ PStateQ<R> load_q(const PartsQ<R> &P, int p) {
 //
 // What bounds it: the instructions and the LDS atomics of about 145 contributions
 // a particle, with three modes.  On 2048 x 256 cells (8 particles each over 250
-// rows, three modes, FP32) a push takes 424 us, 1098 with a box per wave of 64
+// rows, three modes, FP32) a push takes 397 us, 1098 with a box per wave of 64
 // particles, which carried a halo of 8 x 8 nodes for 8 cells and tested every
 // contribution; FP64 on 256 x 61 with two modes 44 us, 56 before.  Of that:
 // tiles in place of waves (a third of the nodes flushed and staged per particle)
 // and contributions without tests, 744; particles in the order of their cells, so
 // that the lanes of an atomic meet different nodes (LDS cycles 374 to 290 us) and
-// 16 x 4 tiles, 672; workgroups of 256 threads, three per compute unit, 424.
+// 16 x 4 tiles, 672; workgroups of 256 threads, three per compute unit, 424; rows and
+// order for the banks, 397.
 template <class R, int MC, int CW>
 __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
     k_q_push_deposit(const RunQ<R> *__restrict__ runs, const Item *__restrict__ items, int parity,
@@ -477,10 +478,10 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
     nbox[1] = nbox[3] = -(1 << 30);
   }
   const int per = 2 * M - 1, NS = 3 * per;
-  const int RS = NS * CW;                       // one row of the current box
+  const int RS = q_row(CW, M);                  // one row of the current box
   // one row of the field box: six components of mode 0 (the real part, all that
   // the gather takes of it), then of each further mode, complex; its used size
-  const int FS = (12 * M - 6) * FWD, Wf = W - 2, Hf = H - 1;
+  const int FS = q_field_row(CW, M), Wf = W - 2, Hf = H - 1;
   const bool local = W <= CW && q_push_bytes(CW, H, M, sizeof(R)) <= (long long)QPush<R>::LDS;
   const lptr<A> box = (lptr<A>)smem_raw;
   const lptr<R> fbox = (lptr<R>)(smem_raw + (size_t)RS * H * sizeof(A));
@@ -729,9 +730,9 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
     if (cc < W) {
       const int col = wrap_pow2(z0 + zlo + cc, n1);
       for (int e = (int)threadIdx.x >> 5; e < H * NS; e += NT / 32) {
-        const A v = box[e * CW + cc];
-        if (v == A(0)) continue;
         const int j = e / NS, slot = e - j * NS;
+        const A v = box[j * RS + slot * CW + cc];
+        if (v == A(0)) continue;
         const int c = slot / per, s2 = slot - c * per;
         const int m = (s2 + 1) >> 1, part = s2 == 0 ? 0 : (s2 - 1) & 1;
         glob_add(G(J) + ((long long)(m * 3 + c) * plane + (long long)(rlo + j) * n1 + col) * 2 + part, v);
@@ -826,26 +827,30 @@ __global__ void __launch_bounds__(256) k_q_jbg(const RunQ<R> *__restrict__ run, 
 // ---------------------------------------------------------------- sort
 // A periodic counting sort by the push's tiles, of sbz z columns x sbr radial
 // rows, that also orders the particles within a tile: by their rank among the
-// particles of their cell, then by cell in q_place_of's order.  Consecutive
-// particles, which the lanes of a wave take, then lie in cells two apart along z
-// or r, so that they neither queue on the same LDS accumulators nor, where their
-// stencils start half a cell apart, on their neighbours'.
-__device__ __forceinline__ int half_up(int n) { return (n + 1) >> 1; }
-// Place of the tile's cell (column z, row j): even rows before odd, then even
-// columns before odd, then by row and column.
+// particles of their place, then by place, of which there is one per column and
+// nearest row of nodes (the tile's last one together with its first).
+// Consecutive particles, which the lanes of a wave take, then touch different
+// accumulators: columns two apart, so that it does not matter where in its cell
+// a particle is along z, and rows whose banks do not meet.  (By cell, with rows where
+// the stride fell, half of the LDS cycles were conflicts: 2048 x 256, three modes,
+// push 425 us, 397 now.)
+
+// Even columns before odd, in each by row and column.
 __device__ __forceinline__ int q_place_of(int z, int j, int tz, int tr) {
-  const int ez = half_up(tz), er = half_up(tr);
-  const int pr = j & 1, pz = z & 1, nr = pr ? tr - er : er;
-  return (pr ? er * tz : 0) + (pz ? nr * ez : 0) + (j >> 1) * (pz ? tz - ez : ez) + (z >> 1);
+  const int even = (tz + 1) >> 1, odd = z & 1;
+  return odd * even * tr + j * (odd ? tz - even : even) + (z >> 1);
 }
-// Tile and place of a particle's cell.
+// Tile and place of a particle.
 template <class R>
 __device__ __forceinline__ int q_sort_cell(const RunQ<R> &r, const PartsQ<R> &P, int p) {
   const float x = (float)*elem(P.ix, p) + (float)*elem(P.fx, p);
   const float y = (float)*elem(P.iy, p) + (float)*elem(P.fy, p);
-  const int j = min(max((int)sqrtf(x * x + y * y), 0), r.n2 - 1), z = *elem(P.cell, p);
+  const float rr = sqrtf(x * x + y * y);
+  const int j = min(max((int)rr, 0), r.n2 - 1), z = *elem(P.cell, p);
   const int tz = z / r.sbz, tr = j / r.sbr;
-  return (tz * r.nbr + tr) * (r.sbz * r.sbr) + q_place_of(z - tz * r.sbz, j - tr * r.sbr, r.sbz, r.sbr);
+  const int near = min(max((int)(rr + 0.5f) - tr * r.sbr, 0), r.sbr);
+  return (tz * r.nbr + tr) * (r.sbz * r.sbr) +
+         q_place_of(z - tz * r.sbz, near == r.sbr ? 0 : near, r.sbz, r.sbr);
 }
 
 template <class R>
