@@ -4,6 +4,7 @@ Every step of the PIC path runs in the library's HIP kernels.  If the library
 is missing this module raises; there is no CPU fallback.
 """
 import ctypes
+import math
 import os
 
 import numpy as np
@@ -192,6 +193,7 @@ class Sim:
         h = _P()
         _check(lib().hp_create(arr, len(self.cfgs), ctypes.byref(h)))
         self.h = h
+        self._shapes = [self.shape(r) for r in range(len(self.cfgs))]
         if stream is not None:
             self.set_stream(stream)
 
@@ -246,9 +248,9 @@ class Sim:
         """Real-space field component comp into the device tensor out (shape
         of the run's grid, float32 in the FP32 form, float64 in the FP64 form);
         asynchronous on the handle's stream."""
-        _check(lib().hp_get_field_device(self.h, run, int(comp),
-                                         _dptr(out, self._real(run), self.shape(run)),
-                                         int(np.prod(self.shape(run)))))
+        sh = self._shapes[run]
+        _check(lib().hp_get_field_device(self.h, run, int(comp), _dptr(out, self._real(run), sh),
+                                         math.prod(sh)))
 
     def current_device(self, run, comp, out, corrected=False):
         """Current component comp of the last step into the float64 device
@@ -256,7 +258,7 @@ class Sim:
         asynchronous on the handle's stream."""
         _check(lib().hp_get_current_device(self.h, run, int(comp), int(bool(corrected)),
                                            _dptr(out, "float64", self.shape(run)),
-                                           int(np.prod(self.shape(run)))))
+                                           math.prod(self.shape(run))))
 
     def particles_device(self, run, cell=None, off=None, u=None, qw=None, pid=None):
         """Particle state into device tensors (any may be None): cell int32
