@@ -525,6 +525,142 @@ __device__ __forceinline__ void count_stat(unsigned *stats, int which) {
 // set per handle from the tile shape (push_lds_bytes), between the minimum
 // and maximum here.
 constexpr int PUSH_THREADS = 256;
+template <class T> using lptr = T __attribute__((address_space(3))) *;
+
+// 1/sqrt(x) and 1/x: hardware approximations (~1 ulp) in FP32, IEEE in FP64.
+__device__ __forceinline__ float rsqrt_(float x) { return __builtin_amdgcn_rsqf(x); }
+__device__ __forceinline__ double rsqrt_(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ float rcp_(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ double rcp_(double x) { return 1.0 / x; }
+
+// Relativistic Boris rotation: u^{n-1/2} -> u^{n+1/2} with E^n, B^n.
+template <class R>
+__device__ __forceinline__ void boris(R qmhdt, const R E[3], const R B[3], R u[3]) {
+  const R e0 = qmhdt * E[0], e1 = qmhdt * E[1], e2 = qmhdt * E[2];
+  const R m0 = u[0] + e0, m1 = u[1] + e1, m2 = u[2] + e2;
+  const R ig = rsqrt_(R(1) + m0 * m0 + m1 * m1 + m2 * m2);
+  const R t0 = qmhdt * B[0] * ig, t1 = qmhdt * B[1] * ig, t2 = qmhdt * B[2] * ig;
+  const R sf = R(2) * rcp_(R(1) + t0 * t0 + t1 * t1 + t2 * t2);
+  const R s0 = t0 * sf, s1 = t1 * sf, s2 = t2 * sf;
+  const R p0 = m0 + (m1 * t2 - m2 * t1);
+  const R p1 = m1 + (m2 * t0 - m0 * t2);
+  const R p2 = m2 + (m0 * t1 - m1 * t0);
+  u[0] = m0 + (p1 * s2 - p2 * s1) + e0;
+  u[1] = m1 + (p2 * s0 - p0 * s2) + e1;
+  u[2] = m2 + (p0 * s1 - p1 * s0) + e2;
+}
+
+// Velocity from momentum, every operation rounded once in this order (the
+// out-of-plane velocity enters the fixed-point deposit, which tests reproduce
+// bit for bit on the host): g = sqrt(((1 + u1 u1) + u2 u2) + u3 u3) and
+// v = u * (1/g), square root and reciprocal correctly rounded.
+template <class R>
+__device__ __forceinline__ void velocity(const R u[3], R v[3]) {
+#pragma clang fp contract(off)
+  R s = R(1) + u[0] * u[0];
+  s = s + u[1] * u[1];
+  s = s + u[2] * u[2];
+  const R ig = inv_gamma(s);
+  v[0] = u[0] * ig;
+  v[1] = u[1] * ig;
+  v[2] = u[2] * ig;
+}
+
+// State of one particle as loaded from the buffers.
+template <class R>
+struct PState {
+  int cell;
+  R f1, f2, u1, u2, u3, qw;
+};
+
+template <class R>
+__device__ __forceinline__ PState<R> load_state(const Parts<R> &P, int p) {
+  PState<R> s;
+  s.cell = *elem(P.cell, p);
+  s.f1 = *elem(P.f1, p);
+  s.f2 = *elem(P.f2, p);
+  s.u1 = *elem(P.u1, p);
+  s.u2 = *elem(P.u2, p);
+  s.u3 = *elem(P.u3, p);
+  s.qw = *elem(P.qw, p);
+  return s;
+}
+
+template <class R>
+__device__ __forceinline__ void store_state(const Parts<R> &P, int p, const PState<R> &s) {
+  *elem(P.cell, p) = s.cell;
+  *elem(P.f1, p) = s.f1;
+  *elem(P.f2, p) = s.f2;
+  *elem(P.u1, p) = s.u1;
+  *elem(P.u2, p) = s.u2;
+  *elem(P.u3, p) = s.u3;
+}
+// Has the loads of s returned here.  Loads and stores are counted in one queue:
+// a state still awaited when the next particle starts would wait out the stores
+// issued after its loads as well (277 -> 265 us on 8192 x 512 cells, two
+// particles a cell).
+template <class R>
+__device__ __forceinline__ void arrived(PState<R> &s) {
+  asm volatile("" : "+v"(s.cell), "+v"(s.f1), "+v"(s.f2), "+v"(s.u1), "+v"(s.u2), "+v"(s.u3), "+v"(s.qw));
+}
+
+__device__ __forceinline__ int wave_min(int v) {
+  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
+  return v;
+}
+__device__ __forceinline__ int wave_max(int v) {
+  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
+  return v;
+}
+
+// Cell i (0 <= i < n) relative to a tile origin, in the tile's frame: the
+// period [-o, n - o) with o = (n - T) / 2, i.e. centred on the tile, so that
+// particles may drift half the rest of the box from their tile before the
+// frame's edge splits them.
+__device__ __forceinline__ int frame_pow2(int d, int o, int n) { return ((d + o) & (n - 1)) - o; }
+__device__ __forceinline__ int frame_any(int d, int o, int n) {
+  d += (d < -o) ? n : 0;
+  d -= (d >= n - o) ? n : 0;
+  return d;
+}
+// i mod n for any i within a few periods
+__device__ __forceinline__ int wrap_any(int i, int n) {
+  while (i >= n) i -= n;
+  while (i < 0) i += n;
+  return i;
+}
+
+// Walks the nodes of a W x H box with the workgroup's threads: f(row, column).
+// Rows of up to 32 (64) nodes take half a wave (a wave) each, so that no
+// thread divides; wider rows are walked in pieces of 64.
+template <class F>
+__device__ __forceinline__ void for_box(int W, int H, F f) {
+  const int sh = W <= 32 ? 5 : 6, lanes = 1 << sh;
+  for (int b = (int)threadIdx.x >> sh; b < H; b += PUSH_THREADS >> sh)
+    for (int a = (int)threadIdx.x & (lanes - 1); a < W; a += lanes) f(b, a);
+}
+
+// Bounding box of the cells a thread's particles move to, then of the
+// workgroup's (nbox, initialised before a barrier).
+struct CellBox {
+  int lo1 = 1 << 30, hi1 = -(1 << 30), lo2 = 1 << 30, hi2 = -(1 << 30);
+  __device__ __forceinline__ void add(int d1, int d2) {
+    lo1 = min(lo1, d1); hi1 = max(hi1, d1);
+    lo2 = min(lo2, d2); hi2 = max(hi2, d2);
+  }
+  __device__ __forceinline__ void reduce(int *nbox) const {
+    const int a = wave_min(lo1), b = wave_max(hi1), c = wave_min(lo2), d = wave_max(hi2);
+    if ((threadIdx.x & 63) == 0) {
+      atomicMin(&nbox[0], a); atomicMax(&nbox[1], b);
+      atomicMin(&nbox[2], c); atomicMax(&nbox[3], d);
+    }
+  }
+};
+
+__device__ __forceinline__ float uniform(float x) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+
 // Columns of the 2D push's current box for tiles t wide: the tile, two cells of
 // drift on each side, the stencil's six and one more, which makes the row
 // stride odd for even widths (rows a multiple of 16 of the 8-byte bank slots
@@ -532,10 +668,10 @@ constexpr int PUSH_THREADS = 256;
 // 2048 x 512 cells).
 __host__ __device__ constexpr int push_cols(int t) { return t + 11; }
 // LDS bytes of its boxes for a current box of w columns and h rows: 64-bit
-// accumulators of three components, then the six fields one node less on
-// every side.
-__host__ __device__ constexpr long long push_box_bytes(int w, int h, size_t real) {
-  return ((3ll * w * h * 8 + 15) & ~15ll) + (long long)(w - 2) * (h - 2) * 6 * (long long)real;
+// accumulators of three components, then the six fields, two nodes less along
+// each axis (one with the cubic shape).
+__host__ __device__ constexpr long long push_box_bytes(int w, int h, size_t real, int less = 2) {
+  return ((3ll * w * h * 8 + 15) & ~15ll) + (long long)(w - less) * (h - less) * 6 * (long long)real;
 }
 constexpr int PUSH_LDS_MIN = 16384;
 constexpr int PUSH_LDS_MAX = 64512;  // with the static LDS, under 64 KiB
@@ -602,7 +738,7 @@ void launch_rho_fixed(const Run<float> *run_dev, int pp, int np, long long *rho,
 // deposit's units (FP32 form: integers, FP64 form: physical)
 template <class R>
 void launch_push_cubic(const Run<R> *runs, const Item *items, int nitems, int parity, int pp,
-                       int lds_bytes, bool unit, bool ec, unsigned *err, hipStream_t s);
+                       int lds_bytes, int tile1, bool unit, bool ec, unsigned *err, hipStream_t s);
 template <class R>
 void launch_rho_cubic(const Run<R> *run_dev, int pp, int np, typename AccOf<R>::T *rho,
                       hipStream_t s);

@@ -5,37 +5,20 @@
 // quadratic shape along a component's staggered directions), relativistic
 // Boris push, and the Esirkepov deposit over a 5 x 5 window.
 //
-// One workgroup per particle tile of the periodic tile sort.  The workgroup
-// bounds its tile's particle cells, accumulates the current of all of them
-// into one LDS box (a move is under a cell: columns and rows -2 .. +3 around
-// the cells) and adds the box to the global accumulators at the end; a box
-// too large for LDS falls back to global atomics.  FP32 form: integer cubic
+// One workgroup per particle tile of the periodic tile sort, with the tile's
+// fields and currents in LDS boxes that follow its particles, as in the
+// quadratic push; a box too large for LDS falls back to global atomics.  FP32 form: integer cubic
 // weights with exact sum 2^P and the integer Esirkepov products of the
 // quadratic kernel, so 2 (rho_new - rho_old) = div J holds exactly in the
 // integers and the sums do not depend on the order; FP64 form: physical
 // current in FP64.
+#include <type_traits>
+
 #include "hpic_internal.h"
 
 namespace hp {
 
 namespace {
-
-constexpr int CLDS_BYTES = 64512;
-
-template <class T> using lptrc = T __attribute__((address_space(3))) *;
-
-__device__ __forceinline__ int wminc(int v) {
-  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ int wmaxc(int v) {
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ float rsqrtc(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double rsqrtc(double x) { return 1.0 / sqrt(x); }
-__device__ __forceinline__ float rcpc(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double rcpc(double x) { return 1.0 / x; }
 
 // Cubic B-spline weights of the nodes m-1, m, m+1, m+2 for a position m + d,
 // d in [0, 1): S3 at the distances 1 + d, d, 1 - d, 2 - d.
@@ -81,71 +64,65 @@ __device__ __forceinline__ int stencil4(int i, R f, bool half, bool lower, R w[4
   return m - 1;
 }
 
+// Fields as seen by the gather: a node's pairs (E1, B2) on (i1+1/2, i2) and (E2, B1) on
+// (i1, i2+1/2), E3 on (i1, i2), B3 on (i1+1/2, i2+1/2), from the grid or from the tile's
+// field box in LDS (row stride FS, or W where FS is 0).
 template <class R>
-__device__ __forceinline__ void borisc(R qmhdt, const R E[3], const R B[3], R u[3]) {
-  const R e0 = qmhdt * E[0], e1 = qmhdt * E[1], e2 = qmhdt * E[2];
-  const R m0 = u[0] + e0, m1 = u[1] + e1, m2 = u[2] + e2;
-  const R ig = rsqrtc(R(1) + m0 * m0 + m1 * m1 + m2 * m2);
-  const R t0 = qmhdt * B[0] * ig, t1 = qmhdt * B[1] * ig, t2 = qmhdt * B[2] * ig;
-  const R sf = R(2) * rcpc(R(1) + t0 * t0 + t1 * t1 + t2 * t2);
-  const R s0 = t0 * sf, s1 = t1 * sf, s2 = t2 * sf;
-  const R p0 = m0 + (m1 * t2 - m2 * t1);
-  const R p1 = m1 + (m2 * t0 - m0 * t2);
-  const R p2 = m2 + (m0 * t1 - m1 * t0);
-  u[0] = m0 + (p1 * s2 - p2 * s1) + e0;
-  u[1] = m1 + (p2 * s0 - p0 * s2) + e1;
-  u[2] = m2 + (p0 * s1 - p1 * s0) + e2;
+struct GlobalC {
+  gptr<const R> F;
+  int n1, n2, cells;
+  __device__ int col(int i) const { return wrap_pow2(i, n1); }
+  __device__ int row(int j) const { return wrap_small(j, n2) * n1; }
+  __device__ R get(int c, int r, int a) const { return F[c * (long long)cells + r + col(a)]; }
+  __device__ void p0(int r, int a, R &x, R &y) const { x = get(0, r, a); y = get(4, r, a); }
+  __device__ void p1(int r, int a, R &x, R &y) const { x = get(1, r, a); y = get(3, r, a); }
+  __device__ R e3(int r, int a) const { return get(2, r, a); }
+  __device__ R b3(int r, int a) const { return get(5, r, a); }
+};
+template <class R, int FS>
+struct LdsC {
+  typedef R T2 __attribute__((ext_vector_type(2)));
+  lptr<const T2> P0, P1;
+  lptr<const R> E3, B3;
+  int W;
+  __device__ int row(int j) const { return __mul24(j, FS > 0 ? FS : W); }
+  __device__ void p0(int r, int a, R &x, R &y) const { const T2 v = P0[r + a]; x = v.x; y = v.y; }
+  __device__ void p1(int r, int a, R &x, R &y) const { const T2 v = P1[r + a]; x = v.x; y = v.y; }
+  __device__ R e3(int r, int a) const { return E3[r + a]; }
+  __device__ R b3(int r, int a) const { return B3[r + a]; }
+};
+template <class R> __device__ __forceinline__ R dot4c(const R w[4], const R v[4]) {
+  return fmaq(w[3], v[3], fmaq(w[2], v[2], fmaq(w[1], v[1], w[0] * v[0])));
 }
-
-template <class R>
-__device__ __forceinline__ int advc(R f, R d, R &g) {
-  g = f + d;
-  int s = 0;
-  if (g >= R(1)) {
-    g = g - R(1);
-    s = 1;
-  } else if (g < R(0)) {
-    g = g + R(1);
-    s = -1;
-    if (g >= R(1)) {
-      g = R(0);
-      s = 0;
+// Gather at cell (i1, i2) of the source's frame; EC lowers the order along the
+// staggered directions.
+template <class R, bool EC, class Src>
+__device__ __forceinline__ void gather_c(const Src &S, int i1, int i2, R f1, R f2, R E[3], R B[3]) {
+  R wi1[4], wh1[4], wi2[4], wh2[4];
+  const int ci = stencil4<R>(i1, f1, false, false, wi1);
+  const int ch = stencil4<R>(i1, f1, true, EC, wh1);
+  const int ri = stencil4<R>(i2, f2, false, false, wi2);
+  const int rh = stencil4<R>(i2, f2, true, EC, wh2);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) E[c] = B[c] = R(0);
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int rib = S.row(ri + b), rhb = S.row(rh + b);
+    R e1[4], b2[4], e2[4], b1[4], e3[4], b3[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      S.p0(rib, ch + a, e1[a], b2[a]);
+      S.p1(rhb, ci + a, e2[a], b1[a]);
+      e3[a] = S.e3(rib, ci + a);
+      b3[a] = S.b3(rhb, ch + a);
     }
+    E[0] = fmaq(wi2[b], dot4c(wh1, e1), E[0]);
+    E[1] = fmaq(wh2[b], dot4c(wi1, e2), E[1]);
+    E[2] = fmaq(wi2[b], dot4c(wi1, e3), E[2]);
+    B[0] = fmaq(wh2[b], dot4c(wi1, b1), B[0]);
+    B[1] = fmaq(wi2[b], dot4c(wh1, b2), B[1]);
+    B[2] = fmaq(wh2[b], dot4c(wh1, b3), B[2]);
   }
-  return s;
-}
-
-// One staggered component: 4 x 4 nodes, stencil origins (c0, r0), weights.
-template <class R>
-__device__ __forceinline__ R gather_c(const R *__restrict__ F, int n1, int n2, int c0, const R w1[4],
-                                      int r0, const R w2[4]) {
-  R acc = 0;
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const R *row = F + (long long)wrap_small(r0 + b, n2) * n1;
-    R s = 0;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) s += w1[a] * row[wrap_pow2(c0 + a, n1)];
-    acc += w2[b] * s;
-  }
-  return acc;
-}
-
-// The same from the tile's field box in LDS (row stride FW, box-local first
-// nodes c0, r0).
-template <class R>
-__device__ __forceinline__ R gather_cl(const lptrc<R> Fl, int FW, int c0, const R w1[4], int r0,
-                                       const R w2[4]) {
-  R acc = 0;
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const lptrc<R> row = Fl + (r0 + b) * FW + c0;
-    R s = 0;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) s += w1[a] * row[a];
-    acc += w2[b] * s;
-  }
-  return acc;
 }
 
 // Integer cubic weights of the nodes m-1 .. m+2 for a position m + d: the
@@ -163,67 +140,88 @@ __device__ __forceinline__ void cubic_fixed(float d, int P, int s[4]) {
   s[2] = (1 << P) - s[0] - s[1] - s[3];
 }
 
-// deposit targets (values already in the accumulator's type)
-template <class A>
+// Deposit targets: window() gives row b of component c in the window from (i1, i2), add()
+// adds to its column a.  LDS box: rows of three component rows, [row][component]
+// [column], CS columns (a literal), or W where CS is 0; added to without a test (an
+// exact zero changes nothing, and costs less than the test).
+template <class A, int CS>
 struct SinkLdsC {
-  lptrc<A> box;
-  int H, W, c0, r0;  // window origin in the box
-  __device__ __forceinline__ void operator()(int comp, int b, int a, A v) const {
-    if (v != A(0))
-      __hip_atomic_fetch_add(box + (comp * H + (r0 + b)) * W + (c0 + a), v, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
+  lptr<A> box;
+  int W;
+  struct Window {
+    lptr<A> w;
+    int W;
+    __device__ __forceinline__ lptr<A> row(int c, int b) const { return w + (3 * b + c) * (CS > 0 ? CS : W); }
+    __device__ __forceinline__ void add(lptr<A> r, int a, A v) const {
+      __hip_atomic_fetch_add(r + a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  };
+  __device__ __forceinline__ Window window(int i1, int i2) const {
+    return Window{box + (__mul24(i2, 3 * (CS > 0 ? CS : W)) + i1), W};
   }
 };
 template <class A>
 struct SinkGlobC {
   A *J;
   long long cells;
-  int n1, n2, c0, r0;  // window origin (global, unwrapped)
-  __device__ __forceinline__ void operator()(int comp, int b, int a, A v) const {
-    if (v != A(0))
-      __hip_atomic_fetch_add(G(J) + comp * cells + (long long)wrap_small(r0 + b, n2) * n1 +
-                                 wrap_pow2(c0 + a, n1),
-                             v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  int n1, n2;
+  struct Window {
+    A *J;
+    long long cells;
+    int n1, n2, i1, i2;
+    __device__ __forceinline__ gptr<A> row(int c, int b) const {
+      return G(J) + (c * cells + (long long)wrap_small(i2 + b, n2) * n1);
+    }
+    __device__ __forceinline__ void add(gptr<A> r, int a, A v) const {
+      if (v != A(0))
+        __hip_atomic_fetch_add(r + wrap_pow2(i1 + a, n1), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  };
+  __device__ __forceinline__ Window window(int i1, int i2) const { return Window{J, cells, n1, n2, i1, i2}; }
 };
+
+// Both deposits below leave out what is zero: a particle that keeps its cell along an
+// axis has four-node stencils there, so that the window's fifth node and the
+// fourth running sum along the axis are zero (the FP64 form's up to the rounding
+// of 1 - 1).  The fifth column is left to the lanes that change their cell along
+// x1, the fifth row to the waves with a lane that changes it along x2.
 
 // FP64 Esirkepov deposit over the 5 x 5 window: J1 = C1 T2 g1, J2 = C2 T1 g2
 // (C the running sums of S1 - S0, T = (S0 + S1)/2), J3 = W3 g3.
-template <class R, class Sink>
-__device__ __forceinline__ void deposit_c(const Sink &put, const R S0x[5], const R S1x[5],
-                                          const R S0y[5], const R S1y[5], R g1, R g2, R g3) {
-  R C1[5], C2[5], T1[5], T2[5];
-  R a1 = 0, a2 = 0;
+template <class Win>
+__device__ __forceinline__ void deposit_c(const Win &K, const double S0x[5], const double S1x[5],
+                                          const double S0y[5], const double S1y[5], bool sw1,
+                                          bool row4, double g1, double g2, double g3) {
+  double C1[4], C2[4], T1[5], T2[5];
+  double a1 = 0, a2 = 0;
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
     a1 = a1 + (S1x[k] - S0x[k]);
     a2 = a2 + (S1y[k] - S0y[k]);
-    C1[k] = a1;
-    C2[k] = a2;
-    T1[k] = R(0.5) * (S0x[k] + S1x[k]);
-    T2[k] = R(0.5) * (S0y[k] + S1y[k]);
-  }
-#pragma unroll
-  for (int b = 0; b < 5; ++b) {
-    if (T2[b] == R(0)) continue;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) put(0, b, a, C1[a] * T2[b] * g1);
-  }
-#pragma unroll
-  for (int a = 0; a < 5; ++a) {
-    if (T1[a] == R(0)) continue;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) put(1, b, a, C2[b] * T1[a] * g2);
-  }
-#pragma unroll
-  for (int b = 0; b < 5; ++b) {
-#pragma unroll
-    for (int a = 0; a < 5; ++a) {
-      const R W3 = S0x[a] * S0y[b] * R(1.0 / 3.0) + S1x[a] * S0y[b] * R(1.0 / 6.0) +
-                   S0x[a] * S1y[b] * R(1.0 / 6.0) + S1x[a] * S1y[b] * R(1.0 / 3.0);
-      if (W3 != R(0)) put(2, b, a, W3 * g3);
+    if (k < 4) {
+      C1[k] = a1;
+      C2[k] = a2;
     }
+    T1[k] = 0.5 * (S0x[k] + S1x[k]);
+    T2[k] = 0.5 * (S0y[k] + S1y[k]);
   }
+  auto columns = [&](int c0, int c1) {  // of the window's nodes: J1 has one less
+#pragma unroll
+    for (int b = 0; b < 5; ++b) {
+      if (b == 4 && !row4) break;
+      const auto j1 = K.row(0, b), j2 = K.row(1, b), j3 = K.row(2, b);
+#pragma unroll
+      for (int a = c0; a < c1; ++a) {
+        if (a > 0) K.add(j1, a - 1, C1[a - 1] * T2[b] * g1);
+        if (b < (row4 ? 4 : 3)) K.add(j2, a, C2[b] * T1[a] * g2);
+        const double W3 = S0x[a] * S0y[b] * (1.0 / 3.0) + S1x[a] * S0y[b] * (1.0 / 6.0) +
+                          S0x[a] * S1y[b] * (1.0 / 6.0) + S1x[a] * S1y[b] * (1.0 / 3.0);
+        K.add(j3, a, W3 * g3);
+      }
+    }
+  };
+  columns(0, 4);
+  if (sw1) columns(4, 5);
 }
 
 // Fixed-point Esirkepov deposit over the 5 x 5 window from integer weights
@@ -231,64 +229,81 @@ __device__ __forceinline__ void deposit_c(const Sink &put, const R S0x[5], const
 // sums of S1 - S0, A = S0 + S1) as exact integer products, so the integer
 // divergence equals twice the integer change of Q S_x S_y node by node; J3 as
 // the quadratic kernel's: rint(x0 t0 + x1 t1), x = S h, t0 = 2 S0y + S1y,
-// t1 = S0y + 2 S1y (|value| < 2^31 by the choice of c3).  UNIT: |Q C| and A
-// fit 24 signed bits, so each product is one full-rate 24-bit pair.
-template <bool UNIT, class Sink>
-__device__ __forceinline__ void deposit_cf(const Sink &put, const int S0x[5], const int S1x[5],
-                                           const int S0y[5], const int S1y[5], int Q, float h) {
+// t1 = S0y + 2 S1y (|value| < 2^31 by the choice of c3), left out where |h| < hz
+// rounds every value to zero.  UNIT: |Q C| and A fit 24 signed bits, so each
+// product is one full-rate 24-bit pair.
+template <bool UNIT, class Win>
+__device__ __forceinline__ void deposit_cf(const Win &K, const int S0x[5], const int S1x[5],
+                                           const int S0y[5], const int S1y[5], bool sw1, bool row4,
+                                           int Q, float h, float hz) {
 #pragma clang fp contract(off)
-  int C1[5], C2[5], A1[5], A2[5];
+  int C1[4], C2[4], A1[5], A2[5];
   int a1 = 0, a2 = 0;
+  bool mv2 = false;
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
     a1 += S1x[k] - S0x[k];
     a2 += S1y[k] - S0y[k];
-    C1[k] = a1;
-    C2[k] = a2;
+    if (k < 4) {
+      C1[k] = a1;
+      C2[k] = a2;
+      mv2 |= a2 != 0;
+    }
     A1[k] = S0x[k] + S1x[k];
     A2[k] = S0y[k] + S1y[k];
   }
+  auto prod = [&](int c, int qc, int f) -> long long {
+    if (UNIT) return mul24_wide(qc, f);
+    return ((long long)Q * (long long)c) * (long long)f;
+  };
+  const bool on3 = !(fabsf(h) < hz);
+  int q2[4];
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    if (C1[a] == 0) continue;
-    const int qc = UNIT ? mul24_lo(Q, C1[a]) : 0;
+  for (int b = 0; b < 4; ++b) q2[b] = UNIT ? mul24_lo(Q, C2[b]) : 0;
+  auto columns = [&](int c0, int c1) {  // of the window's nodes: J1 has one less
 #pragma unroll
-    for (int b = 0; b < 5; ++b) {
-      const long long v = UNIT ? mul24_wide(qc, A2[b])
-                               : ((long long)Q * (long long)C1[a]) * (long long)A2[b];
-      put(0, b, a, v);
+    for (int a = c0 > 0 ? c0 - 1 : 0; a < c1 - 1; ++a) {
+      const int qc = UNIT ? mul24_lo(Q, C1[a]) : 0;
+#pragma unroll
+      for (int b = 0; b < 5; ++b) {
+        if (b == 4 && !row4) break;
+        K.add(K.row(0, b), a, prod(C1[a], qc, A2[b]));
+      }
     }
-  }
+    if (mv2) {
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    if (C2[b] == 0) continue;
-    const int qc = UNIT ? mul24_lo(Q, C2[b]) : 0;
+      for (int b = 0; b < 4; ++b) {
+        if (b == 3 && !row4) break;
+        const auto j2 = K.row(1, b);
 #pragma unroll
-    for (int a = 0; a < 5; ++a) {
-      const long long v = UNIT ? mul24_wide(qc, A1[a])
-                               : ((long long)Q * (long long)C2[b]) * (long long)A1[a];
-      put(1, b, a, v);
+        for (int a = c0; a < c1; ++a) K.add(j2, a, prod(C2[b], q2[b], A1[a]));
+      }
     }
-  }
-  float x0[5], x1[5];
+    if (on3) {
+      float x0[5], x1[5];
 #pragma unroll
-  for (int a = 0; a < 5; ++a) {
-    x0[a] = (float)S0x[a] * h;
-    x1[a] = (float)S1x[a] * h;
-  }
+      for (int a = c0; a < c1; ++a) {
+        x0[a] = (float)S0x[a] * h;
+        x1[a] = (float)S1x[a] * h;
+      }
 #pragma unroll
-  for (int b = 0; b < 5; ++b) {
-    const float B0 = (float)S0y[b], B1 = (float)S1y[b];
-    if (B0 == 0.0f && B1 == 0.0f) continue;
-    const float t0 = 2.0f * B0 + B1;
-    const float t1 = B0 + 2.0f * B1;
+      for (int b = 0; b < 5; ++b) {
+        if (b == 4 && !row4) break;
+        const float B0 = (float)S0y[b], B1 = (float)S1y[b];
+        const float t0 = 2.0f * B0 + B1;
+        const float t1 = B0 + 2.0f * B1;
+        const auto j3 = K.row(2, b);
 #pragma unroll
-    for (int a = 0; a < 5; ++a) {
-      const float p1 = x1[a] * t1;
-      const float v = __builtin_fmaf(x0[a], t0, p1);
-      put(2, b, a, (long long)(int)rintf(v));
+        for (int a = c0; a < c1; ++a) {
+          const float p1 = x1[a] * t1;
+          const float v = __builtin_fmaf(x0[a], t0, p1);
+          K.add(j3, a, (long long)(int)rintf(v));
+        }
+      }
     }
-  }
+  };
+  columns(0, 4);
+  if (sw1) columns(4, 5);
 }
 
 template <class R>
@@ -300,203 +315,212 @@ __device__ __forceinline__ void place5(const R s[4], int off, R out[5]) {
   out[4] = off ? s[3] : R(0);
 }
 
+// Pushes one particle (state s) as the quadratic push does: gather from S and deposit into
+// K at the cell (li1, li2) of their frame; false, with no move, if it was rejected.
+template <class R, bool UNIT, bool EC, class Src, class Sink>
+__device__ __forceinline__ bool push_one_c(const Run<R> &r, float hz, PState<R> &s, int gi1, int gi2,
+                                           int fi1, int fi2, int ji1, int ji2, const Src &S,
+                                           const Sink &K, unsigned *err, int &d1, int &d2) {
+  R u[3] = {s.u1, s.u2, s.u3};
+  R E[3], B[3];
+  gather_c<R, EC>(S, fi1, fi2, s.f1, s.f2, E, B);
+  boris<R>(r.qmhdt, E, B, u);
+  R v[3];
+  velocity<R>(u, v);
+  const R m1 = r.dtdx1 * v[0], m2 = r.dtdx2 * v[1];
+  d1 = d2 = 0;
+  if (!(fabs(m1) < R(1) && fabs(m2) < R(1) && fabs(v[2]) < R(2))) {
+    const bool fin = isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]) && isfinite(m1) && isfinite(m2);
+    atomicOr(err, fin ? ERR_RANGE : ERR_NUMERIC);
+    return false;
+  }
+  R g1, g2;
+  d1 = advance<R>(s.f1, m1, g1);
+  d2 = advance<R>(s.f2, m2, g2);
+  // window: nodes from min(cell_old, cell_new) - 1, five per axis
+  const int o1 = min(0, d1), o2 = min(0, d2);
+  const bool row4 = __ballot(d2 != 0) != 0;
+  const auto W = K.window(ji1 - 1 + o1, ji2 - 1 + o2);
+  if constexpr (sizeof(R) == 4) {
+    int sa[4], sb[4], S0x[5], S1x[5], S0y[5], S1y[5];
+    cubic_fixed(s.f1, r.P, sa);
+    cubic_fixed(g1, r.P, sb);
+    place5<int>(sa, 0 - o1, S0x);
+    place5<int>(sb, d1 - o1, S1x);
+    cubic_fixed(s.f2, r.P, sa);
+    cubic_fixed(g2, r.P, sb);
+    place5<int>(sa, 0 - o2, S0y);
+    place5<int>(sb, d2 - o2, S1y);
+    const float qs = s.qw * r.inv_wunit;
+    const float hv = qs * v[2];
+    deposit_cf<UNIT>(W, S0x, S1x, S0y, S1y, d1 != 0, row4, (int)rintf(qs), hv * r.c3, hz);
+  } else {
+    R sa[4], sb[4], S0x[5], S1x[5], S0y[5], S1y[5];
+    cubic4<R>(s.f1, sa);
+    cubic4<R>(g1, sb);
+    place5<R>(sa, 0 - o1, S0x);
+    place5<R>(sb, d1 - o1, S1x);
+    cubic4<R>(s.f2, sa);
+    cubic4<R>(g2, sb);
+    place5<R>(sa, 0 - o2, S0y);
+    place5<R>(sb, d2 - o2, S1y);
+    deposit_c(W, S0x, S1x, S0y, S1y, d1 != 0, row4, s.qw * r.jfx1, s.qw * r.jfx2, s.qw * v[2]);
+  }
+  s.cell = (wrap_small(gi2 + d2, r.n2) << r.log2n1) | wrap_pow2(gi1 + d1, r.n1);
+  s.f1 = g1;
+  s.f2 = g2;
+  s.u1 = u[0];
+  s.u2 = u[1];
+  s.u3 = u[2];
+  return true;
+}
+
+// |h| below which every value of J3 rounds to zero: the bracket is at most 2 (2/3) (3 2/3)
+// 2^(2P) = 2.667 2^(2P); 0.45 leaves room for the FP32 rounding of the products.
+template <class R> __device__ __forceinline__ float j3_zero(const Run<R> &r) {
+  return uniform((0.45f / 2.667f) / ((float)(1 << r.P) * (float)(1 << r.P)));
+}
+
+// The workgroup's tile through LDS boxes with column strides CS (current) and CS - 1
+// (fields), or the boxes' own where CS is 0; s0 is the thread's first particle,
+// loaded.  Both boxes start at cell lo - 2.
+template <class R, bool UNIT, bool EC, int CS>
+__device__ __forceinline__ void push_tile_c(const Run<R> &r, const Parts<R> &P, int parity, int start,
+                                            int end, PState<R> s0, int ref1, int ref2, int lo1,
+                                            int lo2, int W, int H, unsigned char *smem,
+                                            unsigned *err, int *nbox) {
+  using A = typename AccOf<R>::T;
+  using LF = LdsC<R, (CS > 0 ? CS - 1 : 0)>;
+  using T2 = typename LF::T2;
+  const int n1 = r.n1, n2 = r.n2;
+  const long long cells = r.cells;
+  const int cs = CS > 0 ? CS : W, fs = cs - 1, jrow = 3 * cs, fnodes = fs * (H - 1);
+  const lptr<A> lj = (lptr<A>)smem;
+  const lptr<T2> lp0 = (lptr<T2>)(smem + ((jrow * H * (int)sizeof(A) + 15) & ~15));
+  const lptr<T2> lp1 = lp0 + fnodes;
+  const lptr<R> le3 = (lptr<R>)(lp1 + fnodes);
+  const lptr<R> lb3 = le3 + fnodes;
+  const gptr<const R> F = G((const R *)r.F);
+  const int o1 = ref1 + lo1 - 2, o2 = ref2 + lo2 - 2;
+  for_box(W - 1, H - 1, [&](int b, int a) {
+    const long long g = (long long)wrap_any(o2 + b, n2) * n1 + wrap_pow2(o1 + a, n1);
+    const int q = b * fs + a;
+    const R e1 = F[g], e2 = F[cells + g], e3 = F[2 * cells + g];
+    const R b1 = F[3 * cells + g], b2 = F[4 * cells + g], b3 = F[5 * cells + g];
+    lp0[q] = T2{e1, b2};
+    lp1[q] = T2{e2, b1};
+    le3[q] = e3;
+    lb3[q] = b3;
+  });
+  for (int q = threadIdx.x; q < jrow * H; q += PUSH_THREADS) lj[q] = 0;
+  __syncthreads();
+  const LF S{lp0, lp1, le3, lb3, fs};
+  const SinkLdsC<A, CS> K{lj, cs};
+  const int f1 = (n1 - r.T1) >> 1, f2 = (n2 - r.T2) >> 1;
+  const float hz = j3_zero(r);
+  CellBox box;
+  PState<R> st = s0;
+  for (int p = start + (int)threadIdx.x; p < end;) {
+    // the next particle's loads are in flight while this one is pushed
+    const int pn = p + PUSH_THREADS;
+    PState<R> sn = st;
+    if (pn < end) sn = load_state(P, pn);
+    const int i1 = st.cell & (n1 - 1), i2 = st.cell >> r.log2n1;
+    const int l1 = frame_pow2(i1 - ref1, f1, n1), l2 = frame_any(i2 - ref2, f2, n2);
+    const int b1 = l1 - lo1 + 2, b2 = l2 - lo2 + 2;
+    int d1, d2;
+    const bool ok = push_one_c<R, UNIT, EC>(r, hz, st, i1, i2, b1, b2, b1, b2, S, K, err, d1, d2);
+    box.add(l1 + d1, l2 + d2);
+    arrived(sn);
+    if (ok) store_state(P, p, st);
+    st = sn;
+    p = pn;
+  }
+  box.reduce(nbox);
+  __syncthreads();
+  const gptr<A> J = G((A *)r.J[parity]);
+  for_box(W, H, [&](int b, int a) {
+    const long long g = (long long)wrap_any(o2 + b, n2) * n1 + wrap_pow2(o1 + a, n1);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const A v = lj[b * jrow + c * cs + a];
+      if (v != A(0))
+        __hip_atomic_fetch_add(J + (c * cells + g), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  });
+}
+
 }  // namespace
 
-// One workgroup per particle tile (items: run, tile).  The tile's particles
-// are bounded first (cells relative to the tile origin, periodic), the
-// current box (bounds -2 .. +3) is accumulated in LDS by all of them and added
-// to the global accumulators at the end; a box too large for LDS falls back to
-// global atomics.  The FP32 form is built for 5 waves per SIMD (96 VGPRs;
-// it held 103, i.e. 4 waves, and spills three values off the hot path); the
-// FP64 form keeps its registers.
-template <class R, bool UNIT, bool EC>
-__global__ void __launch_bounds__(256, sizeof(R) == 4 ? 5 : 1) k_push_deposit_cubic(const Run<R> *__restrict__ runs,
-                                                            const Item *__restrict__ items,
-                                                            int parity, int pp, int lds_bytes,
-                                                            unsigned *err) {
+// One workgroup per particle tile (items: run, tile), as the quadratic push: the box of
+// the tile's particles (from the previous push, or the tile itself after a sort)
+// sizes the LDS boxes, with literal column strides CS for boxes that are no
+// wider; a box too large for the LDS goes through global memory.
+//
+// What bounds it: the instructions, about 930 a particle (40 to 65 contributions and 96
+// field values).  A pass of its own to bound the particles, divisions for every
+// node staged and flushed, and a test for every contribution made them 1330: 1024
+// x 300, four particles a cell, push 72 us, 49 now; 2048 x 512 189 and 127; FP64 form
+// 340 and 232.
+template <class R, bool UNIT, bool EC, int CS>
+__global__ void __launch_bounds__(PUSH_THREADS, sizeof(R) == 4 ? 5 : 2)
+k_push_deposit_cubic(const Run<R> *__restrict__ runs, const Item *__restrict__ items, int parity,
+                     int pp, int lds_bytes, unsigned *err) {
   using A = typename AccOf<R>::T;
   extern __shared__ unsigned char smem_raw[];
-  __shared__ int red[4][4];
+  __shared__ int nbox[4];
   const Item it = items[blockIdx.x];
   const Run<R> &r = runs[it.run];
   const int t = it.a;
-  const int start = r.tile_start[t], end = r.tile_start[t + 1];
+  const int start = G(r.tile_start)[t], end = G(r.tile_start)[t + 1];
   if (start >= end) return;  // the whole workgroup
   const Parts<R> P = r.pt[pp];
+  PState<R> s0{};
+  if (start + (int)threadIdx.x < end) s0 = load_state(P, start + (int)threadIdx.x);
   const int n1 = r.n1, n2 = r.n2;
-  const int t2i = t / r.nt1, t1i = t - t2i * r.nt1;
-  const int ref1 = t1i * r.T1, ref2 = t2i * r.T2;
-  auto rel = [&](int c, int &a, int &b) {
-    const int i1 = c & (n1 - 1), i2 = c >> r.log2n1;
-    a = ((i1 - ref1 + (n1 >> 1)) & (n1 - 1)) - (n1 >> 1);
-    int d = i2 - ref2;
-    d += d < -(n2 >> 1) ? n2 : 0;
-    d -= d >= n2 - (n2 >> 1) ? n2 : 0;
-    b = d;
-  };
-  // ---- bounds of the tile's particle cells
-  int lo1 = 1 << 29, hi1 = -(1 << 29), lo2 = 1 << 29, hi2 = -(1 << 29);
-  for (int p = start + (int)threadIdx.x; p < end; p += 256) {
-    int a, b;
-    rel(G(P.cell)[p], a, b);
-    lo1 = min(lo1, a);
-    hi1 = max(hi1, a);
-    lo2 = min(lo2, b);
-    hi2 = max(hi2, b);
+  const int t2 = t / r.nt1, t1 = t - t2 * r.nt1;
+  const int ref1 = t1 * r.T1, ref2 = t2 * r.T2;
+  const auto tbox = G(r.tile_box) + 6 * t;
+  const int lo1 = tbox[0], hi1 = tbox[1], lo2 = tbox[2], hi2 = tbox[3];
+  if (threadIdx.x == 0) {
+    nbox[0] = nbox[2] = 1 << 30;
+    nbox[1] = nbox[3] = -(1 << 30);
   }
-  lo1 = wminc(lo1);
-  hi1 = wmaxc(hi1);
-  lo2 = wminc(lo2);
-  hi2 = wmaxc(hi2);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (lane == 0) {
-    red[wave][0] = lo1;
-    red[wave][1] = hi1;
-    red[wave][2] = lo2;
-    red[wave][3] = hi2;
+  const int W = hi1 - lo1 + 6, H = hi2 - lo2 + 6;
+  const int f1 = (n1 - r.T1) >> 1, f2 = (n2 - r.T2) >> 1;
+  if (CS > 0 && W <= CS && push_box_bytes(CS, H, sizeof(R), 1) <= lds_bytes) {
+    push_tile_c<R, UNIT, EC, CS>(r, P, parity, start, end, s0, ref1, ref2, lo1, lo2, W, H, smem_raw,
+                                 err, nbox);
+  } else if (push_box_bytes(W, H, sizeof(R), 1) <= lds_bytes) {
+    push_tile_c<R, UNIT, EC, 0>(r, P, parity, start, end, s0, ref1, ref2, lo1, lo2, W, H, smem_raw, err,
+                                nbox);
+  } else {
+    __syncthreads();
+    CellBox nb;
+    const GlobalC<R> S{G((const R *)r.F), n1, n2, r.cells};
+    const SinkGlobC<A> K{r.J[parity], r.cells, n1, n2};
+    const float hz = j3_zero(r);
+    for (int p = start + (int)threadIdx.x; p < end; p += PUSH_THREADS) {
+      PState<R> s = load_state(P, p);
+      const int i1 = s.cell & (n1 - 1), i2 = s.cell >> r.log2n1;
+      int d1, d2;
+      if (push_one_c<R, UNIT, EC>(r, hz, s, i1, i2, i1, i2, i1, i2, S, K, err, d1, d2)) store_state(P, p, s);
+      nb.add(frame_pow2(i1 - ref1, f1, n1) + d1, frame_any(i2 - ref2, f2, n2) + d2);
+    }
+    nb.reduce(nbox);
+    __syncthreads();
   }
-  __syncthreads();
-  lo1 = min(min(red[0][0], red[1][0]), min(red[2][0], red[3][0])) - 2;
-  hi1 = max(max(red[0][1], red[1][1]), max(red[2][1], red[3][1])) + 3;
-  lo2 = min(min(red[0][2], red[1][2]), min(red[2][2], red[3][2])) - 2;
-  hi2 = max(max(red[0][3], red[1][3]), max(red[2][3], red[3][3])) + 3;
-  const int W = hi1 - lo1 + 1, H = hi2 - lo2 + 1;
-  // field box: relative cells lo1 .. hi1 - 1 (a stencil reaches cell - 2 .. cell + 2)
-  const int FW = W - 1, FH = H - 1;
-  const long long jbytes = (3LL * W * H * (long long)sizeof(A) + 15) & ~15LL;
-  const bool use_lds = W <= n1 && H <= n2 && jbytes <= lds_bytes;
-  const bool use_fl = use_lds && jbytes + 6LL * FW * FH * (long long)sizeof(R) <= lds_bytes;
-  const lptrc<A> box = (lptrc<A>)smem_raw;
-  const lptrc<R> fl = (lptrc<R>)(smem_raw + jbytes);
-  const long long cells = r.cells;
-  const R *F = r.F;
-  if (use_lds)
-    for (int e = threadIdx.x; e < 3 * W * H; e += 256) box[e] = 0;
-  if (use_fl) {
-    const int plane = FW * FH;
-    for (int e = threadIdx.x; e < 6 * plane; e += 256) {
-      const int comp = e / plane, q = e - comp * plane;
-      const int b = q / FW, a = q - b * FW;
-      int g2 = (ref2 + lo2 + b) % n2;
-      g2 += g2 < 0 ? n2 : 0;
-      fl[e] = G(F)[comp * cells + (long long)g2 * n1 + wrap_pow2(ref1 + lo1 + a, n1)];
+  // new box of the tile's particles; one that reaches past the frame's edge wraps, so
+  // it becomes the whole frame
+  if (threadIdx.x < 2) {
+    const int k = threadIdx.x, f = k ? f2 : f1, n = k ? n2 : n1;
+    int lo = nbox[2 * k], hi = nbox[2 * k + 1];
+    if (lo < -f || hi >= n - f) {
+      lo = -f;
+      hi = n - f - 1;
     }
-  }
-  __syncthreads();
-  for (int p = start + (int)threadIdx.x; p < end; p += 256) {
-    const int cell = G(P.cell)[p];
-    const int i1 = cell & (n1 - 1), i2 = cell >> r.log2n1;
-    int rel1, rel2;
-    rel(cell, rel1, rel2);
-    const R f1 = G(P.f1)[p], f2 = G(P.f2)[p];
-    R u[3] = {G(P.u1)[p], G(P.u2)[p], G(P.u3)[p]};
-    const R qw = G(P.qw)[p];
-    // ---- gather: integer (i) and half (h) stencils; EC lowers the order
-    // along the staggered directions
-    R wi1[4], wh1[4], wi2[4], wh2[4];
-    const int ci = stencil4<R>(i1, f1, false, false, wi1);
-    const int ch = stencil4<R>(i1, f1, true, EC, wh1);
-    const int ri = stencil4<R>(i2, f2, false, false, wi2);
-    const int rh = stencil4<R>(i2, f2, true, EC, wh2);
-    R E[3], B[3];
-    if (use_fl) {
-      // box-local first nodes: the stencil starts 1 or 2 cells before the cell
-      const int lci = rel1 - lo1 + (ci - i1), lch = rel1 - lo1 + (ch - i1);
-      const int lri = rel2 - lo2 + (ri - i2), lrh = rel2 - lo2 + (rh - i2);
-      const int plane = FW * FH;
-      E[0] = gather_cl<R>(fl, FW, lch, wh1, lri, wi2);
-      E[1] = gather_cl<R>(fl + plane, FW, lci, wi1, lrh, wh2);
-      E[2] = gather_cl<R>(fl + 2 * plane, FW, lci, wi1, lri, wi2);
-      B[0] = gather_cl<R>(fl + 3 * plane, FW, lci, wi1, lrh, wh2);
-      B[1] = gather_cl<R>(fl + 4 * plane, FW, lch, wh1, lri, wi2);
-      B[2] = gather_cl<R>(fl + 5 * plane, FW, lch, wh1, lrh, wh2);
-    } else {
-      E[0] = gather_c<R>(F, n1, n2, ch, wh1, ri, wi2);
-      E[1] = gather_c<R>(F + cells, n1, n2, ci, wi1, rh, wh2);
-      E[2] = gather_c<R>(F + 2 * cells, n1, n2, ci, wi1, ri, wi2);
-      B[0] = gather_c<R>(F + 3 * cells, n1, n2, ci, wi1, rh, wh2);
-      B[1] = gather_c<R>(F + 4 * cells, n1, n2, ch, wh1, ri, wi2);
-      B[2] = gather_c<R>(F + 5 * cells, n1, n2, ch, wh1, rh, wh2);
-    }
-    borisc<R>(r.qmhdt, E, B, u);
-    R v[3];
-    {
-#pragma clang fp contract(off)
-      R s = R(1) + u[0] * u[0];
-      s = s + u[1] * u[1];
-      s = s + u[2] * u[2];
-      const R ig = R(1) / sqrt(s);
-      v[0] = u[0] * ig;
-      v[1] = u[1] * ig;
-      v[2] = u[2] * ig;
-    }
-    const R m1 = r.dtdx1 * v[0], m2 = r.dtdx2 * v[1];
-    if (!(isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]) && isfinite(m1) && isfinite(m2))) {
-      atomicOr(err, ERR_NUMERIC);
-      continue;
-    }
-    if (!(fabs(m1) < R(1)) || !(fabs(m2) < R(1))) {
-      atomicOr(err, ERR_RANGE);
-      continue;
-    }
-    R g1, g2;
-    const int d1 = advc<R>(f1, m1, g1);
-    const int d2 = advc<R>(f2, m2, g2);
-    // window: nodes from min(cell_old, cell_new) - 1, five per axis
-    const int o1 = min(0, d1), o2 = min(0, d2);  // window origin relative to i - 1
-    auto deposit = [&](const auto &K) {
-      if constexpr (sizeof(R) == 4) {
-        int sa[4], sb[4], S0x[5], S1x[5], S0y[5], S1y[5];
-        cubic_fixed(f1, r.P, sa);
-        cubic_fixed(g1, r.P, sb);
-        place5<int>(sa, 0 - o1, S0x);
-        place5<int>(sb, d1 - o1, S1x);
-        cubic_fixed(f2, r.P, sa);
-        cubic_fixed(g2, r.P, sb);
-        place5<int>(sa, 0 - o2, S0y);
-        place5<int>(sb, d2 - o2, S1y);
-        const float qs = qw * r.inv_wunit;
-        const float hv = qs * v[2];
-        deposit_cf<UNIT>(K, S0x, S1x, S0y, S1y, (int)rintf(qs), hv * r.c3);
-      } else {
-        R sa[4], sb[4], S0x[5], S1x[5], S0y[5], S1y[5];
-        cubic4<R>(f1, sa);
-        cubic4<R>(g1, sb);
-        place5<R>(sa, 0 - o1, S0x);
-        place5<R>(sb, d1 - o1, S1x);
-        cubic4<R>(f2, sa);
-        cubic4<R>(g2, sb);
-        place5<R>(sa, 0 - o2, S0y);
-        place5<R>(sb, d2 - o2, S1y);
-        deposit_c<R>(K, S0x, S1x, S0y, S1y, qw * r.jfx1, qw * r.jfx2, qw * v[2]);
-      }
-    };
-    if (use_lds)
-      deposit(SinkLdsC<A>{box, H, W, rel1 - 1 + o1 - lo1, rel2 - 1 + o2 - lo2});
-    else
-      deposit(SinkGlobC<A>{r.J[parity], cells, n1, n2, i1 - 1 + o1, i2 - 1 + o2});
-    const int j1 = wrap_pow2(i1 + d1, n1), j2 = wrap_small(i2 + d2, n2);
-    G(P.cell)[p] = (j2 << r.log2n1) | j1;
-    G(P.f1)[p] = g1;
-    G(P.f2)[p] = g2;
-    G(P.u1)[p] = u[0];
-    G(P.u2)[p] = u[1];
-    G(P.u3)[p] = u[2];
-  }
-  __syncthreads();
-  if (use_lds) {
-    A *J = r.J[parity];
-    for (int e = threadIdx.x; e < 3 * W * H; e += 256) {
-      const A v = box[e];
-      if (v == A(0)) continue;
-      const int cc = e % W, rest = e / W;
-      const int rr = rest % H, comp = rest / H;
-      const int col = wrap_pow2(ref1 + lo1 + cc, n1);
-      int row = (ref2 + lo2 + rr) % n2;
-      row += row < 0 ? n2 : 0;
-      __hip_atomic_fetch_add(G(J) + comp * cells + (long long)row * n1 + col, v, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-    }
+    tbox[2 * k] = lo;
+    tbox[2 * k + 1] = hi;
   }
 }
 
@@ -541,23 +565,29 @@ __global__ void __launch_bounds__(256) k_rho_cubic(const Run<R> *__restrict__ ru
 
 template <class R>
 void launch_push_cubic(const Run<R> *runs, const Item *items, int nitems, int parity, int pp,
-                       int lds_bytes, bool unit, bool ec, unsigned *err, hipStream_t s) {
+                       int lds_bytes, int tile1, bool unit, bool ec, unsigned *err, hipStream_t s) {
   if (nitems <= 0) return;
-  lds_bytes = min(lds_bytes, CLDS_BYTES);
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(nitems), dim3(256), (size_t)lds_bytes, s, runs, items, parity,
-                       pp, lds_bytes, err);
+    hipLaunchKernelGGL(kernel, dim3(nitems), dim3(PUSH_THREADS), (size_t)lds_bytes, s, runs, items,
+                       parity, pp, lds_bytes, err);
   };
   // UNIT selects the 24-bit integer products of the FP32 form; the FP64 form
   // has no integer products and is instantiated without it
-  constexpr bool U = sizeof(R) == 4;
-  if (U && unit) {
-    if (ec) go(k_push_deposit_cubic<R, U, true>);
-    else go(k_push_deposit_cubic<R, U, false>);
-  } else {
-    if (ec) go(k_push_deposit_cubic<R, false, true>);
-    else go(k_push_deposit_cubic<R, false, false>);
-  }
+  constexpr bool F = sizeof(R) == 4;
+  auto by_width = [&](auto u) {
+    constexpr bool U = decltype(u)::value;
+    if (ec) return go(k_push_deposit_cubic<R, U, true, 0>);
+    switch (tile1) {
+      case 8: return go(k_push_deposit_cubic<R, U, false, push_cols(8)>);
+      case 16: return go(k_push_deposit_cubic<R, U, false, push_cols(16)>);
+      case 32: return go(k_push_deposit_cubic<R, U, false, push_cols(32)>);
+      default: return go(k_push_deposit_cubic<R, U, false, 0>);
+    }
+  };
+  if (F && unit)
+    by_width(std::integral_constant<bool, F>{});
+  else
+    by_width(std::false_type{});
 }
 template <class R>
 void launch_rho_cubic(const Run<R> *run_dev, int pp, int np, typename AccOf<R>::T *rho,
@@ -565,9 +595,9 @@ void launch_rho_cubic(const Run<R> *run_dev, int pp, int np, typename AccOf<R>::
   if (np <= 0) return;
   hipLaunchKernelGGL(k_rho_cubic<R>, dim3((np + 255) / 256), dim3(256), 0, s, run_dev, pp, rho);
 }
-template void launch_push_cubic<float>(const Run<float> *, const Item *, int, int, int, int, bool,
-                                       bool, unsigned *, hipStream_t);
-template void launch_push_cubic<double>(const Run<double> *, const Item *, int, int, int, int,
+template void launch_push_cubic<float>(const Run<float> *, const Item *, int, int, int, int, int,
+                                       bool, bool, unsigned *, hipStream_t);
+template void launch_push_cubic<double>(const Run<double> *, const Item *, int, int, int, int, int,
                                         bool, bool, unsigned *, hipStream_t);
 template void launch_rho_cubic<float>(const Run<float> *, int, int, long long *, hipStream_t);
 template void launch_rho_cubic<double>(const Run<double> *, int, int, double *, hipStream_t);

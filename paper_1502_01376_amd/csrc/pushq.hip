@@ -157,7 +157,6 @@ __device__ __forceinline__ int wmax(int v) {
   for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
   return v;
 }
-template <class T> using lptr = T __attribute__((address_space(3))) *;
 // A complex value as a clang vector (copyable to and from LDS).
 template <class R> struct LdsC;
 template <> struct LdsC<float> { typedef float T __attribute__((ext_vector_type(2))); };

@@ -112,7 +112,7 @@ double dk_mod(const hp_config &c, double k1) {
 const int SORT_CHUNK = 256;   // particles per sort workgroup
 const int UPD_BLOCK = 256;    // (row or row strip, kappa) elements per update workgroup
 const int TILE1 = 32, TILE2 = 8;  // default particle tile (cells along x1, x2)
-const int SLACK1 = 2, SLACK2 = 1;  // drift beyond the tile the LDS budget allows for
+const int SLACK2 = 1;  // drift along x2 beyond the tile that the LDS budget allows for
 const int TILE1_3D = 8, TILE2_3D = 4;  // default 3D tile: 8 x 4 x 4 cells
 const double CJ3 = 1099511627776.0;     // 2^40: integer scale of the 3D FP32 deposit
 const int DEFAULT_SORT_INTERVAL = 16;
@@ -743,7 +743,7 @@ class Sim : public SimBase {
       Launch<R>::push_deposit3(d_runs_, d_tiles_, n_tiles_, p, pp_, push_lds_, d_err_, d_stats_,
                                stream_);
     else if (runs_[0].d.shape == 3)
-      launch_push_cubic<R>(d_runs_, d_tiles_, n_tiles_, p, pp_, push_lds_, all_unit(),
+      launch_push_cubic<R>(d_runs_, d_tiles_, n_tiles_, p, pp_, push_lds_, tile1_, all_unit(),
                            runs_[0].cfg.interp == 1, d_err_, stream_);
     else
       Launch<R>::push_deposit(d_runs_, d_tiles_, n_tiles_, p, pp_, push_lds_, tile1_, all_unit(),
@@ -1683,7 +1683,6 @@ class Sim : public SimBase {
   int make_tiles(int t1, int t2) {
     drop_graphs();
     std::vector<Item> tiles, cblocks;
-    int maxbox = 0;
     // 3D: the push takes 2 x 2 neighbours in x2 and x3 together, or 2 in x1, for as
     // long as the box fits and at least 1024 workgroups remain: fewer halo nodes a
     // particle, and two particles a thread to share them (512 x 128 x 128, two
@@ -1720,21 +1719,14 @@ class Sim : public SimBase {
         return rc;
       for (int b = 0; b < nb; ++b) cblocks.push_back(Item{i, b, 0});
       for (int t = 0; t < d.ntiles; ++t) tiles.push_back(Item{i, t, 0});
-      // staged box of a tile whose particles spread SLACK cells beyond it
-      const int b1 = std::min(d.T1 + 2 * SLACK1, d.n1) + 6;
-      const int b2 = std::min(d.T2 + 2 * SLACK2, d.n2) + 6;
-      maxbox = std::max(maxbox, b1 * b2);
     }
     tile1_ = t1;
     tile2_ = t2;
-    const int node_bytes = FIXED ? 48 : 72;  // 3 accumulators + 6 staged field values
-    long long need = (long long)maxbox * node_bytes;
-    if (dim_ == 2 && runs_[0].d.shape == 2) {
-      need = 0;
-      for (const RunHost &h : runs_)
-        need = std::max(need, push_box_bytes(push_cols(std::min(t1, h.d.n1)),
-                                             std::min(h.d.T2 + 2 * SLACK2, h.d.n2) + 6, sizeof(R)));
-    }
+    long long need = 0;
+    for (const RunHost &h : runs_)
+      need = std::max(need, push_box_bytes(push_cols(std::min(t1, h.d.n1)),
+                                           std::min(h.d.T2 + 2 * SLACK2, h.d.n2) + 6, sizeof(R),
+                                           h.d.shape == 3 ? 1 : 2));
     push_lds_ = (int)std::min<long long>(PUSH_LDS_MAX, std::max<long long>(PUSH_LDS_MIN, (need + 511) / 512 * 512));
     // 3D: all the LDS that the occupancy leaves, for the particles' spread
     using O3 = Push3Occupancy<R>;
