@@ -7,11 +7,11 @@
 //
 // One workgroup per particle tile of the periodic tile sort, with the tile's
 // fields and currents in LDS boxes that follow its particles, as in the
-// quadratic push; a box too large for LDS falls back to global atomics.  FP32 form: integer cubic
-// weights with exact sum 2^P and the integer Esirkepov products of the
-// quadratic kernel, so 2 (rho_new - rho_old) = div J holds exactly in the
-// integers and the sums do not depend on the order; FP64 form: physical
-// current in FP64.
+// quadratic push; a box too large for LDS falls back to global atomics.  FP32
+// form: integer cubic weights with exact sum 2^P and the integer Esirkepov
+// products of the quadratic kernel, so 2 (rho_new - rho_old) = div J holds
+// exactly in the integers and the sums do not depend on the order; FP64 form:
+// physical current in FP64.
 #include <type_traits>
 
 #include "hpic_internal.h"

@@ -34,8 +34,9 @@
 // stored positions, their radius and direction in R) is FP64 in both forms;
 // the FP32 form rounds each contribution once to a 64-bit integer on a fine
 // scale (2^40 per unit charge), so the sums do not depend on the order and
-// continuity holds to about 2^-41 of a particle's charge per node and step.  (With FP32 weights and a 2^28 scale, long
-// drifting-beam runs grew a spurious k1 = 0 mode.)
+// continuity holds to about 2^-41 of a particle's charge per node and step.
+// (With FP32 weights and a 2^28 scale, long drifting-beam runs grew a spurious
+// k1 = 0 mode.)
 #include "hpic_q3d.h"
 
 namespace hp {
@@ -441,7 +442,7 @@ __device__ __forceinline__ PStateQ<R> load_q(const PartsQ<R> &P, int p) {
 // a particle, with three modes.  On 2048 x 256 cells (8 particles each over 250
 // rows, three modes, FP32) a push takes 397 us, 1098 with a box per wave of 64
 // particles, which carried a halo of 8 x 8 nodes for 8 cells and tested every
-// contribution; FP64 on 256 x 61 with two modes 44 us, 56 before.  Of that:
+// contribution; FP64 on 256 x 61 with two modes 37 us, 56 before.  Of that:
 // tiles in place of waves (a third of the nodes flushed and staged per particle)
 // and contributions without tests, 744; particles in the order of their cells, so
 // that the lanes of an atomic meet different nodes (LDS cycles 374 to 290 us) and

@@ -443,7 +443,7 @@ class Sim : public SimBase {
   }
 
   // Threads of a run's k-space update with strips of that many rows (2D; 3D:
-  // one thread per plane).
+  // one thread per row and mode).
   static int update_threads(const Run<R> &d, int strip) {
     return d.dim == 3 ? d.rows * d.nk : ((d.n2 + strip - 1) / strip) * d.nk;
   }
