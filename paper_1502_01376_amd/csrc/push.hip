@@ -965,7 +965,9 @@ __global__ void k_kinetic(const Run<R> *run, int pp, double *partial) {
 
 // ---------------------------------------------------------------- launches
 // Literal strides for the tile widths in use; other widths, and the
-// energy-conserving gather, take the box's own stride.
+// energy-conserving gather, take the box's own stride (its kernel gains nothing by
+// a literal one: 2048 x 512 laser 140 us without, 144 with; four 256 x 256 38.5 and
+// 37.9).
 template <class R>
 void Launch<R>::push_deposit(const Run<R> *runs, const Item *items, int nitems, int parity, int pp,
                              int lds_bytes, int tile1, bool unit, bool ec, unsigned *err,

@@ -573,6 +573,8 @@ void launch_push_cubic(const Run<R> *runs, const Item *items, int nitems, int pa
   };
   // UNIT selects the 24-bit integer products of the FP32 form; the FP64 form
   // has no integer products and is instantiated without it
+  // (the energy-conserving gather gains nothing by a literal stride: 1024 x 300 54.4 us
+  // without, 53.8 with)
   constexpr bool F = sizeof(R) == 4;
   auto by_width = [&](auto u) {
     constexpr bool U = decltype(u)::value;
