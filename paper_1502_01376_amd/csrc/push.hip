@@ -721,9 +721,9 @@ k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, 
 // and the lanes of one LDS atomic met on the same nodes (24 runs, 34M particles
 // loaded at random: push 667 us, 518 now) or came to (512 x 128 x 128 cells: 1380 us in
 // the first 64 steps, 1540 after four sorts, with the push as it was).  What bounds
-// it is the scatter's traffic, 80 bytes a particle, at 2.8 TB/s (893 us for the 24
-// runs, the whole sort 1160, 1600 when one workgroup a run scanned and
-// cleared the counts and a wave's lanes went to the tiles one by one).
+// it is the scatter's traffic, 80 bytes a particle in pieces of lines (the whole
+// sort of the 24 runs 1110 us, 1600 when one workgroup a run scanned and cleared the
+// counts and a wave's lanes went to the tiles one by one).
 
 // a / b for 0 <= a < 2^23, 0 < b, and the remainder
 __device__ __forceinline__ int div_small(int a, int b, int &rem) {
@@ -756,6 +756,17 @@ __device__ __forceinline__ int tile_of(const Run<R> &r, int cell, int &place) {
   return (t3 * r.nt2 + t2) * r.nt1 + t1;
 }
 
+// Block b of n in an order that gives each of the eight dies, to which blocks go in
+// turn, a contiguous run of them: the particles of a tile lie in a few blocks, so the
+// pieces of a line that they write meet in one L2.  Whole sort, in turn and in runs:
+// 2048 x 512 laser 440 and 367 us, its FP64 form at 1024 x 512 264 and 215, four 256 x
+// 256 71 and 59, 1024 x 300 68 and 48, the 24 runs 1160 and 1110; 512 x 128 x 128 573
+// and 574, as its blocks write few lines together.
+__device__ __forceinline__ int die_run(int b, int n) {
+  const int per = n >> 3;
+  return b < 8 * per ? (b & 7) * per + (b >> 3) : b;
+}
+
 template <class R>
 __global__ void __launch_bounds__(256) k_sort_clear(const Run<R> *runs, const Item *blocks) {
   const Item it = blocks[blockIdx.x];
@@ -767,7 +778,7 @@ __global__ void __launch_bounds__(256) k_sort_clear(const Run<R> *runs, const It
 
 template <class R>
 __global__ void __launch_bounds__(256) k_sort_count(const Run<R> *runs, const Item *chunks, int pp) {
-  const Item it = chunks[blockIdx.x];
+  const Item it = chunks[die_run(blockIdx.x, gridDim.x)];
   const Run<R> &r = runs[it.run];
   if (threadIdx.x >= (unsigned)it.b) return;
   int place;
@@ -845,7 +856,7 @@ __global__ void __launch_bounds__(256) k_sort_tiles(const Run<R> *runs, const It
 
 template <class R>
 __global__ void __launch_bounds__(256) k_sort_scatter(const Run<R> *runs, const Item *chunks, int pp) {
-  const Item it = chunks[blockIdx.x];
+  const Item it = chunks[die_run(blockIdx.x, gridDim.x)];
   const Run<R> &r = runs[it.run];
   if (threadIdx.x >= (unsigned)it.b) return;
   const int p = it.a + (int)threadIdx.x;

@@ -41,3 +41,20 @@ def test_order_after_a_sort(hpic, n, t1, t2, per, dense, shuffled):
         flat = np.ravel_multi_index(tuple(raw["cell"][:dim][::-1]), n[::-1])
         for t in full[:50]:
             assert np.unique(flat[np.flatnonzero(tile == t)[:area]]).size == area
+
+
+# counts at the edges of the blocks of 256 particles and of their order in eight runs
+@pytest.mark.parametrize("np_", [1, 255, 7 * 256, 7 * 256 + 1, 8 * 256, 8 * 256 + 1, 17 * 256 - 1])
+def test_every_particle_once_for_any_count(hpic, np_):
+    gen = np.random.default_rng(np_)
+    i = np.stack([gen.integers(0, 64, np_), gen.integers(0, 30, np_)])
+    sim = hpic.Sim([hpic.config(64, 30, 0.2, 0.2, 0.05, precision="fp32")])
+    sim.set_particles(0, (i + gen.uniform(0.05, 0.95, i.shape)) * 0.2, gen.normal(0, 0.1, (3, np_)),
+                      np.ones(np_))
+    sim.set_tiling(8, 4, 4)
+    raw = sim.particles_raw(0)
+    sim.close()
+    assert np.array_equal(np.sort(raw["id"]), np.arange(np_))
+    assert np.array_equal(raw["cell"][:2], i[:, raw["id"]])
+    a = raw["cell"][:2] // np.array([[8], [4]])
+    assert np.all(np.diff(a[0] + 8 * a[1]) >= 0)
