@@ -12,6 +12,7 @@
 // back to gathering and depositing in global memory directly.
 #include <type_traits>
 
+#include "hpic_divide.h"
 #include "hpic_internal.h"
 
 namespace hp {
@@ -725,19 +726,9 @@ k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, 
 // sort of the 24 runs 1110 us, 1600 when one workgroup a run scanned and cleared the
 // counts and a wave's lanes went to the tiles one by one).
 
-// a / b for 0 <= a < 2^23, 0 < b, and the remainder
+// a / b for 0 <= a < 2^30, 0 < b, and the remainder
 __device__ __forceinline__ int div_small(int a, int b, int &rem) {
-  int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
-  int m = a - q * b;
-  if (m < 0) {
-    --q;
-    m += b;
-  } else if (m >= b) {
-    ++q;
-    m -= b;
-  }
-  rem = m;
-  return q;
+  return settle_quotient(a, b, (int)((float)a * __builtin_amdgcn_rcpf((float)b)), rem);
 }
 // Tile of a cell, and the cell's place in the tile.  (Even columns and rows first, so
 // that lanes whose nearest node lies beside their cell still differ, moves more
@@ -838,7 +829,7 @@ __global__ void __launch_bounds__(256) k_sort_tiles(const Run<R> *runs, const It
   }
   const int c0 = it.a * SORT_BLOCK, c1 = min(c0 + SORT_BLOCK, r.ntiles * r.area);
   const int first = (c0 + r.area - 1) / r.area;
-  for (int t = first + (int)threadIdx.x; t * r.area < c1 && t < r.ntiles; t += 256) {
+  for (int t = first + (int)threadIdx.x; t < r.ntiles && t * r.area < c1; t += 256) {
     G(r.tile_start)[t] = base + G(r.cell_cnt)[t * r.area];
     // right after the sort every particle of tile t lies in the tile, which the
     // frame of the push (centred on the tile) always holds whole
