@@ -8,6 +8,11 @@
 
 namespace hp {
 
+// The dynamic LDS of every kernel.  It follows a kernel's static LDS, so without an
+// alignment of its own it may start at any byte: behind the six ints of the 3D
+// push's box the 16-byte stores that clear it lay 8 bytes off.
+extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+
 // ---------------------------------------------------------------- types
 template <class R> struct Cplx;
 template <> struct Cplx<float> { using T = float2; };

@@ -648,7 +648,6 @@ __global__ void __launch_bounds__(PUSH_THREADS, sizeof(R) == 4 ? 5 : 3)
 k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, int parity, int pp,
                int lds_bytes, unsigned *err, unsigned *stats) {
   using SK = Sinks<R, 0>;
-  extern __shared__ unsigned char smem_raw[];
   __shared__ int nbox[4];
   const Item it = items[blockIdx.x];
   const Run<R> &r = runs[it.run];

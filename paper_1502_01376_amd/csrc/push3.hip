@@ -520,9 +520,9 @@ __device__ __noinline__ void push_tile3_global(const Run<R> *run, int t, int par
 // at once left the LDS to 12 waves of 168 registers on tiles of 8 x 4 x 4 cells;
 // taking turns they leave it to 16 waves of 128 on tiles of 8 x 8 x 8, which also halves
 // the halo nodes a particle stages and flushes.  512 x 128 x 128 cells, two particles
-// a cell, mean of the first 128 steps: 1530 us before, 1200 now; 128 x 37 x 45, three
-// a cell: 85 and 67, 220 and 155 once it is so hot that the boxes outgrow 53 KB; FP64
-// form, 128 x 64 x 64: 234 us when it gathered through the cache, 159 now.  (The
+// a cell, mean over 128 steps: 1530 us before, 1160 now; 128 x 37 x 45, three
+// a cell: 85 and 62, 220 and 155 once it is so hot that the boxes outgrow 53 KB; FP64
+// form, 128 x 64 x 64: 234 us when it gathered through the cache, 147 now.  (The
 // slabs' loops in the same body spilled 26 registers: 1460 us.)
 template <class R, int NT, bool ONE>
 __device__ __forceinline__ void push_tile3(const Run<R> &r, const Tile3 &T, int tile_first, int tile_end,
@@ -664,7 +664,6 @@ template <class R, int NT>
 __global__ void __launch_bounds__(NT, Push3Occupancy<R>::WAVES_PER_SIMD)
 k_push_deposit3(const Run<R> *__restrict__ runs, const Item *__restrict__ items, int parity, int pp,
                 int lds_bytes, unsigned *err, unsigned *stats) {
-  extern __shared__ unsigned char smem_raw[];
   __shared__ int nbox[6];
   const Item it = items[blockIdx.x];
   const Run<R> &r = runs[it.run];

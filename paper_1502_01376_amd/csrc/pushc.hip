@@ -467,7 +467,6 @@ __global__ void __launch_bounds__(PUSH_THREADS, sizeof(R) == 4 ? 5 : 2)
 k_push_deposit_cubic(const Run<R> *__restrict__ runs, const Item *__restrict__ items, int parity,
                      int pp, int lds_bytes, unsigned *err) {
   using A = typename AccOf<R>::T;
-  extern __shared__ unsigned char smem_raw[];
   __shared__ int nbox[4];
   const Item it = items[blockIdx.x];
   const Run<R> &r = runs[it.run];

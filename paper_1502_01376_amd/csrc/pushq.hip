@@ -457,7 +457,6 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
   using V2 = typename LdsC<R>::T;
   constexpr bool STAGE = sizeof(R) == 4;
   constexpr int FWD = CW - 2;
-  extern __shared__ unsigned char smem_raw[];
   __shared__ int nbox[4];
   const Item it = items[blockIdx.x];
   const RunQ<R> &r = runs[it.run];

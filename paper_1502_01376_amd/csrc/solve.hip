@@ -49,7 +49,6 @@ template <class R, int MAXB, int NC>
 __global__ void __launch_bounds__(256) k_fft_j(const Run<R> *__restrict__ runs,
                                                const Item *__restrict__ items, int parity) {
   using C = typename Cplx<R>::T;
-  extern __shared__ unsigned char smem_raw[];
   C *lds = (C *)smem_raw;
   const Item it = items[blockIdx.x];
   const Run<R> &r = runs[it.run];
@@ -113,7 +112,6 @@ __global__ void __launch_bounds__(256) k_fields_to_k(const Run<R> *__restrict__ 
                                                      const Item *__restrict__ items, int parity,
                                                      int ncomp) {
   using C = typename Cplx<R>::T;
-  extern __shared__ unsigned char smem_raw[];
   C *lds = (C *)smem_raw;
   const Item it = items[blockIdx.x];
   const Run<R> &r = runs[it.run];
@@ -356,7 +354,6 @@ template <class R, int MAXB, int NC>
 __global__ void __launch_bounds__(256) k_ifft_eb(const Run<R> *__restrict__ runs,
                                                  const Item *__restrict__ items, int parity) {
   using C = typename Cplx<R>::T;
-  extern __shared__ unsigned char smem_raw[];
   C *lds = (C *)smem_raw;
   const Item it = items[blockIdx.x];
   const Run<R> &r = runs[it.run];
@@ -405,7 +402,6 @@ __global__ void __launch_bounds__(256) k_inverse_rows(const typename Cplx<R>::T 
                                                       const typename Cplx<R>::T *tw, R scale,
                                                       R *out) {
   using C = typename Cplx<R>::T;
-  extern __shared__ unsigned char smem_raw[];
   C *lds = (C *)smem_raw;
   const int row = blockIdx.x;
   const int M = n1 >> 1;
@@ -457,7 +453,6 @@ template <class R>
 __global__ void __launch_bounds__(256) k_gauss(const Run<R> *run, int parity, const double *rho,
                                                const double2 *tw64, const double *sym64,
                                                const double *filt, double idx2, double *rows_out) {
-  extern __shared__ unsigned char smem_raw[];
   double2 *lds = (double2 *)smem_raw;
   __shared__ double red[256][3];
   const Run<R> &r = *run;
@@ -587,7 +582,6 @@ __global__ void __launch_bounds__(256) k_gauss3(const Run<R> *run, int parity, c
                                                 const double2 *tw64, const double *sym64,
                                                 const double *filt, double idx2, double idx3,
                                                 double *rows_out) {
-  extern __shared__ unsigned char smem_raw[];
   double2 *lds = (double2 *)smem_raw;
   __shared__ double red[256][3];
   const Run<R> &r = *run;

@@ -21,7 +21,6 @@ template <class R>
 __global__ void __launch_bounds__(256) k_q_fields_to_k(const RunQ<R> *__restrict__ runs,
                                                        const Item *__restrict__ items, int parity) {
   using C = typename Cplx<R>::T;
-  extern __shared__ unsigned char smem_raw[];
   C *lds = (C *)smem_raw;
   const Item it = items[blockIdx.x];
   const RunQ<R> &r = runs[it.run];
@@ -41,7 +40,6 @@ template <class R>
 __global__ void __launch_bounds__(256) k_q_ifft(const RunQ<R> *__restrict__ runs,
                                                 const Item *__restrict__ items, int parity) {
   using C = typename Cplx<R>::T;
-  extern __shared__ unsigned char smem_raw[];
   C *lds = (C *)smem_raw;
   const Item it = items[blockIdx.x];
   const RunQ<R> &r = runs[it.run];
@@ -91,7 +89,6 @@ __global__ void __launch_bounds__(256) k_q_fft_j(const RunQ<R> *__restrict__ run
                                                  const Item *__restrict__ items, int parity) {
   using C = typename Cplx<R>::T;
   using A = typename AccQ<R>::T;
-  extern __shared__ unsigned char smem_raw[];
   C *lds = (C *)smem_raw;
   const Item it = items[blockIdx.x];
   const RunQ<R> &r = runs[it.run];
@@ -200,7 +197,6 @@ __global__ void __launch_bounds__(256) k_q_update(const RunQ<R> *__restrict__ ru
 template <class R>
 __global__ void __launch_bounds__(256) k_q_rho_fft(const RunQ<R> *__restrict__ runs,
                                                    const Item *__restrict__ items, double2 *rho) {
-  extern __shared__ unsigned char smem_raw[];
   double2 *lds = (double2 *)smem_raw;
   const Item it = items[blockIdx.x];
   const RunQ<R> &r = runs[it.run];
