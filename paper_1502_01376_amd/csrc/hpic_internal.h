@@ -662,6 +662,63 @@ struct CellBox {
   }
 };
 
+// The current box of a tile whose particles have spread too far for the boxes of
+// fields and currents: all of its nodes where they number at most cap, or as many around
+// the particles' mean cell, the margin about the tile the same on all sides.  Holds
+// the deposits of the particles in cells lo .. hi; cells lo - 2 .. hi + 3.
+struct WideBox {
+  int lo1, hi1, lo2, hi2, W, H;
+  __device__ __forceinline__ bool holds(int l1, int l2) const {
+    return l1 >= lo1 && l1 <= hi1 && l2 >= lo2 && l2 <= hi2;
+  }
+};
+// smem: 16 bytes of LDS, free again when this returns.  Called by the whole workgroup.
+template <class R>
+__device__ __forceinline__ WideBox wide_box(const Run<R> &r, const Parts<R> &P, int start, int end,
+                                            int ref1, int ref2, int lo1, int hi1, int lo2, int hi2,
+                                            int cap, unsigned char *smem) {
+  WideBox b{lo1, hi1, lo2, hi2, hi1 - lo1 + 6, hi2 - lo2 + 6};
+  if ((long long)b.W * b.H > cap) {
+    const lptr<unsigned long long> sum = (lptr<unsigned long long>)smem;
+    if (threadIdx.x < 2) sum[threadIdx.x] = 0;
+    __syncthreads();
+    const int f1 = (r.n1 - r.T1) >> 1, f2 = (r.n2 - r.T2) >> 1;
+    long long s1 = 0, s2 = 0;
+    for (int p = start + (int)threadIdx.x; p < end; p += PUSH_THREADS) {
+      const int cell = *elem(P.cell, p);
+      s1 += frame_pow2((cell & (r.n1 - 1)) - ref1, f1, r.n1);
+      s2 += frame_any((cell >> r.log2n1) - ref2, f2, r.n2);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      s1 += __shfl_xor(s1, o);
+      s2 += __shfl_xor(s2, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+      __hip_atomic_fetch_add(sum, (unsigned long long)s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(sum + 1, (unsigned long long)s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __syncthreads();
+    const int m1 = (int)((long long)sum[0] / (end - start)), m2 = (int)((long long)sum[1] / (end - start));
+    __syncthreads();
+    int W = min(b.W, r.T1 + 6), H = min(b.H, r.T2 + 6);
+    if ((long long)W * H > cap) W = min(W, 64);  // a tile that is too large by itself
+    for (;;) {
+      const int w = min(b.W, W + 2), h = min(b.H, H + 2);
+      if ((w == W && h == H) || (long long)w * h > cap) break;
+      W = w;
+      H = h;
+    }
+    H = min(b.H, cap / W);
+    b.lo1 = max(lo1, min(m1 - (W - 6) / 2, hi1 - (W - 6)));
+    b.lo2 = max(lo2, min(m2 - (H - 6) / 2, hi2 - (H - 6)));
+    b.hi1 = b.lo1 + W - 6;
+    b.hi2 = b.lo2 + H - 6;
+    b.W = W;
+    b.H = H;
+  }
+  return b;
+}
+
 __device__ __forceinline__ float uniform(float x) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }

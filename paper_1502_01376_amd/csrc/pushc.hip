@@ -7,7 +7,7 @@
 //
 // One workgroup per particle tile of the periodic tile sort, with the tile's
 // fields and currents in LDS boxes that follow its particles, as in the
-// quadratic push; a box too large for LDS falls back to global atomics.  FP32
+// quadratic push; where they do not fit, LDS holds the currents alone.  FP32
 // form: integer cubic weights with exact sum 2^P and the integer Esirkepov
 // products of the quadratic kernel, so 2 (rho_new - rho_old) = div J holds
 // exactly in the integers and the sums do not depend on the order; FP64 form:
@@ -141,7 +141,8 @@ __device__ __forceinline__ void cubic_fixed(float d, int P, int s[4]) {
 }
 
 // Deposit targets: window() gives row b of component c in the window from (i1, i2), add()
-// adds to its column a.  LDS box: rows of three component rows, [row][component]
+// adds to its column a; at() calls f with the window at the particle's cell plus
+// (o1, o2).  LDS box: rows of three component rows, [row][component]
 // [column], CS columns (a literal), or W where CS is 0; added to without a test (an
 // exact zero changes nothing, and costs less than the test).
 template <class A, int CS>
@@ -158,6 +159,9 @@ struct SinkLdsC {
   };
   __device__ __forceinline__ Window window(int i1, int i2) const {
     return Window{box + (__mul24(i2, 3 * (CS > 0 ? CS : W)) + i1), W};
+  }
+  template <class F> __device__ __forceinline__ void at(int i1, int i2, int o1, int o2, const F &f) const {
+    f(window(i1 + o1, i2 + o2));
   }
 };
 template <class A>
@@ -178,6 +182,21 @@ struct SinkGlobC {
     }
   };
   __device__ __forceinline__ Window window(int i1, int i2) const { return Window{J, cells, n1, n2, i1, i2}; }
+};
+// A particle's deposit into an LDS box that does not hold every particle of the tile:
+// at its cell (l1, l2) there, or at its cell of the grid if it is outside.
+template <class A>
+struct SinkWideC {
+  SinkLdsC<A, 0> lds;
+  SinkGlobC<A> grid;
+  bool in;
+  int l1, l2;
+  template <class F> __device__ __forceinline__ void at(int i1, int i2, int o1, int o2, const F &f) const {
+    if (in)
+      f(lds.window(l1 + o1, l2 + o2));
+    else
+      f(grid.window(i1 + o1, i2 + o2));
+  }
 };
 
 // Both deposits below leave out what is zero: a particle that keeps its cell along an
@@ -319,11 +338,11 @@ __device__ __forceinline__ void place5(const R s[4], int off, R out[5]) {
 // K at the cell (li1, li2) of their frame; false, with no move, if it was rejected.
 template <class R, bool UNIT, bool EC, class Src, class Sink>
 __device__ __forceinline__ bool push_one_c(const Run<R> &r, float hz, PState<R> &s, int gi1, int gi2,
-                                           int fi1, int fi2, int ji1, int ji2, const Src &S,
-                                           const Sink &K, unsigned *err, int &d1, int &d2) {
+                                           int li1, int li2, const Src &S, const Sink &K,
+                                           unsigned *err, int &d1, int &d2) {
   R u[3] = {s.u1, s.u2, s.u3};
   R E[3], B[3];
-  gather_c<R, EC>(S, fi1, fi2, s.f1, s.f2, E, B);
+  gather_c<R, EC>(S, li1, li2, s.f1, s.f2, E, B);
   boris<R>(r.qmhdt, E, B, u);
   R v[3];
   velocity<R>(u, v);
@@ -340,7 +359,6 @@ __device__ __forceinline__ bool push_one_c(const Run<R> &r, float hz, PState<R> 
   // window: nodes from min(cell_old, cell_new) - 1, five per axis
   const int o1 = min(0, d1), o2 = min(0, d2);
   const bool row4 = __ballot(d2 != 0) != 0;
-  const auto W = K.window(ji1 - 1 + o1, ji2 - 1 + o2);
   if constexpr (sizeof(R) == 4) {
     int sa[4], sb[4], S0x[5], S1x[5], S0y[5], S1y[5];
     cubic_fixed(s.f1, r.P, sa);
@@ -353,7 +371,9 @@ __device__ __forceinline__ bool push_one_c(const Run<R> &r, float hz, PState<R> 
     place5<int>(sb, d2 - o2, S1y);
     const float qs = s.qw * r.inv_wunit;
     const float hv = qs * v[2];
-    deposit_cf<UNIT>(W, S0x, S1x, S0y, S1y, d1 != 0, row4, (int)rintf(qs), hv * r.c3, hz);
+    K.at(li1, li2, o1 - 1, o2 - 1, [&](const auto &W) {
+      deposit_cf<UNIT>(W, S0x, S1x, S0y, S1y, d1 != 0, row4, (int)rintf(qs), hv * r.c3, hz);
+    });
   } else {
     R sa[4], sb[4], S0x[5], S1x[5], S0y[5], S1y[5];
     cubic4<R>(s.f1, sa);
@@ -364,7 +384,9 @@ __device__ __forceinline__ bool push_one_c(const Run<R> &r, float hz, PState<R> 
     cubic4<R>(g2, sb);
     place5<R>(sa, 0 - o2, S0y);
     place5<R>(sb, d2 - o2, S1y);
-    deposit_c(W, S0x, S1x, S0y, S1y, d1 != 0, row4, s.qw * r.jfx1, s.qw * r.jfx2, s.qw * v[2]);
+    K.at(li1, li2, o1 - 1, o2 - 1, [&](const auto &W) {
+      deposit_c(W, S0x, S1x, S0y, S1y, d1 != 0, row4, s.qw * r.jfx1, s.qw * r.jfx2, s.qw * v[2]);
+    });
   }
   s.cell = (wrap_small(gi2 + d2, r.n2) << r.log2n1) | wrap_pow2(gi1 + d1, r.n1);
   s.f1 = g1;
@@ -429,7 +451,7 @@ __device__ __forceinline__ void push_tile_c(const Run<R> &r, const Parts<R> &P, 
     const int l1 = frame_pow2(i1 - ref1, f1, n1), l2 = frame_any(i2 - ref2, f2, n2);
     const int b1 = l1 - lo1 + 2, b2 = l2 - lo2 + 2;
     int d1, d2;
-    const bool ok = push_one_c<R, UNIT, EC>(r, hz, st, i1, i2, b1, b2, b1, b2, S, K, err, d1, d2);
+    const bool ok = push_one_c<R, UNIT, EC>(r, hz, st, i1, i2, b1, b2, S, K, err, d1, d2);
     box.add(l1 + d1, l2 + d2);
     arrived(sn);
     if (ok) store_state(P, p, st);
@@ -450,12 +472,56 @@ __device__ __forceinline__ void push_tile_c(const Run<R> &r, const Parts<R> &P, 
   });
 }
 
+// A tile whose particles have spread so far that the two boxes do not fit: fields
+// through the cache, so that the LDS holds twice the current box, and only the particles
+// outside that deposit into global memory.  (1024 x 300, eight particles a cell, sorted
+// every 16 steps, push with a thermal spread of 0.3: 189 us, 1563 with such tiles in
+// global memory; of 1: 228 and 2304; FP64 form of 0.3: 226 and 1624.)
+template <class R, bool UNIT, bool EC>
+__device__ __forceinline__ void push_wide_c(const Run<R> &r, const Parts<R> &P, int parity, int start, int end,
+                                         int ref1, int ref2, int lo1, int hi1, int lo2, int hi2,
+                                         int lds_bytes, unsigned char *smem, unsigned *err, int *nbox) {
+  using A = typename AccOf<R>::T;
+  const int n1 = r.n1, n2 = r.n2;
+  const long long cells = r.cells;
+  const int f1 = (n1 - r.T1) >> 1, f2 = (n2 - r.T2) >> 1;
+  const WideBox w = wide_box(r, P, start, end, ref1, ref2, lo1, hi1, lo2, hi2, lds_bytes / 24, smem);
+  const lptr<A> lj = (lptr<A>)smem;
+  const int jrow = 3 * w.W, o1 = ref1 + w.lo1 - 2, o2 = ref2 + w.lo2 - 2;
+  for (int q = threadIdx.x; q < jrow * w.H; q += PUSH_THREADS) lj[q] = 0;
+  __syncthreads();
+  const GlobalC<R> S{G((const R *)r.F), n1, n2, r.cells};
+  const float hz = j3_zero(r);
+  CellBox box;
+  for (int p = start + (int)threadIdx.x; p < end; p += PUSH_THREADS) {
+    PState<R> s = load_state(P, p);
+    const int i1 = s.cell & (n1 - 1), i2 = s.cell >> r.log2n1;
+    const int l1 = frame_pow2(i1 - ref1, f1, n1), l2 = frame_any(i2 - ref2, f2, n2);
+    const SinkWideC<A> K{{lj, w.W}, {r.J[parity], cells, n1, n2}, w.holds(l1, l2), l1 - w.lo1 + 2, l2 - w.lo2 + 2};
+    int d1, d2;
+    if (push_one_c<R, UNIT, EC>(r, hz, s, i1, i2, i1, i2, S, K, err, d1, d2)) store_state(P, p, s);
+    box.add(l1 + d1, l2 + d2);
+  }
+  box.reduce(nbox);
+  __syncthreads();
+  const gptr<A> J = G((A *)r.J[parity]);
+  for_box(w.W, w.H, [&](int b, int a) {
+    const long long g = (long long)wrap_any(o2 + b, n2) * n1 + wrap_pow2(o1 + a, n1);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const A v = lj[b * jrow + c * w.W + a];
+      if (v != A(0))
+        __hip_atomic_fetch_add(J + (c * cells + g), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  });
+}
+
 }  // namespace
 
 // One workgroup per particle tile (items: run, tile), as the quadratic push: the box of
 // the tile's particles (from the previous push, or the tile itself after a sort)
 // sizes the LDS boxes, with literal column strides CS for boxes that are no
-// wider; a box too large for the LDS goes through global memory.
+// wider; where the two do not fit, the LDS holds the current box alone.
 //
 // What bounds it: the instructions, about 930 a particle (40 to 65 contributions and 96
 // field values).  A pass of its own to bound the particles, divisions for every
@@ -494,20 +560,8 @@ k_push_deposit_cubic(const Run<R> *__restrict__ runs, const Item *__restrict__ i
     push_tile_c<R, UNIT, EC, 0>(r, P, parity, start, end, s0, ref1, ref2, lo1, lo2, W, H, smem_raw, err,
                                 nbox);
   } else {
-    __syncthreads();
-    CellBox nb;
-    const GlobalC<R> S{G((const R *)r.F), n1, n2, r.cells};
-    const SinkGlobC<A> K{r.J[parity], r.cells, n1, n2};
-    const float hz = j3_zero(r);
-    for (int p = start + (int)threadIdx.x; p < end; p += PUSH_THREADS) {
-      PState<R> s = load_state(P, p);
-      const int i1 = s.cell & (n1 - 1), i2 = s.cell >> r.log2n1;
-      int d1, d2;
-      if (push_one_c<R, UNIT, EC>(r, hz, s, i1, i2, i1, i2, i1, i2, S, K, err, d1, d2)) store_state(P, p, s);
-      nb.add(frame_pow2(i1 - ref1, f1, n1) + d1, frame_any(i2 - ref2, f2, n2) + d2);
-    }
-    nb.reduce(nbox);
-    __syncthreads();
+    push_wide_c<R, UNIT, EC>(r, P, parity, start, end, ref1, ref2, lo1, hi1, lo2, hi2, lds_bytes, smem_raw,
+                             err, nbox);
   }
   // new box of the tile's particles; one that reaches past the frame's edge wraps, so
   // it becomes the whole frame
