@@ -8,8 +8,8 @@
 // box (plus the stencil halo) in LDS, pushes its particles gathering from LDS,
 // accumulates the current of the box in LDS (64-bit integer atomics in the FP32
 // form, so the result does not depend on the order), and adds the box to the
-// global accumulators with one atomic per node.  A box too large for LDS falls
-// back to gathering and depositing in global memory directly.
+// global accumulators with one atomic per node.  Where the two boxes do not fit
+// the LDS, it holds the currents alone.
 #include <type_traits>
 
 #include "hpic_divide.h"
@@ -514,6 +514,50 @@ template <class R, int CS> struct Sinks;
 template <int CS> struct Sinks<float, CS> { using G = GlobalFixed; using L = LdsFixed<CS>; using T = unsigned long long; };
 template <int CS> struct Sinks<double, CS> { using G = GlobalFp64; using L = LdsFp64<CS>; using T = double; };
 
+// A particle's deposit into an LDS box that does not hold every particle of the tile:
+// at its cell (l1, l2) there, or at its cell (i1, i2) of the grid if it is outside.
+template <class R>
+struct SinkWide {
+  typename Sinks<R, 0>::L lds;
+  typename Sinks<R, 0>::T *J;
+  bool in;
+  int l1, l2;
+};
+// (The grid's half out of line, with plain arguments: it is rare, and takes no
+// registers from the other so.)
+template <bool UNIT>
+__device__ __noinline__ void deposit_grid(const Run<float> *r, unsigned long long *J, int i1, int i2,
+                                          float fa1, float fa2, int d1, int d2, float fb1, float fb2,
+                                          float v3, float qw) {
+  deposit2_fixed<UNIT>(GlobalFixed{G(J), r->n1, r->n2, r->cells}, r->P, r->inv_wunit, r->c3, i1, i2, fa1, fa2,
+                       d1, d2, fb1, fb2, v3, qw);
+}
+template <bool UNIT>
+__device__ __noinline__ void deposit_grid(const Run<double> *r, double *J, int i1, int i2, double fa1,
+                                          double fa2, int d1, int d2, double fb1, double fb2, double v3,
+                                          double qw) {
+  deposit2_fp64(GlobalFp64{J, r->n1, r->n2, r->cells}, r->jfx1, r->jfx2, i1, i2, fa1, fa2, d1, d2, fb1, fb2, v3,
+                qw);
+}
+template <bool UNIT>
+__device__ __forceinline__ void deposit_one(const Run<float> &r, const Fix &fx, const SinkWide<float> &K,
+                                            int i1, int i2, float fa1, float fa2, int d1, int d2,
+                                            float fb1, float fb2, float v3, float qw) {
+  if (K.in)
+    deposit_one<UNIT>(r, fx, K.lds, K.l1, K.l2, fa1, fa2, d1, d2, fb1, fb2, v3, qw);
+  else
+    deposit_grid<UNIT>(&r, K.J, i1, i2, fa1, fa2, d1, d2, fb1, fb2, v3, qw);
+}
+template <bool UNIT>
+__device__ __forceinline__ void deposit_one(const Run<double> &r, const NoFix &fx, const SinkWide<double> &K,
+                                            int i1, int i2, double fa1, double fa2, int d1, int d2,
+                                            double fb1, double fb2, double v3, double qw) {
+  if (K.in)
+    deposit_one<UNIT>(r, fx, K.lds, K.l1, K.l2, fa1, fa2, d1, d2, fb1, fb2, v3, qw);
+  else
+    deposit_grid<UNIT>(&r, K.J, i1, i2, fa1, fa2, d1, d2, fb1, fb2, v3, qw);
+}
+
 // Push one particle (state s): gather from S at the particle's cell (li1, li2)
 // in S's frame, Boris, move, deposit into K in the same frame; s becomes the new
 // state, (gi1, gi2) being the global cell.  Sets the cell moves (d1, d2), zero
@@ -637,6 +681,63 @@ __device__ __forceinline__ void push_tile(const Run<R> &r, const Parts<R> &P, in
   });
 }
 
+// A tile whose particles have spread so far that the two boxes do not fit: fields
+// through the cache, so that the LDS holds twice the current box, and only the particles
+// outside that deposit into global memory.  (1024 x 512, eight particles a cell, sorted
+// every 16 steps, push with a thermal spread of 0.3: 288 us, 1413 with such tiles in
+// global memory; of 1: 374 and 2124; FP64 form of 0.3: 314 and 1831.)
+template <class R, bool UNIT, bool EC>
+__device__ __forceinline__ void push_wide(const Run<R> *run, int t, int parity, int pp, int lds_bytes,
+                                       lptr<unsigned char> smem, lptr<int> nbox, unsigned *err) {
+  using SK = Sinks<R, 0>;
+  using T = typename SK::T;
+  const Run<R> &r = *run;
+  const Parts<R> P = r.pt[pp];
+  const int n1 = r.n1, n2 = r.n2, cells = n1 * n2;
+  const int f1 = (n1 - r.T1) >> 1, f2 = (n2 - r.T2) >> 1;
+  const int start = G(r.tile_start)[t], end = G(r.tile_start)[t + 1];
+  const int t2 = t / r.nt1, ref1 = (t - t2 * r.nt1) * r.T1, ref2 = t2 * r.T2;
+  const auto tb = G(r.tile_box) + 6 * t;
+  const WideBox w = wide_box(r, P, start, end, ref1, ref2, tb[0], tb[1], tb[2], tb[3], lds_bytes / 24,
+                             (unsigned char *)smem);
+  const lptr<T> lj = (lptr<T>)smem;
+  const int jrow = 3 * w.W, o1 = ref1 + w.lo1 - 2, o2 = ref2 + w.lo2 - 2;
+  for (int q = threadIdx.x; q < jrow * w.H; q += PUSH_THREADS) lj[q] = 0;
+  __syncthreads();
+  const GlobalFields<R> S{G((const R *)r.F), n1, n2, cells};
+  const auto fx = fix_of(r);
+  const gptr<T> J = G((T *)r.J[parity]);
+  CellBox box;
+  for (int p = start + (int)threadIdx.x; p < end; p += PUSH_THREADS) {
+    PState<R> s = load_state(P, p);
+    const int i1 = s.cell & (n1 - 1), i2 = s.cell >> r.log2n1;
+    const int l1 = frame_pow2(i1 - ref1, f1, n1), l2 = frame_any(i2 - ref2, f2, n2);
+    const SinkWide<R> K{{(decltype(SK::L::J))lj, w.W}, (T *)r.J[parity], w.holds(l1, l2), l1 - w.lo1 + 2, l2 - w.lo2 + 2};
+    int d1, d2;
+    if (push_one<R, UNIT, EC>(r, fx, s, i1, i2, i1, i2, S, K, err, d1, d2)) store_state(P, p, s);
+    box.add(l1 + d1, l2 + d2);
+  }
+  box.reduce((int *)nbox);
+  __syncthreads();
+  for_box(w.W, w.H, [&](int b, int a) {
+    const int g = wrap_any(o2 + b, n2) * n1 + wrap_pow2(o1 + a, n1);
+#pragma unroll
+    for (int comp = 0; comp < 3; ++comp) {
+      const T v = lj[b * jrow + comp * w.W + a];
+      if (v != 0)
+        __scoped_atomic_fetch_add(J + comp * cells + g, v, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+    }
+  });
+}
+
+// Out of line, where it would take registers from the paths of a tile that fits (8192 x
+// 512, two particles a cell: push 222 us, 232 with it in line).
+template <class R, bool UNIT>
+__device__ __noinline__ void push_wide_call(const Run<R> *run, int t, int parity, int pp, int lds_bytes,
+                                            lptr<unsigned char> smem, lptr<int> nbox, unsigned *err) {
+  push_wide<R, UNIT, false>(run, t, parity, pp, lds_bytes, smem, nbox, err);
+}
+
 // One workgroup per (run, tile).  The tile's bounding box (from the previous
 // push, or the tile itself right after a sort) sizes the LDS staging; the new
 // box of the pushed particles is written back for the next step.  CS: the
@@ -647,7 +748,6 @@ template <class R, bool UNIT, bool EC, int CS>
 __global__ void __launch_bounds__(PUSH_THREADS, sizeof(R) == 4 ? 5 : 3)
 k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, int parity, int pp,
                int lds_bytes, unsigned *err, unsigned *stats) {
-  using SK = Sinks<R, 0>;
   __shared__ int nbox[4];
   const Item it = items[blockIdx.x];
   const Run<R> &r = runs[it.run];
@@ -657,7 +757,7 @@ k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, 
   if (start >= end) return;
   PState<R> s0{};
   if (start + (int)threadIdx.x < end) s0 = load_state(P, start + (int)threadIdx.x);
-  const int n1 = r.n1, n2 = r.n2, cells = n1 * n2;
+  const int n1 = r.n1, n2 = r.n2;
   const int t2 = t / r.nt1, t1 = t - t2 * r.nt1;
   const int ref1 = t1 * r.T1, ref2 = t2 * r.T2;  // tile origin
   const int *box = r.tile_box + 6 * t;
@@ -677,22 +777,11 @@ k_push_deposit(const Run<R> *__restrict__ runs, const Item *__restrict__ items, 
     push_tile<R, UNIT, EC, 0>(r, P, parity, start, end, s0, ref1, ref2, lo1, lo2, W, H, smem_raw,
                               err, nbox);
   } else {
-    // fallback: gather and deposit in global memory.  The barrier orders the
-    // box initialisation above before every wave's min/max at the end (the
-    // LDS paths have their own barriers).
-    __syncthreads();
-    CellBox nb;
-    const GlobalFields<R> S{G((const R *)r.F), n1, n2, cells};
-    const typename SK::G K{(decltype(SK::G::J))G((typename SK::T *)r.J[parity]), n1, n2, cells};
-    for (int p = start + threadIdx.x; p < end; p += PUSH_THREADS) {
-      PState<R> s = load_state(P, p);
-      const int i1 = s.cell & (n1 - 1), i2 = s.cell >> r.log2n1;
-      int d1, d2;
-      if (push_one<R, UNIT, EC>(r, fix_of(r), s, i1, i2, i1, i2, S, K, err, d1, d2)) store_state(P, p, s);
-      nb.add(frame_pow2(i1 - ref1, f1, n1) + d1, frame_any(i2 - ref2, f2, n2) + d2);
-    }
-    nb.reduce(nbox);
-    __syncthreads();
+    const lptr<unsigned char> smem = (lptr<unsigned char>)smem_raw;
+    if constexpr (EC)
+      push_wide<R, UNIT, true>(&r, t, parity, pp, lds_bytes, smem, (lptr<int>)nbox, err);
+    else
+      push_wide_call<R, UNIT>(&r, t, parity, pp, lds_bytes, smem, (lptr<int>)nbox, err);
   }
   // new bounding box of the tile's particles; one that reaches past the
   // frame's edge wraps, so it becomes the whole frame

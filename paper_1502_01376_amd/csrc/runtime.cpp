@@ -1727,7 +1727,10 @@ class Sim : public SimBase {
       need = std::max(need, push_box_bytes(push_cols(std::min(t1, h.d.n1)),
                                            std::min(h.d.T2 + 2 * SLACK2, h.d.n2) + 6, sizeof(R),
                                            h.d.shape == 3 ? 1 : 2));
-    push_lds_ = (int)std::min<long long>(PUSH_LDS_MAX, std::max<long long>(PUSH_LDS_MIN, (need + 511) / 512 * 512));
+    // up to the next piece in which the LDS is given out, less the kernels' static 16 bytes:
+    // what the launch holds anyway
+    need = std::max<long long>(PUSH_LDS_MIN, (need + 16 + LDS_PIECE - 1) / LDS_PIECE * LDS_PIECE - 16);
+    push_lds_ = (int)std::min<long long>(PUSH_LDS_MAX, need);
     // 3D: all the LDS that the occupancy leaves, for the particles' spread
     using O3 = Push3Occupancy<R>;
     if (dim_ == 3) push_lds_ = box3(p1, p2) <= O3::LDS_256 ? O3::LDS_256 : O3::LDS_MAX;

@@ -5,6 +5,8 @@ costs."""
 import numpy as np
 import pytest
 
+from paper_1502_01376_amd import workloads as W
+
 pytestmark = pytest.mark.gpu
 
 
@@ -33,9 +35,46 @@ def _cartesian(hpic, prec, sigma, gamma, **kw):
 # half of the tiles outgrow the boxes of fields and currents at sigma 0.3, three
 # quarters at 1
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
-@pytest.mark.parametrize("shape", [3])
-def test_warm_plasma_stays_in_the_lds(hpic, prec, shape):
-    cold = _cartesian(hpic, prec, 0.0, 20.0, shape=shape)
+@pytest.mark.parametrize("shape,interp", [(2, 0), (2, 1), (3, 0)])
+def test_warm_plasma_stays_in_the_lds(hpic, prec, shape, interp):
+    cold = _cartesian(hpic, prec, 0.0, 20.0, shape=shape, interp=interp)
     for sigma in (0.3, 1.0):
-        warm = _cartesian(hpic, prec, sigma, 1.0, shape=shape)
+        warm = _cartesian(hpic, prec, sigma, 1.0, shape=shape, interp=interp)
         assert warm < 4 * cold, (sigma, warm, cold)
+
+
+# boxes of tiles of 32 x 8 outgrow the LDS in 24 steps at the speed of light, and the whole
+# grid as a tile does from the first on; unequal weights take the general products
+@pytest.mark.parametrize("shape,interp,spread", [(2, 0, 0.0), (2, 1, 0.0), (3, 0, 0.0), (3, 1, 0.0),
+                                                 (2, 0, 0.3), (3, 0, 0.3)])
+def test_particles_outside_the_box_give_the_same_bits(hpic, shape, interp, spread):
+    d = W.drift2d(128, 37, 0.2, 0.2, 0.1, sub=(2, 2), gamma=3.0, sigma_u=4.0, jitter=True,
+                  seed=W.SEED0 + 601, name="warm")
+    d["w"] = d["w"] * (1.0 + spread * np.sin(np.arange(d["w"].size)))
+    ref = None
+    for t1, t2, K in ((3, 1, 1), (32, 8, 24), (128, 37, 24), (16, 4, 24)):
+        sim = hpic.from_workload(d, "fp32", shape=shape, interp=interp)
+        sim.set_tiling(t1, t2, K)
+        sim.step(24)
+        raw = sim.particles_raw(0)
+        o = np.argsort(raw["id"])
+        got = [*sim.fields(0), sim.current_fixed(0)] + [v[..., o] for _, v in sorted(raw.items())]
+        sim.close()
+        ref = ref or got
+        for a, b in zip(got, ref):
+            assert np.array_equal(a, b), (t1, t2, K)
+
+
+@pytest.mark.parametrize("shape", [2, 3])
+def test_fp64_particles_outside_the_box_agree(hpic, shape):
+    d = W.drift2d(128, 37, 0.2, 0.2, 0.1, sub=(2, 2), gamma=3.0, sigma_u=4.0, jitter=True,
+                  seed=W.SEED0 + 602, name="warm")
+    out = []
+    for t1, t2, K in ((3, 1, 1), (32, 8, 12), (128, 37, 12)):
+        sim = hpic.from_workload(d, "fp64", shape=shape)
+        sim.set_tiling(t1, t2, K)
+        sim.step(12)
+        out.append(np.concatenate(sim.fields(0)))
+        sim.close()
+    for o in out[1:]:  # sums of some hundred terms in another order, over 12 steps
+        assert np.abs(out[0] - o).max() <= 1e-11 * np.abs(out[0]).max()
