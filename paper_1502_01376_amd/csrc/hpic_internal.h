@@ -362,12 +362,16 @@ template <class R> __device__ __forceinline__ void half3(R d, R w[3], bool ec) {
     spline3<R>(d, w);
 }
 
+// Contractions spelled out: a tile whose box leaves the LDS takes another path through
+// the code, and gives the same bits.
+__device__ __forceinline__ float fmaq(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmaq(double a, double b, double c) { return __builtin_fma(a, b, c); }
 // Twice the quadratic weights (the gather scales its sums by 1/2 per
 // axis), or twice the energy-conserving gather's along a staggered direction.
 template <class R> __device__ __forceinline__ void spline3x2(R d, R w[3]) {
   const R a = R(0.5) - d, b = R(0.5) + d;
   w[0] = a * a;
-  w[1] = R(1.5) - R(2) * d * d;
+  w[1] = fmaq(R(-2) * d, d, R(1.5));
   w[2] = b * b;
 }
 template <class R> __device__ __forceinline__ void half3x2(R d, R w[3], bool ec) {
@@ -380,10 +384,6 @@ template <class R> __device__ __forceinline__ void half3x2(R d, R w[3], bool ec)
   }
 }
 
-// A gather's sums with their contractions spelled out: a tile whose box leaves the
-// LDS takes them from global memory, and gives the same bits.
-__device__ __forceinline__ float fmaq(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fmaq(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <class R> __device__ __forceinline__ R dot3q(const R w[3], R a, R b, R c) {
   return fmaq(w[2], c, fmaq(w[1], b, w[0] * a));
 }
@@ -662,6 +662,27 @@ struct CellBox {
   }
 };
 
+// Means of the n values whose parts of the sums the workgroup's threads hold.  smem: 16
+// bytes of LDS, free again when this returns.
+__device__ __forceinline__ void group_mean(long long s1, long long s2, int n, unsigned char *smem, int &m1,
+                                           int &m2) {
+  const lptr<unsigned long long> sum = (lptr<unsigned long long>)smem;
+  if (threadIdx.x < 2) sum[threadIdx.x] = 0;
+  __syncthreads();
+  for (int o = 32; o > 0; o >>= 1) {
+    s1 += __shfl_xor(s1, o);
+    s2 += __shfl_xor(s2, o);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    __hip_atomic_fetch_add(sum, (unsigned long long)s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add(sum + 1, (unsigned long long)s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __syncthreads();
+  m1 = (int)((long long)sum[0] / n);
+  m2 = (int)((long long)sum[1] / n);
+  __syncthreads();
+}
+
 // The current box of a tile whose particles have spread too far for the boxes of
 // fields and currents: all of its nodes where they number at most cap, or as many around
 // the particles' mean cell, the margin about the tile the same on all sides.  Holds
@@ -672,16 +693,13 @@ struct WideBox {
     return l1 >= lo1 && l1 <= hi1 && l2 >= lo2 && l2 <= hi2;
   }
 };
-// smem: 16 bytes of LDS, free again when this returns.  Called by the whole workgroup.
+// smem: 16 bytes of LDS.  Called by the whole workgroup.
 template <class R>
 __device__ __forceinline__ WideBox wide_box(const Run<R> &r, const Parts<R> &P, int start, int end,
                                             int ref1, int ref2, int lo1, int hi1, int lo2, int hi2,
                                             int cap, unsigned char *smem) {
   WideBox b{lo1, hi1, lo2, hi2, hi1 - lo1 + 6, hi2 - lo2 + 6};
   if ((long long)b.W * b.H > cap) {
-    const lptr<unsigned long long> sum = (lptr<unsigned long long>)smem;
-    if (threadIdx.x < 2) sum[threadIdx.x] = 0;
-    __syncthreads();
     const int f1 = (r.n1 - r.T1) >> 1, f2 = (r.n2 - r.T2) >> 1;
     long long s1 = 0, s2 = 0;
     for (int p = start + (int)threadIdx.x; p < end; p += PUSH_THREADS) {
@@ -689,17 +707,8 @@ __device__ __forceinline__ WideBox wide_box(const Run<R> &r, const Parts<R> &P, 
       s1 += frame_pow2((cell & (r.n1 - 1)) - ref1, f1, r.n1);
       s2 += frame_any((cell >> r.log2n1) - ref2, f2, r.n2);
     }
-    for (int o = 32; o > 0; o >>= 1) {
-      s1 += __shfl_xor(s1, o);
-      s2 += __shfl_xor(s2, o);
-    }
-    if ((threadIdx.x & 63) == 0) {
-      __hip_atomic_fetch_add(sum, (unsigned long long)s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      __hip_atomic_fetch_add(sum + 1, (unsigned long long)s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    __syncthreads();
-    const int m1 = (int)((long long)sum[0] / (end - start)), m2 = (int)((long long)sum[1] / (end - start));
-    __syncthreads();
+    int m1, m2;
+    group_mean(s1, s2, end - start, smem, m1, m2);
     int W = min(b.W, r.T1 + 6), H = min(b.H, r.T2 + 6);
     if ((long long)W * H > cap) W = min(W, 64);  // a tile that is too large by itself
     for (;;) {

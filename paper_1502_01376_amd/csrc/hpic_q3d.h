@@ -113,6 +113,13 @@ __host__ __device__ constexpr long long q_push_bytes(int w, int h, int M, size_t
   return 8ll * q_row(w, M) * h + (real == 4 ? 4ll * q_field_row(w, M) * (h - 1) : 0);
 }
 
+// Rows that the LDS holds, with the fields or without.
+template <class R>
+__host__ __device__ constexpr int q_push_rows(int w, int M, bool fields) {
+  const int a = 8 * q_row(w, M), f = fields ? 4 * q_field_row(w, M) : 0;
+  return (QPush<R>::LDS + f) / (a + f);
+}
+
 template <class R>
 struct LaunchQ {
   // forward transform of the real-space fields into the master of a parity

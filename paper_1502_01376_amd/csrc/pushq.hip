@@ -29,7 +29,7 @@
 // z columns x radial rows every few steps): the FP32 form stages the fields its
 // particles gather in LDS, and both forms accumulate the current of the tile's
 // box in LDS, which is then added to the global accumulators with one atomic per
-// node (a tile whose particles spread too far gathers and deposits in global
+// node (particles too far from the rest of their tile gather and deposit in global
 // memory).  The deposit's arithmetic (shapes, phases and fluxes of the
 // stored positions, their radius and direction in R) is FP64 in both forms;
 // the FP32 form rounds each contribution once to a 64-bit integer on a fine
@@ -52,7 +52,7 @@ template <class R>
 __device__ __forceinline__ void splineq(R d, R w[3]) {
   const R a = R(0.5) - d, b = R(0.5) + d;
   w[0] = R(0.5) * a * a;
-  w[1] = R(0.75) - d * d;
+  w[1] = fmaq(-d, d, R(0.75));
   w[2] = R(0.5) * b * b;
 }
 
@@ -79,20 +79,22 @@ __device__ __forceinline__ void radial(int ix, R fx, int iy, R fy, int &m, R &d,
   s = rho > R(0) ? Y / rho : R(0);
 }
 
+// a b - c d, the second product rounded.
+template <class R> __device__ __forceinline__ R crossq(R a, R b, R c, R d) { return fmaq(a, b, -(c * d)); }
+
 template <class R>
 __device__ __forceinline__ void borisq(R qmhdt, const R E[3], const R B[3], R u[3]) {
-  const R e0 = qmhdt * E[0], e1 = qmhdt * E[1], e2 = qmhdt * E[2];
-  const R m0 = u[0] + e0, m1 = u[1] + e1, m2 = u[2] + e2;
-  const R ig = rsqrtq(R(1) + m0 * m0 + m1 * m1 + m2 * m2);
+  const R m0 = fmaq(qmhdt, E[0], u[0]), m1 = fmaq(qmhdt, E[1], u[1]), m2 = fmaq(qmhdt, E[2], u[2]);
+  const R ig = rsqrtq(fmaq(m2, m2, fmaq(m1, m1, fmaq(m0, m0, R(1)))));
   const R t0 = qmhdt * B[0] * ig, t1 = qmhdt * B[1] * ig, t2 = qmhdt * B[2] * ig;
-  const R sf = R(2) * rcpq(R(1) + t0 * t0 + t1 * t1 + t2 * t2);
+  const R sf = R(2) * rcpq(fmaq(t2, t2, fmaq(t1, t1, fmaq(t0, t0, R(1)))));
   const R s0 = t0 * sf, s1 = t1 * sf, s2 = t2 * sf;
-  const R p0 = m0 + (m1 * t2 - m2 * t1);
-  const R p1 = m1 + (m2 * t0 - m0 * t2);
-  const R p2 = m2 + (m0 * t1 - m1 * t0);
-  u[0] = m0 + (p1 * s2 - p2 * s1) + e0;
-  u[1] = m1 + (p2 * s0 - p0 * s2) + e1;
-  u[2] = m2 + (p0 * s1 - p1 * s0) + e2;
+  const R p0 = m0 + crossq(m1, t2, m2, t1);
+  const R p1 = m1 + crossq(m2, t0, m0, t2);
+  const R p2 = m2 + crossq(m0, t1, m1, t0);
+  u[0] = fmaq(qmhdt, E[0], m0 + crossq(p1, s2, p2, s1));
+  u[1] = fmaq(qmhdt, E[1], m1 + crossq(p2, s0, p0, s2));
+  u[2] = fmaq(qmhdt, E[2], m2 + crossq(p0, s1, p1, s0));
 }
 
 // Quadratic shape of a coordinate given as cell + offset f in [0,1) along z:
@@ -257,12 +259,8 @@ __device__ __forceinline__ void deposit_q(const Sink &K, int M, const double S0z
   if (MC > 0) M = MC;
   for (int m = 0; m < M; ++m) {
     if (m > 0) {
-      const D t0 = P0r * cta + P0i * sta;
-      P0i = P0i * cta - P0r * sta;
-      P0r = t0;
-      const D t1 = P1r * ctb + P1i * stb;
-      P1i = P1i * ctb - P1r * stb;
-      P1r = t1;
+      next_phase(cta, sta, P0r, P0i);
+      next_phase(ctb, stb, P1r, P1i);
     }
     const D cm = m == 0 ? 1.0 : 2.0;
     const D even = (m & 1) ? -1.0 : 1.0;  // (-1)^m
@@ -333,12 +331,12 @@ __device__ __forceinline__ void deposit_q(const Sink &K, int M, const double S0z
         }
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-          const D w = S0z[a] * k0 + S1z[a] * k1;
+          const D w = fmaq(S0z[a], k0, S1z[a] * k1);
           K.put(row[b], s, 0, a, w, xr);
           if (m > 0) K.put(row[b], s, 1, a, w, xi);
         }
         if (zswitch) {
-          const D w = S0z[3] * k0 + S1z[3] * k1;
+          const D w = fmaq(S0z[3], k0, S1z[3] * k1);
           K.put(row[b], s, 0, 3, w, xr);
           if (m > 0) K.put(row[b], s, 1, 3, w, xi);
         }
@@ -353,7 +351,7 @@ __device__ __forceinline__ void deposit_q(const Sink &K, int M, const double S0z
 #pragma unroll
           for (int a = 0; a < 4; ++a) {
             if (a == 3 && !zswitch) break;
-            const D w = S0z[a] * k0 + S1z[a] * k1;
+            const D w = fmaq(S0z[a], k0, S1z[a] * k1);
             K.put(row[b], s, 0, a, w, Pmr);
             K.put(row[b], s, 1, a, w, Pmi);
           }
@@ -425,91 +423,86 @@ __device__ __forceinline__ PStateQ<R> load_q(const PartsQ<R> &P, int p) {
   return s;
 }
 
-}  // namespace
+// The columns (x .. y) and nearest nodes (z .. w) whose particles a push's LDS boxes
+// hold where a segment's own box is too large for them: as many as fit, around the
+// particles' mean.  Called by the whole workgroup.
+template <class R>
+__device__ __forceinline__ int4 q_window(const RunQ<R> &r, const QSeg *seg, int cols, int rows,
+                                         lptr<unsigned char> smem) {
+  const PartsQ<R> &P = r.pt;
+  const auto s = G(seg);
+  const int start = s->start, end = s->end, fo = (r.n1 - r.sbz) >> 1, z0 = s->tile / r.nbr * r.sbz;
+  int4 w = make_int4(s->zlo, s->zhi, s->rlo, s->rhi);
+  long long sz = 0, sr = 0;
+  for (int p = start + (int)threadIdx.x; p < end; p += 256) {
+    const float x = (float)*elem(P.ix, p) + (float)*elem(P.fx, p);
+    const float y = (float)*elem(P.iy, p) + (float)*elem(P.fy, p);
+    sz += frame_pow2(*elem(P.cell, p) - z0, fo, r.n1);
+    sr += (int)(sqrtf(x * x + y * y) + 0.5f);
+  }
+  int mz, mr;
+  group_mean(sz, sr, end - start, (unsigned char *)smem, mz, mr);
+  auto clamp = [](int &lo, int &hi, int mean, int n) {
+    if (hi - lo < n) return;
+    lo = max(lo, min(mean - (n - 1) / 2, hi - (n - 1)));
+    hi = lo + n - 1;
+  };
+  clamp(w.x, w.y, mz, cols);
+  clamp(w.z, w.w, mr, rows);
+  return w;
+}
 
-// One workgroup per (run, segment of a tile).  A segment's box (from the previous push, or the
-// whole tile right after a sort) bounds the cells of its particles: z columns
-// relative to the tile and nearest integer-r nodes; a move is less than a cell,
-// so the current box is columns lo - 2 .. hi + 3 and rows lo - 2 .. hi + 2 (ghost
-// rows folded onto rows 0 and 1).  In the FP32 form the fields over columns
-// lo - 1 .. hi + 2 and rows lo - 2 .. hi + 1 are staged next to it.  Every row of
-// either box holds all components and modes, with CW columns each (CW - 2 of the
-// fields), so that an address found for one row serves them all.  MC: the mode
-// count when every run of the launch has it (the gather's mode loop is then
-// unrolled and the deposit's has a constant trip count), or 0.
-//
-// What bounds it: the instructions and the LDS atomics of about 145 contributions
-// a particle, with three modes.  On 2048 x 256 cells (8 particles each over 250
-// rows, three modes, FP32) a push takes 397 us, 1098 with a box per wave of 64
-// particles, which carried a halo of 8 x 8 nodes for 8 cells and tested every
-// contribution; FP64 on 256 x 61 with two modes 37 us, 56 before.  Of that:
-// tiles in place of waves (a third of the nodes flushed and staged per particle)
-// and contributions without tests, 744; particles in the order of their cells, so
-// that the lanes of an atomic meet different nodes (LDS cycles 374 to 290 us) and
-// 16 x 4 tiles, 672; workgroups of 256 threads, three per compute unit, 424; rows and
-// order for the banks, 397.
-template <class R, int MC, int CW>
-__global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
-    k_q_push_deposit(const RunQ<R> *__restrict__ runs, const Item *__restrict__ items, int parity,
-                     unsigned *err) {
+// A segment with boxes of CW columns for the particles in columns clo .. chi and at nodes
+// mlo .. mhi: all of them (ALL), or the others gather and deposit in global memory.  st is
+// the thread's first particle, loaded.
+template <class R, int MC, int CW, bool ALL, bool STAGE>
+__device__ __forceinline__ void q_push(const RunQ<R> &r, const QSeg *qseg, int parity, int clo, int chi,
+                                       int mlo, int mhi, PStateQ<R> st, lptr<unsigned char> smem,
+                                       lptr<int> nbox, unsigned *err) {
   constexpr int NT = 256;
   using A = typename AccQ<R>::T;
   using V2 = typename LdsC<R>::T;
-  constexpr bool STAGE = sizeof(R) == 4;
   constexpr int FWD = CW - 2;
-  __shared__ int nbox[4];
-  const Item it = items[blockIdx.x];
-  const RunQ<R> &r = runs[it.run];
-  const gptr<QSeg> seg = G(r.seg) + it.a;
+  const gptr<QSeg> seg = G((QSeg *)qseg);
   const int t = seg->tile, start = seg->start, end = seg->end;
-  if (start >= end) return;
   const PartsQ<R> P = r.pt;
-  PStateQ<R> st{};
-  if (start + (int)threadIdx.x < end) st = load_q(P, start + (int)threadIdx.x);
   const int n1 = r.n1, M = MC > 0 ? MC : r.M;
   const long long plane = r.plane;
   const int z0 = (t / r.nbr) * r.sbz;   // first column of the tile
   const int fo = (n1 - r.sbz) >> 1;     // the tile's frame along z: [-fo, n1 - fo), centred on it
-  const int zlo = seg->zlo - 2, W = seg->zhi - seg->zlo + 6;
-  const int rlo = max(0, seg->rlo - 2), H = min(seg->rhi + 2, r.n2) - rlo + 1;
-  if (threadIdx.x == 0) {
-    nbox[0] = nbox[2] = 1 << 30;
-    nbox[1] = nbox[3] = -(1 << 30);
-  }
   const int per = 2 * M - 1, NS = 3 * per;
   const int RS = q_row(CW, M);                  // one row of the current box
   // one row of the field box: six components of mode 0 (the real part, all that
   // the gather takes of it), then of each further mode, complex; its used size
-  const int FS = q_field_row(CW, M), Wf = W - 2, Hf = H - 1;
-  const bool local = W <= CW && q_push_bytes(CW, H, M, sizeof(R)) <= (long long)QPush<R>::LDS;
-  const lptr<A> box = (lptr<A>)smem_raw;
-  const lptr<R> fbox = (lptr<R>)(smem_raw + (size_t)RS * H * sizeof(A));
+  const int FS = q_field_row(CW, M);
+  const int zlo = clo - 2, W = chi - clo + 6, Wf = W - 2;
+  const int rlo = max(0, mlo - 2), H = min(mhi + 2, r.n2) - rlo + 1, Hf = H - 1;
+  const lptr<A> box = (lptr<A>)smem;
+  const lptr<R> fbox = (lptr<R>)(smem + RS * H * (int)sizeof(A));
   const gptr<const V2> F = G((const V2 *)r.F);
-  if (local) {
-    for (int q = threadIdx.x; q < RS * H; q += NT) box[q] = 0;
-    if constexpr (STAGE) {
-      // half a wave per (row, mode): its six components' loads all in flight
-      // before their LDS stores
-      const int cc = threadIdx.x & 31;
-      if (cc < Wf)
-        for (int e = (int)threadIdx.x >> 5; e < Hf * M; e += NT / 32) {
-          const int j = e / M, m = e - j * M;
-          const gptr<const V2> src = F + (long long)(6 * m) * plane + (long long)(rlo + j) * n1 +
-                         wrap_pow2(z0 + zlo + 1 + cc, n1);
-          V2 v[6];
+  for (int q = threadIdx.x; q < RS * H; q += NT) box[q] = 0;
+  if constexpr (STAGE) {
+    // half a wave per (row, mode): its six components' loads all in flight
+    // before their LDS stores
+    const int cc = threadIdx.x & 31;
+    if (cc < Wf)
+      for (int e = (int)threadIdx.x >> 5; e < Hf * M; e += NT / 32) {
+        const int j = e / M, m = e - j * M;
+        const gptr<const V2> src = F + (long long)(6 * m) * plane + (long long)(rlo + j) * n1 +
+                       wrap_pow2(z0 + zlo + 1 + cc, n1);
+        V2 v[6];
 #pragma unroll
-          for (int c = 0; c < 6; ++c) v[c] = src[c * plane];
-          const lptr<R> row = fbox + j * FS;
-          if (m == 0) {
+        for (int c = 0; c < 6; ++c) v[c] = src[c * plane];
+        const lptr<R> row = fbox + j * FS;
+        if (m == 0) {
 #pragma unroll
-            for (int c = 0; c < 6; ++c) row[c * FWD + cc] = v[c].x;
-          } else {
-            const lptr<V2> crow = (lptr<V2>)(row + (12 * m - 6) * FWD);
+          for (int c = 0; c < 6; ++c) row[c * FWD + cc] = v[c].x;
+        } else {
+          const lptr<V2> crow = (lptr<V2>)(row + (12 * m - 6) * FWD);
 #pragma unroll
-            for (int c = 0; c < 6; ++c) crow[c * FWD + cc] = v[c];
-          }
+          for (int c = 0; c < 6; ++c) crow[c * FWD + cc] = v[c];
         }
-    }
+      }
   }
   __syncthreads();
   int blo = 1 << 30, bhi = -(1 << 30), rlo2 = 1 << 30, rhi2 = -(1 << 30);
@@ -526,6 +519,7 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
     radial<R>(ix, fx, iy, fy, mri, dri, ct, sn);
     const int mrh = dri >= R(0) ? mri : mri - 1;
     const R drh = dri >= R(0) ? dri - R(0.5) : dri + R(0.5);
+    const bool in = ALL || (relz >= clo && relz <= chi && mri >= mlo && mri <= mhi);
     // ---- gather: integer (i) and half (h) stencils along z and r, weights
     // doubled along both
     R wzi[3], wzh[3], wri[3], wrh[3];
@@ -539,7 +533,8 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
     // recurrence (m = 0: the real part alone)
     R Ec[3] = {0, 0, 0}, Bc[3] = {0, 0, 0};
     R Pr = 1, Pi = 0;
-    constexpr int MU = MC > 0 ? MC : 1;
+    // (four modes in line spill 17 registers of the FP32 form: push of 1024 x 160 198 us, 180 so)
+  constexpr int MU = STAGE && MC > 3 ? 1 : MC > 0 ? MC : 1;
     int rri[3], rrh[3];
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
@@ -547,7 +542,7 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
       rri[b] = ji < 0 ? -ji : ji;
       rrh[b] = jh < 0 ? -jh - 1 : jh;
     }
-    if (STAGE && local) {
+    if (STAGE && in) {
       // first node of each stencil row, integer (i) or half (h) along z and r
       int oi[3], oh[3];
       const int c0 = relz - zlo - 2;
@@ -632,22 +627,21 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
         }
       }
     }
-    const R E[3] = {Ec[0], Ec[1] * ct - Ec[2] * sn, Ec[1] * sn + Ec[2] * ct};
-    const R B[3] = {Bc[0], Bc[1] * ct - Bc[2] * sn, Bc[1] * sn + Bc[2] * ct};
+    const R E[3] = {Ec[0], crossq(Ec[1], ct, Ec[2], sn), fmaq(Ec[1], sn, Ec[2] * ct)};
+    const R B[3] = {Bc[0], crossq(Bc[1], ct, Bc[2], sn), fmaq(Bc[1], sn, Bc[2] * ct)};
     borisq<R>(R(0.25) * r.qmhdt, E, B, u);
-    R v[3];
+    // moves in cells
+    R mz, mx, my;
     {
 #pragma clang fp contract(off)
       R s = R(1) + u[0] * u[0];
       s = s + u[1] * u[1];
       s = s + u[2] * u[2];
       const R ig = inv_gamma(s);
-      v[0] = u[0] * ig;
-      v[1] = u[1] * ig;
-      v[2] = u[2] * ig;
+      mz = r.dtdz * (u[0] * ig);
+      mx = r.dtdr * (u[1] * ig);
+      my = r.dtdr * (u[2] * ig);
     }
-    // moves in cells
-    const R mz = r.dtdz * v[0], mx = r.dtdr * v[1], my = r.dtdr * v[2];
     bool ok = true;
     if (!(isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]) && isfinite(mz) && isfinite(mx) &&
           isfinite(my))) {
@@ -696,10 +690,10 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
       // azimuthal velocity at the mid point times dt: the move (mx, my) dr
       // projected on the azimuthal direction of the mid point
       const D xmid = D(ix) + (D)fx + 0.5 * (D)mx, ymid = D(iy) + (D)fy + 0.5 * (D)my;
-      const D rmid = sqrt(xmid * xmid + ymid * ymid);
-      const D vthdt = rmid > 0.0 ? (xmid * (D)my - ymid * (D)mx) / rmid * (D)r.dr : 0.0;
+      const D rmid = sqrt(fmaq(xmid, xmid, ymid * ymid));
+      const D vthdt = rmid > 0.0 ? crossq(xmid, (D)my, ymid, (D)mx) / rmid * (D)r.dr : 0.0;
       const D g = (D)st.qw * (D)r.wscale;
-      if (local) {
+      if (in) {
         deposit_move<MC>(MoveQ{cz, dz, mri, mrb, (D)fz, (D)gz, (D)dri, (D)drb, (D)ct, (D)sn, (D)ctb,
                                (D)stb, g, vthdt},
                          M, [&](int bz) {
@@ -716,26 +710,24 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
   rlo2 = wmin(rlo2);
   rhi2 = wmax(rhi2);
   if ((threadIdx.x & 63) == 0) {
-    atomicMin(&nbox[0], blo);
-    atomicMax(&nbox[1], bhi);
-    atomicMin(&nbox[2], rlo2);
-    atomicMax(&nbox[3], rhi2);
+    atomicMin((int *)nbox + 0, blo);
+    atomicMax((int *)nbox + 1, bhi);
+    atomicMin((int *)nbox + 2, rlo2);
+    atomicMax((int *)nbox + 3, rhi2);
   }
   __syncthreads();
-  if (local) {
-    // add the box to the global accumulators: half a wave per (row, slot)
-    A *J = r.J[parity];
-    const int cc = threadIdx.x & 31;
-    if (cc < W) {
-      const int col = wrap_pow2(z0 + zlo + cc, n1);
-      for (int e = (int)threadIdx.x >> 5; e < H * NS; e += NT / 32) {
-        const int j = e / NS, slot = e - j * NS;
-        const A v = box[j * RS + slot * CW + cc];
-        if (v == A(0)) continue;
-        const int c = slot / per, s2 = slot - c * per;
-        const int m = (s2 + 1) >> 1, part = s2 == 0 ? 0 : (s2 - 1) & 1;
-        glob_add(G(J) + ((long long)(m * 3 + c) * plane + (long long)(rlo + j) * n1 + col) * 2 + part, v);
-      }
+  // add the box to the global accumulators: half a wave per (row, slot)
+  A *J = r.J[parity];
+  const int cc = threadIdx.x & 31;
+  if (cc < W) {
+    const int col = wrap_pow2(z0 + zlo + cc, n1);
+    for (int e = (int)threadIdx.x >> 5; e < H * NS; e += NT / 32) {
+      const int j = e / NS, slot = e - j * NS;
+      const A v = box[j * RS + slot * CW + cc];
+      if (v == A(0)) continue;
+      const int c = slot / per, s2 = slot - c * per;
+      const int m = (s2 + 1) >> 1, part = s2 == 0 ? 0 : (s2 - 1) & 1;
+      glob_add(G(J) + ((long long)(m * 3 + c) * plane + (long long)(rlo + j) * n1 + col) * 2 + part, v);
     }
   }
   // the box of the pushed particles; one that reaches past the frame's edge
@@ -750,6 +742,98 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
     seg->zhi = hi;
     seg->rlo = nbox[2];
     seg->rhi = nbox[3];
+  }
+}
+template <class R>
+__device__ __noinline__ int4 q_window_call(const RunQ<R> *run, const QSeg *seg, int cols, int rows,
+                                           lptr<unsigned char> smem) {
+  return q_window<R>(*run, seg, cols, rows, smem);
+}
+// With the box laid around the particles' mean, as large as fits.  Out of line, so that it
+// takes no registers from a segment that fits.  Up to three modes leave room for 32
+// columns, up to two for the fields of the FP32 form; with more, the fields come through the
+// cache.  (256 x 128, eight particles a cell, thermal spread 0.1, FP32, push: one mode 24 us,
+// 37 with 24 columns; two 40 and 63; four 137, 213 with their fields in the LDS.)
+template <class R, int MC, int CW>
+__device__ __noinline__ void q_push_spread(const RunQ<R> *run, const QSeg *seg, int parity,
+                                           lptr<unsigned char> smem, lptr<int> nbox, unsigned *err) {
+  constexpr int CS = MC > 0 && MC < 4 && CW > 16 ? 32 : CW;
+  constexpr bool STAGE = sizeof(R) == 4 && MC > 0 && MC < 3;
+  const RunQ<R> &r = *run;
+  const int first = G(seg)->start + (int)threadIdx.x;
+  const int4 w = q_window<R>(r, seg, CS - 5, q_push_rows<R>(CS, MC > 0 ? MC : r.M, STAGE) - 4, smem);
+  PStateQ<R> st{};
+  if (first < G(seg)->end) st = load_q(r.pt, first);
+  q_push<R, MC, CS, false, STAGE>(r, seg, parity, __builtin_amdgcn_readfirstlane(w.x),
+                                  __builtin_amdgcn_readfirstlane(w.y), __builtin_amdgcn_readfirstlane(w.z),
+                                  __builtin_amdgcn_readfirstlane(w.w), st, smem, nbox, err);
+}
+
+}  // namespace
+
+// One workgroup per (run, segment of a tile).  A segment's box (from the previous push, or the
+// whole tile right after a sort) bounds the cells of its particles: z columns
+// relative to the tile and nearest integer-r nodes; a move is less than a cell,
+// so the current box is columns lo - 2 .. hi + 3 and rows lo - 2 .. hi + 2 (ghost
+// rows folded onto rows 0 and 1).  In the FP32 form the fields over columns
+// lo - 1 .. hi + 2 and rows lo - 2 .. hi + 1 are staged next to it.  Every row of
+// either box holds all components and modes, with CW columns each (CW - 2 of the
+// fields), so that an address found for one row serves them all.  MC: the mode
+// count when every run of the launch has it (the gather's mode loop is then
+// unrolled and the deposit's has a constant trip count), or 0.
+//
+// What bounds it: the instructions and the LDS atomics of about 145 contributions
+// a particle, with three modes.  On 2048 x 256 cells (8 particles each over 250
+// rows, three modes, FP32) a push takes 385 us, 1098 with a box per wave of 64
+// particles, which carried a halo of 8 x 8 nodes for 8 cells and tested every
+// contribution; FP64 on 256 x 61 with two modes 37 us, 56 before.  Of that:
+// tiles in place of waves (a third of the nodes flushed and staged per particle)
+// and contributions without tests, 744; particles in the order of their cells, so
+// that the lanes of an atomic meet different nodes (LDS cycles 374 to 290 us) and
+// 16 x 4 tiles, 672; workgroups of 256 threads, three per compute unit, 424; rows and
+// order for the banks, 397; a path without global memory for the segments that fit,
+// 385.  Warm columns, with a thermal spread of 0.1, sorted every 64 steps (512 x 160, eight a
+// cell): 68 us with two modes, 588 with whole segments in global memory; with one mode 34
+// and 212; FP64 form 110 and 681, 71 and 238.
+template <class R, int MC, int CW>
+__global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
+    k_q_push_deposit(const RunQ<R> *__restrict__ runs, const Item *__restrict__ items, int parity,
+                     unsigned *err) {
+  __shared__ int nbox[4];
+  const Item it = items[blockIdx.x];
+  const RunQ<R> &r = runs[it.run];
+  const gptr<const QSeg> seg = G((const QSeg *)r.seg) + it.a;
+  const int start = seg->start, end = seg->end;
+  if (start >= end) return;
+  PStateQ<R> st{};
+  if (start + (int)threadIdx.x < end) st = load_q(r.pt, start + (int)threadIdx.x);
+  if (threadIdx.x == 0) {
+    nbox[0] = nbox[2] = 1 << 30;
+    nbox[1] = nbox[3] = -(1 << 30);
+  }
+  const int rows = q_push_rows<R>(CW, MC > 0 ? MC : r.M, sizeof(R) == 4);
+  int clo = seg->zlo, chi = seg->zhi, mlo = seg->rlo, mhi = seg->rhi;
+  const bool fits = chi - clo + 6 <= CW && min(mhi + 2, r.n2) - max(0, mlo - 2) < rows;
+  const lptr<unsigned char> smem = (lptr<unsigned char>)smem_raw;
+  // A path of its own for the segments that fit, with no global memory in it, is the faster
+  // one in FP32 and with one or two modes (2048 x 256, three modes, FP32: 385 us, 411 in
+  // one path; FP64 on 1024 x 160: 81 and 92 with one mode, 193 and 190 with three).
+  if constexpr (sizeof(R) == 4 || MC == 1 || MC == 2) {
+    if (fits)
+      q_push<R, MC, CW, true, sizeof(R) == 4>(r, r.seg + it.a, parity, clo, chi, mlo, mhi, st, smem,
+                                              (lptr<int>)nbox, err);
+    else
+      q_push_spread<R, MC, CW>(&r, r.seg + it.a, parity, smem, (lptr<int>)nbox, err);
+  } else {
+    if (!fits) {
+      const int4 w = q_window_call<R>(&r, r.seg + it.a, CW - 5, rows - 4, smem);
+      clo = __builtin_amdgcn_readfirstlane(w.x);
+      chi = __builtin_amdgcn_readfirstlane(w.y);
+      mlo = __builtin_amdgcn_readfirstlane(w.z);
+      mhi = __builtin_amdgcn_readfirstlane(w.w);
+    }
+    q_push<R, MC, CW, false, false>(r, r.seg + it.a, parity, clo, chi, mlo, mhi, st, smem, (lptr<int>)nbox,
+                                    err);
   }
 }
 

@@ -43,6 +43,28 @@ def test_warm_plasma_stays_in_the_lds(hpic, prec, shape, interp):
         assert warm < 4 * cold, (sigma, warm, cold)
 
 
+def _column(hpic, prec, modes, uth):
+    gen = np.random.default_rng(9)
+    n1, n2, fill, dz, dr = 256, 128, 70, 0.1, 0.2
+    shape = (n1, fill, 8)
+    r = (np.arange(fill)[None, :, None] + gen.random(shape)) * dr
+    th = 2 * np.pi * gen.random(shape)
+    z = (np.arange(n1)[:, None, None] + gen.random(shape)) * dz
+    x = np.stack([v.ravel() for v in (z, r * np.cos(th), r * np.sin(th))])
+    u = uth * gen.standard_normal(x.shape)
+    w = (1e-3 * 2 * np.pi * r * dr * dz / 8).ravel()
+    return _push_us(hpic, hpic.config(n1, n2, dz, dr, 0.04, precision=prec, modes=modes), x, u, w, 64)
+
+
+# a spread of 0.1 moves the particles by 2.6 columns and 1.3 rows between two sorts, and
+# three in a hundred out of their boxes
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("modes", [1, 2, 4])
+def test_warm_column_stays_in_the_lds(hpic, prec, modes):
+    cold, warm = _column(hpic, prec, modes, 1e-3), _column(hpic, prec, modes, 0.1)
+    assert warm < 4.5 * cold, (warm, cold)
+
+
 # boxes of tiles of 32 x 8 outgrow the LDS in 24 steps at the speed of light, and the whole
 # grid as a tile does from the first on; unequal weights take the general products
 @pytest.mark.parametrize("shape,interp,spread", [(2, 0, 0.0), (2, 1, 0.0), (3, 0, 0.0), (3, 1, 0.0),
