@@ -685,7 +685,10 @@ __device__ __forceinline__ void q_push(const RunQ<R> &r, const QSeg *qseg, int p
       *elem(P.uz, p) = u[0];
       *elem(P.ux, p) = u[1];
       *elem(P.uy, p) = u[2];
-      // ---- deposit (FP64)
+    }
+    // ---- deposit (FP64); a particle at rest adds nothing but exact zeros (512 x 128, three
+    // modes, FP32, all at rest: 28 us, 40 with the zeros)
+    if (ok && (mz != R(0) || mx != R(0) || my != R(0))) {
       using D = double;
       // azimuthal velocity at the mid point times dt: the move (mx, my) dr
       // projected on the azimuthal direction of the mid point

@@ -65,6 +65,28 @@ def test_warm_column_stays_in_the_lds(hpic, prec, modes):
     assert warm < 4.5 * cold, (warm, cold)
 
 
+@pytest.mark.parametrize("modes", [2, 3, 4])
+def test_particles_at_rest_deposit_nothing(hpic, modes):
+    """They leave out their contributions, all exact zeros, which take more than a third of a
+    push, and the current of their neighbours is the same without them."""
+    assert _column(hpic, "fp32", modes, 0.0) < 0.66 * _column(hpic, "fp32", modes, 1e-3)
+    gen = np.random.default_rng(11)
+    n1, n2, n = 64, 24, 4000
+    r, th = gen.random(n) * 12 * 0.2, 2 * np.pi * gen.random(n)
+    x = np.stack([gen.random(n) * n1 * 0.1, r * np.cos(th), r * np.sin(th)])
+    u = 0.3 * gen.standard_normal((3, n))
+    u[:, n // 2:] = 0.0
+    out = []
+    for m in (n, n // 2):
+        sim = hpic.Sim([hpic.config(n1, n2, 0.1, 0.2, 0.04, precision="fp32", modes=modes)])
+        sim.set_particles(0, x[:, :m], u[:, :m], np.full(m, 0.01))
+        sim.step(1)
+        out.append([sim.current_mode(0, c, k) for c in range(3) for k in range(modes)])
+        sim.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
 # boxes of tiles of 32 x 8 outgrow the LDS in 24 steps at the speed of light, and the whole
 # grid as a tile does from the first on; unequal weights take the general products
 @pytest.mark.parametrize("shape,interp,spread", [(2, 0, 0.0), (2, 1, 0.0), (3, 0, 0.0), (3, 1, 0.0),
