@@ -29,12 +29,12 @@ template <> struct AccQ<float> { using T = long long; };
 template <> struct AccQ<double> { using T = double; };
 
 // The cells of a tile (at most 64) that hold more than k particles, and how many
-// particles of the tile have a lower rank than k in their cell.
+// particles of the tile have a lower rank than k in their cell.  A tile has as many of
+// these as cells: 16 bytes a cell.
 struct QLevel {
   unsigned long long mask;
   int base, pad;
 };
-constexpr int Q_LEVELS = 64;
 
 // Part of a tile's particles that one workgroup pushes, in storage order, and the
 // box of their cells: z columns relative to the tile, radial nodes.  Segment t is
@@ -67,7 +67,7 @@ struct RunQ {
   PartsQ<R> pt2;     // the other particle buffer: target of the periodic sort
   int *skey, *srank; // [np]: cell of each particle (tile by tile) and its rank in it
   int *ccnt;         // [nbins sbz sbr]: particles per cell
-  QLevel *level;     // [nbins][Q_LEVELS]: order of a tile's particles by rank
+  QLevel *level;     // [nbins][sbz sbr]: order of a tile's particles by rank
   int *sbin;         // [nbins + 1]: particles per tile, then their exclusive prefix
                      // sums (the first particle of each tile after a sort)
   QSeg *seg;         // [nbins + np / Q_SEG]: the push's work
@@ -97,7 +97,7 @@ template <> struct QPush<double> {
 };
 // Columns of the push's current box for tiles tz wide (literal in the kernels): the
 // tile, the stencils' five and three of drift.
-__host__ __device__ constexpr int q_push_cols(int tz) { return tz > 8 ? 24 : tz > 4 ? 16 : 12; }
+__host__ __device__ constexpr int q_push_cols(int tz) { return tz > 8 ? 24 : 16; }
 // Rows of its boxes for w columns of M modes: 64-bit accumulators, and in the FP32
 // form the fields next to them (the real part of mode 0, both parts of the
 // others), one row less and two columns less.  Neighbouring rows lie half of
@@ -107,10 +107,6 @@ __host__ __device__ constexpr int q_row(int w, int M) {
 }
 __host__ __device__ constexpr int q_field_row(int w, int M) {
   return (12 * M - 6) * (w - 2) + ((32 - (12 * M - 6) * (w - 2)) & 63);
-}
-// LDS bytes of the boxes for h rows.
-__host__ __device__ constexpr long long q_push_bytes(int w, int h, int M, size_t real) {
-  return 8ll * q_row(w, M) * h + (real == 4 ? 4ll * q_field_row(w, M) * (h - 1) : 0);
 }
 
 // Rows that the LDS holds, with the fields or without.
@@ -142,9 +138,9 @@ struct LaunchQ {
   static void sort(RunQ<R> *run_dev, int np, int nbins, hipStream_t s);
   // gather, Boris, move and per-mode deposit into J[parity]; items (run, tile);
   // modes: the mode count of every run in the launch, or 0 when they differ;
-  // tz: the widest tile's z columns
+  // tz: the widest tile's z columns; staged: with the fields in the LDS (FP32 form)
   static void push_deposit(const RunQ<R> *runs, const Item *items, int nitems, int parity,
-                           int modes, int tz, unsigned *err, hipStream_t s);
+                           int modes, int tz, bool staged, unsigned *err, hipStream_t s);
   // per (run, 3 m + c, row): accumulator J[parity] -> complex current, forward
   // transform, correction and filter, background; clears J[parity ^ 1]
   static void fft_j(const RunQ<R> *runs, const Item *items, int nitems, int parity, int maxn1,

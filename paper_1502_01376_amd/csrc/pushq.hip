@@ -229,9 +229,9 @@ __device__ __forceinline__ void glob_add(gptr<double> p, double v) {
 // the fourth row to the waves with a lane that changes it along r (rswitch, wave-
 // uniform); everything else is added without a test.
 template <int MC, class Sink>
-__device__ __forceinline__ void deposit_q(const Sink &K, int M, const double S0z[4],
-                                          const double S1z[4], const double S0r[4],
-                                          const double S1r[4], int br, bool zswitch, bool rswitch,
+__device__ __forceinline__ void deposit_q(const Sink &K, int M, double S0z[4],
+                                          double S1z[4], double S0r[4],
+                                          double S1r[4], int br, bool zswitch, bool rswitch,
                                           double cta, double sta, double ctb, double stb, double g,
                                           double vthdt) {
   using D = double;
@@ -258,6 +258,10 @@ __device__ __forceinline__ void deposit_q(const Sink &K, int M, const double S0z
   D P1r = 1, P1i = 0;  // phase at the new position
   if (MC > 0) M = MC;
   for (int m = 0; m < M; ++m) {
+    if constexpr (MC == 0) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a) asm volatile("" : "+v"(S0z[a]), "+v"(S1z[a]), "+v"(S0r[a]), "+v"(S1r[a]));
+    }
     if (m > 0) {
       next_phase(cta, sta, P0r, P0i);
       next_phase(ctb, stb, P1r, P1i);
@@ -609,6 +613,14 @@ __device__ __forceinline__ void q_push(const RunQ<R> &r, const QSeg *qseg, int p
       }
 #pragma unroll MU
       for (int m = 0; m < M; ++m) {
+        // not all nodes' loads at once: they spilled with a general mode count, and cost FP64
+        // pushes of one and two modes 2 to 4% (three and four gain 25% by them)
+        constexpr bool FEW = MC == 0 || (sizeof(R) == 8 && MC < 3);
+        if constexpr (MC == 0) {
+          // keeps the nodes' addresses from being formed before the loop and spilled
+#pragma unroll
+          for (int a = 0; a < 3; ++a) asm volatile("" : "+v"(ozi[a]), "+v"(ozh[a]), "+v"(rri[a]), "+v"(rrh[a]));
+        }
         if (m > 0) next_phase(ct, sn, Pr, Pi);
         const bool odd = m & 1;
         R vx[6], vy[6];
@@ -616,8 +628,10 @@ __device__ __forceinline__ void q_push(const RunQ<R> &r, const QSeg *qseg, int p
         const gptr<const V2> Fm = F + 6 * m * plane;
         gather_q<R>(Fm, wzh, ozh, wri, rri, gi, odd, false, rs, vx[0], vy[0]);
         gather_q<R>(Fm + plane, wzi, ozi, wrh, rrh, gh, odd, true, rs, vx[1], vy[1]);
+        if constexpr (FEW) asm volatile("" ::: "memory");
         gather_q<R>(Fm + 2 * plane, wzi, ozi, wri, rri, gi, odd, true, rs, vx[2], vy[2]);
         gather_q<R>(Fm + 3 * plane, wzi, ozi, wrh, rrh, gh, odd, false, rs, vx[3], vy[3]);
+        if constexpr (FEW) asm volatile("" ::: "memory");
         gather_q<R>(Fm + 4 * plane, wzh, ozh, wri, rri, gi, odd, true, rs, vx[4], vy[4]);
         gather_q<R>(Fm + 5 * plane, wzh, ozh, wrh, rrh, gh, odd, true, rs, vx[5], vy[5]);
 #pragma unroll
@@ -798,7 +812,7 @@ __device__ __noinline__ void q_push_spread(const RunQ<R> *run, const QSeg *seg, 
 // 385.  Warm columns, with a thermal spread of 0.1, sorted every 64 steps (512 x 160, eight a
 // cell): 68 us with two modes, 588 with whole segments in global memory; with one mode 34
 // and 212; FP64 form 110 and 681, 71 and 238.
-template <class R, int MC, int CW>
+template <class R, int MC, int CW, bool STAGE>
 __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
     k_q_push_deposit(const RunQ<R> *__restrict__ runs, const Item *__restrict__ items, int parity,
                      unsigned *err) {
@@ -814,7 +828,7 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
     nbox[0] = nbox[2] = 1 << 30;
     nbox[1] = nbox[3] = -(1 << 30);
   }
-  const int rows = q_push_rows<R>(CW, MC > 0 ? MC : r.M, sizeof(R) == 4);
+  const int rows = q_push_rows<R>(CW, MC > 0 ? MC : r.M, STAGE);
   int clo = seg->zlo, chi = seg->zhi, mlo = seg->rlo, mhi = seg->rhi;
   const bool fits = chi - clo + 6 <= CW && min(mhi + 2, r.n2) - max(0, mlo - 2) < rows;
   const lptr<unsigned char> smem = (lptr<unsigned char>)smem_raw;
@@ -823,8 +837,8 @@ __global__ void __launch_bounds__(256, QPush<R>::WAVES_PER_SIMD)
   // one path; FP64 on 1024 x 160: 81 and 92 with one mode, 193 and 190 with three).
   if constexpr (sizeof(R) == 4 || MC == 1 || MC == 2) {
     if (fits)
-      q_push<R, MC, CW, true, sizeof(R) == 4>(r, r.seg + it.a, parity, clo, chi, mlo, mhi, st, smem,
-                                              (lptr<int>)nbox, err);
+      q_push<R, MC, CW, true, STAGE>(r, r.seg + it.a, parity, clo, chi, mlo, mhi, st, smem, (lptr<int>)nbox,
+                                     err);
     else
       q_push_spread<R, MC, CW>(&r, r.seg + it.a, parity, smem, (lptr<int>)nbox, err);
   } else {
@@ -976,10 +990,10 @@ __global__ void __launch_bounds__(256) k_q_sort_tiles(const RunQ<R> *__restrict_
   const int area = r.sbz * r.sbr;
   const int cnt = lane < area ? G(r.ccnt)[t * area + lane] : 0;
   int base = 0;
-  for (int k = 0; k < Q_LEVELS; ++k) {
+  for (int k = 0; k < area; ++k) {
     const unsigned long long mask = __ballot(cnt > k);
     if (!mask) break;
-    if (lane == 0) r.level[(long long)t * Q_LEVELS + k] = QLevel{mask, base, 0};
+    if (lane == 0) r.level[(long long)t * area + k] = QLevel{mask, base, 0};
     base += __popcll(mask);
   }
   int n = cnt;
@@ -1074,8 +1088,8 @@ __global__ void __launch_bounds__(256) k_q_sort_scatter(const RunQ<R> *__restric
   if (p >= r.np) return;
   const int area = r.sbz * r.sbr, c = r.skey[p], t = c / area, place = c - t * area, k = r.srank[p];
   int d = r.sbin[t];
-  if (k < Q_LEVELS) {
-    const QLevel l = r.level[(long long)t * Q_LEVELS + k];
+  if (k < area) {
+    const QLevel l = r.level[(long long)t * area + k];
     d += l.base + __popcll(l.mask & ((1ull << place) - 1));
   } else {
     for (int i = 0; i < area; ++i) d += min(r.ccnt[t * area + i], i < place ? k + 1 : k);
@@ -1119,23 +1133,26 @@ void LaunchQ<R>::sort(RunQ<R> *run_dev, int np, int nbins, hipStream_t s) {
 
 template <class R>
 void LaunchQ<R>::push_deposit(const RunQ<R> *runs, const Item *items, int nitems, int parity,
-                              int modes, int tz, unsigned *err, hipStream_t s) {
+                              int modes, int tz, bool staged, unsigned *err, hipStream_t s) {
   if (nitems <= 0) return;
   // kernels with the mode loops unrolled for the common mode counts, and literal
   // column strides for the tile widths the runtime uses
-  constexpr int C16 = q_push_cols(16), C8 = q_push_cols(8), C4 = q_push_cols(4);
-  auto k = k_q_push_deposit<R, 0, C4>;
-  if (tz > 8)
-    k = modes == 1   ? k_q_push_deposit<R, 1, C16>
-        : modes == 2 ? k_q_push_deposit<R, 2, C16>
-        : modes == 3 ? k_q_push_deposit<R, 3, C16>
-        : modes == 4 ? k_q_push_deposit<R, 4, C16>
-                     : k_q_push_deposit<R, 0, C16>;
-  else if (tz > 4)
-    k = modes == 2   ? k_q_push_deposit<R, 2, C8>
-        : modes == 3 ? k_q_push_deposit<R, 3, C8>
-        : modes == 4 ? k_q_push_deposit<R, 4, C8>
-                     : k_q_push_deposit<R, 0, C8>;
+  constexpr int C16 = q_push_cols(16), C8 = q_push_cols(8);
+  constexpr bool S = sizeof(R) == 4;
+  auto k = k_q_push_deposit<R, 0, C8, false>;
+  if (S && !staged)
+    ;  // (tiles of up to 8 columns)
+  else if (tz > 8)
+    k = modes == 1   ? k_q_push_deposit<R, 1, C16, S>
+        : modes == 2 ? k_q_push_deposit<R, 2, C16, S>
+        : modes == 3 ? k_q_push_deposit<R, 3, C16, S>
+        : modes == 4 ? k_q_push_deposit<R, 4, C16, S>
+                     : k_q_push_deposit<R, 0, C16, S>;
+  else
+    k = modes == 2   ? k_q_push_deposit<R, 2, C8, S>
+        : modes == 3 ? k_q_push_deposit<R, 3, C8, S>
+        : modes == 4 ? k_q_push_deposit<R, 4, C8, S>
+                     : k_q_push_deposit<R, 0, C8, S>;
   hipLaunchKernelGGL(k, dim3(nitems), dim3(256), (size_t)QPush<R>::LDS, s, runs, items, parity, err);
 }
 template <class R>
@@ -1150,9 +1167,9 @@ void LaunchQ<R>::jbg(const RunQ<R> *run_dev, int np, double *jbg, hipStream_t s)
 }
 
 template void LaunchQ<float>::push_deposit(const RunQ<float> *, const Item *, int, int, int, int,
-                                           unsigned *, hipStream_t);
+                                           bool, unsigned *, hipStream_t);
 template void LaunchQ<double>::push_deposit(const RunQ<double> *, const Item *, int, int, int, int,
-                                            unsigned *, hipStream_t);
+                                            bool, unsigned *, hipStream_t);
 template void LaunchQ<float>::sort(RunQ<float> *, int, int, hipStream_t);
 template void LaunchQ<double>::sort(RunQ<double> *, int, int, hipStream_t);
 template void LaunchQ<float>::rho(const RunQ<float> *, int, int, double2 *, hipStream_t);

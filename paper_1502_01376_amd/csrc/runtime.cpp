@@ -2129,7 +2129,7 @@ class SimQ : public SimBase {
         ++since_sort_;
         mark(HP_K_PUSH_DEPOSIT, true);
         LaunchQ<R>::push_deposit(d_runs_, d_push_, n_push_, parity_, common_modes(), push_tz_,
-                                 d_err_, stream_);
+                                 push_staged_, d_err_, stream_);
         mark(HP_K_PUSH_DEPOSIT, false);
         mark(HP_K_FFT_J, true);
         LaunchQ<R>::fft_j(d_runs_, d_jitems_, n_jitems_, parity_, maxn1_, stream_);
@@ -2714,15 +2714,22 @@ class SimQ : public SimBase {
     return HP_OK;
   }
   // Push tiles: 4 x 2 bins of sbz z columns x sbr radial rows, 8 to 16 x 2 to 4
-  // cells, halved until the boxes of every run's modes fit the LDS (three modes:
-  // 16 x 4, four: 8 x 4).  The particles are sorted by tile, so a change needs a
+  // cells, halved until the boxes of every run's modes fit the LDS (FP32, three modes:
+  // 16 x 4, four: 8 x 4, eight: 8 x 2).  The particles are sorted by tile, so a change needs a
   // sort before the next push.
   int set_bins(int sbz, int sbr) {
-    int tz = 4 * std::min(std::max(sbz, 2), 4), tr = 2 * std::min(sbr, 2), modes = 1;
+    int tr = 2 * std::min(sbr, 2), modes = 1;
     for (const RunHostQ &h : runs_) modes = std::max(modes, h.d.M);
-    // rows: the tile's, its far edge, the stencil's four and one of drift
-    while (tz * tr > 1 && q_push_bytes(q_push_cols(tz), tr + 6, modes, sizeof(R)) > QPush<R>::LDS)
-      (tz > tr ? tz : tr) /= 2;
+    // The FP32 form's fields lie in the LDS next to the currents up to four modes.  More
+    // would leave tiles of 4 x 4 to 4 x 1 cells for it, each with the halo of a box
+    // around them: through the cache, five modes 126 us against 147 (512 x 128, eight
+    // particles a cell), eight 195 against 857.
+    push_staged_ = sizeof(R) == 4 && modes <= 4;
+    int tz = 4 * std::min(std::max(sbz, 2), sizeof(R) == 8 || push_staged_ ? 4 : 2);
+    // rows: the tile's, its far edge, the stencil's four and one of drift (eight modes, FP32:
+    // 195 us with 8 x 2 cells, 247 with 4 x 4)
+    while (tz * tr > 1 && q_push_rows<R>(q_push_cols(tz), modes, push_staged_) < tr + 6)
+      (tz > 2 * tr || tr == 1 ? tz : tr) /= 2;
     // few workgroups: half as high (256 x 61, two modes, FP64: 35.6 us with 256 of 16 x 4
     // cells, 27.8 with 512 of 16 x 2; 1024 x 150: 203 with 2432, 202 with 4800)
     long long tiles = 0;
@@ -2746,7 +2753,7 @@ class SimQ : public SimBase {
       if ((rc = alloc(&d.sbin, (size_t)d.nbins + 1)) ||
           (rc = alloc(&d.ssum, (size_t)(d.nbins + 1023) / 1024 + 1)) ||
           (rc = alloc(&d.ccnt, (size_t)d.nbins * d.sbz * d.sbr)) ||
-          (rc = alloc(&d.level, (size_t)d.nbins * Q_LEVELS)))
+          (rc = alloc(&d.level, (size_t)d.nbins * d.sbz * d.sbr)))
         return rc;
     }
     sbz_ = sbz;
@@ -2856,6 +2863,7 @@ class SimQ : public SimBase {
   // particle sort: push tiles of 4 x 2 bins of sbz_ z columns x sbr_ radial rows,
   // every sort_interval_ steps, and before the first step after a load
   int push_tz_ = 1;  // z columns of the tiles
+  bool push_staged_ = false;  // the push holds its fields in the LDS
   int sbz_ = 4, sbr_ = 2, sort_interval_ = 64, since_sort_ = 0;
 };
 

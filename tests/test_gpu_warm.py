@@ -43,7 +43,7 @@ def test_warm_plasma_stays_in_the_lds(hpic, prec, shape, interp):
         assert warm < 4 * cold, (sigma, warm, cold)
 
 
-def _column(hpic, prec, modes, uth):
+def _column(hpic, prec, modes, uth, dt=0.04):
     gen = np.random.default_rng(9)
     n1, n2, fill, dz, dr = 256, 128, 70, 0.1, 0.2
     shape = (n1, fill, 8)
@@ -53,7 +53,7 @@ def _column(hpic, prec, modes, uth):
     x = np.stack([v.ravel() for v in (z, r * np.cos(th), r * np.sin(th))])
     u = uth * gen.standard_normal(x.shape)
     w = (1e-3 * 2 * np.pi * r * dr * dz / 8).ravel()
-    return _push_us(hpic, hpic.config(n1, n2, dz, dr, 0.04, precision=prec, modes=modes), x, u, w, 64)
+    return _push_us(hpic, hpic.config(n1, n2, dz, dr, dt, precision=prec, modes=modes), x, u, w, 64)
 
 
 # a spread of 0.1 moves the particles by 2.6 columns and 1.3 rows between two sorts, and
