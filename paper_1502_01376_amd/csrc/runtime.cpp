@@ -205,38 +205,54 @@ static bool device_pointer(const void *p) {
   return a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged;
 }
 
-// Reads device arrays into the caller's doubles through two pinned pieces, kept with
-// the handle: one is converted while the other is copied.  (Through a buffer of the
-// array's size, allocated and paged in for each read, 2048 x 257 complex values
-// took 488 us, 210 so.)
+// Reads device arrays into the caller's doubles.  Large ones go through two pinned pieces,
+// kept from the first such read on: one is converted while the other is copied.  (Through
+// a buffer of the array's size, allocated and paged in for each read, 2048 x 257 complex
+// values took 488 us, 210 so; 1 MiB 141 and 84, half of that 65 and 59.)  Small ones
+// go through a pinned block that is made with the handle (8 KB: 25 us against 36; made in the
+// first read, it cost that one 30).  Without pinned memory, and between the two, a read
+// takes a buffer of its own.
 class Reader {
  public:
   ~Reader() {
-    if (buf_) (void)hipHostFree(buf_);
+    if (small_) (void)hipHostFree(small_);
+    if (pieces_) (void)hipHostFree(pieces_);
   }
+  void init() { pinned(small_, SMALL); }
   template <class R>
   int read(const R *src, size_t n, double *out, hipStream_t s) {
-    if (!buf_) HIPCHK(hipHostMalloc(&buf_, 2 * PIECE, hipHostMallocDefault));
     constexpr size_t PER = PIECE / sizeof(R);
+    const bool large = n >= PER, small = n * sizeof(R) <= SMALL && small_;
+    if (large) pinned(pieces_, 2 * PIECE);
+    std::vector<R> own(small || (large && pieces_) ? 0 : std::min(n, PER));
+    R *const buf = small ? (R *)small_ : own.empty() ? (R *)pieces_ : own.data();
+    const size_t other = own.empty() && large ? PER : 0;  // the second piece
     auto copy = [&](size_t i) {
       return i >= n ? hipSuccess
-                    : hipMemcpyAsync((char *)buf_ + (i / PER & 1) * PIECE, src + i,
-                                     std::min(PER, n - i) * sizeof(R), hipMemcpyDeviceToHost, s);
+                    : hipMemcpyAsync(buf + (i / PER & 1) * other, src + i, std::min(PER, n - i) * sizeof(R),
+                                     hipMemcpyDeviceToHost, s);
     };
     HIPCHK(copy(0));
     for (size_t i = 0; i < n; i += PER) {
       HIPCHK(hipStreamSynchronize(s));
-      HIPCHK(copy(i + PER));
-      const R *p = (const R *)((char *)buf_ + (i / PER & 1) * PIECE);
+      if (other) HIPCHK(copy(i + PER));
+      const R *p = buf + (i / PER & 1) * other;
       const size_t m = std::min(PER, n - i);
       for (size_t k = 0; k < m; ++k) out[i + k] = (double)p[k];
+      if (!other) HIPCHK(copy(i + PER));
     }
     return HP_OK;
   }
 
  private:
-  static constexpr size_t PIECE = 1 << 20;
-  void *buf_ = nullptr;
+  static constexpr size_t SMALL = 1 << 16, PIECE = 1 << 20;
+  void *small_ = nullptr, *pieces_ = nullptr;
+  static void pinned(void *&p, size_t bytes) {
+    if (!p && hipHostMalloc(&p, bytes, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      p = nullptr;
+    }
+  }
 };
 
 struct hp_sim {
@@ -284,6 +300,7 @@ class Sim : public SimBase {
 
   int init(const hp_config *cfgs, int nruns) {
     HIPCHK(hipGetDevice(&device_));
+    reader_.init();
     {
       int rc;
       if ((rc = scratch_address(device_, &scratch_))) return rc;
@@ -1964,6 +1981,7 @@ class SimQ : public SimBase {
 
   int init(const hp_config *cfgs, int nruns) {
     HIPCHK(hipGetDevice(&device_));
+    reader_.init();
     runs_.resize(nruns);
     std::vector<Item> rows, upd, gitems, jitems;
     for (int i = 0; i < nruns; ++i) {
