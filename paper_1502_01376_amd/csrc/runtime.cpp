@@ -984,15 +984,17 @@ class Sim : public SimBase {
       return true;
     };
     for (const auto &sh : shapes) {
+      // shapes that come to the same tiles are timed once
       std::vector<int> key;
+      const auto [p1, p2] = joined(sh[0], sh[1]);
       for (const RunHost &h : runs_) {
-        key.push_back(std::min(sh[0], h.d.n1));
-        key.push_back(std::min(sh[1], h.d.n2));
-        key.push_back(std::min(sh[1], h.d.n3));
+        key.push_back(std::min(p1, h.d.n1));
+        key.push_back(std::min(p2, h.d.n2));
+        key.push_back(std::min(p2, h.d.n3));
       }
       if (std::find(seen.begin(), seen.end(), key) != seen.end()) continue;
       seen.push_back(key);
-      if (!fits(sh[0], sh[1])) continue;
+      if (!fits(p1, p2)) continue;
       if (left < 2 * K0) break;
       double ms;
       if ((rc = trial(sh[0], sh[1], K0, &ms))) break;
@@ -1683,10 +1685,6 @@ class Sim : public SimBase {
     const int rc = h2d(d_runs_, v.data(), v.size());
     return rc ? rc : upload_antennas();
   }
-  // Sort chunks: (run, first particle, count <= SORT_CHUNK) over all particles.
-  // Particle tiles of every run (t1 x t2 cells, clipped to the grid), the
-  // push work list and the push LDS budget; the caller uploads the runs and
-  // re-sorts.
   // Tiles of t1 x t2 x t2 cells in all 3D runs, and the LDS for the current box of
   // particles that drift by part of a cell, but not apart.
   long long tiles3(int t1, int t2) const {
@@ -1696,20 +1694,27 @@ class Sim : public SimBase {
     return n;
   }
   static long long box3(int t1, int t2) { return 24ll * (t1 + 6) * (t2 + 6) * (t2 + 6); }
+  // The tiles that the push works on where t1 x t2 are asked for.
+  // 3D: it takes 2 x 2 neighbours in x2 and x3 together, or 2 in x1, for as
+  // long as the box fits and at least 1024 workgroups remain: fewer halo nodes a
+  // particle, and two particles a thread to share them (512 x 128 x 128, two
+  // particles a cell: 8 x 4 x 4 cells 1620 us, 8 x 8 x 8 1200; 256 x 40 x 40, 800
+  // workgroups of 8 x 8 x 8: 90 us, 3200 of 8 x 4 x 4 83)
+  std::array<int, 2> joined(int t1, int t2) const {
+    for (; dim_ == 3; (t1 <= t2 ? t1 : t2) *= 2) {
+      const int q1 = t1 <= t2 ? 2 * t1 : t1, q2 = t1 <= t2 ? t2 : 2 * t2;
+      if (box3(q1, q2) > Push3Occupancy<R>::LDS_MAX * 7 / 8 || tiles3(q1, q2) < 1024) break;
+    }
+    return {t1, t2};
+  }
 
+  // Particle tiles of every run (t1 x t2 cells, clipped to the grid), the
+  // push work list and the push LDS budget; the caller uploads the runs and
+  // re-sorts.
   int make_tiles(int t1, int t2) {
     drop_graphs();
     std::vector<Item> tiles, cblocks;
-    // 3D: the push takes 2 x 2 neighbours in x2 and x3 together, or 2 in x1, for as
-    // long as the box fits and at least 1024 workgroups remain: fewer halo nodes a
-    // particle, and two particles a thread to share them (512 x 128 x 128, two
-    // particles a cell: 8 x 4 x 4 cells 1620 us, 8 x 8 x 8 1200; 256 x 40 x 40, 800
-    // workgroups of 8 x 8 x 8: 90 us, 3200 of 8 x 4 x 4 83)
-    int p1 = t1, p2 = t2;
-    for (; dim_ == 3; (p1 <= p2 ? p1 : p2) *= 2) {
-      const int q1 = p1 <= p2 ? 2 * p1 : p1, q2 = p1 <= p2 ? p2 : 2 * p2;
-      if (box3(q1, q2) > Push3Occupancy<R>::LDS_MAX * 7 / 8 || tiles3(q1, q2) < 1024) break;
-    }
+    const auto [p1, p2] = joined(t1, t2);
     for (int i = 0; i < (int)runs_.size(); ++i) {
       Run<R> &d = runs_[i].d;
       int **arrs[] = {&d.tile_start, &d.cell_cnt, &d.tile_box, &d.blk_sum, &d.blk_base};
@@ -1767,6 +1772,7 @@ class Sim : public SimBase {
     return true;
   }
 
+  // Sort chunks: (run, first particle, count <= SORT_CHUNK) over all particles.
   int rebuild_sort_items() {
     drop_graphs();  // captured launches hold the old item lists and counts
     std::vector<Item> items;

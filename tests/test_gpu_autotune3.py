@@ -1,0 +1,29 @@
+"""The autotuner in 3D, where the push joins neighbouring tiles: shapes that come to the same
+tiles are timed once."""
+import pytest
+
+from paper_1502_01376_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(8, 4), (16, 4), (8, 8), (16, 2), (4, 4), (32, 2)]
+
+
+@pytest.mark.parametrize("n", [(256, 64, 64), (32, 12, 10)])
+def test_every_candidate_is_another_tiling(hpic, n):
+    d = W.drift3d(*n, spread=0.0, sigma_u=1e-3, gamma=3.0, jitter=True, sub=(1, 1, 1), seed=W.SEED0 + 611,
+                  name="autotune3")
+    sim = hpic.from_workload(d, "fp32")
+    tiles = set()
+    for t1, t2 in SHAPES:
+        sim.set_tiling(t1, t2, 16)
+        sim.profile(True)
+        sim.step(1)
+        tiles.add(sim.push_stats()["tiles"])
+        sim.profile(False)
+    sim.set_tiling(8, 4, 16)
+    tune = sim.autotune(2 * (6 * 16 + 8 + 32 + 64 + 128))
+    sim.close()
+    # these grids give every tiling another number of tiles; the sort intervals but the
+    # first follow
+    assert tune["candidates"] == len(tiles) + 4
