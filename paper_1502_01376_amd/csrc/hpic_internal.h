@@ -353,15 +353,6 @@ template <class R> __device__ __forceinline__ void line3(R d, R w[3]) {
   w[1] = R(1) - (d < R(0) ? -d : d);
   w[2] = d > R(0) ? d : R(0);
 }
-// Weights of a half-node (staggered) stencil: quadratic, or linear for the
-// energy-conserving gather.
-template <class R> __device__ __forceinline__ void half3(R d, R w[3], bool ec) {
-  if (ec)
-    line3<R>(d, w);
-  else
-    spline3<R>(d, w);
-}
-
 // Contractions spelled out: a tile whose box leaves the LDS takes another path through
 // the code, and gives the same bits.
 __device__ __forceinline__ float fmaq(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
@@ -381,6 +372,24 @@ template <class R> __device__ __forceinline__ void half3x2(R d, R w[3], bool ec)
     for (int k = 0; k < 3; ++k) w[k] = R(2) * w[k];
   } else {
     spline3x2<R>(d, w);
+  }
+}
+
+// Half the quadratic weights, or the energy-conserving gather's: the other axis's doubled
+// ones then need no factor, and no partial sum exceeds the largest field.
+template <class R> __device__ __forceinline__ void spline3h(R d, R w[3]) {
+  const R h = R(0.5) * d, a = R(0.25) - h, b = R(0.25) + h;
+  w[0] = a * a;
+  w[1] = fmaq(-h, d, R(0.375));
+  w[2] = b * b;
+}
+template <class R> __device__ __forceinline__ void half3h(R d, R w[3], bool ec) {
+  if (ec) {
+    line3<R>(d, w);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k] = R(0.5) * w[k];
+  } else {
+    spline3h<R>(d, w);
   }
 }
 

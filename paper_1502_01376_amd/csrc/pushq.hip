@@ -524,12 +524,12 @@ __device__ __forceinline__ void q_push(const RunQ<R> &r, const QSeg *qseg, int p
     const int mrh = dri >= R(0) ? mri : mri - 1;
     const R drh = dri >= R(0) ? dri - R(0.5) : dri + R(0.5);
     const bool in = ALL || (relz >= clo && relz <= chi && mri >= mlo && mri <= mhi);
-    // ---- gather: integer (i) and half (h) stencils along z and r, weights
-    // doubled along both
+    // ---- gather: integer (i) and half (h) stencils along z, weights halved, and r,
+    // weights doubled
     R wzi[3], wzh[3], wri[3], wrh[3];
     const int upz = fz >= R(0.5);
-    spline3x2<R>(fz - R(upz), wzi);
-    half3x2<R>(fz - R(0.5), wzh, r.interp != 0);
+    spline3h<R>(fz - R(upz), wzi);
+    half3h<R>(fz - R(0.5), wzh, r.interp != 0);
     spline3x2<R>(dri, wri);
     half3x2<R>(drh, wrh, r.interp != 0);
     const bool gi = mri == 0, gh = mrh == 0;  // ghost row in the stencil
@@ -643,7 +643,7 @@ __device__ __forceinline__ void q_push(const RunQ<R> &r, const QSeg *qseg, int p
     }
     const R E[3] = {Ec[0], crossq(Ec[1], ct, Ec[2], sn), fmaq(Ec[1], sn, Ec[2] * ct)};
     const R B[3] = {Bc[0], crossq(Bc[1], ct, Bc[2], sn), fmaq(Bc[1], sn, Bc[2] * ct)};
-    borisq<R>(R(0.25) * r.qmhdt, E, B, u);
+    borisq<R>(r.qmhdt, E, B, u);
     // moves in cells
     R mz, mx, my;
     {
