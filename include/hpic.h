@@ -59,7 +59,9 @@ extern "C" {
 #define HP_ENOMEM (-3)   /* device allocation failed */
 #define HP_EDEVICE (-4)  /* HIP runtime error or no device */
 #define HP_ERANGE (-5)   /* particle moved a cell or more, or fixed-point headroom exceeded */
-#define HP_ENUMERIC (-6) /* non-finite particle momentum or position */
+#define HP_ENUMERIC (-6) /* non-finite particle momentum or position (2D with
+                            quadratic shape and momentum-conserving gather: also a field above 1/4
+                            of the precision's largest number; 3D: above 1/8) */
 #define HP_ESTATE (-7)   /* call out of order (e.g. step before particles) */
 
 #define HP_GEOM_2D 2

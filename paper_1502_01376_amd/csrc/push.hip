@@ -67,7 +67,8 @@ struct LdsFields {
 };
 
 // Factor of gather2's result: weights along both axes are doubled in the
-// momentum-conserving gather.
+// momentum-conserving gather (a field above 1/4 of the largest number is then
+// reported as non-finite).
 template <class R, bool EC> constexpr R GATHER_SCALE = EC ? R(1) : R(0.25);
 
 // Quadratic gather (Appendix A): momentum-conserving (every component uses the
