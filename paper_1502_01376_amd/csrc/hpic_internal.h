@@ -471,10 +471,12 @@ __device__ __forceinline__ double inv_gamma(double s) {
 }
 // 1/g with g = sqrt(s), both correctly rounded, for s >= 1: no scaling against
 // underflow is needed there, which leaves half the instructions of the general
-// square root and division.  g: the hardware root is within one unit, the
-// residuals of its neighbours decide.  1/g: two residual corrections of the
-// hardware reciprocal.  (Equal to the general operations for every float s >=
-// 1, checked exhaustively; infinity gives 0.)
+// square root and division.  The method is the usual one with a fused multiply-add
+// (P. Markstein, Computation of elementary functions on the IBM RISC System/6000
+// processor, IBM J. Res. Dev. 34, 1990): g, the hardware root is within one unit and
+// the exact residuals of its neighbours decide; 1/g, two residual corrections of the
+// hardware reciprocal.  (A test compares every significand with either parity of the
+// exponent, beyond which both only scale; infinity gives 0.)
 __device__ __forceinline__ float inv_gamma(float s) {
 #pragma clang fp contract(off)
   float g = __builtin_amdgcn_sqrtf(s);
