@@ -464,10 +464,12 @@ class Sim : public SimBase {
   static int update_threads(const Run<R> &d, int strip) {
     return d.dim == 3 ? d.rows * d.nk : ((d.n2 + strip - 1) / strip) * d.nk;
   }
-  // Rows per thread of the 2D update.  A long strip reads each row once (2048 x
-  // 512: 27.6 us with strips of 8, 32.9 with 2), but leaves too few threads on
-  // small grids: 1024 x 300 18.0 -> 12.0 us with strips of 2, four 256 x 256
-  // 13.3 -> 10.7, and 64 x 32 10.3 -> 7.0, 6.5 with single rows.
+  // Rows per thread of the 2D update.  A long strip reads each row once, but leaves
+  // too few threads on small grids.  Strips of 8 against 2, by threads of 8 rows: 512 x
+  // 512 (32768) 11.7 and 10.9 us, 1024 x 300 (38912) 16.5 and 11.7, 1024 x 384 (49152)
+  // 12.4 and 13.2, 1024 x 512 (65536) 13.4 and 17.2.  Of 2 against 1, by threads of 2
+  // rows: 64 x 64 (2048) 6.5 and 6.9, 128 x 128 (8192) 6.5 and 6.4, 256 x 256 (32768) 7.8
+  // and 7.5, 512 x 256 (65536) 7.7 and 9.1: level up to there.
   int update_strip() const {
     long long rows8 = 0, rows2 = 0;
     for (const RunHost &h : runs_) {
@@ -1697,9 +1699,11 @@ class Sim : public SimBase {
   // The tiles that the push works on where t1 x t2 are asked for.
   // 3D: it takes 2 x 2 neighbours in x2 and x3 together, or 2 in x1, for as
   // long as the box fits and at least 1024 workgroups remain: fewer halo nodes a
-  // particle, and two particles a thread to share them (512 x 128 x 128, two
-  // particles a cell: 8 x 4 x 4 cells 1620 us, 8 x 8 x 8 1200; 256 x 40 x 40, 800
-  // workgroups of 8 x 8 x 8: 90 us, 3200 of 8 x 4 x 4 83)
+  // particle, and two particles a thread to share them.  Push of 8 x 8 x 8 against 8 x
+  // 4 x 4 cells with two and eight particles a cell, by workgroups of 8 x 8 x 8: 128 x 48
+  // x 48 (576) 72 and 198 us against 69 and 161, 256 x 40 x 40 (800) 91 and 252 against
+  // 86 and 215, 128 x 64 x 64 (1024) 93 and 258 against 104 and 260, 256 x 128 x 128
+  // (8192) 617 and 1949 against 708 and 1913.
   std::array<int, 2> joined(int t1, int t2) const {
     for (; dim_ == 3; (t1 <= t2 ? t1 : t2) *= 2) {
       const int q1 = t1 <= t2 ? 2 * t1 : t1, q2 = t1 <= t2 ? t2 : 2 * t2;
@@ -2737,9 +2741,9 @@ class SimQ : public SimBase {
     since_sort_ = sort_interval_;  // sort before the first step
     return HP_OK;
   }
-  // Push tiles: 4 x 2 bins of sbz z columns x sbr radial rows, 8 to 16 x 2 to 4
-  // cells, halved until the boxes of every run's modes fit the LDS (FP32, three modes:
-  // 16 x 4, four: 8 x 4, eight: 8 x 2).  The particles are sorted by tile, so a change needs a
+  // Push tiles: 4 sbz z columns x 2 sbr radial rows within 8 to 16 (FP32, more than four
+  // modes: 8) x 2 to 4 cells, halved until the boxes of every run's modes fit the LDS
+  // (FP32, three modes: 16 x 4, four: 8 x 4, eight: 8 x 2).  The particles are sorted by tile, so a change needs a
   // sort before the next push.
   int set_bins(int sbz, int sbr) {
     int tr = 2 * std::min(sbr, 2), modes = 1;
@@ -2754,8 +2758,11 @@ class SimQ : public SimBase {
     // 195 us with 8 x 2 cells, 247 with 4 x 4)
     while (tz * tr > 1 && q_push_rows<R>(q_push_cols(tz), modes, push_staged_) < tr + 6)
       (tz > 2 * tr || tr == 1 ? tz : tr) /= 2;
-    // few workgroups: half as high (256 x 61, two modes, FP64: 35.6 us with 256 of 16 x 4
-    // cells, 27.8 with 512 of 16 x 2; 1024 x 150: 203 with 2432, 202 with 4800)
+    // Few workgroups: half as high.  Push with 4 against 2 rows, two modes, FP64, eight
+    // and 32 particles a cell, by tiles of 4 rows: 256 x 61 (256) 40 and 104 us against 35
+    // and 72, 512 x 92 (736) 78 and 187 against 80 and 185, 512 x 124 (992) 90 and 287
+    // against 103 and 246, 1024 x 152 (2432) 210 with eight against 230.  Few particles a
+    // tile would have the line at 400, many beyond 1000.
     long long tiles = 0;
     for (const RunHostQ &h : runs_)
       tiles += (long long)((h.d.n1 + tz - 1) / tz) * ((h.d.n2 + tr - 1) / tr);
@@ -2884,7 +2891,7 @@ class SimQ : public SimBase {
   std::vector<Event2> events_;
   double kms_[HP_NK] = {0};
   int64_t kn_[HP_NK] = {0};
-  // particle sort: push tiles of 4 x 2 bins of sbz_ z columns x sbr_ radial rows,
+  // particle sort: push tiles after bins of sbz_ z columns x sbr_ radial rows,
   // every sort_interval_ steps, and before the first step after a load
   int push_tz_ = 1;  // z columns of the tiles
   bool push_staged_ = false;  // the push holds its fields in the LDS
