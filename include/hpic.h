@@ -255,7 +255,8 @@ int hp_get_tiling(hp_sim *sim, hp_tune *out);
 /* Autotuner: advances every run by exactly nsteps steps (as hp_step) while
  * timing candidate tile shapes and then sort intervals on the live runs, each
  * over two sort blocks, and keeps the fastest (also for later hp_step calls).
- * With too few steps the remaining candidates are skipped.  Synchronous.
+ * With too few steps the remaining candidates are skipped; steps that none
+ * takes come first, untimed.  Synchronous.
  * out may be NULL. */
 int hp_autotune(hp_sim *sim, int32_t nsteps, hp_tune *out);
 
