@@ -803,7 +803,8 @@ __device__ __noinline__ void q_push_spread(const RunQ<R> *run, const QSeg *seg, 
 // a particle, with three modes.  On 2048 x 256 cells (8 particles each over 250
 // rows, three modes, FP32) a push takes 385 us, 1098 with a box per wave of 64
 // particles, which carried a halo of 8 x 8 nodes for 8 cells and tested every
-// contribution; FP64 on 256 x 61 with two modes 37 us, 56 before.  Of that:
+// contribution; FP64 on 256 x 61 with two modes 36 us (28 in the 64 steps after a load,
+// until the second sort), 56 before.  Of that:
 // tiles in place of waves (a third of the nodes flushed and staged per particle)
 // and contributions without tests, 744; particles in the order of their cells, so
 // that the lanes of an atomic meet different nodes (LDS cycles 374 to 290 us) and
