@@ -538,7 +538,7 @@ __device__ __forceinline__ void q_push(const RunQ<R> &r, const QSeg *qseg, int p
     R Ec[3] = {0, 0, 0}, Bc[3] = {0, 0, 0};
     R Pr = 1, Pi = 0;
     // (four modes in line spill 17 registers of the FP32 form: push of 1024 x 160 198 us, 180 so)
-  constexpr int MU = STAGE && MC > 3 ? 1 : MC > 0 ? MC : 1;
+    constexpr int MU = STAGE && MC > 3 ? 1 : MC > 0 ? MC : 1;
     int rri[3], rrh[3];
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
