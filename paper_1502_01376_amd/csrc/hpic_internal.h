@@ -759,14 +759,14 @@ constexpr int PUSH_LDS_MIN = 16384;
 constexpr int PUSH_LDS_MAX = 64512;  // with the static LDS, under 64 KiB
 constexpr int LDS_PIECE = 1280;      // a compute unit's 160 KiB are given out in pieces of these
 // The 3D push.  FP32 form: 4 waves per SIMD (128 registers), four workgroups of 256
-// threads per compute unit with LDS_256 bytes each, or two of NT_MAX = 512 with
-// LDS_MAX for tiles that need more.  FP64 form: 2 waves per SIMD (256 registers),
-// two workgroups of 256.
+// threads per compute unit with LDS_256 bytes each (three with LDS_3), or two of NT_MAX =
+// 512 with LDS_MAX for tiles that need more.  FP64 form: 2 waves per SIMD (256
+// registers), two workgroups of 256.
 template <class R> struct Push3Occupancy {
-  static constexpr int WAVES_PER_SIMD = 2, NT_MAX = 256, LDS_256 = 80896, LDS_MAX = 80896;
+  static constexpr int WAVES_PER_SIMD = 2, NT_MAX = 256, LDS_256 = 80896, LDS_3 = 80896, LDS_MAX = 80896;
 };
 template <> struct Push3Occupancy<float> {
-  static constexpr int WAVES_PER_SIMD = 4, NT_MAX = 512, LDS_256 = 40448, LDS_MAX = 80896;
+  static constexpr int WAVES_PER_SIMD = 4, NT_MAX = 512, LDS_256 = 40448, LDS_3 = 53248, LDS_MAX = 80896;
 };
 
 // ---------------------------------------------------------------- launches

@@ -684,11 +684,14 @@ k_push_deposit3(const Run<R> *__restrict__ runs, const Item *__restrict__ items,
     hi[d] = tbox[2 * d + 1];
   }
   const int W = hi[0] - lo[0] + 6, H = hi[1] - lo[1] + 6, FW = W - 2, FH = H - 2;
-  // Slabs of Z planes of cells whose two boxes both fit; none: through global memory.
+  // Slabs of Z planes of cells whose two boxes both fit; none, or more of their nodes than
+  // 64 a particle: through global memory (64 x 33 x 33, one particle a cell, thermal spread
+  // 2: 160 us, 217 in slabs alone; from 32 a particle on: 166, 16: 181).
   const int all = hi[2] - lo[2] + 1;
   const int jplane = 24 * (int)min((long long)W * H, 1ll << 20);
   const int fplane = 6 * (int)sizeof(R) * (int)min((long long)FW * FH, 1ll << 20);
-  const int Z = min(all, min(lds_bytes / jplane - 5, lds_bytes / fplane - 3));
+  int Z = min(all, min(lds_bytes / jplane - 5, lds_bytes / fplane - 3));
+  if (Z > 0 && Z < all && (long long)((all + Z - 1) / Z) * (Z + 5) * W * H > 64ll * (tile_end - tile_first)) Z = 0;
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -730,7 +733,7 @@ void Launch<R>::push_deposit3(const Run<R> *runs, const Item *items, int nitems,
                               int pp, int lds_bytes, unsigned *err, unsigned *stats,
                               hipStream_t s) {
   if (nitems <= 0) return;
-  const bool wide = lds_bytes > Push3Occupancy<R>::LDS_256;
+  const bool wide = lds_bytes > Push3Occupancy<R>::LDS_3;
   constexpr int NT = Push3Occupancy<R>::NT_MAX;
   hipLaunchKernelGGL((wide ? k_push_deposit3<R, NT> : k_push_deposit3<R, 256>), dim3(nitems),
                      dim3(wide ? NT : 256), lds_bytes, s, runs, items, parity, pp, lds_bytes, err,

@@ -1774,9 +1774,17 @@ class Sim : public SimBase {
     // what the launch holds anyway
     need = std::max<long long>(PUSH_LDS_MIN, (need + 16 + LDS_PIECE - 1) / LDS_PIECE * LDS_PIECE - 16);
     push_lds_ = (int)std::min<long long>(PUSH_LDS_MAX, need);
-    // 3D: all the LDS that the occupancy leaves, for the particles' spread
+    // 3D: all the LDS that the occupancy leaves, for the particles' spread.  Few tiles have
+    // a third or half of a compute unit's to themselves anyway (FP32, four particles a
+    // cell, thermal spread 0 / 0.1 / 0.5, push: 32 x 22 x 21, 144 tiles: 22 / 25 / 61 us,
+    // 25 / 65 / 188 with LDS_256; 128 x 37 x 45, 1920 tiles: 89 / 113 / 256 and 82 / 247 / 927
+    // with LDS_256).
     using O3 = Push3Occupancy<R>;
-    if (dim_ == 3) push_lds_ = box3(p1, p2) <= O3::LDS_256 ? O3::LDS_256 : O3::LDS_MAX;
+    constexpr int CUS = 256;
+    if (dim_ == 3)
+      push_lds_ = box3(p1, p2) > O3::LDS_256 || tiles.size() <= 2 * CUS ? O3::LDS_MAX
+                  : tiles.size() <= 3 * CUS                              ? O3::LDS_3
+                                                                         : O3::LDS_256;
     if (d_tiles_) release(d_tiles_);
     if (d_cblocks_) release(d_cblocks_);
     d_tiles_ = d_cblocks_ = nullptr;

@@ -122,3 +122,42 @@ def test_fp64_particles_outside_the_box_agree(hpic, shape):
         sim.close()
     for o in out[1:]:  # sums of some hundred terms in another order, over 12 steps
         assert np.abs(out[0] - o).max() <= 1e-11 * np.abs(out[0]).max()
+
+
+def _box(hpic, sigma, n, ppc=4):
+    gen = np.random.default_rng(13)
+    d, np_ = 0.2, ppc * n[0] * n[1] * n[2]
+    x = np.stack([gen.random(np_) * k * d for k in n])
+    u = sigma * gen.standard_normal((3, np_))
+    u[0] += 20.0 if sigma == 0 else 0.0
+    cfg = hpic.config(n[0], n[1], d, d, 0.07, n3=n[2], dx3=d, precision="fp32")
+    return _push_us(hpic, cfg, x, u, np.full(np_, 1e-3 / ppc), 16)
+
+
+# tiles that do not fill the compute units have their LDS to themselves; within a quarter
+# of it, which is all that a full one leaves, these ratios were 2.6, 7.4 and 2.6
+@pytest.mark.parametrize("n,sigma,most", [((32, 22, 21), 0.1, 1.8), ((32, 22, 21), 0.5, 4.5),
+                                          ((64, 33, 33), 0.1, 1.8)])
+def test_warm_small_box_stays_in_the_lds(hpic, n, sigma, most):
+    cold, warm = _box(hpic, 0.0, n), _box(hpic, sigma, n)
+    assert warm < most * cold, (warm, cold)
+
+
+# one particle a cell: thin slabs hold more nodes than they save, so tiles go through
+# global memory; 648 tiles take a third of a compute unit's LDS, 1296 a quarter
+@pytest.mark.parametrize("n", [(64, 33, 33), (128, 33, 33)])
+def test_sparse_hot_tiles_give_the_same_bits(hpic, n):
+    d = W.drift3d(*n, spread=0.05, sigma_u=2.0, gamma=3.0, jitter=True, sub=(1, 1, 1), seed=W.SEED0 + 603,
+                  name="warm3")
+    ref = None
+    for t1, t2, K in ((5, 3, 1), (8, 4, 12), (16, 4, 12)):
+        sim = hpic.from_workload(d, "fp32")
+        sim.set_tiling(t1, t2, K)
+        sim.step(12)
+        raw = sim.particles_raw(0)
+        o = np.argsort(raw["id"])
+        got = [*sim.fields(0), sim.current_fixed(0)] + [v[..., o] for _, v in sorted(raw.items())]
+        sim.close()
+        ref = ref or got
+        for a, b in zip(got, ref):
+            assert np.array_equal(a, b), (t1, t2, K)
