@@ -245,10 +245,10 @@ typedef struct hp_tune {
  * tile2 radial rows (default 4 x 2), and its interval (default 64 steps; a
  * load sorts before the first step); the push works on tiles of 4 x 2 bins,
  * tile1 taken as 2 to 4 and tile2 as 1 or 2: 8 to 16 x 2 to 4 cells, smaller for
- * many modes or few tiles (FP32 with more than four modes: at most 8 columns),
- * in whose cells the sort leaves the particles.  The sort only permutes storage: FP32_FIXED
- * results are bit-identical for every setting (FP64: equal to rounding, the
- * deposit's atomics add in another order).  lds_bytes reads 0 for these handles. */
+ * many modes (FP32 with more than four: at most 8 columns) or few tiles and
+ * particles, in whose cells the sort leaves the particles.  The sort only
+ * permutes storage: FP32_FIXED results are bit-identical for every setting (FP64:
+ * equal to rounding, the deposit's atomics add in another order).  lds_bytes reads 0 for these handles. */
 int hp_set_tiling(hp_sim *sim, int32_t tile1, int32_t tile2, int32_t sort_interval);
 int hp_get_tiling(hp_sim *sim, hp_tune *out);
 

@@ -2295,7 +2295,7 @@ class SimQ : public SimBase {
         return fail(HP_ERANGE, "fixed-point headroom: %d particles in one (z, r) cell", cmax);
     }
     set_jconv(run);
-    if ((rc = rebuild_push_items())) return rc;
+    if ((rc = rebin())) return rc;
     return upload_runs();
   }
 
@@ -2697,7 +2697,7 @@ class SimQ : public SimBase {
       }
       set_jconv(i);
     }
-    if ((rc = rebuild_push_items())) return rc;
+    if ((rc = rebin())) return rc;
     return upload_runs();
   }
 
@@ -2766,6 +2766,23 @@ class SimQ : public SimBase {
     since_sort_ = sort_interval_;  // sort before the first step
     return HP_OK;
   }
+  // Whether tiles of tz x tr cells are to be half as high: so few of them that twice as many
+  // still run at once, or not many, of ten particles a cell and more.  Push with 4 against
+  // 2 rows, two modes, 2 / 8 / 32 particles a cell, by tiles of 4 rows: FP64 256 x 61 (256)
+  // 40 and 104 us (8 / 32) against 35 and 72, 512 x 61 (512) 25 / 50 / 140 against 40 / 56 /
+  // 128, 512 x 124 (992) 48 / 90 / 287 against 74 / 103 / 246, 1024 x 152 (2432) 210 (8) against
+  // 230; FP32 512 x 61 28 and 73 (8 / 32) against 24 and 52, 512 x 92 (736) 20 / 35 / 90
+  // against 29 / 38 / 79.
+  bool flat(int tz, int tr) const {
+    long long tiles = 0, np = 0;
+    for (const RunHostQ &h : runs_) {
+      tiles += (long long)((h.d.n1 + tz - 1) / tz) * ((h.d.n2 + tr - 1) / tr);
+      np += h.d.np;
+    }
+    return tr > 2 && (tiles <= (sizeof(R) == 4 ? 512 : 320) || (tiles < 1024 && np >= 10 * tz * tr * tiles));
+  }
+  // After a load: the tiles for its particles, and the push's work.
+  int rebin() { return flat(push_tz_, push_tr_) != flat_ ? set_bins(sbz_, sbr_) : rebuild_push_items(); }
   // Push tiles: 4 sbz z columns x 2 sbr radial rows within 8 to 16 (FP32, more than four
   // modes: 8) x 2 to 4 cells, halved until the boxes of every run's modes fit the LDS
   // (FP32, three modes: 16 x 4, four: 8 x 4, eight: 8 x 2).  The particles are sorted by tile, so a change needs a
@@ -2783,15 +2800,9 @@ class SimQ : public SimBase {
     // 195 us with 8 x 2 cells, 247 with 4 x 4)
     while (tz * tr > 1 && q_push_rows<R>(q_push_cols(tz), modes, push_staged_) < tr + 6)
       (tz > 2 * tr || tr == 1 ? tz : tr) /= 2;
-    // Few workgroups: half as high.  Push with 4 against 2 rows, two modes, FP64, eight
-    // and 32 particles a cell, by tiles of 4 rows: 256 x 61 (256) 40 and 104 us against 35
-    // and 72, 512 x 92 (736) 78 and 187 against 80 and 185, 512 x 124 (992) 90 and 287
-    // against 103 and 246, 1024 x 152 (2432) 210 with eight against 230.  Few particles a
-    // tile would have the line at 400, many beyond 1000.
-    long long tiles = 0;
-    for (const RunHostQ &h : runs_)
-      tiles += (long long)((h.d.n1 + tz - 1) / tz) * ((h.d.n2 + tr - 1) / tr);
-    if (tiles < 1024 && tr > 2) tr = 2;
+    push_tr_ = tr;
+    flat_ = flat(tz, tr);
+    if (flat_) tr = 2;
     push_tz_ = tz;
     for (RunHostQ &h : runs_) {
       RunQ<R> &d = h.d;
@@ -2918,7 +2929,8 @@ class SimQ : public SimBase {
   int64_t kn_[HP_NK] = {0};
   // particle sort: push tiles after bins of sbz_ z columns x sbr_ radial rows,
   // every sort_interval_ steps, and before the first step after a load
-  int push_tz_ = 1;  // z columns of the tiles
+  int push_tz_ = 1, push_tr_ = 1;  // z columns and rows of the tiles, before they are halved
+  bool flat_ = false;              // to two rows
   bool push_staged_ = false;  // the push holds its fields in the LDS
   int sbz_ = 4, sbr_ = 2, sort_interval_ = 64, since_sort_ = 0;
 };
