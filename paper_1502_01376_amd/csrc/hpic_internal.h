@@ -757,7 +757,7 @@ __host__ __device__ constexpr long long push_box_bytes(int w, int h, size_t real
 }
 constexpr int PUSH_LDS_MIN = 16384;
 constexpr int PUSH_LDS_MAX = 64512;  // with the static LDS, under 64 KiB
-constexpr int LDS_PIECE = 1280;      // a compute unit's 160 KiB are given out in pieces of these
+constexpr int LDS_PIECE = 1280, LDS_PIECES = 128;  // a compute unit's LDS is given out in pieces
 // The 3D push.  FP32 form: 4 waves per SIMD (128 registers), four workgroups of 256
 // threads per compute unit with LDS_256 bytes each (three with LDS_3), or two of NT_MAX =
 // 512 with LDS_MAX for tiles that need more.  FP64 form: 2 waves per SIMD (256

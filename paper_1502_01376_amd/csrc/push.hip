@@ -685,8 +685,8 @@ __device__ __forceinline__ void push_tile(const Run<R> &r, const Parts<R> &P, in
 // A tile whose particles have spread so far that the two boxes do not fit: fields
 // through the cache, so that the LDS holds twice the current box, and only the particles
 // outside that deposit into global memory.  (1024 x 512, eight particles a cell, sorted
-// every 16 steps, push with a thermal spread of 0.3: 288 us, 1413 with such tiles in
-// global memory; of 1: 374 and 2124; FP64 form of 0.3: 314 and 1831.)
+// every 16 steps, push with a thermal spread of 0.3: 251 us, 1413 with such tiles in
+// global memory; of 1: 338 and 2124; FP64 form of 0.3: 229 and 1831.)
 template <class R, bool UNIT, bool EC>
 __device__ __forceinline__ void push_wide(const Run<R> *run, int t, int parity, int pp, int lds_bytes,
                                        lptr<unsigned char> smem, lptr<int> nbox, unsigned *err) {

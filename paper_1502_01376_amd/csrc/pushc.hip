@@ -476,7 +476,7 @@ __device__ __forceinline__ void push_tile_c(const Run<R> &r, const Parts<R> &P, 
 // through the cache, so that the LDS holds twice the current box, and only the particles
 // outside that deposit into global memory.  (1024 x 300, eight particles a cell, sorted
 // every 16 steps, push with a thermal spread of 0.3: 189 us, 1563 with such tiles in
-// global memory; of 1: 228 and 2304; FP64 form of 0.3: 226 and 1624.)
+// global memory; of 1: 228 and 2304; FP64 form of 0.3: 182 and 1624.)
 template <class R, bool UNIT, bool EC>
 __device__ __forceinline__ void push_wide_c(const Run<R> &r, const Parts<R> &P, int parity, int start, int end,
                                          int ref1, int ref2, int lo1, int hi1, int lo2, int hi2,
