@@ -1781,13 +1781,14 @@ class Sim : public SimBase {
     // a third or half of a compute unit's to themselves anyway (FP32, four particles a
     // cell, thermal spread 0 / 0.1 / 0.5, push: 32 x 22 x 21, 144 tiles: 22 / 25 / 61 us,
     // 25 / 65 / 188 with LDS_256; 128 x 37 x 45, 1920 tiles: 89 / 113 / 256 and 82 / 247 / 927
-    // with LDS_256).
+    // with LDS_256).  Tiles joined to larger ones than were asked for keep the room that the
+    // small ones had to spread in (64 x 62 x 41, asked for 8 x 2 x 2, eight a cell, spread 0 /
+    // 0.1 / 0.2: 104 / 144 / 179 us, 110 / 338 / 520 with LDS_256).
     using O3 = Push3Occupancy<R>;
     constexpr int CUS = 256;
+    const bool half = box3(p1, p2) > O3::LDS_256 || tiles.size() <= 2 * CUS || p1 > t1 || p2 > t2;
     if (dim_ == 3)
-      push_lds_ = box3(p1, p2) > O3::LDS_256 || tiles.size() <= 2 * CUS ? O3::LDS_MAX
-                  : tiles.size() <= 3 * CUS                              ? O3::LDS_3
-                                                                         : O3::LDS_256;
+      push_lds_ = half ? O3::LDS_MAX : tiles.size() <= 3 * CUS ? O3::LDS_3 : O3::LDS_256;
     if (d_tiles_) release(d_tiles_);
     if (d_cblocks_) release(d_cblocks_);
     d_tiles_ = d_cblocks_ = nullptr;

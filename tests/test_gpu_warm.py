@@ -10,9 +10,11 @@ from paper_1502_01376_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-def _push_us(hpic, cfg, x, u, w, steps):
+def _push_us(hpic, cfg, x, u, w, steps, tile=None):
     sim = hpic.Sim([cfg])
     sim.set_particles(0, x, u, w)
+    if tile:
+        sim.set_tiling(*tile, steps)
     sim.step(steps)
     sim.profile(True)
     sim.step(2 * steps)
@@ -124,14 +126,14 @@ def test_fp64_particles_outside_the_box_agree(hpic, shape):
         assert np.abs(out[0] - o).max() <= 1e-11 * np.abs(out[0]).max()
 
 
-def _box(hpic, sigma, n, ppc=4):
+def _box(hpic, sigma, n, ppc=4, tile=None):
     gen = np.random.default_rng(13)
     d, np_ = 0.2, ppc * n[0] * n[1] * n[2]
     x = np.stack([gen.random(np_) * k * d for k in n])
     u = sigma * gen.standard_normal((3, np_))
     u[0] += 20.0 if sigma == 0 else 0.0
     cfg = hpic.config(n[0], n[1], d, d, 0.07, n3=n[2], dx3=d, precision="fp32")
-    return _push_us(hpic, cfg, x, u, np.full(np_, 1e-3 / ppc), 16)
+    return _push_us(hpic, cfg, x, u, np.full(np_, 1e-3 / ppc), 16, tile)
 
 
 # tiles that do not fill the compute units have their LDS to themselves; within a quarter
@@ -141,6 +143,13 @@ def _box(hpic, sigma, n, ppc=4):
 def test_warm_small_box_stays_in_the_lds(hpic, n, sigma, most):
     cold, warm = _box(hpic, 0.0, n), _box(hpic, sigma, n)
     assert warm < most * cold, (warm, cold)
+
+
+# 1408 tiles of 8 x 4 x 4 joined from ones of 8 x 2 x 2; in a quarter of the LDS the
+# ratio was 3.1
+def test_joined_tiles_have_room_to_spread(hpic):
+    cold, warm = (_box(hpic, s, (64, 62, 41), 8, (8, 2)) for s in (0.0, 0.1))
+    assert warm < 2 * cold, (warm, cold)
 
 
 # one particle a cell: thin slabs hold more nodes than they save, so tiles go through
